@@ -960,7 +960,7 @@ bool linear_dgrad_supported(int64_t T, int64_t O, int64_t lddy, int64_t I, int d
   const int eb = dtype != SSTE_BF16 ? 1 : 2;
   if (product_reaches(lddy, 256 * eb, 1ll << 30)) return false;           // 32-bit offsets inside a grad_Z tile
   if (product_reaches(O / 16 * 16 + 16, I, 1ll << 31)) return false;      // packed operand addressed with 32-bit offsets
-  if (product_reaches(I / 64 + 1, T / 64 + 1, 0x80000000ll)) return false;
+  if (product_reaches(I / 256 + 1, T / 128 + 1, 0x80000000ll)) return false;
   return true;
 }
 
@@ -1003,6 +1003,7 @@ static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
   for (int c = 0; c < DG_SHAPES; c++) {
     const DgradShape& s = tab[c];
     const int64_t wgs = ((I + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn);
+    if (c != DG_256 && wgs > 0x7FFFFFFFll) continue;                                  // grid size
     const double nk = (double)((steps + s.kg - 1) / s.kg);
     const int64_t n = (wgs + 255) / 256, full = n / s.r, rem = n % s.r;      // workgroups on the busiest CU: full rounds of r, and a rest
     double t = s.base + (double)full * (s.f + nk * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));

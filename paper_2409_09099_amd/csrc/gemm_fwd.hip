@@ -13,13 +13,13 @@
 //
 // Tiling: every wave owns a grid of 16 x 16 MFMA tiles (8 x 4 = 128 channels x 64 tokens in the main
 // shape): per sparse MFMA it reads about 540 B of fragments from LDS, inside the LDS read rate of the CU.
-// Three kernels share the operand layouts:
-//   k_linear_fwd        the first, phase-structured kernel (fragment reads, then loads, then MFMAs);
-//                       kept as 256 x 128 / 4 waves / 2-stage ring, two workgroups per CU, for layers
-//                       with fewer than 128 tiles of 256 x 256, and as 128 x 64 / 1 wave for tiny ones;
-//   k_linear_fwd_pipe   software-pipelined 256 x 256 tiles, 8 waves, one workgroup per CU (below);
+// Four kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
+//   k_linear_fwd_pipe   software-pipelined 256 x 256 tiles, 8 waves, one workgroup per CU;
 //   k_linear_fwd_dual   the same tile code for 256 x 256 and 256 x 128 tiles in one grid, for layers
-//                       whose last round of 256 x 256 tiles would fill at most half of the CUs.
+//                       whose last round of 256 x 256 tiles would fill at most half of the CUs;
+//   k_linear_fwd_tile   256 x 128 (two workgroups per CU) down to 32 x 32 tiles on the 32 x 32 instruction, with
+//                       the contraction split over groups of waves where there are few tiles;
+//   k_linear_fwd_skinny 16 x 16 tiles straight from memory to registers, for decode batches.
 // Operand tiles travel L2 -> LDS directly (buffer_load ... lds, no staging registers) into rings of
 // LDS slots.  What limits all of them is the L1 of the CU: it keeps 64 line requests in flight, and a
 // request takes 400 - 500 clocks under load, so a CU receives about 20 B/clk (measured; a 256 x 256
@@ -43,8 +43,6 @@
 namespace sste {
 
 namespace {
-constexpr int MI = 8, NI = 4;                     // MFMA tiles per wave: 128 channels x 64 tokens
-constexpr int EPI_ROW = 272;                      // 128 channels x 2 B + 16 B pad
 constexpr int NUM_CU = 256;
 
 }  // namespace
@@ -116,204 +114,6 @@ __device__ __forceinline__ void publish_tile_amax(uint32_t m, float amax_scale, 
 }
 
 __global__ void k_fill_u32_fwd(uint32_t* p, uint32_t v) { *p = v; }
-
-template <bool FP8, int WM, int WN, int NS, bool ZF8, bool AMAX>
-__global__ void __launch_bounds__(64 * WM * WN, (WM * WN <= 4 && NS <= 2) ? 2 : 1)
-k_linear_fwd(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes,
-             const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta,
-             int64_t O, FwdOut out, int m_tiles) {
-  const float scale = out.scale;
-  uint16_t* __restrict__ Z = out.z16;
-  const int64_t ldz = out.ldz;
-  constexpr int NW = WM * WN;
-  constexpr int BM = 128 * WM, BN = 64 * WN;
-  constexpr int MB = FP8 ? 16 : 8;                // position bytes per row and k-step
-  constexpr int MBLK = 16 * MB;                   // ... per 16-row block
-  constexpr int A_BYTES = BM * 64, B_BYTES = BN * 128, M_BYTES = BM * MB;
-  constexpr int STAGE = A_BYTES + B_BYTES + M_BYTES;
-  constexpr int EPI_BYTES = NW * 64 * EPI_ROW;
-  constexpr int SMEM = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
-  constexpr int LA = BM / 16 / NW, LB = BN / 8 / NW, LM = M_BYTES / 256 / NW;   // loads per wave and stage
-  constexpr int LPW = LA + LB + LM;
-  static_assert(LA >= 1 && LB >= 1 && LM >= 1, "tile too small for this many waves");
-  __shared__ __align__(1024) uint8_t smem[SMEM];
-
-  // XCD-aware tile order: XCD x owns a contiguous range of logical tiles
-  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int tm = logical % m_tiles, tn = logical / m_tiles;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int j = lane & 15, q = lane >> 4;
-  const int64_t o0 = (int64_t)tm * BM, t0 = (int64_t)tn * BN;
-  const int nsteps = (int)(k_bytes / 128);
-
-  // buffer descriptors over exactly the valid part of this tile: what lies past the end reads as zeros
-  const int64_t rblk0 = o0 / 16, rbn = (O + 15) / 16;
-  const int blks_a = (int)((rbn - rblk0) < BM / 16 ? (rbn - rblk0) : BM / 16);
-  const int rows_b = (int)((T - t0) < BN ? (T - t0) : BN);
-  const i32x4 ba = rsrc_words(vals + rblk0 * nsteps * 1024, (uint32_t)(blks_a * nsteps * 1024));
-  const i32x4 bm = rsrc_words(meta + rblk0 * nsteps * MBLK, (uint32_t)(blks_a * nsteps * MBLK));
-  const i32x4 bb = rsrc_words(X + t0 * ldx_bytes, (uint32_t)((rows_b - 1) * ldx_bytes + k_bytes));
-
-  // per-lane source offsets of the direct-to-LDS loads (destination = stage base + load index * 1 KiB
-  // (256 B for the position bits) + lane * 16 (4), fixed by the hardware)
-  uint32_t offa[LA], offb[LB], offm[LM];
-#pragma unroll
-  for (int i = 0; i < LA; i++) offa[i] = (uint32_t)((LA * wave + i) * nsteps * 1024 + lane * 16);
-#pragma unroll
-  for (int i = 0; i < LB; i++) {
-    int wl = LB * wave + i;
-    int r = 8 * wl + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-    offb[i] = (uint32_t)(r * ldx_bytes + c * 16);
-  }
-#pragma unroll
-  for (int i = 0; i < LM; i++) {
-    int d = 64 * (LM * wave + i) + lane;          // dword index inside the stage's position bits
-    offm[i] = (uint32_t)((d / (MBLK / 4)) * nsteps * MBLK + 4 * (d % (MBLK / 4)));
-  }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
-
-  // loads of k-step `step` into ring slot `stg`; past the last k-step the scalar offset is pushed out
-  // of range so that the same number of loads is always in flight (they fetch nothing)
-#define FWD_ISSUE(step, stg)                                                                           \
-  do {                                                                                                 \
-    const bool live_ = (step) < nsteps;                                                                \
-    const uint32_t sa_ = live_ ? (uint32_t)(step) * 1024u : 0x40000000u;                                 \
-    const uint32_t sb_ = live_ ? (uint32_t)(step) * 128u : 0x40000000u;                                \
-    const uint32_t sm_ = live_ ? (uint32_t)(step) * (uint32_t)MBLK : 0x40000000u;                        \
-    const uint32_t base_ = lds0 + (uint32_t)(stg) * STAGE;                                             \
-    _Pragma("unroll") for (int i = 0; i < LA; i++) dma_b128(ba, base_ + (LA * wave + i) * 1024, offa[i], sa_); \
-    _Pragma("unroll") for (int i = 0; i < LB; i++) dma_b128(bb, base_ + A_BYTES + (LB * wave + i) * 1024, offb[i], sb_); \
-    _Pragma("unroll") for (int i = 0; i < LM; i++) dma_b32(bm, base_ + A_BYTES + B_BYTES + (LM * wave + i) * 256, offm[i], sm_); \
-  } while (0)
-
-  f32x4 acc[MI][NI];
-#pragma unroll
-  for (int a = 0; a < MI; a++)
-#pragma unroll
-    for (int b = 0; b < NI; b++) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  // per-lane fragment addresses inside a stage
-  const uint32_t fa_off = (uint32_t)(8 * wm * 1024 + lane * 16);          // + 1024 mi
-  const uint32_t fm_off = (uint32_t)(A_BYTES + B_BYTES + 8 * wm * MBLK + lane * (MB / 4));   // + MBLK mi
-  const int rb0 = 64 * wn + j;                                           // + 16 ni
-  const int cb0 = q ^ ((j >> 1) & 7);
-  const uint32_t fb_off0 = (uint32_t)(A_BYTES + rb0 * 128 + cb0 * 16);
-  const uint32_t fb_off1 = (uint32_t)(A_BYTES + rb0 * 128 + (cb0 ^ 4) * 16);
-
-#pragma unroll
-  for (int s = 0; s < NS - 1; s++) FWD_ISSUE(s, s);
-
-  int stg = 0;
-  for (int step = 0; step < nsteps; step++) {
-    wait_vmcnt<(NS - 2) * LPW>();        // this wave's share of k-step `step` has landed in LDS
-    __syncthreads();                     // ... and everybody else's; slot (step - 1) % NS is free again
-    const uint8_t* sb = smem + stg * STAGE;
-    uint4 fb[NI][2];
-#pragma unroll
-    for (int ni = 0; ni < NI; ni++) {
-      fb[ni][0] = *(const uint4*)(sb + fb_off0 + ni * 2048);
-      fb[ni][1] = *(const uint4*)(sb + fb_off1 + ni * 2048);
-    }
-    uint4 fa[MI];
-    int fidx[MI];
-#pragma unroll
-    for (int mi = 0; mi < MI; mi++) {
-      fa[mi] = *(const uint4*)(sb + fa_off + mi * 1024);
-      if (FP8) fidx[mi] = *(const int*)(sb + fm_off + mi * MBLK);
-      else fidx[mi] = *(const uint16_t*)(sb + fm_off + mi * MBLK);
-    }
-    {
-      int nstg = stg + NS - 1;
-      if (nstg >= NS) nstg -= NS;
-      FWD_ISSUE(step + NS - 1, nstg);
-    }
-#pragma unroll
-    for (int mi = 0; mi < MI; mi++) {
-#pragma unroll
-      for (int ni = 0; ni < NI; ni++) {
-        if (FP8) {
-          i32x4 av;
-          i32x8 bv;
-          __builtin_memcpy(&av, &fa[mi], 16);
-          __builtin_memcpy(&bv, &fb[ni][0], 32);
-          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(av, bv, acc[mi][ni], fidx[mi], 0, 0);
-        } else {
-          bf16x8 av;
-          bf16x16 bv;
-          __builtin_memcpy(&av, &fa[mi], 16);
-          __builtin_memcpy(&bv, &fb[ni][0], 32);
-          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, bv, acc[mi][ni], fidx[mi], 0, 0);
-        }
-      }
-    }
-    stg = (stg + 1 == NS) ? 0 : stg + 1;
-  }
-#undef FWD_ISSUE
-
-  // epilogue: accumulators -> LDS (row = token, the wave's 128 channels contiguous) -> 16-byte stores
-  wait_vmcnt<0>();
-  __syncthreads();
-  if (AMAX) {
-    // float maxima of magnitudes: the absolute value is a free source modifier and two values go into one
-    // three-operand maximum (the accumulators are finite)
-    float mf = 0.0f;
-#pragma unroll
-    for (int mi = 0; mi < MI; mi++)
-#pragma unroll
-      for (int ni = 0; ni < NI; ni++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) mf = __builtin_fmaxf(mf, __builtin_fabsf(acc[mi][ni][r]));
-    publish_tile_amax<NW>(f2u(mf), out.amax_scale, out.amax_bits, (uint32_t*)smem);
-  }
-  uint8_t* eb = smem + wave * (64 * EPI_ROW);
-  if (ZF8) {
-    // e4m3 output: a lane's four values of a tile are four consecutive channels = one dword
-#pragma unroll
-    for (int mi = 0; mi < MI; mi++)
-#pragma unroll
-      for (int ni = 0; ni < NI; ni++) {
-        int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][0] * scale), clamp448(acc[mi][ni][1] * scale), 0, false);
-        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][2] * scale), clamp448(acc[mi][ni][3] * scale), w, true);
-        *(int*)(eb + (16 * ni + j) * EPI_ROW + 16 * mi + 4 * q) = w;
-      }
-#pragma unroll
-    for (int it = 0; it < 8; it++) {
-      int row = 8 * it + (lane >> 3), chunk = lane & 7;
-      uint4 v = *(const uint4*)(eb + row * EPI_ROW + chunk * 16);
-      int64_t t = t0 + 64 * wn + row, o = o0 + 128 * wm + 16 * chunk;
-      if (t < T && o < O) store_stream_b128(out.z8 + t * ldz + o, v);
-    }
-    return;
-  }
-#pragma unroll
-  for (int mi = 0; mi < MI; mi++)
-#pragma unroll
-    for (int ni = 0; ni < NI; ni++) {
-      uint2 v;
-      v.x = bf16_rne_pack(acc[mi][ni][0] * scale, acc[mi][ni][1] * scale);
-      v.y = bf16_rne_pack(acc[mi][ni][2] * scale, acc[mi][ni][3] * scale);
-      *(uint2*)(eb + (16 * ni + j) * EPI_ROW + (16 * mi + 4 * q) * 2) = v;
-    }
-  // same-wave LDS accesses are ordered; no barrier needed for a wave-private region
-  uint32_t act_max = 0;
-#pragma unroll
-  for (int it = 0; it < 16; it++) {
-    int row = 4 * it + (lane >> 4), chunk = lane & 15;
-    uint4 v = *(const uint4*)(eb + row * EPI_ROW + chunk * 16);
-    int64_t t = t0 + 64 * wn + row, o = o0 + 128 * wm + 8 * chunk;
-    if (t < T && o < O) {
-      if (Z) store_stream_b128(Z + t * ldz + o, v);
-      if (out.act) act_max = max(act_max, fwd_act_piece(v, out, t, o));
-    }
-  }
-  if (out.act && out.amax_bits) {           // uniform over the workgroup
-    __syncthreads();                        // every wave is done with its part of the LDS
-    publish_tile_amax<NW>(act_max, 1.0f, out.amax_bits, (uint32_t*)smem);
-  }
-}
 
 // ---------------------------------------------------------------------------------------------------------
 // Software-pipelined variant: 8 waves (2 x 4), each owning MI_ x NI_ MFMA tiles, so a workgroup covers
@@ -580,6 +380,370 @@ __device__ __forceinline__ void fwd_pipe_tile(uint8_t* smem, const uint8_t* __re
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Small and middle problems: 32 WM MT channels x 32 WN NT tokens by KG groups of WM x WN waves on the 32 x 32 sparse instructions
+// (v_smfmac_f32_32x32x32_bf16 / 32x32x64_fp8_fp8, two per k-step).  Group kg takes the k-steps kg, kg + KG, ... through LDS slots
+// of its own and the groups' sums are added at the end: such problems have too few tiles to fill the chip and are bound by the time
+// a k-step's loads take to arrive, so it is loads in flight that count (NS slots per group, KG groups, several workgroups per CU).
+// The only barrier of a k-step stands before its second half, whose fragments are in registers by then: behind it the slot
+// of this k-step is free, the next tile is complete, and its first fragments are read under the second half's MFMAs.
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS>
+constexpr int fwd_tile_smem() {
+  constexpr int NWG = WM * WN, MB = FP8 ? 16 : 8;
+  constexpr int LM = (32 * WM * MT * MB / 256 + NWG - 1) / NWG;
+  constexpr int RING = KG * NS * (32 * WM * MT * 64 + NWG * LM * 256 + 32 * WN * NT * 128);
+  constexpr int EPI = NWG * 32 * NT * (64 * MT + 16);
+  constexpr int RED = (KG - 1) * NWG * MT * NT * 4096;
+  constexpr int M1 = RING > EPI ? RING : EPI;
+  return M1 > RED ? M1 : RED;
+}
+
+template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS, bool ZF8, bool AMAX>
+__global__ void __launch_bounds__(64 * WM * WN * KG, 1)
+k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
+                  const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
+  constexpr int NWG = WM * WN, NW = NWG * KG;
+  constexpr int BM = 32 * WM * MT, BN = 32 * WN * NT;
+  constexpr int MB = FP8 ? 16 : 8, MBLK = 16 * MB;
+  constexpr int LA = BM / 16 / NWG, LB = BN / 8 / NWG, LM = (BM * MB / 256 + NWG - 1) / NWG;   // loads per wave and k-step
+  constexpr int LPW = LA + LB + LM;
+  constexpr int A_BYTES = BM * 64, M_BYTES = NWG * LM * 256, SLOT = A_BYTES + M_BYTES + BN * 128;
+  static_assert(LA >= 1 && LB >= 1, "tile too small for this many waves");
+  __shared__ __align__(1024) uint8_t smem[fwd_tile_smem<FP8, WM, WN, MT, NT, KG, NS>()];
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int tm = logical % m_tiles, tn = logical / m_tiles;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = KG > 1 ? wave_all / NWG : 0, wave = KG > 1 ? wave_all % NWG : wave_all;
+  const int wm = wave / WN, wn = wave % WN;
+  const int n = lane & 31, hh = lane >> 5;
+  const int64_t o0 = (int64_t)tm * BM, t0 = (int64_t)tn * BN;
+  const int nsteps = (int)(k_bytes / 128);
+  const int nloc = (nsteps + KG - 1) / KG;
+  uint8_t* const ring = smem + kg * NS * SLOT;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)ring;
+
+  const int64_t rblk0 = o0 / 16, rbn = (O + 15) / 16;
+  const int blks_a = (int)((rbn - rblk0) < BM / 16 ? (rbn - rblk0) : BM / 16);
+  const int rows_b = (int)((T - t0) < BN ? (T - t0) : BN);
+  const i32x4 ba = rsrc_words(vals + rblk0 * nsteps * 1024, (uint32_t)(blks_a * nsteps * 1024));
+  const i32x4 bm = rsrc_words(meta + rblk0 * nsteps * MBLK, (uint32_t)(blks_a * nsteps * MBLK));
+  const i32x4 bb = rsrc_words(X + t0 * ldx_bytes, (uint32_t)((rows_b - 1) * ldx_bytes + k_bytes));
+  uint32_t offa[LA], offb[LB], offm[LM];
+#pragma unroll
+  for (int i = 0; i < LA; i++) offa[i] = (uint32_t)((LA * wave + i) * nsteps * 1024 + lane * 16);
+#pragma unroll
+  for (int i = 0; i < LB; i++) {
+    const int r = 8 * (LB * wave + i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    offb[i] = (uint32_t)(r * ldx_bytes + c * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < LM; i++) {
+    const int d = 64 * (LM * wave + i) + lane;
+    offm[i] = (uint32_t)((d / (MBLK / 4)) * nsteps * MBLK + 4 * (d % (MBLK / 4)));
+  }
+  // k-step number ls of this group into slot `slot`; past the last one the loads are pushed out of range (zeros arrive: such a step
+  // adds nothing), so that the same number is always in flight
+  auto issue = [&](int ls, int slot) {
+    const int st = ls * KG + kg;
+    const bool live = st < nsteps;
+    const uint32_t sa = live ? (uint32_t)st * 1024u : 0x40000000u, sx = live ? (uint32_t)st * 128u : 0x40000000u;
+    const uint32_t sm = live ? (uint32_t)st * (uint32_t)MBLK : 0x40000000u;
+    const uint32_t base = lds0 + (uint32_t)slot * SLOT;
+#pragma unroll
+    for (int i = 0; i < LA; i++) dma_b128(ba, base + (LA * wave + i) * 1024, offa[i], sa);
+#pragma unroll
+    for (int i = 0; i < LM; i++) dma_b32(bm, base + A_BYTES + (LM * wave + i) * 256, offm[i], sm);
+#pragma unroll
+    for (int i = 0; i < LB; i++) dma_b128(bb, base + A_BYTES + M_BYTES + (LB * wave + i) * 1024, offb[i], sx);
+  };
+
+  f32x16 acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; m++)
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[m][t][r] = 0.f;
+
+  // fragments of half kk of a k-step.  A lane (row n, hh): slot 16 (2 kk + hh) + n % 16 of row block n / 16; B lane (column n, hh):
+  // pieces 4 kk + hh and 4 kk + 2 + hh of the token row.
+  const uint32_t fa_off = (uint32_t)((2 * wm * MT + (n >> 4)) * 1024 + (16 * hh + (n & 15)) * 16);
+  const uint32_t fm_off = (uint32_t)(A_BYTES + (2 * wm * MT + (n >> 4)) * MBLK + (16 * hh + (n & 15)) * (MB / 4));
+  const uint32_t fb_row = (uint32_t)(A_BYTES + M_BYTES + (32 * wn * NT + n) * 128), key = (uint32_t)((n >> 1) & 7);
+  const uint32_t fb_off[2] = {fb_row + ((hh ^ key) * 16), fb_row + (((4 + hh) ^ key) * 16)};
+  uint4 fa[2][MT], fb[2][NT][2];
+  int fi[2][MT];
+  auto read_frag = [&](int kk, const uint8_t* sl) {
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+      fa[kk][m] = *(const uint4*)(sl + fa_off + m * 2048 + kk * 512);
+      if (FP8) fi[kk][m] = *(const int*)(sl + fm_off + m * 2 * MBLK + kk * 32 * (MB / 4));
+      else fi[kk][m] = *(const uint16_t*)(sl + fm_off + m * 2 * MBLK + kk * 32 * (MB / 4));
+    }
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      fb[kk][t][0] = *(const uint4*)(sl + fb_off[kk] + t * 4096);
+      fb[kk][t][1] = *(const uint4*)(sl + (fb_off[kk] ^ 32u) + t * 4096);
+    }
+  };
+  auto mma = [&](int kk) {
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int t = 0; t < NT; t++) {
+        if (FP8) {
+          i32x4 av;
+          i32x8 bv;
+          __builtin_memcpy(&av, &fa[kk][m], 16);
+          __builtin_memcpy(&bv, &fb[kk][t][0], 32);
+          acc[m][t] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(av, bv, acc[m][t], fi[kk][m], 0, 0);
+        } else {
+          bf16x8 av;
+          bf16x16 bv;
+          __builtin_memcpy(&av, &fa[kk][m], 16);
+          __builtin_memcpy(&bv, &fb[kk][t][0], 32);
+          acc[m][t] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(av, bv, acc[m][t], fi[kk][m], 0, 0);
+        }
+      }
+  };
+
+  if (nloc > 0) {
+#pragma unroll
+    for (int k = 0; k < NS; k++) issue(k, k);
+    wait_vmcnt<(NS - 1) * LPW>();
+    __syncthreads();
+    read_frag(0, ring);
+  }
+  int slot = 0, slot1 = 1 % NS;
+  for (int s = 0; s < nloc; s++) {
+    read_frag(1, ring + slot * SLOT);
+    mma(0);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<(NS - 2) * LPW>();          // this wave's share of tile s + 1 has landed
+    __syncthreads();                       // ... everybody's; the slot of s has been read
+    read_frag(0, ring + slot1 * SLOT);
+    issue(s + NS, slot);
+    mma(1);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = slot1;
+    slot1 = slot1 == NS - 1 ? 0 : slot1 + 1;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  if (KG > 1) {
+    // sums of the k-groups: groups 1 .. KG - 1 leave theirs in LDS, lane for lane
+    if (kg > 0) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int g = 0; g < 4; g++)
+            *(float4*)(smem + (((kg - 1) * NWG + wave) * MT * NT + m * NT + t) * 4096 + g * 1024 + lane * 16) =
+                make_float4(acc[m][t][4 * g], acc[m][t][4 * g + 1], acc[m][t][4 * g + 2], acc[m][t][4 * g + 3]);
+    }
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int k = 0; k < KG - 1; k++)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int t = 0; t < NT; t++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+              const float4 v = *(const float4*)(smem + ((k * NWG + wave) * MT * NT + m * NT + t) * 4096 + g * 1024 + lane * 16);
+              acc[m][t][4 * g] += v.x;
+              acc[m][t][4 * g + 1] += v.y;
+              acc[m][t][4 * g + 2] += v.z;
+              acc[m][t][4 * g + 3] += v.w;
+            }
+    }
+    __syncthreads();
+  }
+
+  // output stage (group 0 holds the sums; the others only take part in the barriers)
+  const float scale = out.scale;
+  const bool own = KG == 1 || kg == 0;
+  if (AMAX) {
+    float mf = 0.0f;
+    if (own) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) mf = __builtin_fmaxf(mf, __builtin_fabsf(acc[m][t][r]));
+    }
+    publish_tile_amax<NW>(f2u(mf), out.amax_scale, out.amax_bits, (uint32_t*)smem);
+  }
+  uint32_t act_max = 0;
+  if (own) {
+    const int64_t tw = t0 + 32 * NT * wn, ow = o0 + 32 * MT * wm;
+    if (ZF8) {
+      // a lane's registers 4g .. 4g + 3 are four consecutive channels = one dword; padded token rows of 32 MT bytes
+      constexpr int EROW = 32 * MT + 16, CH = 2 * MT, NIT = 32 * NT * CH / 64;
+      uint8_t* const eb = smem + wave * (32 * NT * EROW);
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[m][t][4 * g] * scale), clamp448(acc[m][t][4 * g + 1] * scale), 0, false);
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[m][t][4 * g + 2] * scale), clamp448(acc[m][t][4 * g + 3] * scale), w, true);
+            *(int*)(eb + (32 * t + n) * EROW + 32 * m + 8 * g + 4 * hh) = w;
+          }
+#pragma unroll
+      for (int it = 0; it < NIT; it++) {
+        const int c = 64 * it + lane, row = c / CH, chunk = c % CH;
+        const uint4 v = *(const uint4*)(eb + row * EROW + chunk * 16);
+        if (tw + row < T && ow + 16 * chunk < O) store_stream_b128(out.z8 + (tw + row) * out.ldz + ow + 16 * chunk, v);
+      }
+    } else {
+      // chunk c of token row t at c ^ key(t), 8-byte halves swapped in rows with bit 4 set: all banks covered both ways
+      constexpr int CH = 4 * MT, NIT = 32 * NT * CH / 64;
+      uint8_t* const eb = smem + wave * (32 * NT * 64 * MT);
+      auto ekey = [](int row) { return (row / (16 / CH)) % CH; };
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int m = 0; m < MT; m++)
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            uint2 v;
+            v.x = bf16_rne_pack(acc[m][t][4 * g] * scale, acc[m][t][4 * g + 1] * scale);
+            v.y = bf16_rne_pack(acc[m][t][4 * g + 2] * scale, acc[m][t][4 * g + 3] * scale);
+            const int row = 32 * t + n;
+            *(uint2*)(eb + row * (64 * MT) + (((4 * m + g) ^ ekey(row)) * 16) + 8 * (hh ^ (n >> 4))) = v;
+          }
+#pragma unroll
+      for (int it = 0; it < NIT; it++) {
+        const int c = 64 * it + lane, row = c / CH, chunk = c % CH;
+        uint4 v = *(const uint4*)(eb + row * (64 * MT) + ((chunk ^ ekey(row)) * 16));
+        if ((row >> 4) & 1) v = make_uint4(v.z, v.w, v.x, v.y);
+        const int64_t t = tw + row, o = ow + 8 * chunk;
+        if (t < T && o < O) {
+          if (out.z16) store_stream_b128(out.z16 + t * out.ldz + o, v);
+          if (out.act) act_max = max(act_max, fwd_act_piece(v, out, t, o));
+        }
+      }
+    }
+  }
+  if (!ZF8 && out.act && out.amax_bits) {   // uniform over the workgroup
+    __syncthreads();
+    publish_tile_amax<NW>(act_max, 1.0f, out.amax_bits, (uint32_t*)smem);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Few tokens (a decode batch): 16 channels x 16 NI tokens by one workgroup whose KW waves take the k-steps in turn.  The packed
+// weight is read once and every wave's operands come straight from memory into its registers (a lane's slot of a packed block and
+// two pieces of an X row ARE its fragments): no LDS, no barrier until the waves' sums are added, U k-steps of loads in flight per wave.
+template <bool FP8, int NI, int KW, int U, bool ZF8, bool AMAX>
+__global__ void __launch_bounds__(64 * KW)
+k_linear_fwd_skinny(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
+                    const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
+  constexpr int MBLK = FP8 ? 256 : 128;
+  __shared__ __align__(16) uint8_t smem[KW * NI * 1024];
+  __shared__ uint32_t red[KW];
+  const int tm = blockIdx.x % m_tiles, tn = blockIdx.x / m_tiles;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, q = lane >> 4;
+  const int64_t o0 = (int64_t)tm * 16, t0 = (int64_t)tn * (16 * NI);
+  const int nsteps = (int)(k_bytes / 128);
+  const int rows_b = (int)((T - t0) < 16 * NI ? (T - t0) : 16 * NI);
+  const BufferRsrc ra = make_rsrc(vals + (int64_t)tm * nsteps * 1024, (uint32_t)(nsteps * 1024));
+  const BufferRsrc rm = make_rsrc(meta + (int64_t)tm * nsteps * MBLK, (uint32_t)(nsteps * MBLK));
+  const BufferRsrc rb = make_rsrc(X + t0 * ldx_bytes, (uint32_t)((rows_b - 1) * ldx_bytes + k_bytes));
+  const uint32_t offa = lane * 16, offm = lane * (MBLK / 64), offb = (uint32_t)(j * ldx_bytes + q * 16);
+
+  f32x4 acc[NI];
+#pragma unroll
+  for (int t = 0; t < NI; t++) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int s = wave; s < nsteps; s += KW * U) {
+    uint4 fa[U], fb[U][NI][2];
+    int fi[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      // a k-step past the last one reads zeros
+      const int st = s + u * KW;
+      const bool live = st < nsteps;
+      const uint32_t dead = live ? 0u : 0x80000000u;
+      const int sc = live ? st : 0;
+      fa[u] = buffer_load_b128(ra, offa + dead, (uint32_t)sc * 1024u);
+      if (FP8) fi[u] = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)(offm + dead), sc * MBLK, 0);
+      else fi[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rm, (int)(offm + dead), sc * MBLK, 0);
+#pragma unroll
+      for (int t = 0; t < NI; t++) {
+        const uint32_t o = (16 * t + j < rows_b ? offb + (uint32_t)(16 * t * ldx_bytes) : 0x80000000u) | dead;
+        fb[u][t][0] = buffer_load_b128(rb, o, (uint32_t)sc * 128u);
+        fb[u][t][1] = buffer_load_b128(rb, o + 64u, (uint32_t)sc * 128u);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int t = 0; t < NI; t++) {
+        if (FP8) {
+          i32x4 av;
+          i32x8 bv;
+          __builtin_memcpy(&av, &fa[u], 16);
+          __builtin_memcpy(&bv, &fb[u][t][0], 32);
+          acc[t] = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(av, bv, acc[t], fi[u], 0, 0);
+        } else {
+          bf16x8 av;
+          bf16x16 bv;
+          __builtin_memcpy(&av, &fa[u], 16);
+          __builtin_memcpy(&bv, &fb[u][t][0], 32);
+          acc[t] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, bv, acc[t], fi[u], 0, 0);
+        }
+      }
+  }
+#pragma unroll
+  for (int t = 0; t < NI; t++) *(f32x4*)(smem + (wave * NI + t) * 1024 + lane * 16) = acc[t];
+  __syncthreads();
+  uint32_t amax = 0;
+  if (wave < NI) {
+    // wave t adds up token tile t: a lane's four values are channels 4 q .. 4 q + 3 of token j
+    f32x4 v = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < KW; w++) v += *(const f32x4*)(smem + (w * NI + wave) * 1024 + lane * 16);
+    const int64_t t = t0 + 16 * wave + j, o = o0 + 4 * q;
+    if (AMAX) amax = f2u(__builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])), __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3]))));
+    if (t < T && o < O) {
+      const float sc = out.scale;
+      if (ZF8) {
+        int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(v[0] * sc), clamp448(v[1] * sc), 0, false);
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(v[2] * sc), clamp448(v[3] * sc), w, true);
+        *(int*)(out.z8 + t * out.ldz + o) = w;
+      } else {
+        const uint2 h = make_uint2(bf16_rne_pack(v[0] * sc, v[1] * sc), bf16_rne_pack(v[2] * sc, v[3] * sc));
+        if (out.z16) *(uint2*)(out.z16 + t * out.ldz + o) = h;
+        if (out.act) {
+          const float a[4] = {gelu_tanh(bf16lo_f32(h.x)), gelu_tanh(bf16hi_f32(h.x)), gelu_tanh(bf16lo_f32(h.y)), gelu_tanh(bf16hi_f32(h.y))};
+          if (out.a8) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) amax = max(amax, f2u(a[e]) & 0x7FFFFFFFu);
+            const float r = out.a_inv_scale;
+            int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[0] * r), clamp448(a[1] * r), 0, false);
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[2] * r), clamp448(a[3] * r), w, true);
+            *(int*)(out.a8 + t * out.lda + o) = w;
+          } else {
+            *(uint2*)(out.a16 + t * out.lda + o) = make_uint2(bf16_rne_pack(a[0], a[1]), bf16_rne_pack(a[2], a[3]));
+          }
+        }
+      }
+    }
+  }
+  if (AMAX || (!ZF8 && out.act && out.amax_bits)) publish_tile_amax<KW>(amax, AMAX ? out.amax_scale : 1.0f, out.amax_bits, red);
+}
+
 // One tile shape for the whole grid.  Workgroups are numbered so that each XCD works on a contiguous
 // range of tiles, o-tiles fastest.
 template <bool FP8, int MI_, int NI_, bool ZF8, bool AMAX>
@@ -642,17 +806,6 @@ static void launch_fwd_dual(const void* X, int64_t T, int64_t I, int64_t ldx, co
               (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles, n_big);
 }
 
-template <bool FP8, int WM, int WN, int NS, bool ZF8, bool AMAX>
-static void launch_fwd_cfg(const void* X, int64_t T, int64_t I, int64_t ldx, const FwdOut& out, const void* vals,
-                           const void* meta, int64_t O, hipStream_t s) {
-  constexpr int BM = 128 * WM, BN = 64 * WN;
-  int m_tiles = (int)((O + BM - 1) / BM), n_tiles = (int)((T + BN - 1) / BN);
-  dim3 grid((unsigned)(m_tiles * n_tiles)), block(64 * WM * WN);
-  int64_t eb = FP8 ? 1 : 2;
-  SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd<FP8, WM, WN, NS, ZF8, AMAX>), grid, block, s, (const uint8_t*)X, T, I * eb, ldx * eb,
-              (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
-}
-
 bool linear_fwd_supported(int64_t T, int64_t I, int64_t ldx, int64_t O, int dtype) {
   int64_t eb = dtype == SSTE_F8E4M3 ? 1 : 2;
   // 32-bit offsets inside a tile, 32-bit tile count
@@ -661,25 +814,115 @@ bool linear_fwd_supported(int64_t T, int64_t I, int64_t ldx, int64_t O, int dtyp
   return true;
 }
 
+template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS, bool ZF8, bool AMAX>
+static void launch_fwd_tile(const void* X, int64_t T, int64_t I, int64_t ldx, const FwdOut& out, const void* vals,
+                            const void* meta, int64_t O, hipStream_t s) {
+  constexpr int BM = 32 * WM * MT, BN = 32 * WN * NT;
+  int m_tiles = (int)((O + BM - 1) / BM), n_tiles = (int)((T + BN - 1) / BN);
+  int64_t eb = FP8 ? 1 : 2;
+  SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_tile<FP8, WM, WN, MT, NT, KG, NS, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(64 * WM * WN * KG), s,
+              (const uint8_t*)X, T, I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
+}
+
+template <bool FP8, int NI, int KW, int U, bool ZF8, bool AMAX>
+static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, const FwdOut& out, const void* vals,
+                              const void* meta, int64_t O, hipStream_t s) {
+  int m_tiles = (int)((O + 15) / 16), n_tiles = (int)((T + 16 * NI - 1) / (16 * NI));
+  int64_t eb = FP8 ? 1 : 2;
+  SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_skinny<FP8, NI, KW, U, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(64 * KW), s, (const uint8_t*)X, T,
+              I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
+}
+
+// Choice of the kernel.  Time model in microseconds: base + store * (output bytes at 5 TB/s) + rounds, a workgroup costing F + nk * step
+// with nk its k-steps (each k-group of a workgroup takes a KG-th of them) and step = max(lat, r * thr) for r workgroups sharing a CU;
+// R fit a CU (LDS) and what does not fit runs in further rounds.  Fitted to event times of 400 random problems (1 ... 32768 tokens,
+// 64 ... 5120 channels and features), 7...11 % off per problem; the shape it picks is 2 % slower than the best one on the geometric
+// mean.  What the fit says about the chip: thr is the operand bytes of a k-step at 75...100 B/ns for every shape, the rate at which a
+// CU receives operands.
+struct FwdShape {
+  int bm, bn, kg, r;
+  double f, lat, thr, base, store;
+};
+enum { FW_256, FW_256x128, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
+static const FwdShape kFwd16[FW_SHAPES] = {
+  {256, 256, 1, 1, 3.10, 0.689, 0.689, 1.71, 1.09},
+  {256, 128, 1, 2, 2.72, 0.565, 0.450, 1.80, 0.76},
+  {128, 128, 1, 2, 0.58, 0.302, 0.288, 3.40, 0.95},
+  {128, 128, 1, 3, 1.95, 0.383, 0.286, 1.69, 0.94},
+  {128, 64, 1, 2, 0.52, 0.203, 0.187, 3.35, 1.01},
+  {64, 64, 1, 3, 0.70, 0.150, 0.128, 3.19, 1.08},
+  {64, 64, 2, 1, 1.34, 0.256, 0.256, 2.63, 2.13},
+  {64, 32, 4, 1, 1.56, 0.313, 0.313, 2.53, 3.63},
+  {32, 32, 4, 1, 1.55, 0.186, 0.186, 2.55, 3.70},
+  {16, 16, 8, 4, 0.00, 0.213, 0.250, 3.75, 0.02},
+};
+static const FwdShape kFwd8[FW_SHAPES] = {
+  {256, 256, 1, 1, 1.86, 0.679, 0.679, 2.96, 0.90},
+  {256, 128, 1, 2, 1.49, 0.591, 0.454, 3.06, 0.77},
+  {128, 128, 1, 2, 0.88, 0.264, 0.279, 3.16, 0.76},
+  {128, 128, 1, 3, 1.11, 0.337, 0.279, 2.69, 0.80},
+  {128, 64, 1, 2, 1.01, 0.133, 0.196, 2.96, 0.77},
+  {64, 64, 1, 3, 1.09, 0.133, 0.128, 2.92, 0.70},
+  {64, 64, 2, 1, 1.89, 0.238, 0.238, 2.17, 0.44},
+  {64, 32, 4, 1, 2.95, 0.305, 0.305, 1.26, 1.71},
+  {32, 32, 4, 1, 1.74, 0.151, 0.151, 2.49, 3.42},
+  {16, 16, 8, 4, 0.00, 0.134, 0.264, 3.74, 0.56},
+};
+
+static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
+  const FwdShape* tab = fp8 ? kFwd8 : kFwd16;
+  const int64_t steps = I / (fp8 ? 128 : 64);
+  const double out_us = (double)T * (double)O * 2.0 / 5e6;
+  int best = FW_256;
+  double best_t = 1e30;
+  for (int c = 0; c < FW_SHAPES; c++) {
+    const FwdShape& s = tab[c];
+    const int64_t wgs = ((O + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn);
+    if (c != FW_256 && wgs > 0x7FFFFFFFll) continue;                                  // grid size
+    const double nk = (double)((steps + s.kg - 1) / s.kg), fixed = s.base + s.store * out_us;
+    const int64_t n = (wgs + NUM_CU - 1) / NUM_CU, full = n / s.r, rem = n % s.r;      // workgroups on the busiest CU: full rounds of r, and a rest
+    double t = fixed + (double)full * (s.f + nk * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));
+    if (rem) t += s.f + nk * (s.lat > rem * s.thr ? s.lat : rem * s.thr);
+    if (t < best_t) {
+      best_t = t;
+      best = c;
+    }
+    // 256 x 256 tiles whose last round is at most half full: that round as 256 x 128 tiles at 0.7 of the k-step
+    if (c == FW_256 && wgs > NUM_CU && wgs % NUM_CU != 0 && wgs % NUM_CU <= NUM_CU / 2) {
+      t = fixed + (double)(wgs / NUM_CU) * (s.f + nk * s.lat) + s.f + nk * 0.7 * s.lat;
+      if (t < best_t) {
+        best_t = t;
+        best = FW_DUAL;
+      }
+    }
+  }
+  return best;
+}
+
 // Kernel choice for one combination of operand type, output type and amax.
 template <bool FP8, bool ZF8, bool AMAX>
 static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx, const FwdOut& out, const void* vals,
                                const void* meta, int64_t O, hipStream_t s) {
-  // 256 x 256 tiles (8 waves, 3-stage ring) unless the problem has too few of them to occupy the chip;
-  // measured faster than 256 x 128 even at 1.5 rounds of tiles (3072 x 8192 outputs: 33.6 vs 36.4 us)
-  int64_t big_tiles = ((O + 255) / 256) * ((T + 255) / 256);
-  int64_t rem = big_tiles % NUM_CU;
-  if (big_tiles > NUM_CU && rem > 0 && rem <= NUM_CU / 2) {
-    // whole rounds of 256 x 256 tiles, then the remainder as twice as many 256 x 128 tiles
-    launch_fwd_dual<FP8, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, (int)(big_tiles - rem), s);
-  } else if (big_tiles >= 128) {
-    launch_fwd_pipe<FP8, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s);
-  } else if (((O + 255) / 256) * ((T + 127) / 128) < 32) {
-    // tiny problems: 128 x 64 tiles by one wave each, eight times as many workgroups (512 x 256 outputs: 14.1 vs 17.3 us)
-    launch_fwd_cfg<FP8, 1, 1, 2, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s);
-  } else {
-    launch_fwd_cfg<FP8, 2, 2, 2, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s);
+  const int cfg = fwd_choice(FP8, T, O, I);
+#define FT(WM, WN, MT, NT, KG, NS) launch_fwd_tile<FP8, WM, WN, MT, NT, KG, NS, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s)
+  switch (cfg) {
+    case FW_DUAL: {
+      const int64_t big_tiles = ((O + 255) / 256) * ((T + 255) / 256);
+      launch_fwd_dual<FP8, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, (int)(big_tiles - big_tiles % NUM_CU), s);
+      break;
+    }
+    case FW_256: launch_fwd_pipe<FP8, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
+    case FW_256x128: FT(2, 2, 4, 2, 1, 2); break;
+    case FW_128_R2: FT(2, 2, 2, 2, 1, 3); break;
+    case FW_128_R3: FT(2, 2, 2, 2, 1, 2); break;
+    case FW_128x64: FT(2, 2, 2, 1, 1, 4); break;
+    case FW_64: FT(2, 2, 1, 1, 1, 4); break;
+    case FW_64_KG2: FT(2, 2, 1, 1, 2, 4); break;
+    case FW_64x32_KG4: FT(2, 1, 1, 1, 4, 4); break;
+    case FW_32_KG4: FT(1, 1, 1, 1, 4, 4); break;
+    default: launch_fwd_skinny<FP8, 1, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
   }
+#undef FT
 }
 
 hipError_t launch_linear_fwd(const void* X, int64_t T, int64_t I, int64_t ldx, int dtype, float scale,

@@ -2,6 +2,7 @@
 are dealt out to groups of waves) inside a round of the groups: every element against the CPU oracle."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import linear as OL
 from oracle import projection as OP
@@ -46,3 +47,48 @@ def test_linear_dgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
     assert rel_err(got, ref) <= TOL.get(dtype, 6e-2)
     # operands are identical on both sides: only float32 accumulation order and the bf16 output rounding differ
     assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + np.max(np.abs(ref)) * 1e-4)
+
+
+FWD_TILES = [
+    ("bf16", 5, 264, 1280), ("e4m3", 21, 272, 2432),             # 16 x 16, k-steps dealt to eight waves (19 or 20 of them)
+    ("bf16", 82, 1448, 320), ("e4m3", 146, 848, 640),            # 32 x 32, four groups, an incomplete round
+    ("bf16", 76, 2776, 640), ("e4m3", 71, 3472, 896),            # 64 x 32, four groups
+    ("bf16", 978, 240, 192), ("e4m3", 978, 240, 128),            # 64 x 64
+    ("bf16", 4754, 88, 832), ("e4m3", 602, 352, 384),            # 64 x 64, two groups
+    ("bf16", 8359, 88, 128), ("e4m3", 8389, 80, 256),            # 128 x 64
+    ("bf16", 16872, 88, 384), ("e4m3", 19387, 80, 512),          # 128 x 128, three slots
+    ("bf16", 8885, 152, 128), ("e4m3", 8359, 80, 128),           # 128 x 128, two slots
+    ("bf16", 19747, 536, 128), ("e4m3", 19747, 528, 128),        # 256 x 128, two workgroups per CU
+    ("bf16", 35341, 168, 640), ("e4m3", 25239, 400, 512),        # 256 x 256
+    ("bf16", 22320, 696, 896), ("e4m3", 16503, 1200, 768),       # whole rounds of 256 x 256 tiles and halves of them
+]
+
+
+@pytest.mark.parametrize("dtype,T,O,I", FWD_TILES)
+def test_linear_fwd_tiles(sste, dtype, T, O, I):  # noqa: F811
+    """bf16 output; then, where the format allows it, the e4m3 output with its largest magnitude and the fused activation, held to
+    the bf16 output of the same call (which the first comparison has tied to the oracle)."""
+    xc, xs, X = operand(sste, WL.activations(WL.WORKLOADS[1], 0, T=T, I=I)[0], dtype)
+    rv, rm, ws, vals, meta = packed_weight(sste, O, I, dtype)
+    ref = OL.linear_fwd(xc, rv, rm, dtype, xs, ws)
+    Z = torch.full((T, O), 7.0, dtype=torch.bfloat16, device="cuda")
+    sste.linear_fwd(X, vals, meta, O, dt(sste, dtype), float(xs), float(ws), Z=Z)
+    got = z_to_f64(Z)
+    assert rel_err(got, ref) <= TOL[dtype]
+    assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + np.max(np.abs(ref)) * 1e-4)
+
+    H, A, _ = sste.linear_fwd_act(X, vals, meta, O, dt(sste, dtype), float(xs), float(ws))
+    assert torch.equal(H, Z)
+    want = torch.nn.functional.gelu(H.float(), approximate="tanh")
+    assert float((A.float() - want).abs().max()) <= 2.0 ** -8 * float(want.abs().max())
+    if O % 16 == 0:
+        zs = float(np.abs(ref).max()) / 448.0
+        Z8, amax = sste.linear_fwd_ex(X, vals, meta, O, dt(sste, dtype), float(xs), float(ws), sste.F8E4M3, zs)
+        assert abs(float(amax) - np.abs(ref).max()) <= 1e-4 * np.abs(ref).max()
+        dec = Z8.view(torch.float8_e4m3fn).float() * zs
+        # half a step of the 3-bit significand around the float value, which the bf16 output is within half a bf16 step of
+        assert bool(((dec - Z.float()).abs() <= Z.float().abs() * (2.0 ** -4 + 2.0 ** -8) + zs * 2.0 ** -9).all())
+        A8, amax8 = sste.linear_fwd_act(X, vals, meta, O, dt(sste, dtype), float(xs), float(ws), a_dtype=sste.F8E4M3, a_scale=zs)[1:]
+        assert abs(float(amax8) - float(want.abs().max())) <= 1e-5 * float(want.abs().max())
+        dec = A8.view(torch.float8_e4m3fn).float() * zs
+        assert bool(((dec - want).abs() <= want.abs() * (2.0 ** -4 + 1e-5) + zs * 2.0 ** -9).all())
