@@ -1,9 +1,19 @@
-"""ctypes binding of libsste.so: argument marshalling only."""
+"""Binding of libsste.so: argument marshalling only.
+
+The functions below go through ctypes and define the argument rules.  The ones a loop calls for every layer are replaced at the
+end of the file by the functions of the same names of ``_marshal`` (ext/marshal.cpp), which read the arguments natively and
+hand everything out of the ordinary back to the Python definition.
+"""
 import ctypes
 import os
 from typing import Optional, Tuple
 
 import torch
+
+try:
+    from . import _marshal
+except ImportError:            # not built: every call takes the Python definition
+    _marshal = None
 
 BF16 = 0
 F8E4M3 = 1
@@ -82,6 +92,8 @@ def library() -> ctypes.CDLL:
     for name in ("sste_project_pack", "sste_sgd_project_pack", "sste_sgd_project_pack_batch_prepare", "sste_sgd_project_pack_batch", "sste_project_pack_batch_prepare", "sste_project_pack_batch", "sste_linear_fwd", "sste_linear_dgrad",
                  "sste_linear_wgrad", "sste_mvue_materialize", "sste_compute_beta", "sste_flip_count", "sste_cast_fp8"):
         getattr(lib, name).restype = ci
+    if _marshal is not None:
+        _marshal.bind({name: ctypes.cast(getattr(lib, name), vp).value for name in _NATIVE_ENTRY_POINTS}, _PYTHON, SsteError)
     _lib = lib
     return lib
 
@@ -202,6 +214,9 @@ class PackBatch:
 
     def launch(self):
         """sste_project_pack_batch on the current stream of the tensors' device."""
+        if _marshal is not None and self.n > 0:
+            _marshal.pack_batch_launch(self.table, self.n, self.total_blocks, self.val_dtype)
+            return self.vals, self.metas
         _check(library().sste_project_pack_batch(_ptr(self.table), self.n, self.total_blocks, self.val_dtype,
                                                  _stream(self.table)))
         return self.vals, self.metas
@@ -252,6 +267,9 @@ class UpdateBatch:
 
     def launch(self, alpha: float):
         """sste_sgd_project_pack_batch on the current stream of the tensors' device."""
+        if _marshal is not None and self.n > 0:
+            _marshal.update_batch_launch(self.table, self.n, self.total_blocks, self.w_dtype, self.val_dtype, alpha)
+            return self.vals, self.metas
         _check(library().sste_sgd_project_pack_batch(_ptr(self.table), self.n, self.total_blocks, self.w_dtype,
                                                      self.val_dtype, alpha, _stream(self.table)))
         return self.vals, self.metas
@@ -466,3 +484,15 @@ def timing_end():
     n = (ctypes.c_int * len(KERNEL_NAMES))()
     _check(library().sste_timing_end(ms, n))
     return {name: (float(ms[i]), int(n[i])) for i, name in enumerate(KERNEL_NAMES)}
+
+
+# ---- native marshalling of the per-layer calls -------------------------------------------------------------
+_PYTHON = {f.__name__: f for f in (project_pack, sgd_project_pack, linear_fwd, linear_fwd_ex, linear_fwd_act, linear_dgrad, linear_dgrad_act,
+                                   linear_wgrad, cast_fp8)}
+_NATIVE_ENTRY_POINTS = ("sste_project_pack_gamma", "sste_sgd_project_pack", "sste_linear_fwd_ex", "sste_linear_fwd_act", "sste_linear_dgrad_act",
+                        "sste_linear_wgrad_at", "sste_wgrad_workspace_bytes", "sste_cast_fp8", "sste_project_pack_batch",
+                        "sste_sgd_project_pack_batch", "sste_last_error")
+if _marshal is not None:
+    _marshal.bind({}, _PYTHON, SsteError)     # the library's addresses follow when it is loaded, on the first call
+    for _name in _PYTHON:
+        globals()[_name] = getattr(_marshal, _name)
