@@ -298,12 +298,12 @@ float sste_amax_history_push(sste_amax_history* h, float amax, float format_max)
  * Weight-gradient GEMM with the output gradient sparsified 2:4 by the minimum-variance unbiased
  * estimator (Sec. 5.1: grad_W = MVUE(grad_Z^T) X).
  *
- * Which kernels run: problems with T >= 2048, O >= 256 and I >= 256 (every layer of the GPT-2 workloads)
- * sparsify dY ONCE into the workspace (a packed 2:4 operand in the format above, rows = channels,
- * columns = tokens), run a sparse GEMM on it that is split over the token axis, and sum the splits in a
- * fixed order.  Smaller problems sparsify inside the GEMM's operand load (one kernel, the workspace only
- * holds split partial sums, if any).  The result is the same function of (dY, X, seed, offset) on
- * either path.
+ * Which kernels run: problems with T >= 2048, O >= 256 and I >= 256 (every layer of the GPT-2 workloads),
+ * and shorter or narrower ones large enough to gain from it, sparsify dY ONCE into the workspace (a packed
+ * 2:4 operand in the format above, rows = channels, columns = tokens) and run a sparse GEMM on it; where
+ * the token axis is split over workgroups to fill the chip, the splits are summed in a fixed order.  Small
+ * problems sparsify inside the GEMM's operand load (one kernel, no workspace).  The result is the same
+ * function of (dY, X, seed, offset) on either path.
  *
  *   dW (+)= scale * MVUE(dY^T; seed, offset) * X,   scale = dy_scale * x_scale (times 2 for the 8-bit
  *   formats, whose sparsified operand is stored halved), float32 accumulation, dW float32.

@@ -1,24 +1,23 @@
 // Weight-gradient path of the S-STE linear layer (paper Sec. 5.1): grad_W = MVUE(grad_Z^T) X.
 //
-// Large problems run in three kernels on the caller's stream:
+// Most problems run in two or three kernels on the caller's stream:
 //   1. k_mvue_pack: the estimator is applied once per group of four tokens and the result is written
 //      to the workspace as a packed 2:4 operand in sparse-MFMA fragment order (the format of
 //      include/sste.h with rows = output channels, columns = tokens).  It streams dY once: at about
-//      90 vector instructions per group (three of them half-rate 32-bit multiplies of the hash) the
-//      bf16 kernel runs at the rate of a plain copy, the e4m3 kernel (twice the groups per byte) is
-//      bound by the vector pipe.
-//   2. k_wgrad_gemm: sparse MFMA GEMM, rows = channels o, columns = input features i, contraction =
-//      tokens, split over the token axis.  The packed operand is loaded like the packed weight of the
+//      85 vector instructions per group (bf16; 70 for 8-bit types) the bf16 kernel runs at the rate of a
+//      plain copy, the 8-bit kernel (twice the groups per byte) is bound by the vector pipe.
+//   2. k_wgrad_gemm (large tiles) or k_wgrad_tile (small ones): sparse MFMA GEMM, rows = channels o, columns =
+//      input features i, contraction = tokens.  The packed operand is loaded like the packed weight of the
 //      forward GEMM; X arrives with the contraction index strided (X is [t][i]) and its fragments are
-//      read with the transposing LDS load (ds_read_b64_tr_b16 / _b8).  Tile shape and split count are
-//      chosen per problem (wgrad_plan).
-//   3. k_wgrad_reduce: sums the splits in a fixed order (bitwise reproducible) and applies the scale.
+//      read with the transposing LDS load (ds_read_b64_tr_b16 / _b8).
+//   3. where the token axis is split to fill the chip, k_wgrad_reduce: sums the splits in a fixed order
+//      (bitwise reproducible) and applies the scale.
+// Tile shape and split count are chosen per problem (make_wgrad_plan).  Small tiles fill the chip without a split where large ones
+// would need several: 2112 tokens, 1544 x 832, bf16: 14.1 + 4.4 us (256 x 192 tiles, three splits and their sum) -> 12.9 us (128 x 64).
 // Why not fuse the estimator into the GEMM's operand load everywhere: a GEMM tile that is N columns
-// wide re-derives every group I / N times.  With a 128-wide tile that is 6 to 40 times per group and
-// the vector pipe, not the matrix pipe or HBM, sets the time (measured: 176 us fused against 55 us
-// here for the 3072 x 768 layer at 8192 tokens; on the 5120 x 1280 layer a 256-wide tile would issue
-// five times the pre-pass's vector work, about 280 us against the 110 us of the whole GEMM).  The fused kernel (gemm_wgrad_fused.hip) is kept for
-// small problems, where one launch and no workspace matter more.
+// wide re-derives every group I / N times, and the vector pipe, not the matrix pipe or HBM, sets the time (on the 5120 x 1280 layer
+// a 256-wide tile would issue five times the pre-pass's vector work, about 280 us against the 110 us of the whole GEMM).  The fused
+// kernel (gemm_wgrad_fused.hip) is kept for small problems, where one launch and no workspace matter more.
 #include "common.h"
 #include "mvue_device.h"
 
@@ -27,133 +26,145 @@
 
 namespace sste {
 
-hipError_t launch_wgrad_fused(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X, int64_t I,
-                              int64_t ldx, RngKey key, int splits, int steps_per_split, float scale, int accumulate,
-                              float* out, int64_t ld_out, int64_t split_stride, hipStream_t s);
+hipError_t launch_wgrad_fused(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X, int64_t I, int64_t ldx,
+                              RngKey key, float scale, int accumulate, float* dW, int64_t lddw, hipStream_t s);
 
 namespace {
 constexpr int NUM_CU = 256;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
-__device__ __forceinline__ uint32_t comp4(const uint4& v, int c) { return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w)); }
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------------------
-// 1. estimator -> packed operand.  One workgroup: one k-step (64 / 128 tokens) x 128 channels.
-template <bool FP8, bool BF8>
-__global__ void __launch_bounds__(256)
+// 1. estimator -> packed operand.  One workgroup: one k-step (64 / 128 tokens) x BC channels.  A lane works on the two groups of eight
+// consecutive tokens for VB bytes of channels, so that each of its results is a whole metadata byte and a 4-byte (bf16: 8-byte) piece
+// of the packed values.  Measured against one group per lane in four rows of 16 bytes: e5m2 32768 x 5120 83 -> 76 us, e4m3 3200 x 1552
+// 8.4 -> 6.6, bf16 16384 x 4096 41.2 -> 40.2.
+template <bool FP8, int BC, int VB>
+constexpr int mvue_threads() { return (FP8 ? 128 : 64) / 8 * BC * (FP8 ? 1 : 2) / VB; }
+
+template <bool FP8, bool BF8, int BC, int VB>
+__global__ void __launch_bounds__((mvue_threads<FP8, BC, VB>()))
 k_mvue_pack(const uint8_t* __restrict__ dY, int64_t T, int64_t O, int64_t lddy_bytes, RngKey key,
             uint8_t* __restrict__ vals, uint8_t* __restrict__ meta) {
   constexpr int EB = FP8 ? 1 : 2;
   constexpr int KS = FP8 ? 128 : 64;              // tokens per k-step
-  constexpr int GROUPS = KS / 4;                  // 16 / 32 token groups per k-step
-  constexpr int CH = 16 / EB;                     // channels per 16-byte chunk: 8 / 16
-  constexpr int OC = 128 / CH;                    // chunks across the 128 channels: 16 / 8
-  constexpr int GPQ = GROUPS / 4;                 // groups per lane quarter: 4 / 8
+  constexpr int NT = mvue_threads<FP8, BC, VB>();
+  constexpr int CH = VB / EB, DW = VB / 4;        // channels, dwords per row of a lane
+  constexpr int OC = BC / CH;                     // lanes across the channels
+  constexpr int PPQ = KS / 32;                    // group pairs per lane quarter of the operand: 2 / 4
   constexpr int MBLK = FP8 ? 256 : 128;           // metadata bytes per block
-  // LDS staging, padded against bank conflicts: the lanes of a wave write the same slot of 8 different
-  // blocks (1040-byte block pitch puts them 4 banks apart) and the same group of 8 or 16 different
-  // channels (a pitch of GROUPS + 4 bytes spreads those over the banks).
-  constexpr int VPITCH = 1024 + 16, NPITCH = GROUPS + 4;
-  __shared__ __align__(16) uint8_t sV[8 * VPITCH];
-  __shared__ __align__(16) uint8_t sN[128 * NPITCH];
+  // LDS staging in the operand's own order, the blocks of 16 channels padded so that the lanes of a wave, which write the same place of
+  // different blocks, are spread over the banks
+  constexpr int VPITCH = 1024 + 16, MPITCH = MBLK + (FP8 ? 16 : 32);
+  __shared__ __align__(16) uint8_t sV[BC / 16 * VPITCH];
+  __shared__ __align__(16) uint8_t sM[BC / 16 * MPITCH];
 
   const int tid = threadIdx.x;
-  const int kg = tid / OC, oc = tid % OC;
+  const int kp = tid / OC, oc = tid % OC;         // group pair of the k-step, lane across the channels
   const int64_t s = blockIdx.y, steps = T / KS;
-  const int64_t o0 = (int64_t)blockIdx.x * 128;
+  const int64_t o0 = (int64_t)blockIdx.x * BC;
   const int64_t och = o0 + (int64_t)oc * CH;
 
-  uint4 rdy[4];
+  uint32_t rdy[8][DW];
+#pragma unroll
+  for (int r = 0; r < 8; r++)
+#pragma unroll
+    for (int w = 0; w < DW; w++) rdy[r][w] = 0;
   if (och < O) {
-    const uint8_t* p = dY + (s * KS + 4 * kg) * lddy_bytes + och * EB;
+    typedef __attribute__((__vector_size__(VB))) uint32_t row_t;
+    const uint8_t* p = dY + (s * KS + 8 * kp) * lddy_bytes + och * EB;
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      i32x4 t = __builtin_nontemporal_load((const i32x4*)(p + r * lddy_bytes));
-      rdy[r] = make_uint4((uint32_t)t[0], (uint32_t)t[1], (uint32_t)t[2], (uint32_t)t[3]);
+    for (int r = 0; r < 8; r++) {
+      const row_t t = __builtin_nontemporal_load((const row_t*)(p + r * lddy_bytes));
+#pragma unroll
+      for (int w = 0; w < DW; w++) rdy[r][w] = t[w];
     }
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; r++) rdy[r] = make_uint4(0, 0, 0, 0);
   }
-  // Group ids of this lane: gid_base + e.  O and och are multiples of CH, so gid_base is one too and the
+  // Group ids of this lane: gid_a + e and gid_b + e.  O and och are multiples of CH, so both are too and the
   // CH consecutive ids share their high word (no carry out of the low word inside the piece).
-  const uint64_t gid_base = (key.first_group + (uint64_t)(s * GROUPS + kg)) * (uint64_t)O + (uint64_t)och;
-  const uint32_t gid_lo0 = (uint32_t)gid_base;
-  const uint32_t hi_term = (uint32_t)(gid_base >> 32) * 0x9E3779B9u;
-  const int q = kg / GPQ, g = kg % GPQ;
+  const uint64_t gid_a = (key.first_group + (uint64_t)(s * (KS / 4) + 2 * kp)) * (uint64_t)O + (uint64_t)och, gid_b = gid_a + (uint64_t)O;
+  const uint32_t hi_a = (uint32_t)(gid_a >> 32) * 0x9E3779B9u, hi_b = (uint32_t)(gid_b >> 32) * 0x9E3779B9u;
+  const int q = kp / PPQ, gp = kp % PPQ;
   // 8-bit: the four token rows' dwords of four channels, transposed 4 x 4 bytes at a time (eight byte permutes
-  // for four groups): grp[k] holds channel 4 (e / 4) + k with token 0 in byte 0
-  uint32_t grp[4] = {0, 0, 0, 0};
+  // for four groups): grp[h][k] holds channel 4 (e / 4) + k with the group's first token in byte 0
+  uint32_t grp[2][4] = {};
 #pragma unroll
   for (int e = 0; e < CH; e++) {
-    uint32_t x = draw_u32_pre(key.k0, key.k1, gid_lo0 + (uint32_t)e, hi_term);
-    uint32_t nib, v;
-    int c = oc * CH + e;                           // channel inside the tile
-    uint8_t* slot = sV + (c >> 4) * VPITCH + (16 * q + (c & 15)) * 16;
+    const uint32_t xa = draw_u32_pre(key.k0, key.k1, (uint32_t)gid_a + (uint32_t)e, hi_a);
+    const uint32_t xb = draw_u32_pre(key.k0, key.k1, (uint32_t)gid_b + (uint32_t)e, hi_b);
+    const int c = oc * CH + e, row = 16 * q + (c & 15);                // channel inside the tile; row of its block
+    uint8_t* const slot = sV + (c >> 4) * VPITCH + row * 16;
+    uint32_t m;
     if (FP8) {
       if ((e & 3) == 0) {
-        uint32_t w0 = comp4(rdy[0], e >> 2), w1 = comp4(rdy[1], e >> 2), w2 = comp4(rdy[2], e >> 2), w3 = comp4(rdy[3], e >> 2);
-        uint32_t a01 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), b01 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
-        uint32_t a23 = __builtin_amdgcn_perm(w3, w2, 0x05010400u), b23 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
-        grp[0] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
-        grp[1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
-        grp[2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
-        grp[3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          const uint32_t w0 = rdy[4 * h][e >> 2], w1 = rdy[4 * h + 1][e >> 2], w2 = rdy[4 * h + 2][e >> 2], w3 = rdy[4 * h + 3][e >> 2];
+          const uint32_t a01 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), b01 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
+          const uint32_t a23 = __builtin_amdgcn_perm(w3, w2, 0x05010400u), b23 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+          grp[h][0] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+          grp[h][1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+          grp[h][2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+          grp[h][3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+        }
       }
-      v = mvue_group_f8<BF8>(grp[e & 3], x, nib);
-      *(uint16_t*)(slot + 2 * g) = (uint16_t)v;
+      *(uint32_t*)(slot + 4 * gp) = mvue_pair_f8<BF8>(grp[0][e & 3], grp[1][e & 3], xa, xb, m);
     } else {
-      uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-      uint32_t lo = __builtin_amdgcn_perm(comp4(rdy[1], e >> 1), comp4(rdy[0], e >> 1), sel);
-      uint32_t hi = __builtin_amdgcn_perm(comp4(rdy[3], e >> 1), comp4(rdy[2], e >> 1), sel);
-      v = mvue_group_bf16(lo, hi, x, nib);
-      *(uint32_t*)(slot + 4 * g) = v;
+      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      uint2 v;
+      uint32_t ma, mb;
+      v.x = mvue_group_bf16(__builtin_amdgcn_perm(rdy[1][e >> 1], rdy[0][e >> 1], sel), __builtin_amdgcn_perm(rdy[3][e >> 1], rdy[2][e >> 1], sel), xa, ma);
+      v.y = mvue_group_bf16(__builtin_amdgcn_perm(rdy[5][e >> 1], rdy[4][e >> 1], sel), __builtin_amdgcn_perm(rdy[7][e >> 1], rdy[6][e >> 1], sel), xb, mb);
+      *(uint2*)(slot + 8 * gp) = v;
+      m = 0xEEu - (ma + (mb << 4));
     }
-    sN[c * NPITCH + kg] = (uint8_t)(nib << (4 * (kg & 1)));   // pre-shifted: neighbours are OR-ed below
+    sM[(c >> 4) * MPITCH + row * PPQ + gp] = (uint8_t)m;
   }
   __syncthreads();
 
   const int64_t rb0 = o0 / 16, rbn = (O + 15) / 16;
 #pragma unroll
-  for (int it = 0; it < 2; it++) {
-    int ci = tid + 256 * it, rb = ci >> 6, sl = ci & 63;     // block and slot inside the tile
-    if (rb0 + rb < rbn) {
-      int64_t blk = (rb0 + rb) * steps + s;
-      *(uint4*)(vals + blk * 1024 + sl * 16) = *(const uint4*)(sV + rb * VPITCH + sl * 16);
-      int c = rb * 16 + (sl & 15), qq = sl >> 4;
-      if (FP8) {
-        uint32_t wx = *(const uint32_t*)(sN + c * NPITCH + 8 * qq), wy = *(const uint32_t*)(sN + c * NPITCH + 8 * qq + 4);
-        uint32_t a = wx | (wx >> 8), b = wy | (wy >> 8);
-        uint32_t idx = (a & 0xFFu) | ((a >> 8) & 0xFF00u) | ((b & 0xFFu) << 16) | ((b << 8) & 0xFF000000u);
-        *(uint32_t*)(meta + blk * MBLK + sl * 4) = idx;
-      } else {
-        uint32_t w = *(const uint32_t*)(sN + c * NPITCH + 4 * qq);
-        uint32_t a = w | (w >> 8);
-        *(uint16_t*)(meta + blk * MBLK + sl * 2) = (uint16_t)((a & 0xFFu) | ((a >> 8) & 0xFF00u));
-      }
-    }
+  for (int ci = tid; ci < BC * 4; ci += NT) {
+    const int rb = ci >> 6, sl = ci & 63;         // block and slot inside the tile
+    if (rb0 + rb < rbn) *(uint4*)(vals + ((rb0 + rb) * steps + s) * 1024 + sl * 16) = *(const uint4*)(sV + rb * VPITCH + sl * 16);
+  }
+#pragma unroll
+  for (int ci = tid; ci < BC * MBLK / 256; ci += NT) {
+    const int rb = ci / (MBLK / 16), sl = ci % (MBLK / 16);
+    if (rb0 + rb < rbn) *(uint4*)(meta + ((rb0 + rb) * steps + s) * MBLK + sl * 16) = *(const uint4*)(sM + rb * MPITCH + sl * 16);
   }
 }
 
 static void launch_mvue_pack(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, RngKey key, void* vals,
                              void* meta, hipStream_t s, int timed_kind) {
-  bool fp8 = dtype != SSTE_BF16;
-  int ks = fp8 ? 128 : 64;
-  dim3 grid((unsigned)((O + 127) / 128), (unsigned)(T / ks)), block(256);
-#define MP_CASE(F8, B8)                                                                                                  \
+  const bool fp8 = dtype != SSTE_BF16;
+  const int ks = fp8 ? 128 : 64;
+  // Many short-lived lanes fill the chip on small problems and keep each lane's chain of estimators short; large ones stream better with
+  // wider rows per lane.  Crossover near 2^25 elements (bf16 16384 x 1280: 16.9 against 17.4 us, 16384 x 4096: 42.9 against 40.2;
+  // e4m3 3200 x 1552: 6.6 against 7.6, 32768 x 3840: equal, 32768 x 5120: 84 against 76).
+  const bool small = !product_reaches(T, O, 1ll << 25);
+#define MP_CASE(F8, B8, BC, VB)                                                                                          \
   do {                                                                                                                   \
+    const dim3 grid((unsigned)((O + BC - 1) / BC), (unsigned)(T / ks)), block(mvue_threads<F8, BC, VB>());               \
     if (timed_kind >= 0)                                                                                                 \
-      SSTE_LAUNCH(timed_kind, (k_mvue_pack<F8, B8>), grid, block, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key,   \
+      SSTE_LAUNCH(timed_kind, (k_mvue_pack<F8, B8, BC, VB>), grid, block, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
                   (uint8_t*)vals, (uint8_t*)meta);                                                                       \
     else                                                                                                                 \
-      hipLaunchKernelGGL((k_mvue_pack<F8, B8>), grid, block, 0, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key,     \
+      hipLaunchKernelGGL((k_mvue_pack<F8, B8, BC, VB>), grid, block, 0, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
                          (uint8_t*)vals, (uint8_t*)meta);                                                                \
   } while (0)
-  if (dtype == SSTE_F8E5M2) MP_CASE(true, true);
-  else if (fp8) MP_CASE(true, false);
-  else MP_CASE(false, false);
+#define MP_TYPE(BC, VB)                                          \
+  do {                                                           \
+    if (dtype == SSTE_F8E5M2) MP_CASE(true, true, BC, VB);       \
+    else if (fp8) MP_CASE(true, false, BC, VB);                  \
+    else MP_CASE(false, false, BC, VB);                          \
+  } while (0)
+  if (small) MP_TYPE(64, 4);
+  else MP_TYPE(128, 8);
+#undef MP_TYPE
 #undef MP_CASE
 }
 
@@ -399,6 +410,238 @@ k_wgrad_gemm(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta,
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// 2b. the same GEMM for small and middle problems: 32 WM MT channels x 32 WN NT features by KG groups of WM x WN waves on the 32 x 32
+// sparse instructions, group kg taking the k-steps kg, kg + KG, ... of its split through LDS slots of its own; the groups' sums are
+// added inside the workgroup, so a problem with few tiles needs neither split partials in memory nor the kernel that sums them.
+// Structure as k_linear_fwd_tile.  X tile in LDS: one row per token, 32 NT WN features; the block of 32 features (64 B bf16, 32 B 8-bit)
+// number u of token row r lies at position u ^ key(r), so that the rows and columns one transposing read gathers per 32 lanes (4 rows
+// x 64 B, 8 rows x 32 B) cover all 64 banks once.
+template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS>
+constexpr int wgrad_tile_smem() {
+  constexpr int NWG = WM * WN, MB = FP8 ? 16 : 8;
+  constexpr int LM = (32 * WM * MT * MB / 256 + NWG - 1) / NWG;
+  constexpr int RING = KG * NS * (32 * WM * MT * 64 + NWG * LM * 256 + (FP8 ? 128 : 128) * 32 * WN * NT);
+  constexpr int RED = (KG - 1) * NWG * MT * NT * 4096;
+  return RING > RED ? RING : RED;
+}
+
+template <bool FP8, bool BF8, int WM, int WN, int MT, int NT, int KG, int NS>
+__global__ void __launch_bounds__(64 * WM * WN * KG, 1)
+k_wgrad_tile(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int64_t O, int64_t total_steps,
+             const uint8_t* __restrict__ X, int64_t I, int64_t ldx_bytes, int steps_per_split, float scale,
+             int accumulate, float* __restrict__ out, int64_t ld_out, int64_t split_stride, int m_tiles, int n_tiles,
+             int features_fastest) {
+  constexpr int NWG = WM * WN;
+  constexpr int BM = 32 * WM * MT, BN = 32 * WN * NT;
+  constexpr int EB = FP8 ? 1 : 2, KS = FP8 ? 128 : 64;
+  constexpr int MB = FP8 ? 16 : 8, MBLK = 16 * MB;
+  constexpr int ROWB = BN * EB;                     // LDS bytes per token row
+  constexpr int BSLOT = KS * ROWB;                  // 128 BN for both types
+  constexpr int LA = BM / 16 / NWG, LB = BSLOT / 1024 / NWG, LM = (BM * MB / 256 + NWG - 1) / NWG;   // loads per wave and k-step
+  constexpr int LPW = LA + LB + LM;
+  constexpr int A_BYTES = BM * 64, M_BYTES = NWG * LM * 256, SLOT = A_BYTES + M_BYTES + BSLOT;
+  constexpr int UB = 32 * EB, UNITS = ROWB / UB;    // a block of 32 features; blocks per row
+  constexpr int CPR = ROWB / 16;                    // 16-byte chunks per row
+  static_assert(LA >= 1 && LB >= 1 && ROWB <= 256, "tile shape");
+  __shared__ __align__(1024) uint8_t smem[wgrad_tile_smem<FP8, WM, WN, MT, NT, KG, NS>()];
+  auto key = [](int r) { return (r / (256 / ROWB)) % UNITS; };
+
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int tiles = m_tiles * n_tiles;
+  const int z = logical / tiles, tile = logical % tiles;
+  const int tm = features_fastest ? tile / n_tiles : tile % m_tiles;
+  const int tn = features_fastest ? tile % n_tiles : tile / m_tiles;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = KG > 1 ? wave_all / NWG : 0, wave = KG > 1 ? wave_all % NWG : wave_all;
+  const int wm = wave / WN, wn = wave % WN;
+  const int n = lane & 31, hh = lane >> 5, j = lane & 15, jq = (lane >> 4) & 1;
+  const int64_t o0 = (int64_t)tm * BM, i0 = (int64_t)tn * BN;
+  const int64_t step_begin = (int64_t)z * steps_per_split;
+  const int nsteps = (int)((step_begin + steps_per_split < total_steps ? step_begin + steps_per_split : total_steps) - step_begin);
+  const int nloc = (nsteps + KG - 1) / KG;
+  uint8_t* const ring = smem + kg * NS * SLOT;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)ring;
+
+  const int64_t rblk0 = o0 / 16, rbn = (O + 15) / 16;
+  const int blks_a = (int)((rbn - rblk0) < BM / 16 ? (rbn - rblk0) : BM / 16);
+  const i32x4 ba = rsrc_words(vals + (rblk0 * total_steps + step_begin) * 1024, (uint32_t)((blks_a * total_steps - step_begin) * 1024));
+  const i32x4 bm = rsrc_words(meta + (rblk0 * total_steps + step_begin) * MBLK, (uint32_t)((blks_a * total_steps - step_begin) * MBLK));
+  const int cols_b = (int)((I - i0) < BN ? (I - i0) : BN);
+  const i32x4 bb = rsrc_words(X + step_begin * KS * ldx_bytes + i0 * EB, (uint32_t)(((int64_t)nsteps * KS - 1) * ldx_bytes + cols_b * EB));
+  // packed blocks past the tile's last one and chunks past its last feature fetch nothing: zeros arrive
+  constexpr uint32_t DEAD = 0x80000000u;
+  uint32_t offa[LA], offb[LB], offm[LM];
+#pragma unroll
+  for (int i = 0; i < LA; i++)
+    offa[i] = (LA * wave + i) < blks_a ? (uint32_t)((LA * wave + i) * total_steps * 1024 + lane * 16) : DEAD;
+#pragma unroll
+  for (int i = 0; i < LB; i++) {
+    const int d = 64 * (LB * wave + i) + lane;      // 16-byte chunk of the slot
+    const int r = d / CPR, cs = d % CPR;            // token row inside the k-step, stored chunk
+    const int c = ((cs / (UB / 16)) ^ key(r)) * (UB / 16) + cs % (UB / 16);   // source chunk
+    offb[i] = (c * 16 < cols_b * EB) ? (uint32_t)(r * ldx_bytes + c * 16) : DEAD;
+  }
+#pragma unroll
+  for (int i = 0; i < LM; i++) {
+    const int d = 64 * (LM * wave + i) + lane, blk = d / (MBLK / 4);
+    offm[i] = blk < blks_a ? (uint32_t)(blk * total_steps * MBLK + 4 * (d % (MBLK / 4))) : DEAD;
+  }
+  auto issue = [&](int ls, int slot) {
+    // steps past the last one: the packed operand reads zeros; X reads its last step again (finite values against zeros)
+    const int st = ls * KG + kg;
+    const bool live = st < nsteps;
+    const uint32_t base = lds0 + (uint32_t)slot * SLOT;
+#pragma unroll
+    for (int i = 0; i < LA; i++) dma_b128(ba, base + (LA * wave + i) * 1024, offa[i], live ? (uint32_t)st * 1024u : DEAD);
+#pragma unroll
+    for (int i = 0; i < LM; i++) dma_b32(bm, base + A_BYTES + (LM * wave + i) * 256, offm[i], live ? (uint32_t)st * (uint32_t)MBLK : DEAD);
+    const uint32_t sx = (uint32_t)((live ? st : nsteps - 1) * KS * ldx_bytes);
+#pragma unroll
+    for (int i = 0; i < LB; i++) dma_b128(bb, base + A_BYTES + M_BYTES + (LB * wave + i) * 1024, offb[i], sx);
+  };
+
+  f32x16 acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; m++)
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[m][t][r] = 0.f;
+
+  // fragments of half kk of a k-step.  A as in the forward kernel.  B lane (column n, hh): tokens 8 hh .. and 16 + 8 hh .. of the half's 32
+  // (bf16; 8-bit: 16 hh .. and 32 + 16 hh .. of 64), by transposing reads of 4 (8) token rows x 16 features each.
+  const uint32_t fa_off = (uint32_t)((2 * wm * MT + (n >> 4)) * 1024 + (16 * hh + j) * 16);
+  const uint32_t fm_off = (uint32_t)(A_BYTES + (2 * wm * MT + (n >> 4)) * MBLK + (16 * hh + j) * (MB / 4));
+  uint32_t fb_off[NT][4];                           // + kk * KS / 2 * ROWB (the key does not change: KS / 2 rows are whole periods)
+#pragma unroll
+  for (int t = 0; t < NT; t++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int row = FP8 ? 16 * hh + 8 * (r & 1) + 32 * (r >> 1) + (j >> 1) : 8 * hh + 4 * (r & 1) + 16 * (r >> 1) + (j >> 2);
+      const int in_unit = FP8 ? 16 * jq + 8 * (j & 1) : 32 * jq + 8 * (j & 3);
+      fb_off[t][r] = (uint32_t)(A_BYTES + M_BYTES + row * ROWB + (((wn * NT + t) ^ key(row)) * UB) + in_unit);
+    }
+  uint4 fa[2][MT];
+  uint2 fb[2][NT][4];
+  int fi[2][MT];
+  auto read_frag = [&](int kk, const uint8_t* sl) {
+#pragma unroll
+    for (int m = 0; m < MT; m++) {
+      fa[kk][m] = *(const uint4*)(sl + fa_off + m * 2048 + kk * 512);
+      if (FP8) fi[kk][m] = *(const int*)(sl + fm_off + m * 2 * MBLK + kk * 32 * (MB / 4));
+      else fi[kk][m] = *(const uint16_t*)(sl + fm_off + m * 2 * MBLK + kk * 32 * (MB / 4));
+    }
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const uint8_t* p = sl + fb_off[t][r] + kk * (KS / 2) * ROWB;
+        if (FP8) {
+          const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)p);
+          fb[kk][t][r] = make_uint2((uint32_t)v[0], (uint32_t)v[1]);
+        } else {
+          const bf16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
+          __builtin_memcpy(&fb[kk][t][r], &v, 8);
+        }
+      }
+  };
+  auto mma = [&](int kk) {
+#pragma unroll
+    for (int m = 0; m < MT; m++)
+#pragma unroll
+      for (int t = 0; t < NT; t++) {
+        if (FP8) {
+          i32x4 av;
+          i32x8 bv;
+          __builtin_memcpy(&av, &fa[kk][m], 16);
+          __builtin_memcpy(&bv, &fb[kk][t][0], 32);
+          if (BF8) acc[m][t] = __builtin_amdgcn_smfmac_f32_32x32x64_bf8_fp8(av, bv, acc[m][t], fi[kk][m], 0, 0);
+          else acc[m][t] = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(av, bv, acc[m][t], fi[kk][m], 0, 0);
+        } else {
+          bf16x8 av;
+          bf16x16 bv;
+          __builtin_memcpy(&av, &fa[kk][m], 16);
+          __builtin_memcpy(&bv, &fb[kk][t][0], 32);
+          acc[m][t] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(av, bv, acc[m][t], fi[kk][m], 0, 0);
+        }
+      }
+  };
+
+#pragma unroll
+  for (int k = 0; k < NS; k++) issue(k, k);
+  wait_vmcnt<(NS - 1) * LPW>();
+  __syncthreads();
+  read_frag(0, ring);
+  int slot = 0, slot1 = 1 % NS;
+  for (int s = 0; s < nloc; s++) {
+    read_frag(1, ring + slot * SLOT);
+    mma(0);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<(NS - 2) * LPW>();          // this wave's share of tile s + 1 has landed
+    __syncthreads();                       // ... everybody's; the slot of s has been read
+    read_frag(0, ring + slot1 * SLOT);
+    issue(s + NS, slot);
+    mma(1);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = slot1;
+    slot1 = slot1 == NS - 1 ? 0 : slot1 + 1;
+  }
+  wait_vmcnt<0>();
+
+  if (KG > 1) {
+    // sums of the k-groups: groups 1 .. KG - 1 leave theirs in LDS, lane for lane
+    __syncthreads();
+    if (kg > 0) {
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int g = 0; g < 4; g++)
+            *(float4*)(smem + (((kg - 1) * NWG + wave) * MT * NT + m * NT + t) * 4096 + g * 1024 + lane * 16) =
+                make_float4(acc[m][t][4 * g], acc[m][t][4 * g + 1], acc[m][t][4 * g + 2], acc[m][t][4 * g + 3]);
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int k = 0; k < KG - 1; k++)
+#pragma unroll
+      for (int m = 0; m < MT; m++)
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            const float4 v = *(const float4*)(smem + ((k * NWG + wave) * MT * NT + m * NT + t) * 4096 + g * 1024 + lane * 16);
+            acc[m][t][4 * g] += v.x;
+            acc[m][t][4 * g + 1] += v.y;
+            acc[m][t][4 * g + 2] += v.z;
+            acc[m][t][4 * g + 3] += v.w;
+          }
+  }
+  // lane (n, hh) register 4 g + r of tile (m, t) is element (o + 8 g + 4 hh + r, i + n): 128 contiguous bytes per row
+  float* dst = out + (int64_t)z * split_stride;
+#pragma unroll
+  for (int m = 0; m < MT; m++)
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+      const int64_t o = o0 + 32 * (wm * MT + m) + 4 * hh, i = i0 + 32 * (wn * NT + t) + n;
+      if (i < I) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          const int64_t row = o + 8 * (r >> 2) + (r & 3);
+          if (row < O) {
+            const float v = acc[m][t][r] * scale;
+            float* p = dst + row * ld_out + i;
+            *p = accumulate ? (*p + v) : v;
+          }
+        }
+      }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // 3. out[o][i] = scale * sum_z ws[z][o][i]  (+ out[o][i]); z ascending: a fixed order.
 __global__ void __launch_bounds__(256)
 k_wgrad_reduce(const float* __restrict__ ws, int splits, int64_t O, int64_t I, float scale, int accumulate,
@@ -433,153 +676,226 @@ k_zero_rows(float* __restrict__ dW, int64_t O, int64_t I, int64_t lddw) {
 // host: path choice, tile and split choice, workspace layout
 struct WgradPlan {
   bool packed;          // true: estimator pre-pass + GEMM on the packed operand; false: fused kernel
-  int mi, ni;           // MFMA tiles per wave of the packed GEMM (workgroup tile 32 mi x 64 ni)
+  int shape;            // tile of the packed GEMM
   int splits;           // token-axis splits
   int steps_per_split;
+  int64_t chunk_steps;  // k-steps the packed path takes at a time (all of them, unless the operand would not fit the built-in scratch)
   size_t vals_bytes, meta_bytes, partial_bytes;   // workspace sections (each a multiple of 256)
+  size_t bytes() const { return vals_bytes + meta_bytes + partial_bytes; }
 };
 
 static size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Time model (microseconds) behind the tile / split choice of the packed GEMM, fitted to timings of the
-// 3072 x 768 (8192 tokens) and 5120 x 1280 (16384 tokens) layers.  One workgroup per CU; a k-step costs
-// about 0.34 + 0.0175 per MFMA tile of the wave (0.90 for 8 x 4, 0.66 for 6 x 3), a workgroup about 4 us
-// of ramp-up and drain, and the split partials are written once and read once at 5.5 TB/s.  The model
-// only has to rank a handful of candidates; it is within 10 % of the measurements it was fitted to.
-static double wgrad_model_us(int64_t O, int64_t I, int64_t steps, int mi, int ni, int64_t s, int64_t* sps_out) {
-  int64_t bm = 32 * mi, bn = 64 * ni;
-  int64_t tiles = ((O + bm - 1) / bm) * ((I + bn - 1) / bn);
-  int64_t sps = (steps + s - 1) / s;
-  int64_t splits = (steps + sps - 1) / sps;
-  int64_t rounds = (tiles * splits + NUM_CU - 1) / NUM_CU;
-  double t_step = 0.34 + 0.0175 * mi * ni;
-  double t = (double)rounds * ((double)sps * t_step + 4.0);
-  double out_bytes = (double)O * (double)I * 4.0;
-  if (splits > 1) t += 2.0 + (double)(2 * splits + 1) * out_bytes / 5.5e6;
-  *sps_out = sps;
+// Tile shapes of the packed GEMM and their time model in microseconds: a workgroup costs F + nk * step with nk its k-steps (each k-group
+// of a workgroup takes a KG-th of its split's) and step = max(lat, r * thr) for r workgroups sharing a CU; R fit a CU, what does not fit
+// runs in further rounds; base + store * (bytes written at 5 TB/s) on top.  Fitted to 760 problems of random size (64 to 32768 tokens,
+// 64 to 5120 channels and features) in all shapes and up to 24 splits: 2 % rms for the large tiles, 5 % for the small ones; the choice
+// costs 1 % against the fastest candidate on average.
+struct WgradShape {
+  int bm, bn, kg, r;
+  double f, lat, thr, base, store;
+};
+enum { WG_256x256, WG_192x192, WG_256x192, WG_128, WG_128_KG2, WG_128x64, WG_64, WG_64_KG2, WG_SHAPES };
+static const WgradShape kWgrad16[WG_SHAPES] = {
+  {256, 256, 1, 1, 6.40, 0.644, 0.144, 3.52, 0.68},
+  {192, 192, 1, 1, 1.58, 0.499, 0.410, 5.51, 0.89},
+  {256, 192, 1, 1, 2.20, 0.568, 0.165, 6.19, 0.80},
+  {128, 128, 1, 2, 0.00, 0.310, 0.280, 6.21, 1.07},
+  {128, 128, 2, 1, 2.84, 0.569, 0.255, 4.07, 1.55},
+  {128, 64, 1, 2, 0.00, 0.211, 0.221, 4.36, 1.35},
+  {64, 64, 1, 3, 0.00, 0.187, 0.153, 3.53, 1.73},
+  {64, 64, 2, 1, 1.88, 0.006, 0.319, 1.93, 2.38},
+};
+static const WgradShape kWgrad8[WG_SHAPES] = {
+  {256, 256, 1, 1, 7.49, 0.689, 0.587, 1.95, 0.69},
+  {192, 192, 1, 1, 1.73, 0.243, 0.544, 5.34, 0.85},
+  {256, 192, 1, 1, 3.50, 0.056, 0.609, 4.79, 0.72},
+  {128, 128, 1, 2, 0.07, 0.349, 0.313, 5.90, 1.14},
+  {128, 128, 2, 1, 2.90, 0.664, 0.171, 3.76, 1.49},
+  {128, 64, 1, 2, 0.40, 0.247, 0.265, 3.76, 1.27},
+  {64, 64, 1, 3, 0.00, 0.178, 0.201, 3.45, 1.45},
+  {64, 64, 2, 1, 1.94, 0.055, 0.394, 1.78, 1.95},
+};
+
+static double wgrad_model_us(const WgradShape& w, int64_t O, int64_t I, int64_t sps, int64_t splits) {
+  const int64_t wgs = ((O + w.bm - 1) / w.bm) * ((I + w.bn - 1) / w.bn) * splits;
+  const double nk = (double)((sps + w.kg - 1) / w.kg), out_us = (double)O * (double)I * 4.0 / 5e6;
+  const int64_t n = (wgs + NUM_CU - 1) / NUM_CU, full = n / w.r, rem = n % w.r;      // workgroups on the busiest CU: full rounds of r, and a rest
+  double t = w.base + w.store * out_us * (double)splits + (double)full * (w.f + nk * (w.lat > w.r * w.thr ? w.lat : w.r * w.thr));
+  if (rem) t += w.f + nk * (w.lat > rem * w.thr ? w.lat : rem * w.thr);
+  if (splits > 1) {
+    const double red = 2.0 + 0.61 * (double)(splits + 1) * out_us;
+    t += (red > 4.0 ? red : 4.0) + 0.1 * (double)splits;
+  }
   return t;
 }
 
-// Tile shape / split count forced by sste_wgrad_plan_override (0 = automatic choice).
-static std::atomic<int> g_force_mi{0}, g_force_ni{0}, g_force_splits{0};
+// The two ways to run a problem, same units: estimator pre-pass (streaming) and a second launch before the packed GEMM; or the fused
+// kernel, whose workgroups fill a CU each and whose time per k-step is the vector pipe's.
+static double mvue_model_us(int64_t T, int64_t O, bool fp8) {
+  const double t = 3.7 + (fp8 ? 0.56e-6 : 0.68e-6) * (double)T * (double)O;
+  return (t > 4.5 ? t : 4.5) + 1.0;
+}
+static double fused_model_us(int64_t steps, int64_t O, int64_t I, bool fp8) {
+  const int64_t wgs = ((O + 15) / 16) * ((I + 63) / 64), rounds = (wgs + NUM_CU - 1) / NUM_CU;
+  const double t = 1.2 + (double)rounds * ((fp8 ? 1.8 : 2.1) + (double)((steps + 3) / 4) * (fp8 ? 1.37 : 0.77));
+  return t > 4.0 ? t : 4.0;
+}
+
+// Tile shape / split count forced by sste_wgrad_plan_override (-1 / 0 = automatic choice).
+static std::atomic<int> g_force_shape{-1}, g_force_splits{0};
 
 bool wgrad_plan_override(int mi, int ni, int splits) {
-  const bool shape_ok = (mi == 0 && ni == 0) || (mi == 8 && ni == 4) || (mi == 6 && ni == 3) || (mi == 8 && ni == 3);
-  if (!shape_ok || splits < 0 || splits > 32) return false;
-  g_force_mi = mi;
-  g_force_ni = ni;
+  int shape;
+  if (mi == 0 && ni == 0) shape = -1;
+  else if (mi == 8 && ni == 4) shape = WG_256x256;
+  else if (mi == 6 && ni == 3) shape = WG_192x192;
+  else if (mi == 8 && ni == 3) shape = WG_256x192;
+  else return false;
+  if (splits < 0 || splits > 32) return false;
+  g_force_shape = shape;
   g_force_splits = splits;
   return true;
 }
 
-static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
+static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
   WgradPlan p{};
-  bool fp8 = dtype != SSTE_BF16;
-  int ks = fp8 ? 128 : 64;
+  const bool fp8 = dtype != SSTE_BF16;
+  const int ks = fp8 ? 128 : 64;
   int64_t steps = T / ks;
-  // the pre-pass pays off once the GEMM tiles would re-derive each group several times and the problem
-  // is large enough to fill the chip; everything else runs the fused kernel
-  p.packed = (T >= 2048) && (O >= 256) && (I >= 256) && !product_reaches(T, O / 16 * 16 + 16, 1ll << 40);
-  p.mi = 8;
-  p.ni = 4;
-  if (steps <= 0) {
-    p.splits = 1;
-    p.steps_per_split = 1;
-    return p;
+  if (steps <= 0 || O == 0 || I == 0 || product_reaches(T, O / 16 * 16 + 16, 1ll << 40)) return p;
+  const int64_t rows = (O + 15) / 16 * 16, all_steps = steps;
+  const int64_t step_vals = rows * 64, step_meta = rows * (ks / 8);        // operand bytes per k-step
+  const bool long_wide = T >= 2048 && O >= 256 && I >= 256;
+  if (!long_wide) {
+    // Callers without a workspace are served from SSTE_NOALLOC_SCRATCH_BYTES, and short or narrow problems never ask for more: theirs
+    // run in chunks of the token axis, each added to the one before, where the operand alone would take three quarters of that.
+    const int64_t most = (int64_t)(SSTE_NOALLOC_SCRATCH_BYTES / 4 * 3) / (step_vals + step_meta);
+    if (most == 0) return p;
+    const int64_t chunks = (steps + most - 1) / most;
+    steps = (steps + chunks - 1) / chunks;
   }
-  if (p.packed) {
-    static const int shapes[3][2] = {{8, 4}, {6, 3}, {8, 3}};
-    const int fmi = g_force_mi, fni = g_force_ni, fs = g_force_splits;
-    double best = 1e30;
-    for (int k = 0; k < 3; k++) {
-      if (fmi && (shapes[k][0] != fmi || shapes[k][1] != fni)) continue;
-      int64_t smax = steps / 8 < 32 ? steps / 8 : 32;
-      if (smax < 1) smax = 1;
-      for (int64_t s = 1; s <= smax; s++) {
-        if (fs && s != (fs < smax ? fs : smax)) continue;
-        int64_t sps;
-        double t = wgrad_model_us(O, I, steps, shapes[k][0], shapes[k][1], s, &sps);
-        if (t < best) {
-          best = t;
-          p.mi = shapes[k][0];
-          p.ni = shapes[k][1];
-          p.steps_per_split = (int)sps;
-          p.splits = (int)((steps + sps - 1) / sps);
-        }
-      }
+  const size_t vals_bytes = round256((size_t)(steps * step_vals)), meta_bytes = round256((size_t)(steps * step_meta));
+  const WgradShape* tab = fp8 ? kWgrad8 : kWgrad16;
+  const int fshape = g_force_shape, fs = g_force_splits;
+  const int64_t smax = steps / 8 < 1 ? 1 : steps / 8 < 32 ? steps / 8 : 32;
+  struct Choice {
+    double t;
+    int shape;
+    int64_t sps, splits;
+    size_t partial_bytes;
+  } any{1e30, 0, 1, 1, 0}, small = any;                       // the fastest; the fastest that fits the built-in scratch
+  for (int k = 0; k < WG_SHAPES; k++) {
+    if (fshape >= 0 && k != fshape) continue;
+    const int64_t tiles = ((O + tab[k].bm - 1) / tab[k].bm) * ((I + tab[k].bn - 1) / tab[k].bn);
+    for (int64_t s = fs ? (fs < smax ? fs : smax) : 1; s <= smax; s++) {
+      if (s > 1 && !fs && (s - 1) * tiles >= 4 * NUM_CU) break;                          // splits are there to fill the chip
+      const int64_t sps = (steps + s - 1) / s, splits = (steps + sps - 1) / sps;       // no empty split
+      const size_t partial_bytes = splits > 1 ? round256((size_t)splits * (size_t)O * (size_t)I * sizeof(float)) : 0;
+      const double t = wgrad_model_us(tab[k], O, I, sps, splits);
+      if (t < any.t) any = {t, k, sps, splits, partial_bytes};
+      if (t < small.t && vals_bytes + meta_bytes + partial_bytes <= SSTE_NOALLOC_SCRATCH_BYTES) small = {t, k, sps, splits, partial_bytes};
+      if (fs) break;
     }
-    int64_t rows = (O + 15) / 16 * 16;
-    p.vals_bytes = round256((size_t)rows * (size_t)(T / 2) * (fp8 ? 1 : 2));
-    p.meta_bytes = round256((size_t)rows * (size_t)(T / 8));
-  } else {
-    int64_t tiles = ((O + 127) / 128) * ((I + 127) / 128);
-    int64_t s = (2 * NUM_CU + tiles - 1) / tiles;
-    if (s > steps / 8) s = steps / 8;
-    if (s > 32) s = 32;
-    if (s < 1) s = 1;
-    int64_t sps = (steps + s - 1) / s;
-    p.splits = (int)((steps + sps - 1) / sps);                // no empty split
-    p.steps_per_split = (int)sps;
   }
-  p.partial_bytes = p.splits > 1 ? round256((size_t)p.splits * (size_t)O * (size_t)I * sizeof(float)) : 0;
+  const double pre = mvue_model_us(steps * ks, O, fp8);
+  // what fits the built-in scratch is taken where it costs little (more, where few splits have anything to give: the unsplit 192 x 192
+  // tiles nearly fill the chip), so that calls without a workspace run as well
+  const int64_t t192 = ((O + 191) / 192) * ((I + 191) / 192);
+  const double worth = t192 >= NUM_CU * 3 / 4 && t192 <= NUM_CU ? 1.2 : 1.06;
+  const Choice& c = !long_wide || pre + small.t < worth * (pre + any.t) ? small : any;
+  // The fused kernel serves problems that are short or narrow, where the second launch would cost more than the repeated estimator.
+  p.packed = long_wide || (double)((all_steps + steps - 1) / steps) * (pre + c.t) < fused_model_us(all_steps, O, I, fp8);
+  if (p.packed && c.t < 1e30) {
+    p.shape = c.shape;
+    p.splits = (int)c.splits;
+    p.steps_per_split = (int)c.sps;
+    p.chunk_steps = steps;
+    p.vals_bytes = vals_bytes;
+    p.meta_bytes = meta_bytes;
+    p.partial_bytes = c.partial_bytes;
+  } else {
+    p.packed = false;
+  }
   return p;
 }
 
-template <bool FP8, int MI_, int NI_, bool BF8>
-static void launch_wgrad_gemm_cfg(const void* vals, const void* meta, int64_t O, int64_t steps, const void* X, int64_t I,
-                                  int64_t ldx_bytes, int splits, int steps_per_split, float scale, int accumulate,
-                                  float* out, int64_t ld_out, int64_t split_stride, hipStream_t s) {
-  int m_tiles = (int)((O + 32 * MI_ - 1) / (32 * MI_)), n_tiles = (int)((I + 64 * NI_ - 1) / (64 * NI_));
-  dim3 grid((unsigned)(m_tiles * n_tiles * splits)), block(512);
+// The plan of a problem, kept per thread for the last few problems asked for (a call asks several times, and a layer calls again).
+static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
+  struct Entry {
+    int64_t T, O, I;
+    int dtype, shape, splits;
+    WgradPlan plan;
+    bool used;
+  };
+  static thread_local Entry cache[16];
+  const int shape = g_force_shape, splits = g_force_splits;
+  Entry& e = cache[((uint64_t)T * 31 + (uint64_t)O * 7 + (uint64_t)I / 8 * 3 + (uint64_t)dtype) % 16];
+  if (!(e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits))
+    e = Entry{T, O, I, dtype, shape, splits, make_wgrad_plan(T, O, I, dtype), true};
+  return e.plan;
+}
+
+// Arguments of the packed GEMM's kernels.
+struct WgradGemm {
+  const uint8_t* vals;
+  const uint8_t* meta;
+  int64_t O, steps;
+  const uint8_t* X;
+  int64_t I, ldx_bytes;
+  int splits, steps_per_split;
+  float scale;
+  int accumulate;
+  float* out;
+  int64_t ld_out, split_stride;
+};
+
+template <bool FP8, bool BF8>
+static void launch_wgrad_gemm(int shape, const WgradGemm& g, hipStream_t s) {
+  const WgradShape& w = kWgrad16[shape];
+  const int m_tiles = (int)((g.O + w.bm - 1) / w.bm), n_tiles = (int)((g.I + w.bn - 1) / w.bn);
   // Tile order inside a split.  The workgroups of one XCD (an eighth of the grid, consecutive logical numbers)
   // share an L2: with channel tiles fastest they cover many channel tiles of few feature tiles, with feature
   // tiles fastest the other way round.  Each channel tile costs the XCD a slice of the packed operand
   // (0.5625 bytes per element), each feature tile a slice of X (1 byte per element): take the cheaper order
   // (measured 1...4 % on the layers where the choice differs from channel tiles fastest).
-  const int per_xcd = (m_tiles * n_tiles * splits + 7) / 8;
+  const int per_xcd = (m_tiles * n_tiles * g.splits + 7) / 8;
   auto xcd_cost = [&](int fast, int slow, double fast_bytes, double slow_bytes) {
     const int nfast = per_xcd < fast ? per_xcd : fast;
     int nslow = (per_xcd + fast - 1) / fast;
     if (nslow > slow) nslow = slow;
     return nfast * fast_bytes + nslow * slow_bytes;
   };
-  const double a_bytes = 32.0 * MI_ * 0.5625, x_bytes = 64.0 * NI_;
-  int features_fastest = xcd_cost(n_tiles, m_tiles, x_bytes, a_bytes) < xcd_cost(m_tiles, n_tiles, a_bytes, x_bytes) ? 1 : 0;
-  SSTE_LAUNCH(SSTE_K_WGRAD, (k_wgrad_gemm<FP8, MI_, NI_, BF8>), grid, block, s, (const uint8_t*)vals, (const uint8_t*)meta, O, steps,
-              (const uint8_t*)X, I, ldx_bytes, steps_per_split, scale, accumulate, out, ld_out, split_stride, m_tiles, n_tiles,
-              features_fastest);
-}
-
-static void launch_wgrad_gemm(bool fp8, bool bf8, int mi, int ni, const void* vals, const void* meta, int64_t O, int64_t steps,
-                              const void* X, int64_t I, int64_t ldx_bytes, int splits, int steps_per_split, float scale,
-                              int accumulate, float* out, int64_t ld_out, int64_t split_stride, hipStream_t s) {
-#define WG_CASE(F, M, N, B)                                                                                    \
-  if (fp8 == F && bf8 == B && mi == M && ni == N)                                                              \
-    return launch_wgrad_gemm_cfg<F, M, N, B>(vals, meta, O, steps, X, I, ldx_bytes, splits, steps_per_split, scale, \
-                                             accumulate, out, ld_out, split_stride, s)
-  WG_CASE(false, 8, 4, false);
-  WG_CASE(false, 6, 3, false);
-  WG_CASE(false, 8, 3, false);
-  WG_CASE(true, 8, 4, false);
-  WG_CASE(true, 6, 3, false);
-  WG_CASE(true, 8, 3, false);
-  WG_CASE(true, 8, 4, true);
-  WG_CASE(true, 6, 3, true);
-  WG_CASE(true, 8, 3, true);
-#undef WG_CASE
+  const double a_bytes = w.bm * 0.5625, x_bytes = w.bn;
+  const int features_fastest = xcd_cost(n_tiles, m_tiles, x_bytes, a_bytes) < xcd_cost(m_tiles, n_tiles, a_bytes, x_bytes) ? 1 : 0;
+#define WG_LAUNCH(KERNEL, THREADS)                                                                                                    \
+  SSTE_LAUNCH(SSTE_K_WGRAD, (KERNEL), dim3((unsigned)(m_tiles * n_tiles * g.splits)), dim3(THREADS), s, g.vals, g.meta, g.O, g.steps, g.X, g.I, \
+              g.ldx_bytes, g.steps_per_split, g.scale, g.accumulate, g.out, g.ld_out, g.split_stride, m_tiles, n_tiles, features_fastest)
+#define WG_TILE(WM, WN, MT, NT, KG, NS) WG_LAUNCH((k_wgrad_tile<FP8, BF8, WM, WN, MT, NT, KG, NS>), 64 * WM * WN * KG)
+  switch (shape) {
+    case WG_256x256: WG_LAUNCH((k_wgrad_gemm<FP8, 8, 4, BF8>), 512); break;
+    case WG_192x192: WG_LAUNCH((k_wgrad_gemm<FP8, 6, 3, BF8>), 512); break;
+    case WG_256x192: WG_LAUNCH((k_wgrad_gemm<FP8, 8, 3, BF8>), 512); break;
+    case WG_128: WG_TILE(2, 2, 2, 2, 1, 3); break;
+    case WG_128_KG2: WG_TILE(2, 2, 2, 2, 2, 3); break;
+    case WG_128x64: WG_TILE(2, 2, 2, 1, 1, 4); break;
+    case WG_64: WG_TILE(2, 2, 1, 1, 1, 4); break;
+    default: WG_TILE(2, 2, 1, 1, 2, 4); break;
+  }
+#undef WG_TILE
+#undef WG_LAUNCH
 }
 
 size_t wgrad_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype) {
-  WgradPlan p = wgrad_plan(T, O, I, dtype);
-  return p.vals_bytes + p.meta_bytes + p.partial_bytes;
+  return wgrad_plan(T, O, I, dtype).bytes();
 }
 
 bool linear_wgrad_supported(int64_t T, int64_t O, int64_t I, int64_t ldx, int dtype) {
   int64_t eb = dtype != SSTE_BF16 ? 1 : 2;
   if (product_reaches(O / 128 + 1, I / 128 + 1, 0x80000000ll / 32)) return false;
   if (product_reaches(T, O / 16 * 16 + 16, 1ll << 40)) return false;                            // the packed operand's size
-  if (product_reaches(T, ldx, (1ll << 31) / eb)) return wgrad_plan(T, O, I, dtype).packed ? false : true;   // 32-bit offsets in the GEMM
-  return true;
+  // 32-bit offsets of the packed GEMM: short or narrow problems beyond them run the fused kernel
+  return !product_reaches(T, ldx, (1ll << 31) / eb) || T < 2048 || O < 256 || I < 256;
 }
 
 hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X,
@@ -597,30 +913,30 @@ hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t ldd
     }
     return hipGetLastError();
   }
-  WgradPlan p = wgrad_plan(T, O, I, dtype);
-  uint8_t* wsb = (uint8_t*)ws;
-  float* partial = (float*)(wsb + p.vals_bytes + p.meta_bytes);
-  float* out = p.splits > 1 ? partial : dW;
-  int64_t ld_out = p.splits > 1 ? I : lddw;
-  int64_t split_stride = p.splits > 1 ? O * I : 0;
-  float k_scale = p.splits > 1 ? 1.0f : scale;
-  int k_acc = p.splits > 1 ? 0 : accumulate;
-  if (p.packed) {
-    uint8_t* vals = wsb;
-    uint8_t* meta = wsb + p.vals_bytes;
-    launch_mvue_pack(dY, T, O, lddy, dtype, key, vals, meta, s, SSTE_K_MVUE_PACK);
-    launch_wgrad_gemm(fp8, dtype == SSTE_F8E5M2, p.mi, p.ni, vals, meta, O, steps, X, I, ldx * eb, p.splits, p.steps_per_split, k_scale, k_acc, out,
-                      ld_out, split_stride, s);
-  } else {
-    hipError_t e = launch_wgrad_fused(dY, T, O, lddy, dtype, X, I, ldx, key, p.splits, p.steps_per_split, k_scale, k_acc,
-                                      out, ld_out, split_stride, s);
-    if (e != hipSuccess) return e;
-  }
-  if (p.splits > 1) {
-    int64_t blocks = (O * (I / 4) + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    SSTE_LAUNCH(SSTE_K_WGRAD_REDUCE, k_wgrad_reduce, dim3((unsigned)blocks), dim3(256), s, (const float*)partial, p.splits, O, I,
-                scale, accumulate, dW, lddw);
+  const WgradPlan p = wgrad_plan(T, O, I, dtype);
+  if (!p.packed || product_reaches(T, ldx, (1ll << 31) / eb)) return launch_wgrad_fused(dY, T, O, lddy, dtype, X, I, ldx, key, scale, accumulate, dW, lddw, s);
+  uint8_t* const vals = (uint8_t*)ws;
+  uint8_t* const meta = vals + p.vals_bytes;
+  float* const partial = (float*)(meta + p.meta_bytes);
+  for (int64_t step0 = 0; step0 < steps; step0 += p.chunk_steps) {
+    const int64_t n = steps - step0 < p.chunk_steps ? steps - step0 : p.chunk_steps;
+    const int splits = (int)((n + p.steps_per_split - 1) / p.steps_per_split), acc = step0 > 0 ? 1 : accumulate;
+    const uint8_t* const dYc = (const uint8_t*)dY + step0 * ks * lddy * eb;
+    const uint8_t* const Xc = (const uint8_t*)X + step0 * ks * ldx * eb;
+    RngKey kc = key;
+    kc.first_group += (uint64_t)(step0 * (ks / 4));
+    launch_mvue_pack(dYc, n * ks, O, lddy, dtype, kc, vals, meta, s, SSTE_K_MVUE_PACK);
+    const WgradGemm g = splits > 1 ? WgradGemm{vals, meta, O, n, Xc, I, ldx * eb, splits, p.steps_per_split, 1.0f, 0, partial, I, O * I}
+                                   : WgradGemm{vals, meta, O, n, Xc, I, ldx * eb, 1, p.steps_per_split, scale, acc, dW, lddw, 0};
+    if (dtype == SSTE_F8E5M2) launch_wgrad_gemm<true, true>(p.shape, g, s);
+    else if (fp8) launch_wgrad_gemm<true, false>(p.shape, g, s);
+    else launch_wgrad_gemm<false, false>(p.shape, g, s);
+    if (splits > 1) {
+      int64_t blocks = (O * (I / 4) + 255) / 256;
+      if (blocks > 2048) blocks = 2048;
+      SSTE_LAUNCH(SSTE_K_WGRAD_REDUCE, k_wgrad_reduce, dim3((unsigned)blocks), dim3(256), s, (const float*)partial, splits, O, I, scale, acc,
+                  dW, lddw);
+    }
   }
   return hipGetLastError();
 }

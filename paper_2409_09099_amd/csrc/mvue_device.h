@@ -27,10 +27,14 @@ __device__ __forceinline__ uint32_t draw_u32(uint32_t k0, uint32_t k1, uint32_t 
   return draw_u32_pre(k0, k1, gid_lo, gid_hi * 0x9E3779B9u);
 }
 
+// What the rule below costs decides how fast the estimator's kernels run, so the forms are chosen by the measured issue time of the
+// vector instructions (clocks per wave on a full SIMD): 32-bit add, subtract, and, or, xor, right shift, float add and multiply,
+// bitop3 about 3; minima, maxima, compares, left shifts, byte permutes, three-operand integer forms and 32-bit multiplies about 5;
+// a select right behind its compare 2.4; a conversion of two 8-bit codes 4.6 (as much as one of a single code), back 8.7.
 struct Sel {
   float h;        // common magnitude of recorded elements that are not kept as they are
-  uint32_t pos0;  // recorded positions, pos0 < pos1
-  uint32_t pos1;
+  uint32_t n0;    // recorded positions pos0 = 2 - n0 < pos1 = 3 - n1
+  uint32_t n1;
 };
 
 // Steps 1-4 of the rule on the four magnitudes m0..m3 (all >= 0, finite) and the 32-bit draw x.
@@ -56,26 +60,27 @@ __device__ __forceinline__ Sel mvue_select(float m0f, float m1f, float m2f, floa
   uint32_t p0 = f2u(P0), p1 = f2u(P1), p2 = f2u(P2), t0 = f2u(tau0), t1 = f2u(tau1);
   // pos0 = min(#{k : P_k <= tau0}, 2): the prefix sums never decrease, so P2 <= tau0 implies the other
   // two and the count capped at 2 is the count over P0 and P1 alone.  pos1 = min(3, max(i1, pos0 + 1))
-  // with i1 <= 3 and pos0 <= 2: the outer min never acts.
+  // with i1 = #{k <= 2 : P_k <= tau1} <= 3 and pos0 <= 2: the outer min never acts.  Counted are the prefix
+  // sums ABOVE the thresholds, as sign bits of differences of patterns below 2^31:
+  // pos0 = 2 - n0, i1 = 3 - #{k : P_k > tau1}, pos1 = 3 - min(#{k : P_k > tau1}, n0).
   Sel s;
   s.h = h;
-  s.pos0 = (uint32_t)(p0 <= t0) + (uint32_t)(p1 <= t0);
-  uint32_t i1 = (uint32_t)(p0 <= t1) + (uint32_t)(p1 <= t1) + (uint32_t)(p2 <= t1);
-  s.pos1 = max(i1, s.pos0 + 1u);
+  s.n0 = ((t0 - p0) >> 31) + ((t0 - p1) >> 31);
+  const uint32_t above1 = ((t1 - p0) >> 31) + ((t1 - p1) >> 31) + ((t1 - p2) >> 31);
+  s.n1 = min(above1, s.n0);
   return s;
 }
 
 // bf16 group {hi:lo} = (g0 | g1 << 16, g2 | g3 << 16).  Returns the two recorded bf16 values packed
-// (pos0's value in the low half) and writes the metadata nibble pos0 | pos1 << 2.
-__device__ __forceinline__ uint32_t mvue_group_bf16(uint32_t lo, uint32_t hi, uint32_t x, uint32_t& nib) {
+// (pos0's value in the low half); nn = n0 + 4 n1, the metadata nibble pos0 | pos1 << 2 being 14 - nn.
+__device__ __forceinline__ uint32_t mvue_group_bf16(uint32_t lo, uint32_t hi, uint32_t x, uint32_t& nn) {
   float m0 = u2f((lo << 16) & 0x7FFFFFFFu), m1 = u2f(lo & 0x7FFF0000u);
   float m2 = u2f((hi << 16) & 0x7FFFFFFFu), m3 = u2f(hi & 0x7FFF0000u);
   Sel s = mvue_select(m0, m1, m2, m3, x);
   // Both recorded elements at once, as a pair of 16-bit patterns (pos0's in the low half): one byte
   // permute of {hi:lo} with selector bytes (2 pos0, 2 pos0 + 1, 2 pos1, 2 pos1 + 1).
   typedef __attribute__((__vector_size__(2 * sizeof(uint16_t)))) uint16_t u16x2;
-  const uint32_t pp = s.pos0 | (s.pos1 << 16);
-  const uint32_t sel = ((pp << 1) | (pp << 9)) + 0x01000100u;
+  const uint32_t sel = 0x07060504u - 0x0202u * (s.n0 + (s.n1 << 16));
   const uint32_t g = __builtin_amdgcn_perm(hi, lo, sel);
   // An element keeps its own pattern when m_p > h or m_p == 0.  On the 15-bit magnitude fields (the low
   // 16 bits of a bf16's float32 pattern are zero): field > bits(h) >> 16, or field == 0; both at once as
@@ -91,45 +96,46 @@ __device__ __forceinline__ uint32_t mvue_group_bf16(uint32_t lo, uint32_t hi, ui
   __builtin_memcpy(&cm, &common_mask, 4);
   const uint32_t hq = bf16_rne(s.h);
   const uint32_t common = (g & 0x80008000u) | (hq | (hq << 16));
-  nib = s.pos0 | (s.pos1 << 2);
+  nn = s.n0 + (s.n1 << 2);
   return (common & cm) | (g & ~cm);
 }
 
-// 8-bit group (e4m3, or e5m2 when BF8): the four codes of one group in one dword (g0 in byte 0).
-// Returns the two recorded codes of theta / 2 in the low 16 bits (pos0's in byte 0).
+// Two 8-bit groups (e4m3, or e5m2 when BF8), ga and gb: the four codes of a group in one dword (g0 in byte 0).  Returns the recorded
+// codes of theta / 2, group ga's in the low half (pos0's in its low byte), and the metadata byte of the pair.  In pairs because the
+// byte permute that gathers the recorded codes, the conversion of two of them and the signs serve two groups at once.
 template <bool BF8>
-__device__ __forceinline__ float cvt8(uint32_t w) {
-  return BF8 ? __builtin_amdgcn_cvt_f32_bf8((int)w, 0) : __builtin_amdgcn_cvt_f32_fp8((int)w, 0);
-}
-template <bool BF8>
-__device__ __forceinline__ uint32_t mvue_group_f8(uint32_t g, uint32_t x, uint32_t& nib) {
-  uint32_t ga = g & 0x7F7F7F7Fu;
-  float m0, m1, m2, m3;
+__device__ __forceinline__ uint32_t mvue_pair_f8(uint32_t ga, uint32_t gb, uint32_t xa, uint32_t xb, uint32_t& meta) {
+  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+  typedef __attribute__((__vector_size__(2 * sizeof(short)))) short i16x2;
+#define MVUE_CVT2(w, hi) (BF8 ? __builtin_amdgcn_cvt_pk_f32_bf8((int)(w), hi) : __builtin_amdgcn_cvt_pk_f32_fp8((int)(w), hi))
+  const uint32_t maga = ga & 0x7F7F7F7Fu, magb = gb & 0x7F7F7F7Fu;
+  const f32x2 a01 = MVUE_CVT2(maga, false), a23 = MVUE_CVT2(maga, true), b01 = MVUE_CVT2(magb, false), b23 = MVUE_CVT2(magb, true);
+  const Sel sa = mvue_select(a01[0], a01[1], a23[0], a23[1], xa), sb = mvue_select(b01[0], b01[1], b23[0], b23[1], xb);
+  // recorded codes: bytes 2 - n0, 3 - n1 of ga (bytes 0 .. 3 of the permute's source) and of gb (bytes 4 .. 7)
+  const uint32_t na = sa.n0 + (sa.n1 << 8), nb = sb.n0 + (sb.n1 << 8);
+  const uint32_t n = na + (nb << 16);
+  const uint32_t rec = __builtin_amdgcn_perm(gb, ga, 0x07060302u - n);
+  meta = 0xEEu - __builtin_amdgcn_udot4(n, 0x40100401u, 0u, false);       // nibbles 14 - n0 - 4 n1
+  const uint32_t mag = rec & 0x7F7F7F7Fu;
+  const f32x2 ra = MVUE_CVT2(mag, false), rb = MVUE_CVT2(mag, true);
+#undef MVUE_CVT2
+  // stored magnitude: half of m_p where m_p > h or m_p = 0 (then 0), else half of h: the median of m_p, h and 2^40 m_p (in either
+  // format 2^40 times the least positive magnitude is above every h); halved by the conversion, within the format's range
+  auto stored = [](float m, float h) {
+    const uint32_t x = f2u(m), y = f2u(h), z = f2u(m * 0x1p40f);
+    return u2f(max(min(max(x, y), z), min(x, y)));
+  };
+  i16x2 q = {0, 0};
   if (BF8) {
-    m0 = __builtin_amdgcn_cvt_f32_bf8(ga, 0), m1 = __builtin_amdgcn_cvt_f32_bf8(ga, 1);
-    m2 = __builtin_amdgcn_cvt_f32_bf8(ga, 2), m3 = __builtin_amdgcn_cvt_f32_bf8(ga, 3);
+    q = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(q, stored(ra[0], sa.h), stored(ra[1], sa.h), 2.0f, false);
+    q = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(q, stored(rb[0], sb.h), stored(rb[1], sb.h), 2.0f, true);
   } else {
-    m0 = __builtin_amdgcn_cvt_f32_fp8(ga, 0), m1 = __builtin_amdgcn_cvt_f32_fp8(ga, 1);
-    m2 = __builtin_amdgcn_cvt_f32_fp8(ga, 2), m3 = __builtin_amdgcn_cvt_f32_fp8(ga, 3);
+    q = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(q, stored(ra[0], sa.h), stored(ra[1], sa.h), 2.0f, false);
+    q = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(q, stored(rb[0], sb.h), stored(rb[1], sb.h), 2.0f, true);
   }
-  Sel s = mvue_select(m0, m1, m2, m3, x);
-  // the two recorded codes side by side in bytes 0 and 1 (one byte permute; selector bytes 0x0c give zero)
-  const uint32_t rec = __builtin_amdgcn_perm(g, g, s.pos0 | (s.pos1 << 8) | 0x0c0c0000u);
-  const uint32_t reca = rec & 0x7F7Fu;
-  float mp0, mp1;
-  if (BF8) mp0 = __builtin_amdgcn_cvt_f32_bf8((int)reca, 0), mp1 = __builtin_amdgcn_cvt_f32_bf8((int)reca, 1);
-  else mp0 = __builtin_amdgcn_cvt_f32_fp8((int)reca, 0), mp1 = __builtin_amdgcn_cvt_f32_fp8((int)reca, 1);
-  // stored magnitudes: 0.5 * m_p where g_p is kept as it is, else 0.5 * h; all within the format's range
-  bool own0 = (f2u(mp0) - 1u) >= f2u(s.h);
-  bool own1 = (f2u(mp1) - 1u) >= f2u(s.h);
-  float v0 = 0.5f * (own0 ? mp0 : s.h);
-  float v1 = 0.5f * (own1 ? mp1 : s.h);
-  uint32_t q = BF8 ? ((uint32_t)__builtin_amdgcn_cvt_pk_bf8_f32(v0, v1, 0, false) & 0xFFFFu) : e4m3_rne_pack(v0, v1);
-  nib = s.pos0 | (s.pos1 << 2);
-  return q | (rec & 0x8080u);
-}
-__device__ __forceinline__ uint32_t mvue_group_e4m3(uint32_t g, uint32_t x, uint32_t& nib) {
-  return mvue_group_f8<false>(g, x, nib);
+  uint32_t codes;
+  __builtin_memcpy(&codes, &q, 4);
+  return codes | (rec & 0x80808080u);
 }
 
 }  // namespace sste

@@ -92,3 +92,47 @@ def test_linear_fwd_tiles(sste, dtype, T, O, I):  # noqa: F811
         assert abs(float(amax8) - float(want.abs().max())) <= 1e-5 * float(want.abs().max())
         dec = A8.view(torch.float8_e4m3fn).float() * zs
         assert bool(((dec - want).abs() <= want.abs() * (2.0 ** -4 + 1e-5) + zs * 2.0 ** -9).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
+@pytest.mark.parametrize("T,O,I", [
+    (64, 8, 16), (704, 40, 80), (1152, 296, 136),         # estimator in the operand load: fewer k-steps than waves, incomplete rounds
+    (128, 168, 2448), (3840, 24, 40), (2048, 264, 288),   # 64 x 64; split; two k-groups
+    (128, 1032, 1936), (5632, 72, 1672),                  # 128 x 64; split
+    (1152, 408, 2608), (5376, 72, 2904),                  # 128 x 128; split
+    (3968, 456, 2072),                                    # 128 x 128, two k-groups
+    (192, 1048, 5144),                                    # 192 x 192 over few k-steps
+])
+def test_linear_wgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
+    if dtype != "bf16":
+        T, O, I = -(-T // 128) * 128, -(-O // 16) * 16, -(-I // 16) * 16
+    wl = WL.WORKLOADS[1]
+    dyc, dys, dY = operand(sste, WL.output_gradient(wl, 0, T=T, O=O)[0], dtype)
+    xc, xs, X = operand(sste, WL.activations(wl, 0, T=T, I=I)[0], "bf16" if dtype == "bf16" else "e4m3")
+    ref = OL.linear_wgrad(dyc, xc, 5, 8, dtype, dys, xs, x_dtype="bf16" if dtype == "bf16" else "e4m3")
+    dW = torch.full((O, I), 3.0, dtype=torch.float32, device="cuda")
+    sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), float(dys), float(xs), dW=dW)
+    got = dW.cpu().numpy().astype(np.float64)
+    assert rel_err(got, ref) <= 1e-4                       # the sparse operand is bit-identical: only the order of the sums differs
+    twice = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), float(dys), float(xs), dW=dW.clone(), accumulate=True)
+    assert torch.allclose(twice, 2.0 * dW, rtol=1e-6, atol=1e-6 * float(dW.abs().max()))
+
+
+@pytest.mark.parametrize("dtype,T,O,I", [("bf16", 12288, 3880, 168), ("e4m3", 19072, 5744, 80)])
+def test_linear_wgrad_token_chunks(sste, dtype, T, O, I):  # noqa: F811
+    """Narrow problems whose sparse operand does not fit the scratch at once: equal to their own parts added up."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    dys = xs = 1.0
+    if dtype != "bf16":
+        dys, xs = 1e-5, 0.01
+        dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs, dt(sste, dtype))[0]
+    whole = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    cut = [0, 4096, 8192, T]
+    parts = torch.zeros_like(whole)
+    for a, b in zip(cut, cut[1:]):
+        sste.linear_wgrad(dY[a:b], X[a:b], 5, 8, dt(sste, dtype), dys, xs, dW=parts, accumulate=True, first_token=a)
+    assert torch.allclose(whole, parts, rtol=0, atol=1e-5 * float(whole.abs().max()))
+    out = torch.full_like(whole, 7.0)
+    assert torch.equal(sste.linear_wgrad_noalloc(dY, X, 5, 8, out, dt(sste, dtype), dys, xs), whole)
