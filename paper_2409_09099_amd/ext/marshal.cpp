@@ -12,6 +12,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -98,7 +99,7 @@ struct Args {
   }
   const at::Tensor* tensor(PyObject* o) {
     if (!given(o)) return nullptr;
-    if (!THPVariable_Check(o)) return ok = false, nullptr;
+    if (!THPVariable_CheckExact(o)) return ok = false, nullptr;           // Tensor or Parameter; subclasses keep the Python route
     return &THPVariable_Unpack(o);
   }
   const at::Tensor* needed(PyObject* o) {
@@ -408,12 +409,29 @@ PyObject* bind(PyObject*, PyObject* args) {
   Py_RETURN_NONE;
 }
 
-#define FAST(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL | METH_KEYWORDS, "See the function of this name in binding.py."}
+// No C++ exception may leave an entry (a result that does not fit the memory, a tensor without storage): it becomes the Python error
+// that the ctypes route raises.
+using FastCall = PyObject* (*)(PyObject*, PyObject* const*, Py_ssize_t, PyObject*);
+template <FastCall F>
+PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t nargs, PyObject* kwnames) {
+  HANDLE_TH_ERRORS
+  return F(self, args, nargs, kwnames);
+  END_HANDLE_TH_ERRORS
+}
+using PlainCall = PyObject* (*)(PyObject*, PyObject* const*, Py_ssize_t);
+template <PlainCall F>
+PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
+  HANDLE_TH_ERRORS
+  return F(self, args, nargs);
+  END_HANDLE_TH_ERRORS
+}
+
+#define FAST(name) {#name, (PyCFunction)(void (*)(void))(FastCall)guarded<name>, METH_FASTCALL | METH_KEYWORDS, "See the function of this name in binding.py."}
 PyMethodDef methods[] = {
   FAST(project_pack), FAST(sgd_project_pack), FAST(linear_fwd), FAST(linear_fwd_ex), FAST(linear_fwd_act), FAST(linear_dgrad), FAST(linear_dgrad_act),
   FAST(linear_wgrad), FAST(cast_fp8),
-  {"pack_batch_launch", (PyCFunction)(void (*)(void))pack_batch_launch, METH_FASTCALL, "Launches a prepared sste_project_pack_batch table."},
-  {"update_batch_launch", (PyCFunction)(void (*)(void))update_batch_launch, METH_FASTCALL, "Launches a prepared sste_sgd_project_pack_batch table."},
+  {"pack_batch_launch", (PyCFunction)(void (*)(void))(PlainCall)guarded<pack_batch_launch>, METH_FASTCALL, "Launches a prepared sste_project_pack_batch table."},
+  {"update_batch_launch", (PyCFunction)(void (*)(void))(PlainCall)guarded<update_batch_launch>, METH_FASTCALL, "Launches a prepared sste_sgd_project_pack_batch table."},
   {"bind", bind, METH_VARARGS, "bind(addresses, functions, error)"},
   {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Native argument marshalling of the binding.", -1, methods, nullptr, nullptr, nullptr, nullptr};

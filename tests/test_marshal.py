@@ -1,10 +1,16 @@
 """The native argument marshalling (ext/marshal.cpp) against the Python definitions it stands in for: the same results, the same
 errors, outputs given or made."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 import paper_2409_09099_amd as sste
 from paper_2409_09099_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def test_native_functions_stand_in_for_the_python_ones():
@@ -24,6 +30,27 @@ def test_native_functions_stand_in_for_the_python_ones():
 def test_errors_are_those_of_the_python_definitions(call, error):
     with pytest.raises(error):
         call()
+
+
+def test_a_cxx_exception_becomes_a_python_error():
+    """A tensor without storage (tracing) must raise, as through the Python definitions, and not end the process."""
+    code = (
+        "import torch, paper_2409_09099_amd as s\n"
+        "from torch.func import vmap\n"
+        "from torch._subclasses.fake_tensor import FakeTensorMode\n"
+        "s.library()\n"
+        "z = lambda *n, t=torch.bfloat16: torch.empty(n, dtype=t, device='cuda')\n"
+        "def mapped():\n"
+        "    vmap(lambda w: s.project_pack(w, 1.0, vals=w, meta=w))(z(2, 16, 64))\n"
+        "with FakeTensorMode(allow_non_fake_inputs=True):\n"
+        "    for call in (lambda: s.project_pack(z(16, 64), 1.0, vals=z(16, 32), meta=z(16, 8)), lambda: s.linear_fwd(z(4, 64), z(16, 32), z(16, 8), 16),\n"
+        "                 lambda: s.cast_fp8(z(4, 64), 1.0), mapped):\n"
+        "        try:\n"
+        "            call()\n"
+        "        except Exception as e:\n"
+        "            print('raised', type(e).__name__, flush=True)\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.count("raised") == 4, (r.returncode, r.stdout, r.stderr[-2000:])
 
 
 @pytest.mark.gpu
