@@ -802,7 +802,7 @@ static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
   // what fits the built-in scratch is taken where it costs little (more, where few splits have anything to give: the unsplit 192 x 192
   // tiles nearly fill the chip), so that calls without a workspace run as well
   const int64_t t192 = ((O + 191) / 192) * ((I + 191) / 192);
-  const double worth = t192 >= NUM_CU * 3 / 4 && t192 <= NUM_CU ? 1.2 : 1.06;
+  const double worth = t192 >= NUM_CU * 5 / 8 && t192 <= NUM_CU ? 1.2 : 1.1;
   const Choice& c = !long_wide || pre + small.t < worth * (pre + any.t) ? small : any;
   // The fused kernel serves problems that are short or narrow, where the second launch would cost more than the repeated estimator.
   p.packed = long_wide || (double)((all_steps + steps - 1) / steps) * (pre + c.t) < fused_model_us(all_steps, O, I, fp8);
@@ -914,7 +914,7 @@ hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t ldd
     return hipGetLastError();
   }
   const WgradPlan p = wgrad_plan(T, O, I, dtype);
-  if (!p.packed || product_reaches(T, ldx, (1ll << 31) / eb)) return launch_wgrad_fused(dY, T, O, lddy, dtype, X, I, ldx, key, scale, accumulate, dW, lddw, s);
+  if (!p.packed || !ws || product_reaches(T, ldx, (1ll << 31) / eb)) return launch_wgrad_fused(dY, T, O, lddy, dtype, X, I, ldx, key, scale, accumulate, dW, lddw, s);
   uint8_t* const vals = (uint8_t*)ws;
   uint8_t* const meta = vals + p.vals_bytes;
   float* const partial = (float*)(meta + p.meta_bytes);

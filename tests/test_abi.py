@@ -101,6 +101,13 @@ def test_linear_wgrad_validation_and_workspace(lib):
     assert lib.sste_wgrad_workspace_bytes(100, 256, 1024, 0) == 0
 
 
+@pytest.mark.parametrize("T,O,I,dtype", [(14464, 2880, 2032, 3), (10240, 4224, 1312, 3), (9984, 4656, 1152, 1), (13312, 1024, 8176, 3), (6720, 1024, 8128, 0),
+                                         (65536, 128, 4096, 0), (262144, 240, 256, 1), (1984, 20480, 1024, 0)])
+def test_problems_the_built_in_scratch_serves(lib, T, O, I, dtype):
+    """Problems whose unsplit tiles nearly fill the chip, and short or narrow ones of any length, fit the built-in scratch."""
+    assert 0 < lib.sste_wgrad_workspace_bytes(T, O, I, dtype) <= 64 << 20
+
+
 def test_other_entry_points_validation(lib):
     P = ctypes.c_void_p
     fake = P(0x1000)

@@ -136,3 +136,19 @@ def test_linear_wgrad_token_chunks(sste, dtype, T, O, I):  # noqa: F811
     assert torch.allclose(whole, parts, rtol=0, atol=1e-5 * float(whole.abs().max()))
     out = torch.full_like(whole, 7.0)
     assert torch.equal(sste.linear_wgrad_noalloc(dY, X, 5, 8, out, dt(sste, dtype), dys, xs), whole)
+
+
+@pytest.mark.parametrize("dtype,T,O,I", [("bf16", 1984, 1544, 832), ("e4m3", 4096, 240, 2048)])
+def test_linear_wgrad_without_its_workspace(sste, dtype, T, O, I):  # noqa: F811
+    """A short or narrow problem on the packed path: the fused kernel takes it where the workspace is too small."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    dys = xs = 1.0
+    if dtype != "bf16":
+        dys, xs = 1e-5, 0.01
+        dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs, dt(sste, dtype))[0]
+    assert sste.wgrad_workspace_bytes(T, O, I, dt(sste, dtype)) > 0
+    want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))      # float32 sums in another order
