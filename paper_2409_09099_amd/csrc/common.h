@@ -157,18 +157,6 @@ __device__ __forceinline__ void dma_b32(i32x4 rsrc, uint32_t lds_addr, uint32_t 
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
-// Buffer loads into registers whose completion is tracked by hand like that of the direct-to-LDS loads (the compiler's own
-// bookkeeping does not know of those and would wait for them too).  The destination holds its value only behind a wait_vmcnt that
-// covers the load AND an empty asm statement with the register as "+v" operand, which ties the uses to the wait.
-__device__ __forceinline__ void load_b128_async(i32x4& dst, i32x4 rsrc, uint32_t voffset, uint32_t soffset) {
-  asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(dst) : "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
-}
-__device__ __forceinline__ void load_b32_async(int& dst, i32x4 rsrc, uint32_t voffset, uint32_t soffset) {
-  asm volatile("buffer_load_dword %0, %1, %2, %3 offen" : "=v"(dst) : "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
-}
-__device__ __forceinline__ void load_u16_async(int& dst, i32x4 rsrc, uint32_t voffset, uint32_t soffset) {
-  asm volatile("buffer_load_ushort %0, %1, %2, %3 offen" : "=v"(dst) : "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
-}
 // XOR key of the LDS tiles that are read with the transposing loads (ds_read_b64_tr_b16 / _b8): the X tile of
 // the weight-gradient GEMM and the expanded S(W) tile of the input-gradient GEMM.  A tile row (one index of the
 // contraction) is 512 B (bf16) or 256 B (8-bit), so every row starts at bank 0, and the 32-byte (16-byte) unit

@@ -210,7 +210,7 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
 
   i32x4 pk[EBK];
   int pm[EBK];
-  const i32x4 rv = rsrc_words(a.vals, (uint32_t)(rbn * a.isteps * 1024)), rm = rsrc_words(a.meta, (uint32_t)(rbn * a.isteps * MBLK));
+  const BufferRsrc rv = make_rsrc(a.vals, (uint32_t)(rbn * a.isteps * 1024)), rm = make_rsrc(a.meta, (uint32_t)(rbn * a.isteps * MBLK));
   auto load_packed = [&](int step) {
     const uint32_t sv = (uint32_t)step * (uint32_t)RBK * (uint32_t)a.isteps;
 #pragma unroll
@@ -221,14 +221,10 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
       const uint32_t off = live ? pv_off + 512u * ef : 0x80000000u;
       const uint32_t offm = live ? (pv_off + 512u * ef) / (1024 / MBLK) : 0x80000000u;
       const uint32_t se = RBK * step + 2 * ec < (int)rbn ? sv + (uint32_t)(2 * ec * a.isteps) : 0u;
-      load_b128_async(pk[e], rv, off, se * 1024u);
-      if (FP8) load_b32_async(pm[e], rm, offm, se * (uint32_t)MBLK);
-      else load_u16_async(pm[e], rm, offm, se * (uint32_t)MBLK);
+      pk[e] = __builtin_amdgcn_raw_buffer_load_b128(rv, (int)off, (int)(se * 1024u), 0);
+      pm[e] = FP8 ? (int)__builtin_amdgcn_raw_buffer_load_b32(rm, (int)offm, (int)(se * (uint32_t)MBLK), 0)
+                  : (int)__builtin_amdgcn_raw_buffer_load_b16(rm, (int)offm, (int)(se * (uint32_t)MBLK), 0);
     }
-  };
-  auto packed_arrived = [&]() {              // behind the wait for them
-#pragma unroll
-    for (int e = 0; e < EBK; e++) asm volatile("" : "+v"(pk[e]), "+v"(pm[e]));
   };
   f32x16 ex;
   auto expand_mma = [&](int u) {
@@ -355,7 +351,6 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
 #pragma unroll
         for (int i = 0; i < LB; i++) dma_b(i, gstep(k), k);
     wait_vmcnt<0>();
-    packed_arrived();
 #pragma unroll
     for (int u = 0; u < NU; u++) {
       expand_mma(u);
@@ -364,7 +359,6 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
     if (nloc > 1) {
       load_packed(gstep(1));
       wait_vmcnt<0>();
-      packed_arrived();
 #pragma unroll
       for (int u = 0; u < NU0; u++) {
         expand_mma(u);
@@ -393,7 +387,6 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
         // grad_Z tile s + 1 and the packed blocks of s + 2 have arrived (the newest grad_Z tile may be in flight) ...
         if (NSB > 2 && s + NSB - 1 < nloc) wait_vmcnt<LB>();
         else wait_vmcnt<0>();
-        packed_arrived();
         __syncthreads();               // ... everybody's, S(W) tile s + 1 is written and the slots of s have been read
         stage(st, 0, a1, b1, 0, NU0, s + 2 < nloc, a0, LATE, s + 3 < nloc, gstep(s + 3), s + NSB < nloc, gstep(s + NSB), sb0);
       } else if (st == 0) {
