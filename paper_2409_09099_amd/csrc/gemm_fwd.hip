@@ -117,8 +117,8 @@ __global__ void k_fill_u32_fwd(uint32_t* p, uint32_t v) { *p = v; }
 
 // ---------------------------------------------------------------------------------------------------------
 // Software-pipelined variant: 8 waves (2 x 4), each owning MI_ x NI_ MFMA tiles, so a workgroup covers
-// 32 MI_ channels x 64 NI_ tokens (256 x 256, 192 x 256, ...).  The kernel above alternates,
-// workgroup-wide, between a phase that reads fragments from LDS and a phase that issues MFMAs; here the
+// 32 MI_ channels x 64 NI_ tokens (256 x 256, 192 x 256, ...).  Instead of
+// alternating, workgroup-wide, between a phase that reads fragments from LDS and a phase that issues MFMAs, the
 // three pipes (vector memory, LDS, matrix) run side by side within a k-step:
 //   * X fragments are double-buffered in registers: while the MFMAs of k-step s run on one set, the
 //     set for k-step s + 1 is read from LDS, spread over the groups of NI_ MFMAs;
