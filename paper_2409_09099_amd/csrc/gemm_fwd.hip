@@ -645,6 +645,10 @@ k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int
 // Few tokens (a decode batch): 16 channels x 16 NI tokens by one workgroup whose KW waves take the k-steps in turn.  The packed
 // weight is read once and every wave's operands come straight from memory into its registers (a lane's slot of a packed block and
 // two pieces of an X row ARE its fragments): no LDS, no barrier until the waves' sums are added, U k-steps of loads in flight per wave.
+// Bound by the load instructions a CU can take: the 16 rows of X cost more than the weight (bf16 1280 x 5120: 4.2 us with one token,
+// 7.2 with 16), and so do the k-steps past the end that the last turn of KW * U asks for in vain.  Hence U = 2; with U = 4, us
+// (T x O x I): bf16 16x1280x5120 7.50 -> 7.19, 16x768x3072 5.38 -> 5.04, 512x256x1024 5.05 -> 4.33; e4m3 16x1280x5120 5.03 -> 4.69,
+// 16x5120x1280 4.29 -> 3.58, 48x3072x768 4.41 -> 3.60.  16 waves, or more k-steps in flight, are slower (8.5 and 8.3 us on the first).
 template <bool FP8, int NI, int KW, int U, bool ZF8, bool AMAX>
 __global__ void __launch_bounds__(64 * KW)
 k_linear_fwd_skinny(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
@@ -686,6 +690,7 @@ k_linear_fwd_skinny(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, i
         fb[u][t][1] = buffer_load_b128(rb, o + 64u, (uint32_t)sc * 128u);
       }
     }
+    __builtin_amdgcn_sched_barrier(0);       // the loads of all U k-steps are requested before the first use
 #pragma unroll
     for (int u = 0; u < U; u++)
 #pragma unroll
@@ -838,7 +843,8 @@ static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, 
 // R fit a CU (LDS) and what does not fit runs in further rounds.  Fitted to event times of 400 random problems (1 ... 32768 tokens,
 // 64 ... 5120 channels and features), 7...11 % off per problem; the shape it picks is 2 % slower than the best one on the geometric
 // mean.  What the fit says about the chip: thr is the operand bytes of a k-step at 75...100 B/ns for every shape, the rate at which a
-// CU receives operands.
+// CU receives operands.  The row of the register-only kernel is fitted to 30 problems of 1 ... 512 tokens against the 32 x 32 tile at
+// the same problems; its step falls with the token rows a tile really has (one token: 0.44 of sixteen).
 struct FwdShape {
   int bm, bn, kg, r;
   double f, lat, thr, base, store;
@@ -854,7 +860,7 @@ static const FwdShape kFwd16[FW_SHAPES] = {
   {64, 64, 2, 1, 1.34, 0.256, 0.256, 2.63, 2.13},
   {64, 32, 4, 1, 1.56, 0.313, 0.313, 2.53, 3.63},
   {32, 32, 4, 1, 1.55, 0.186, 0.186, 2.55, 3.70},
-  {16, 16, 8, 4, 0.00, 0.213, 0.250, 3.75, 0.02},
+  {16, 16, 8, 4, 0.00, 0.525, 0.525, 2.45, 0.02},
 };
 static const FwdShape kFwd8[FW_SHAPES] = {
   {256, 256, 1, 1, 1.86, 0.679, 0.679, 2.96, 0.90},
@@ -866,7 +872,7 @@ static const FwdShape kFwd8[FW_SHAPES] = {
   {64, 64, 2, 1, 1.89, 0.238, 0.238, 2.17, 0.44},
   {64, 32, 4, 1, 2.95, 0.305, 0.305, 1.26, 1.71},
   {32, 32, 4, 1, 1.74, 0.151, 0.151, 2.49, 3.42},
-  {16, 16, 8, 4, 0.00, 0.134, 0.264, 3.74, 0.56},
+  {16, 16, 8, 4, 0.00, 0.580, 0.480, 2.40, 0.56},
 };
 
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
@@ -881,8 +887,9 @@ static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
     if (c != FW_256 && wgs > 0x7FFFFFFFll) continue;                                  // grid size
     const double nk = (double)((steps + s.kg - 1) / s.kg), fixed = s.base + s.store * out_us;
     const int64_t n = (wgs + NUM_CU - 1) / NUM_CU, full = n / s.r, rem = n % s.r;      // workgroups on the busiest CU: full rounds of r, and a rest
-    double t = fixed + (double)full * (s.f + nk * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));
-    if (rem) t += s.f + nk * (s.lat > rem * s.thr ? s.lat : rem * s.thr);
+    const double part = c == FW_16_KG8 && T < 16 ? 0.4 + 0.6 / 16.0 * (double)T : 1.0;
+    double t = fixed + (double)full * (s.f + nk * part * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));
+    if (rem) t += s.f + nk * part * (s.lat > rem * s.thr ? s.lat : rem * s.thr);
     if (t < best_t) {
       best_t = t;
       best = c;
@@ -920,7 +927,7 @@ static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx,
     case FW_64_KG2: FT(2, 2, 1, 1, 2, 4); break;
     case FW_64x32_KG4: FT(2, 1, 1, 1, 4, 4); break;
     case FW_32_KG4: FT(1, 1, 1, 1, 4, 4); break;
-    default: launch_fwd_skinny<FP8, 1, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
+    default: launch_fwd_skinny<FP8, 1, 8, 2, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
   }
 #undef FT
 }

@@ -51,16 +51,20 @@ def test_linear_dgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
 
 FWD_TILES = [
     ("bf16", 5, 264, 1280), ("e4m3", 21, 272, 2432),             # 16 x 16, k-steps dealt to eight waves (19 or 20 of them)
-    ("bf16", 82, 1448, 320), ("e4m3", 146, 848, 640),            # 32 x 32, four groups, an incomplete round
-    ("bf16", 76, 2776, 640), ("e4m3", 71, 3472, 896),            # 64 x 32, four groups
+    ("bf16", 82, 1448, 320), ("e4m3", 146, 848, 640),            # 16 x 16, fewer k-steps than waves, three workgroups per CU
+    ("bf16", 76, 2776, 640), ("e4m3", 71, 3472, 896),            # 64 x 32, four groups; 16 x 16
     ("bf16", 978, 240, 192), ("e4m3", 978, 240, 128),            # 64 x 64
-    ("bf16", 4754, 88, 832), ("e4m3", 602, 352, 384),            # 64 x 64, two groups
+    ("bf16", 4754, 88, 832), ("e4m3", 602, 352, 384),            # 64 x 64; 16 x 16
     ("bf16", 8359, 88, 128), ("e4m3", 8389, 80, 256),            # 128 x 64
     ("bf16", 16872, 88, 384), ("e4m3", 19387, 80, 512),          # 128 x 128, three slots
     ("bf16", 8885, 152, 128), ("e4m3", 8359, 80, 128),           # 128 x 128, two slots
     ("bf16", 19747, 536, 128), ("e4m3", 19747, 528, 128),        # 256 x 128, two workgroups per CU
     ("bf16", 35341, 168, 640), ("e4m3", 25239, 400, 512),        # 256 x 256
     ("bf16", 22320, 696, 896), ("e4m3", 16503, 1200, 768),       # whole rounds of 256 x 256 tiles and halves of them
+    ("bf16", 1, 1000, 64), ("e4m3", 16, 1296, 5120),             # 16 x 16: one token and one k-step; turns of 16 k-steps, the last half full
+    ("bf16", 33, 1392, 1088), ("e4m3", 33, 2752, 1152),          # 32 x 32, four groups, an incomplete round
+    ("e4m3", 69, 2816, 1152),                                    # 64 x 32, four groups
+    ("bf16", 290, 1656, 1216), ("e4m3", 650, 640, 1152),         # 64 x 64, two groups
 ]
 
 
