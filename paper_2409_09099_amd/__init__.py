@@ -16,6 +16,7 @@ from .binding import (  # noqa: F401
     cast_fp8,
     UpdateBatch,
     compute_beta,
+    describe_plan,
     BETA_MSE,
     BETA_L1,
     flip_count,

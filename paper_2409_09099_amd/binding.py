@@ -73,6 +73,8 @@ def library() -> ctypes.CDLL:
     lib.sste_linear_wgrad_noalloc.restype = ci
     lib.sste_wgrad_plan_override.argtypes = [ci, ci, ci]
     lib.sste_wgrad_plan_override.restype = ci
+    lib.sste_describe_plan.argtypes = [ci, i64, i64, i64, ci, ctypes.c_char_p, sz]
+    lib.sste_describe_plan.restype = ci
     lib.sste_wgrad_workspace_bytes.argtypes = [i64, i64, i64, ci]
     lib.sste_wgrad_workspace_bytes.restype = sz
     lib.sste_mvue_materialize.argtypes = [vp, i64, i64, i64, ci, u64, u64, vp, vp, vp]
@@ -468,6 +470,13 @@ def flip_count(meta_a: torch.Tensor, meta_b: torch.Tensor, O: int) -> torch.Tens
     out = torch.empty(1, dtype=torch.int64, device=meta_a.device)
     _check(library().sste_flip_count(_ptr(meta_a), _ptr(meta_b), O, I8 * 8, _ptr(out), _stream(meta_a)))
     return out
+
+
+def describe_plan(op: str, T: int, O: int, I: int, dtype: int = BF16) -> str:
+    """sste_describe_plan: the kernel that the product `op` ("fwd", "dgrad" or "wgrad") of these sizes runs, as text."""
+    text = ctypes.create_string_buffer(128)
+    _check(library().sste_describe_plan(KERNEL_NAMES.index(op), T, O, I, dtype, text, len(text)))
+    return text.value.decode()
 
 
 KERNEL_NAMES = ("project_pack", "fwd", "wgrad", "wgrad_reduce", "mvue_pack", "dgrad", "sgd_project_pack", "cast")

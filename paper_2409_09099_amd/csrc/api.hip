@@ -422,6 +422,22 @@ int sste_wgrad_plan_override(int mi, int ni, int splits) {
   return SSTE_OK;
 }
 
+int sste_describe_plan(int op, int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t text_bytes) {
+  clear_error();
+  if (!text || text_bytes == 0) return fail(SSTE_ERR_NULL, "describe_plan: no room for the text");
+  text[0] = 0;
+  const bool fwd = op == SSTE_K_FWD, dgrad = op == SSTE_K_DGRAD;
+  if (!fwd && !dgrad && op != SSTE_K_WGRAD) return fail(SSTE_ERR_VALUE, "describe_plan: op %d is no product", op);
+  if (fwd ? !good_dtype(dtype) : !good_grad_dtype(dtype)) return fail(SSTE_ERR_VALUE, "describe_plan: dtype %d", dtype);
+  const int ks = is_8bit(dtype) ? 128 : 64, e16 = elems_per_16B(dtype);
+  const bool refused = fwd     ? I % ks || O % 8 || !linear_fwd_supported(T, I, I, O, dtype)
+                       : dgrad ? I % ks || O % e16 || !linear_dgrad_supported(T, O, O, I, dtype)
+                               : T % ks || O % e16 || I % e16 || !linear_wgrad_supported(T, O, I, I, dtype);
+  if (T <= 0 || O <= 0 || I <= 0 || refused) return fail(SSTE_ERR_VALUE, "describe_plan: the product does not take these sizes");
+  (fwd ? describe_fwd : dgrad ? describe_dgrad : describe_wgrad)(T, O, I, dtype, text, text_bytes);
+  return SSTE_OK;
+}
+
 size_t sste_wgrad_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype) {
   if (wgrad_shape_check(T, O, I, dtype, "wgrad_workspace_bytes") != SSTE_OK) return 0;
   return wgrad_workspace_bytes(T, O, I, dtype);

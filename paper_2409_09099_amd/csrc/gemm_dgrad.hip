@@ -34,6 +34,8 @@
 // Epilogue as in the forward GEMM: transposed through LDS, 16-byte streaming stores of bf16 rows.
 #include "common.h"
 
+#include <stdio.h>
+
 namespace sste {
 
 namespace {
@@ -978,27 +980,27 @@ bool linear_dgrad_supported(int64_t T, int64_t O, int64_t lddy, int64_t I, int d
 // features) for every shape: 5...10 % off per problem, and the shape it picks is 1 % (bf16) / 2 % (8-bit) slower than the best one on
 // the geometric mean, 10 / 16 % at worst.
 struct DgradShape {
-  int bm, bn, kg, r;
+  int bm, bn, kg, r, threads;
   double f, lat, thr, base;
 };
 enum { DG_256, DG_256x128, DG_128_KG1, DG_128_KG2, DG_64_KG1, DG_64_KG2, DG_64_KG4, DG_SHAPES, DG_DUAL = DG_SHAPES };
 static const DgradShape kDgrad16[DG_SHAPES] = {
-  {256, 256, 1, 1, 6.24, 1.34, 0.00, 0.0},
-  {256, 128, 1, 1, 4.71, 0.825, 0.00, 0.0},
-  {128, 128, 1, 2, 2.61, 0.818, 0.627, 1.7},
-  {128, 128, 2, 1, 3.26, 1.17, 0.00, 0.8},
-  {64, 64, 1, 3, 0.77, 0.427, 0.248, 2.9},
-  {64, 64, 2, 2, 1.52, 0.548, 0.446, 2.1},
-  {64, 64, 4, 1, 2.30, 0.927, 0.00, 1.5},
+  {256, 256, 1, 1, 512, 6.24, 1.34, 0.00, 0.0},
+  {256, 128, 1, 1, 512, 4.71, 0.825, 0.00, 0.0},
+  {128, 128, 1, 2, 256, 2.61, 0.818, 0.627, 1.7},
+  {128, 128, 2, 1, 512, 3.26, 1.17, 0.00, 0.8},
+  {64, 64, 1, 3, 256, 0.77, 0.427, 0.248, 2.9},
+  {64, 64, 2, 2, 512, 1.52, 0.548, 0.446, 2.1},
+  {64, 64, 4, 1, 1024, 2.30, 0.927, 0.00, 1.5},
 };
 static const DgradShape kDgrad8[DG_SHAPES] = {
-  {256, 256, 1, 1, 6.19, 1.536, 0.00, 0.0},
-  {256, 128, 1, 1, 4.33, 1.036, 0.00, 0.4},
-  {128, 128, 1, 2, 2.28, 1.044, 0.774, 1.9},
-  {128, 128, 2, 1, 3.13, 1.437, 0.00, 1.2},
-  {64, 64, 1, 3, 0.73, 0.524, 0.292, 3.0},
-  {64, 64, 2, 2, 1.42, 0.610, 0.543, 2.4},
-  {64, 64, 4, 1, 2.32, 1.098, 0.00, 1.6},
+  {256, 256, 1, 1, 512, 6.19, 1.536, 0.00, 0.0},
+  {256, 128, 1, 1, 512, 4.33, 1.036, 0.00, 0.4},
+  {128, 128, 1, 2, 256, 2.28, 1.044, 0.774, 1.9},
+  {128, 128, 2, 1, 512, 3.13, 1.437, 0.00, 1.2},
+  {64, 64, 1, 3, 256, 0.73, 0.524, 0.292, 3.0},
+  {64, 64, 2, 2, 512, 1.42, 0.610, 0.543, 2.4},
+  {64, 64, 4, 1, 1024, 2.32, 1.098, 0.00, 1.6},
 };
 
 static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
@@ -1028,6 +1030,17 @@ static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
     }
   }
   return best;
+}
+
+void describe_dgrad(int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t n) {
+  const int cfg = dgrad_choice(dtype != SSTE_BF16, T, O, I);
+  if (cfg == DG_DUAL) {
+    const int64_t big = ((I + 255) / 256) * ((T + 255) / 256);
+    snprintf(text, n, "256x256+256x128 kg 1 r 1 grid %lld block 512", (long long)(big + big % 256));
+    return;
+  }
+  const DgradShape& s = kDgrad16[cfg];
+  snprintf(text, n, "%dx%d kg %d r %d grid %lld block %d", s.bm, s.bn, s.kg, s.r, (long long)(((I + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn)), s.threads);
 }
 
 template <bool FP8, bool BF8>

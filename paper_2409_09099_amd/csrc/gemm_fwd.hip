@@ -40,6 +40,8 @@
 // XCD's L2 and an X tile is fetched from HBM once per XCD.
 #include "common.h"
 
+#include <stdio.h>
+
 namespace sste {
 
 namespace {
@@ -846,33 +848,33 @@ static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, 
 // CU receives operands.  The row of the register-only kernel is fitted to 30 problems of 1 ... 512 tokens against the 32 x 32 tile at
 // the same problems; its step falls with the token rows a tile really has (one token: 0.44 of sixteen).
 struct FwdShape {
-  int bm, bn, kg, r;
+  int bm, bn, kg, r, threads;
   double f, lat, thr, base, store;
 };
 enum { FW_256, FW_256x128, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
 static const FwdShape kFwd16[FW_SHAPES] = {
-  {256, 256, 1, 1, 3.10, 0.689, 0.689, 1.71, 1.09},
-  {256, 128, 1, 2, 2.72, 0.565, 0.450, 1.80, 0.76},
-  {128, 128, 1, 2, 0.58, 0.302, 0.288, 3.40, 0.95},
-  {128, 128, 1, 3, 1.95, 0.383, 0.286, 1.69, 0.94},
-  {128, 64, 1, 2, 0.52, 0.203, 0.187, 3.35, 1.01},
-  {64, 64, 1, 3, 0.70, 0.150, 0.128, 3.19, 1.08},
-  {64, 64, 2, 1, 1.34, 0.256, 0.256, 2.63, 2.13},
-  {64, 32, 4, 1, 1.56, 0.313, 0.313, 2.53, 3.63},
-  {32, 32, 4, 1, 1.55, 0.186, 0.186, 2.55, 3.70},
-  {16, 16, 8, 4, 0.00, 0.525, 0.525, 2.45, 0.02},
+  {256, 256, 1, 1, 512, 3.10, 0.689, 0.689, 1.71, 1.09},
+  {256, 128, 1, 2, 256, 2.72, 0.565, 0.450, 1.80, 0.76},
+  {128, 128, 1, 2, 256, 0.58, 0.302, 0.288, 3.40, 0.95},
+  {128, 128, 1, 3, 256, 1.95, 0.383, 0.286, 1.69, 0.94},
+  {128, 64, 1, 2, 256, 0.52, 0.203, 0.187, 3.35, 1.01},
+  {64, 64, 1, 3, 256, 0.70, 0.150, 0.128, 3.19, 1.08},
+  {64, 64, 2, 1, 512, 1.34, 0.256, 0.256, 2.63, 2.13},
+  {64, 32, 4, 1, 512, 1.56, 0.313, 0.313, 2.53, 3.63},
+  {32, 32, 4, 1, 256, 1.55, 0.186, 0.186, 2.55, 3.70},
+  {16, 16, 8, 4, 512, 0.00, 0.525, 0.525, 2.45, 0.02},
 };
 static const FwdShape kFwd8[FW_SHAPES] = {
-  {256, 256, 1, 1, 1.86, 0.679, 0.679, 2.96, 0.90},
-  {256, 128, 1, 2, 1.49, 0.591, 0.454, 3.06, 0.77},
-  {128, 128, 1, 2, 0.88, 0.264, 0.279, 3.16, 0.76},
-  {128, 128, 1, 3, 1.11, 0.337, 0.279, 2.69, 0.80},
-  {128, 64, 1, 2, 1.01, 0.133, 0.196, 2.96, 0.77},
-  {64, 64, 1, 3, 1.09, 0.133, 0.128, 2.92, 0.70},
-  {64, 64, 2, 1, 1.89, 0.238, 0.238, 2.17, 0.44},
-  {64, 32, 4, 1, 2.95, 0.305, 0.305, 1.26, 1.71},
-  {32, 32, 4, 1, 1.74, 0.151, 0.151, 2.49, 3.42},
-  {16, 16, 8, 4, 0.00, 0.580, 0.480, 2.40, 0.56},
+  {256, 256, 1, 1, 512, 1.86, 0.679, 0.679, 2.96, 0.90},
+  {256, 128, 1, 2, 256, 1.49, 0.591, 0.454, 3.06, 0.77},
+  {128, 128, 1, 2, 256, 0.88, 0.264, 0.279, 3.16, 0.76},
+  {128, 128, 1, 3, 256, 1.11, 0.337, 0.279, 2.69, 0.80},
+  {128, 64, 1, 2, 256, 1.01, 0.133, 0.196, 2.96, 0.77},
+  {64, 64, 1, 3, 256, 1.09, 0.133, 0.128, 2.92, 0.70},
+  {64, 64, 2, 1, 512, 1.89, 0.238, 0.238, 2.17, 0.44},
+  {64, 32, 4, 1, 512, 2.95, 0.305, 0.305, 1.26, 1.71},
+  {32, 32, 4, 1, 256, 1.74, 0.151, 0.151, 2.49, 3.42},
+  {16, 16, 8, 4, 512, 0.00, 0.580, 0.480, 2.40, 0.56},
 };
 
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
@@ -904,6 +906,17 @@ static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
     }
   }
   return best;
+}
+
+void describe_fwd(int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t n) {
+  const int cfg = fwd_choice(dtype == SSTE_F8E4M3, T, O, I);
+  if (cfg == FW_DUAL) {
+    const int64_t big = ((O + 255) / 256) * ((T + 255) / 256);
+    snprintf(text, n, "256x256+256x128 kg 1 r 1 grid %lld block 512", (long long)(big + big % NUM_CU));
+    return;
+  }
+  const FwdShape& s = kFwd16[cfg];
+  snprintf(text, n, "%dx%d kg %d r %d grid %lld block %d", s.bm, s.bn, s.kg, s.r, (long long)(((O + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn)), s.threads);
 }
 
 // Kernel choice for one combination of operand type, output type and amax.

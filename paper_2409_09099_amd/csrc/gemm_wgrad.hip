@@ -24,6 +24,8 @@
 #include <atomic>
 #include <mutex>
 
+#include <stdio.h>
+
 namespace sste {
 
 hipError_t launch_wgrad_fused(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X, int64_t I, int64_t ldx,
@@ -834,6 +836,18 @@ static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
   if (!(e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits))
     e = Entry{T, O, I, dtype, shape, splits, make_wgrad_plan(T, O, I, dtype), true};
   return e.plan;
+}
+
+void describe_wgrad(int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t n) {
+  const WgradPlan p = wgrad_plan(T, O, I, dtype);
+  if (!p.packed) {
+    snprintf(text, n, "fused kg 8 r 1 splits 1 chunks 1 grid %lld block 512", (long long)(((O + 15) / 16) * ((I + 63) / 64)));
+    return;
+  }
+  const WgradShape& w = kWgrad16[p.shape];
+  const int64_t steps = T / (dtype != SSTE_BF16 ? 128 : 64), chunks = (steps + p.chunk_steps - 1) / p.chunk_steps;
+  snprintf(text, n, "%dx%d kg %d r %d splits %d chunks %lld grid %lld block %d", w.bm, w.bn, w.kg, w.r, p.splits, (long long)chunks,
+           (long long)(((O + w.bm - 1) / w.bm) * ((I + w.bn - 1) / w.bn) * p.splits), p.shape <= WG_256x192 ? 512 : 256 * w.kg);
 }
 
 // Arguments of the packed GEMM's kernels.

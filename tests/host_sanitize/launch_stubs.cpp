@@ -35,6 +35,9 @@ bool linear_wgrad_supported(int64_t, int64_t, int64_t, int64_t, int) { return tr
 bool wgrad_plan_override(int mi, int ni, int splits) {
   return ((mi == 0 && ni == 0) || (mi == 8 && ni == 4) || (mi == 6 && ni == 3) || (mi == 8 && ni == 3)) && splits >= 0 && splits <= 32;
 }
+void describe_fwd(int64_t, int64_t, int64_t, int, char*, size_t) { reached("describe_fwd"); }
+void describe_dgrad(int64_t, int64_t, int64_t, int, char*, size_t) { reached("describe_dgrad"); }
+void describe_wgrad(int64_t, int64_t, int64_t, int, char*, size_t) { reached("describe_wgrad"); }
 void* noalloc_scratch(hipError_t*) { reached("noalloc_scratch"); }
 hipError_t launch_linear_wgrad(const void*, int64_t, int64_t, int64_t, int, const void*, int64_t, int64_t, float, RngKey, float*, int64_t, int, void*, hipStream_t) { reached("linear_wgrad"); }
 }  // namespace sste

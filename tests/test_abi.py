@@ -316,3 +316,26 @@ def test_amax_history_is_a_sliding_window_maximum(lib):
     assert h.length == 64
     assert lib.sste_amax_history_push(ctypes.byref(h), 57344.0 * 2, 57344.0) == 2.0
     assert lib.sste_amax_history_push(None, 1.0, 448.0) == 1.0
+
+
+@pytest.mark.parametrize("op,sizes,dtype,want", [
+    ("fwd", (16384, 1024, 4096), 0, "256x256 kg 1 r 1 grid 256 block 512"),
+    ("fwd", (1, 1000, 64), 0, "16x16 kg 8 r 4 grid 63 block 512"),
+    ("dgrad", (16500, 400, 1152), 0, "256x256+256x128 kg 1 r 1 grid 394 block 512"),      # 325 tiles: 256 whole ones and 2 x 69 halves
+    ("wgrad", (64, 8, 16), 0, "fused kg 8 r 1 splits 1 chunks 1 grid 1 block 512"),
+    ("wgrad", (12288, 3880, 168), 0, "128x128 kg 1 r 2 splits 4 chunks 2 grid 248 block 256"),
+])
+def test_describe_plan(op, sizes, dtype, want):
+    import paper_2409_09099_amd as sste
+    assert sste.describe_plan(op, *sizes, dtype) == want
+
+
+def test_describe_plan_refuses(lib):
+    f = lib.sste_describe_plan
+    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]
+    text = ctypes.create_string_buffer(128)
+    assert f(1, 64, 64, 64, 0, None, 128) == 1 and f(1, 64, 64, 64, 0, text, 0) == 1
+    for args in [(0, 64, 64, 64, 0), (9, 64, 64, 64, 0), (1, 64, 64, 64, 3), (5, 64, 64, 64, 2), (1, 64, 64, 32, 0), (1, 64, 4, 64, 0), (5, 64, 64, 64, 1),
+                 (2, 32, 64, 64, 0), (2, 64, 4, 64, 0), (1, 0, 64, 64, 0), (1, -64, 64, 64, 0), (1, 64, 64, 1 << 40, 0)]:
+        assert f(*args, text, 128) == 5 and text.value == b"", args
+    assert f(1, 64, 64, 64, 0, text, 8) == 0 and len(text.value) == 7                     # cut short, terminated
