@@ -63,6 +63,14 @@ __device__ __forceinline__ uint32_t expand_group8(uint32_t w, uint32_t b0, uint3
 }
 }  // namespace
 
+// grad_Z loads.  A row's bytes past its last channel belong to somebody else (the next token's row, padding of any content): S(W) has
+// zeros there, but zero times a NaN pattern is NaN, so the 16-byte pieces past the last channel are pushed out of range and arrive as zeros.
+// `live` bytes of a row are left at this k-step (O x element size - 128 x step), `piece` = 16 x the piece's number inside the k-step.
+constexpr uint32_t NO_PIECE = 0x80000000u;
+__device__ __forceinline__ uint32_t dy_offset(uint32_t off, int piece, int live) { return piece < live ? off : NO_PIECE; }
+// the piece a lane fetches in load number wl of a tile (8 rows x 128 bytes per load, row r's piece c at position c ^ ((r / 2) % 8)), times 16
+__device__ __forceinline__ int dy_piece(int lane, int wl) { return 16 * ((lane & 7) ^ ((4 * (wl & 1) + (lane >> 4)) & 7)); }
+
 // sixteen accumulator registers set to zero by sixteen moves (the compiler otherwise builds a zero vector and copies it)
 __device__ __forceinline__ void zero16(f32x16& v) {
 #pragma unroll
@@ -197,11 +205,12 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   // grad_Z tile
   const int rows_b = (int)((a.T - t0) < BN ? (a.T - t0) : BN);
   const i32x4 bb = rsrc_words(a.dY + t0 * a.lddy_bytes, (uint32_t)((rows_b - 1) * a.lddy_bytes + a.O * EB));
+  const int row_bytes = (int)a.O * EB;
   uint32_t offb[LB];
 #pragma unroll
   for (int i = 0; i < LB; i++) {
-    const int r = 8 * (LB * wave + i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-    offb[i] = (uint32_t)(r * a.lddy_bytes + c * 16);
+    const int r = 8 * (LB * wave + i) + (lane >> 3);
+    offb[i] = (uint32_t)(r * a.lddy_bytes + dy_piece(lane, LB * wave + i));
   }
   const uint32_t ldsB = (uint32_t)(uintptr_t)(lds_u8*)smemB;
 
@@ -288,7 +297,7 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   auto dma_b = [&](int i, int step, int slot) {
     // k-groups past the last k-step read the last one again: finite values against an all-zero S(W) tile
     const int st = KG > 1 ? (step < nsteps ? step : nsteps - 1) : step;
-    dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), offb[i], (uint32_t)st * 128u);
+    dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), dy_offset(offb[i], dy_piece(lane, LB * wave + i), row_bytes - 128 * st), (uint32_t)st * 128u);
   };
   auto gstep = [&](int ls) { return KG > 1 ? ls * KG + kg : ls; };
 
@@ -501,12 +510,13 @@ __device__ __forceinline__ void dgrad_direct_tile(uint8_t* smem, const DgradArgs
   const int rows_b = (int)((a.T - t0) < BN ? (a.T - t0) : BN);
   const i32x4 bb = rsrc_words(a.dY + t0 * a.lddy_bytes, (uint32_t)((rows_b - 1) * a.lddy_bytes + a.O * EB));
   const i32x4 bp = rsrc_words(a.vals, (uint32_t)(rbn * a.isteps * 1024)), bm = rsrc_words(a.meta, (uint32_t)(rbn * a.isteps * MBLK));
+  const int row_bytes = (int)a.O * EB;
   constexpr uint32_t DEAD = 0x80000000u;            // offset past every descriptor: zeros arrive
   uint32_t offb[LB], offp[LP], offm[LM];
 #pragma unroll
   for (int i = 0; i < LB; i++) {
-    const int r = 8 * (LB * wave + i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-    offb[i] = (uint32_t)(r * a.lddy_bytes + c * 16);
+    const int r = 8 * (LB * wave + i) + (lane >> 3);
+    offb[i] = (uint32_t)(r * a.lddy_bytes + dy_piece(lane, LB * wave + i));
   }
 #pragma unroll
   for (int i = 0; i < LP; i++) {
@@ -531,7 +541,8 @@ __device__ __forceinline__ void dgrad_direct_tile(uint8_t* smem, const DgradArgs
   auto load_b = [&](int step, int slot) {
 #pragma unroll
     for (int i = 0; i < LB; i++)
-      dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), offb[i], step < nsteps ? (uint32_t)step * 128u : DEAD);
+      dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), dy_offset(offb[i], dy_piece(lane, LB * wave + i), row_bytes - 128 * step),
+               (uint32_t)step * 128u);
   };
 
   // expansion: the lane's slot of the packed blocks and the identity operand
@@ -702,15 +713,15 @@ __device__ __forceinline__ void dgrad8_tile(uint8_t* smem, const DgradArgs& a, i
   // grad_Z tile: exactly the valid rows and channels; what lies outside reads as zeros
   const int rows_b = (int)((a.T - t0) < BN ? (a.T - t0) : BN);
   const i32x4 bb = rsrc_words(a.dY + t0 * a.lddy_bytes, (uint32_t)((rows_b - 1) * a.lddy_bytes + a.O));
+  const int row_bytes = (int)a.O;
   uint32_t offb[LB];
 #pragma unroll
   for (int i = 0; i < LB; i++) {
     int wl = LB * wave + i;
-    int r = 8 * wl + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-    offb[i] = (uint32_t)(r * a.lddy_bytes + c * 16);
+    int r = 8 * wl + (lane >> 3);
+    offb[i] = (uint32_t)(r * a.lddy_bytes + dy_piece(lane, wl));
   }
   const uint32_t ldsB = (uint32_t)(uintptr_t)(lds_u8*)smemB;
-  constexpr uint32_t DEAD = 0x40000000u;
 
   // packed S(W): this wave's two blocks of a k-step are (row block RBK s + rbl, column step CST tm + csl)
   const BufferRsrc rv = make_rsrc(a.vals, (uint32_t)(rbn * isteps * 1024));
@@ -760,8 +771,8 @@ __device__ __forceinline__ void dgrad8_tile(uint8_t* smem, const DgradArgs& a, i
     _Pragma("unroll") for (int d_ = 0; d_ < 8; d_++) DG_DECODE_PIECE(slot_, d_ >> 2, d_ & 3, PK, PM);     \
   } while (0)
 #define DG_DMA_B(i, step, slot_)                                                                          \
-  dma_b128(bb, ldsB + (uint32_t)(slot_) * BSLOT + (LB * wave + (i)) * 1024, offb[i],                      \
-           (step) < nsteps ? (uint32_t)(step) * 128u : DEAD)
+  dma_b128(bb, ldsB + (uint32_t)(slot_) * BSLOT + (LB * wave + (i)) * 1024,                               \
+           dy_offset(offb[i], dy_piece(lane, LB * wave + (i)), row_bytes - 128 * (int)(step)), (uint32_t)(step) * 128u)
 
   f32x4 acc[MI_][NI_];
 #pragma unroll

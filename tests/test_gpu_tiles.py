@@ -49,6 +49,43 @@ def test_linear_dgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
     assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + np.max(np.abs(ref)) * 1e-4)
 
 
+# every tile of the input gradient, with an incomplete last k-step: (8-bit?, T, O, I, tile of sste_describe_plan)
+DGRAD_PARTIAL_STEPS = [
+    (False, 325, 136, 2816, "64x64 kg 1"), (False, 65, 136, 64, "64x64 kg 2"), (False, 65, 416, 64, "64x64 kg 4"),
+    (False, 16509, 136, 320, "128x128 kg 1"), (False, 771, 200, 2560, "128x128 kg 2"), (False, 16738, 136, 192, "256x128 kg 1"),
+    (False, 11074, 136, 704, "256x256 kg 1"), (False, 10098, 136, 1600, "256x256+256x128 kg 1"),
+    (True, 403, 192, 2432, "64x64 kg 1"), (True, 65, 192, 128, "64x64 kg 2"), (True, 65, 272, 128, "64x64 kg 4"),
+    (True, 17018, 192, 384, "128x128 kg 1"), (True, 3487, 192, 896, "128x128 kg 2"), (True, 16391, 192, 256, "256x128 kg 1"),
+    (True, 4997, 192, 1664, "256x256 kg 1"), (True, 5940, 192, 2816, "256x256+256x128 kg 1"),
+]
+DGRAD_PARTIAL_STEPS = [(dtype, *c[1:]) for c in DGRAD_PARTIAL_STEPS for dtype in (("e4m3", "e5m2") if c[0] else ("bf16",))]
+
+
+def gaussian_operands(sste, dtype, T, O, I):
+    """(grad_Z and its scale, packed weight and its scale) of Gaussian data made on the GPU."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    W = torch.empty((O, I), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=g)
+    if dtype == "bf16":
+        return dY, 1.0, sste.project_pack(W, 1.4830322), 1.0
+    dys, ws = (1e-5 if dtype == "e4m3" else 1e-7), 3e-4
+    return sste.cast_fp8(dY, dys, dt(sste, dtype))[0], dys, sste.project_pack(W, 1.4830322, sste.F8E4M3, ws), ws
+
+
+@pytest.mark.parametrize("dtype,T,O,I,tile", DGRAD_PARTIAL_STEPS)
+def test_linear_dgrad_ignores_what_lies_between_rows(sste, dtype, T, O, I, tile):  # noqa: F811
+    """A row's bytes past its last channel may hold anything: NaN patterns there change no bit of the result."""
+    assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith(tile + " ")
+    dY, dys, packed, ws = gaussian_operands(sste, dtype, T, O, I)
+    pitch = (O // 128 + 1) * 128 + 128
+    padded = torch.full((T, pitch), -1, dtype=torch.int16 if dtype == "bf16" else torch.int8, device="cuda").view(dY.dtype)
+    assert dtype != "bf16" or bool(padded.isnan().all())     # all ones is a NaN in every one of the formats
+    padded[:, :O] = dY
+    want = sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws)
+    got = sste.linear_dgrad(padded[:, :O], *packed, I, dt(sste, dtype), dys, ws)
+    assert bool(want.isfinite().all()) and torch.equal(got, want)
+
+
 FWD_TILES = [
     ("bf16", 5, 264, 1280), ("e4m3", 21, 272, 2432),             # 16 x 16, k-steps dealt to eight waves (19 or 20 of them)
     ("bf16", 82, 1448, 320), ("e4m3", 146, 848, 640),            # 16 x 16, fewer k-steps than waves, three workgroups per CU
