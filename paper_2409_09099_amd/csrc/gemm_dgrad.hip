@@ -295,9 +295,9 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
     }
   };
   auto dma_b = [&](int i, int step, int slot) {
-    // k-groups past the last k-step read the last one again: finite values against an all-zero S(W) tile
-    const int st = KG > 1 ? (step < nsteps ? step : nsteps - 1) : step;
-    dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), dy_offset(offb[i], dy_piece(lane, LB * wave + i), row_bytes - 128 * st), (uint32_t)st * 128u);
+    // a k-step past the last one (of a k-group) has no live piece: zeros against the zeros of its S(W) tile
+    dma_b128(bb, ldsB + (uint32_t)(slot * BSLOT + (LB * wave + i) * 1024), dy_offset(offb[i], dy_piece(lane, LB * wave + i), row_bytes - 128 * step),
+             (uint32_t)step * 128u);
   };
   auto gstep = [&](int ls) { return KG > 1 ? ls * KG + kg : ls; };
 

@@ -491,17 +491,17 @@ k_wgrad_tile(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta,
     offm[i] = blk < blks_a ? (uint32_t)(blk * total_steps * MBLK + 4 * (d % (MBLK / 4))) : DEAD;
   }
   auto issue = [&](int ls, int slot) {
-    // steps past the last one: the packed operand reads zeros; X reads its last step again (finite values against zeros)
+    // a step past the last one reads zeros on both sides (its own operand's last values would do for finite inputs only: zero times an
+    // infinity is a NaN)
     const int st = ls * KG + kg;
-    const bool live = st < nsteps;
+    const uint32_t dead = st < nsteps ? 0u : DEAD, sc = st < nsteps ? (uint32_t)st : 0u;
     const uint32_t base = lds0 + (uint32_t)slot * SLOT;
 #pragma unroll
-    for (int i = 0; i < LA; i++) dma_b128(ba, base + (LA * wave + i) * 1024, offa[i], live ? (uint32_t)st * 1024u : DEAD);
+    for (int i = 0; i < LA; i++) dma_b128(ba, base + (LA * wave + i) * 1024, offa[i] | dead, sc * 1024u);
 #pragma unroll
-    for (int i = 0; i < LM; i++) dma_b32(bm, base + A_BYTES + (LM * wave + i) * 256, offm[i], live ? (uint32_t)st * (uint32_t)MBLK : DEAD);
-    const uint32_t sx = (uint32_t)((live ? st : nsteps - 1) * KS * ldx_bytes);
+    for (int i = 0; i < LM; i++) dma_b32(bm, base + A_BYTES + (LM * wave + i) * 256, offm[i] | dead, sc * (uint32_t)MBLK);
 #pragma unroll
-    for (int i = 0; i < LB; i++) dma_b128(bb, base + A_BYTES + M_BYTES + (LB * wave + i) * 1024, offb[i], sx);
+    for (int i = 0; i < LB; i++) dma_b128(bb, base + A_BYTES + M_BYTES + (LB * wave + i) * 1024, offb[i] | dead, sc * (uint32_t)(KS * ldx_bytes));
   };
 
   f32x16 acc[MT][NT];

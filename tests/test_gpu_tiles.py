@@ -193,3 +193,40 @@ def test_linear_wgrad_without_its_workspace(sste, dtype, T, O, I):  # noqa: F811
     want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
     got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
     assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))      # float32 sums in another order
+
+
+@pytest.mark.parametrize("dtype,T,O,I,tile", [
+    ("bf16", 65, 136, 64, "64x64 kg 2"), ("bf16", 65, 416, 64, "64x64 kg 4"), ("bf16", 2340, 144, 1344, "128x128 kg 2"),
+    ("e5m2", 65, 272, 128, "64x64 kg 4"), ("e5m2", 18, 560, 128, "64x64 kg 2"), ("e5m2", 834, 272, 3584, "128x128 kg 2"),
+])
+def test_linear_dgrad_infinity_stays_with_its_weights(sste, dtype, T, O, I, tile):  # noqa: F811
+    """The k-groups of a tile end on different k-steps; what an idle group multiplies must not turn an infinite gradient into NaN where
+    its weight is recorded."""
+    assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith(tile + " ")
+    dY, dys, packed, ws = gaussian_operands(sste, dtype, T, O, I)
+    dY.view(torch.bfloat16 if dtype == "bf16" else torch.float8_e5m2)[3, O - 1] = float("inf")
+    got = sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws)
+    pick = torch.zeros((1, O), dtype=torch.bfloat16, device="cuda")
+    pick[0, O - 1] = 1.0
+    wdt = sste.BF16 if dtype == "bf16" else sste.F8E4M3
+    recorded = sste.linear_dgrad(pick if dtype == "bf16" else sste.cast_fp8(pick, 1.0)[0], *packed, I, wdt, 1.0, ws)[0] != 0
+    assert bool(got[3].isinf().eq(recorded).all()) and bool(got[3].isnan().eq(~recorded).all())     # zero times infinity is NaN
+    assert bool(got[:3].isfinite().all()) and bool(got[4:].isfinite().all())
+
+
+@pytest.mark.parametrize("T,O,I,tile", [(2368, 272, 280, "64x64 kg 2"), (4544, 1200, 1768, "128x128 kg 2")])
+def test_linear_wgrad_infinity_stays_with_its_records(sste, T, O, I, tile):  # noqa: F811
+    """As above for the weight gradient: an infinite activation meets the gradients the estimator recorded for its token, no others."""
+    assert sste.describe_plan("wgrad", T, O, I).startswith(tile + " ")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    X[:, 7] = 0.0
+    X[T - 1, 7] = 1.0
+    recorded = sste.linear_wgrad(dY, X, 5, 8)[:, 7] != 0
+    assert 0 < int(recorded.sum()) < O
+    X[T - 1, 7] = float("inf")
+    got = sste.linear_wgrad(dY, X, 5, 8)
+    assert bool(got[:, 7].isinf().eq(recorded).all()) and bool(got[:, 7].isfinite().eq(~recorded).all())
+    got[:, 7] = 0.0
+    assert bool(got.isfinite().all())
