@@ -5,14 +5,15 @@ end of the file by the functions of the same names of ``_marshal`` (ext/marshal.
 hand everything out of the ordinary back to the Python definition.
 """
 import ctypes
+import inspect
 import os
 from typing import Optional, Tuple
 
 import torch
 
-try:
-    from . import _marshal
-except ImportError:            # not built: every call takes the Python definition
+if os.path.exists(os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")):
+    from . import _marshal     # one that does not fit this interpreter or this torch raises here: falling back would cost every call 8 us unseen
+else:                          # not built: every call takes the Python definition
     _marshal = None
 
 BF16 = 0
@@ -42,6 +43,8 @@ def library() -> ctypes.CDLL:
     if not os.path.exists(_LIB_PATH):
         from . import build
         build.build_library(verbose=False)
+        if _marshal is None:
+            build.build_marshal(verbose=False)       # this process has its functions already; the next one finds the module
     lib = ctypes.CDLL(_LIB_PATH)
     i64, f32, vp, ci, u64, sz = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p, ctypes.c_int, ctypes.c_uint64, ctypes.c_size_t
     lib.sste_version.restype = ci
@@ -269,7 +272,7 @@ class UpdateBatch:
 
     def launch(self, alpha: float):
         """sste_sgd_project_pack_batch on the current stream of the tensors' device."""
-        if _marshal is not None and self.n > 0:
+        if _marshal is not None and self.n > 0 and isinstance(alpha, (int, float)):      # ctypes refuses anything else (a GPU tensor, say)
             _marshal.update_batch_launch(self.table, self.n, self.total_blocks, self.w_dtype, self.val_dtype, alpha)
             return self.vals, self.metas
         _check(library().sste_sgd_project_pack_batch(_ptr(self.table), self.n, self.total_blocks, self.w_dtype,
@@ -501,7 +504,16 @@ _PYTHON = {f.__name__: f for f in (project_pack, sgd_project_pack, linear_fwd, l
 _NATIVE_ENTRY_POINTS = ("sste_project_pack_gamma", "sste_sgd_project_pack", "sste_linear_fwd_ex", "sste_linear_fwd_act", "sste_linear_dgrad_act",
                         "sste_linear_wgrad_at", "sste_wgrad_workspace_bytes", "sste_cast_fp8", "sste_project_pack_batch",
                         "sste_sgd_project_pack_batch", "sste_last_error")
+
+
+def _native_doc(f) -> str:
+    """Signature and documentation of a Python definition, in the form a native function carries them."""
+    params = [p.replace(annotation=inspect.Parameter.empty) for p in inspect.signature(f).parameters.values()]
+    return "%s(%s)\n--\n\n%s" % (f.__name__, ", ".join(["$module"] + [str(p) for p in params]), inspect.getdoc(f) or "")
+
+
 if _marshal is not None:
     _marshal.bind({}, _PYTHON, SsteError)     # the library's addresses follow when it is loaded, on the first call
+    _marshal.document({name: _native_doc(f) for name, f in _PYTHON.items()})
     for _name in _PYTHON:
         globals()[_name] = getattr(_marshal, _name)

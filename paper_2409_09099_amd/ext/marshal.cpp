@@ -367,9 +367,8 @@ PyObject* update_batch_launch(PyObject*, PyObject* const* args, Py_ssize_t nargs
   const at::Tensor* t = a.needed(args[0]);
   const int n = a.small(args[1], 0), wdt = a.small(args[3], 0), dt = a.small(args[4], 0);
   const int64_t total = a.integer(args[2], 0);
+  const double alpha = a.number(args[5], 0);
   if (!a.ok) return PyErr_SetString(PyExc_TypeError, "update_batch_launch: a tensor, four integers and a number"), nullptr;
-  const double alpha = PyFloat_AsDouble(args[5]);
-  if (PyErr_Occurred()) return nullptr;
   void* s = stream_of(*t);
   CALL(st, p_sgd_project_pack_batch(address(t), n, total, wdt, dt, (float)alpha, s));
   if (st) return fail(st);
@@ -426,14 +425,31 @@ PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
   END_HANDLE_TH_ERRORS
 }
 
-#define FAST(name) {#name, (PyCFunction)(void (*)(void))(FastCall)guarded<name>, METH_FASTCALL | METH_KEYWORDS, "See the function of this name in binding.py."}
+#define FAST(name) {#name, (PyCFunction)(void (*)(void))(FastCall)guarded<name>, METH_FASTCALL | METH_KEYWORDS, nullptr}
+PyObject* document(PyObject*, PyObject* docs);
 PyMethodDef methods[] = {
   FAST(project_pack), FAST(sgd_project_pack), FAST(linear_fwd), FAST(linear_fwd_ex), FAST(linear_fwd_act), FAST(linear_dgrad), FAST(linear_dgrad_act),
   FAST(linear_wgrad), FAST(cast_fp8),
   {"pack_batch_launch", (PyCFunction)(void (*)(void))(PlainCall)guarded<pack_batch_launch>, METH_FASTCALL, "Launches a prepared sste_project_pack_batch table."},
   {"update_batch_launch", (PyCFunction)(void (*)(void))(PlainCall)guarded<update_batch_launch>, METH_FASTCALL, "Launches a prepared sste_sgd_project_pack_batch table."},
   {"bind", bind, METH_VARARGS, "bind(addresses, functions, error)"},
+  {"document", document, METH_O, "document(dict of function name -> signature and documentation)"},
   {nullptr, nullptr, 0, nullptr}};
+// The functions' signatures and documentation, from the Python definitions.  The dict is kept: a method table holds plain pointers.
+PyObject* document(PyObject*, PyObject* docs) {
+  static PyObject* kept = nullptr;
+  if (!PyDict_Check(docs)) return PyErr_SetString(PyExc_TypeError, "document: a dict"), nullptr;
+  PyObject* d = PyDict_Copy(docs);
+  if (!d) return nullptr;
+  for (PyMethodDef* m = methods; m->ml_name; m++)
+    if (PyObject* text = PyDict_GetItemString(d, m->ml_name)) {
+      const char* p = PyUnicode_AsUTF8(text);
+      if (!p) return Py_DECREF(d), nullptr;
+      m->ml_doc = p;
+    }
+  Py_XSETREF(kept, d);
+  Py_RETURN_NONE;
+}
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Native argument marshalling of the binding.", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,6 +1,8 @@
 """The native argument marshalling (ext/marshal.cpp) against the Python definitions it stands in for: the same results, the same
 errors, outputs given or made."""
+import inspect
 import os
+import shutil
 import subprocess
 import sys
 
@@ -17,6 +19,34 @@ def test_native_functions_stand_in_for_the_python_ones():
     assert binding._marshal is not None, "_marshal.so is not built"
     for name, fn in binding._PYTHON.items():
         assert getattr(sste, name) is getattr(binding._marshal, name) and fn.__name__ == name
+
+
+def test_native_functions_keep_signature_and_documentation():
+    for name, fn in binding._PYTHON.items():
+        want, got = inspect.signature(fn).parameters, inspect.signature(getattr(sste, name)).parameters
+        assert [(p.name, p.default, p.kind) for p in got.values()] == [(p.name, p.default, p.kind) for p in want.values()], name
+        assert getattr(sste, name).__doc__ == inspect.getdoc(fn)
+
+
+def test_a_module_that_cannot_be_loaded_is_reported(tmp_path):
+    """A _marshal.so that does not fit raises when the package is imported; without one the Python definitions serve."""
+    pkg = tmp_path / "paper_2409_09099_amd"
+    shutil.copytree(os.path.join(ROOT, "paper_2409_09099_amd"), pkg, ignore=shutil.ignore_patterns("*.so", "csrc", "ext", "__pycache__"))
+    run = lambda: subprocess.run([sys.executable, "-c", "import paper_2409_09099_amd as s; print(s.linear_fwd.__module__)"], cwd=tmp_path,  # noqa: E731
+                                 capture_output=True, text=True, timeout=100)
+    assert run().stdout.strip() == "paper_2409_09099_amd.binding"
+    (pkg / "_marshal.so").write_bytes(b"not a module")
+    r = run()
+    assert r.returncode != 0 and "ImportError" in r.stderr, r.stderr[-500:]
+
+
+def test_update_step_takes_numbers_only():
+    """Anything else that could pass for a float (a GPU tensor would synchronise) is refused, as through ctypes."""
+    table = torch.zeros(64, dtype=torch.uint8)
+    sste.library()
+    for alpha in (torch.tensor(0.1), "0.1", None):
+        with pytest.raises(TypeError):
+            binding._marshal.update_batch_launch(table, 1, 1, 0, 0, alpha)
 
 
 @pytest.mark.parametrize("call,error", [
