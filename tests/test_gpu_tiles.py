@@ -222,10 +222,10 @@ def test_linear_wgrad_infinity_stays_with_its_records(sste, T, O, I, tile):  # n
     dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
     X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
     X[:, 7] = 0.0
-    X[T - 1, 7] = 1.0
+    X[T - 4, 7] = 1.0                  # first token of the last group: what an operand of all zeros points at
     recorded = sste.linear_wgrad(dY, X, 5, 8)[:, 7] != 0
     assert 0 < int(recorded.sum()) < O
-    X[T - 1, 7] = float("inf")
+    X[T - 4, 7] = float("inf")
     got = sste.linear_wgrad(dY, X, 5, 8)
     assert bool(got[:, 7].isinf().eq(recorded).all()) and bool(got[:, 7].isfinite().eq(~recorded).all())
     got[:, 7] = 0.0
