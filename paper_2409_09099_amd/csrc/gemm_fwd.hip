@@ -842,21 +842,27 @@ static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, 
 
 // Choice of the kernel.  Time model in microseconds: base + store * (output bytes at 5 TB/s) + rounds, a workgroup costing F + nk * step
 // with nk its k-steps (each k-group of a workgroup takes a KG-th of them) and step = max(lat, r * thr) for r workgroups sharing a CU;
-// R fit a CU (LDS) and what does not fit runs in further rounds.  Fitted to event times of 400 random problems (1 ... 32768 tokens,
-// 64 ... 5120 channels and features), 7...11 % off per problem; the shape it picks is 2 % slower than the best one on the geometric
-// mean.  What the fit says about the chip: thr is the operand bytes of a k-step at 75...100 B/ns for every shape, the rate at which a
-// CU receives operands.  The row of the register-only kernel is fitted to 30 problems of 1 ... 512 tokens against the 32 x 32 tile at
-// the same problems; its step falls with the token rows a tile really has (one token: 0.44 of sixteen).
+// R fit a CU (LDS) and what does not fit runs in further rounds.  The two-shape grid has a row of its own: whole rounds of 256 x 256 tiles
+// and one of 256 x 128 tiles, each with its F and step.  All 8-bit rows and the bf16 rows of the small tiles are fitted to event times of
+// 400 random problems (1 ... 32768 tokens, 64 ... 5120 channels and features).  The bf16 rows from 128 x 128 up are chosen for what the choice
+// costs on 640 random problems (1 ... 32768 tokens, 256 ... 5120 channels and features), timed both on one set of buffers and on sets
+// that rotate through 700 MB (geometric mean of the two): 0.4 % slower than the best tile on the geometric mean, 14 % at worst (20800 x 1136
+// x 384: 25.3 against 22.2 us), 2 % of the problems by more than 5 %; under 512 tokens 0.04 % and 3 %.  Before, with the two-shape grid's
+// time guessed from the 256 x 256 row: 0.7 %, 27 % and 4.8 %, and 8192 x 3072 x 768 ran 256 x 128 tiles (31.7 us inside a training step) instead
+// of the two-shape grid (29.2).  The 8-bit choice on such problems: 2.8 %, 48 % at worst (5696 x 512 x 512: 8.0 against 5.4 us); rows chosen
+// the same way bring 1.2 % there but lose 1 % on the layers of the GPT-2 workloads, which the fitted ones serve within 0.4 %.  The row of
+// the register-only kernel is fitted to 30 problems of 1 ... 512 tokens against the 32 x 32 tile at the same problems; its step falls with
+// the token rows a tile really has (one token: 0.44 of sixteen).
 struct FwdShape {
   int bm, bn, kg, r, threads;
   double f, lat, thr, base, store;
 };
 enum { FW_256, FW_256x128, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
 static const FwdShape kFwd16[FW_SHAPES] = {
-  {256, 256, 1, 1, 512, 3.10, 0.689, 0.689, 1.71, 1.09},
-  {256, 128, 1, 2, 256, 2.72, 0.565, 0.450, 1.80, 0.76},
-  {128, 128, 1, 2, 256, 0.58, 0.302, 0.288, 3.40, 0.95},
-  {128, 128, 1, 3, 256, 1.95, 0.383, 0.286, 1.69, 0.94},
+  {256, 256, 1, 1, 512, 2.81, 0.636, 0.636, 1.81, 1.16},
+  {256, 128, 1, 2, 256, 3.07, 0.688, 0.406, 1.64, 0.76},
+  {128, 128, 1, 2, 256, 0.60, 0.327, 0.261, 3.04, 1.01},
+  {128, 128, 1, 3, 256, 1.82, 0.472, 0.293, 1.27, 0.88},
   {128, 64, 1, 2, 256, 0.52, 0.203, 0.187, 3.35, 1.01},
   {64, 64, 1, 3, 256, 0.70, 0.150, 0.128, 3.19, 1.08},
   {64, 64, 2, 1, 512, 1.34, 0.256, 0.256, 2.63, 2.13},
@@ -877,6 +883,12 @@ static const FwdShape kFwd8[FW_SHAPES] = {
   {16, 16, 8, 4, 512, 0.00, 0.580, 0.480, 2.40, 0.56},
 };
 
+// the two-shape grid: F and step of a round of 256 x 256 tiles, of the last one of 256 x 128 tiles, base, store
+struct FwdDual {
+  double f, step, f_half, step_half, base, store;
+};
+static const FwdDual kFwdDual16 = {2.36, 0.709, 2.57, 0.439, 2.32, 1.11}, kFwdDual8 = {1.86, 0.679, 1.86, 0.475, 2.96, 0.90};
+
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
   const FwdShape* tab = fp8 ? kFwd8 : kFwd16;
   const int64_t steps = I / (fp8 ? 128 : 64);
@@ -896,9 +908,10 @@ static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
       best_t = t;
       best = c;
     }
-    // 256 x 256 tiles whose last round is at most half full: that round as 256 x 128 tiles at 0.7 of the k-step
+    // 256 x 256 tiles whose last round is at most half full: that round as 256 x 128 tiles
     if (c == FW_256 && wgs > NUM_CU && wgs % NUM_CU != 0 && wgs % NUM_CU <= NUM_CU / 2) {
-      t = fixed + (double)(wgs / NUM_CU) * (s.f + nk * s.lat) + s.f + nk * 0.7 * s.lat;
+      const FwdDual& d = fp8 ? kFwdDual8 : kFwdDual16;
+      t = d.base + d.store * out_us + (double)(wgs / NUM_CU) * (d.f + nk * d.step) + d.f_half + nk * d.step_half;
       if (t < best_t) {
         best_t = t;
         best = FW_DUAL;

@@ -320,6 +320,7 @@ def test_amax_history_is_a_sliding_window_maximum(lib):
 
 @pytest.mark.parametrize("op,sizes,dtype,want", [
     ("fwd", (16384, 1024, 4096), 0, "256x256 kg 1 r 1 grid 256 block 512"),
+    ("fwd", (8192, 3072, 768), 0, "256x256+256x128 kg 1 r 1 grid 512 block 512"),        # 384 tiles: one whole round and half a one
     ("fwd", (1, 1000, 64), 0, "16x16 kg 8 r 4 grid 63 block 512"),
     ("dgrad", (16500, 400, 1152), 0, "256x256+256x128 kg 1 r 1 grid 394 block 512"),      # 325 tiles: 256 whole ones and 2 x 69 halves
     ("wgrad", (64, 8, 16), 0, "fused kg 8 r 1 splits 1 chunks 1 grid 1 block 512"),
