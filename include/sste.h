@@ -324,7 +324,7 @@ float sste_amax_history_push(sste_amax_history* h, float amax, float format_max)
  *                 bytes of dY) next to the partial sums of the token-axis splits, which are reduced in
  *                 a fixed order, so the result is bitwise reproducible from run to run.  May be NULL
  *                 when that size is 0.  Problems with T < 2048, O < 256 or I < 256 also run with less
- *                 (or NULL), at the speed of the fused kernel.
+ *                 (or NULL, or misaligned), at the speed of the fused kernel.
  */
 int sste_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, float dy_scale,
                       const void* X, int64_t I, int64_t ldx, float x_scale,
@@ -357,7 +357,9 @@ int sste_linear_wgrad_at(const void* dY, int64_t T, int64_t O, int64_t lddy, int
  * SSTE_ERR_WORKSPACE before anything is launched (64 MiB covers the 3072 x 768 layer at 8192 tokens;
  * larger layers need sste_linear_wgrad with a caller-owned workspace).
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different
- * streams, or different threads) race; calls on one stream are ordered and safe.  Nothing in the array
+ * streams, or different threads) race; calls on one stream are ordered and safe.  This holds for problems
+ * of every size: which of them use the array is the planner's choice (today nearly all but the smallest; a
+ * problem uses it where sste_wgrad_workspace_bytes() is not 0) and changes from version to version.  Nothing in the array
  * has to start at zero (every byte a call reads it has written before), so the previous call's contents,
  * of any size, do no harm.
  */

@@ -543,9 +543,9 @@ int sste_linear_wgrad_at(const void* dY, int64_t T, int64_t O, int64_t lddy, int
   st = check_first_token("linear_wgrad", first_token, T, O);
   if (st != SSTE_OK) return st;
   size_t need = sste_wgrad_workspace_bytes(T, O, I, dtype);
-  // a short or narrow problem given no workspace, or too small a one, runs the fused kernel, which needs none (the same function of its
-  // arguments, slower where the packed path was the choice)
-  if (workspace_bytes < need && (T < 2048 || O < 256 || I < 256)) need = 0, workspace = nullptr;
+  // a short or narrow problem given no workspace, too small or a misaligned one runs the fused kernel, which needs none (the same function
+  // of its arguments, slower where the packed path was the choice)
+  if ((workspace_bytes < need || !workspace || !aligned16(workspace)) && (T < 2048 || O < 256 || I < 256)) need = 0, workspace = nullptr;
   if (need > 0) {
     if (!workspace) return fail(SSTE_ERR_WORKSPACE, "linear_wgrad: workspace is NULL, %zu bytes needed", need);
     if (workspace_bytes < need) return fail(SSTE_ERR_WORKSPACE, "linear_wgrad: workspace has %zu bytes, %zu needed", workspace_bytes, need);

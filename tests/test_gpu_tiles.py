@@ -191,8 +191,10 @@ def test_linear_wgrad_without_its_workspace(sste, dtype, T, O, I):  # noqa: F811
         dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs, dt(sste, dtype))[0]
     assert sste.wgrad_workspace_bytes(T, O, I, dt(sste, dtype)) > 0
     want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
-    got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
-    assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))      # float32 sums in another order
+    need = sste.wgrad_workspace_bytes(T, O, I, dt(sste, dtype))
+    for workspace in (torch.empty(16, dtype=torch.uint8, device="cuda"), torch.empty(need + 16, dtype=torch.uint8, device="cuda")[4:]):   # too small; misaligned
+        got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=workspace)
+        assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))  # float32 sums in another order
 
 
 @pytest.mark.parametrize("dtype,T,O,I,tile", [
