@@ -831,10 +831,13 @@ static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
     bool used;
   };
   static thread_local Entry cache[16];
+  static thread_local unsigned oldest = 0;
   const int shape = g_force_shape, splits = g_force_splits;
-  Entry& e = cache[((uint64_t)T * 31 + (uint64_t)O * 7 + (uint64_t)I / 8 * 3 + (uint64_t)dtype) % 16];
-  if (!(e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits))
-    e = Entry{T, O, I, dtype, shape, splits, make_wgrad_plan(T, O, I, dtype), true};
+  for (const Entry& e : cache)
+    if (e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits) return e.plan;
+  Entry& e = cache[oldest];
+  oldest = (oldest + 1) % 16;
+  e = Entry{T, O, I, dtype, shape, splits, make_wgrad_plan(T, O, I, dtype), true};
   return e.plan;
 }
 
