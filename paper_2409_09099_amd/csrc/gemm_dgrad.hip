@@ -189,10 +189,8 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   constexpr int EBK = BM / 16 / NWG;                // packed blocks per wave and k-step: 32 channels x 32 (bf16) / 64 (8-bit) features
   constexpr int NU = FP8 ? 2 * EBK : EBK;           // expansion instructions per wave and k-step
   constexpr int NU0 = NU > 2 ? NU / 2 : (FP8 ? 1 : NU);            // ... of which in the last stage (the rest in the next k-step's first)
-  constexpr int MH = (FP8 && MT == 4) ? 2 : 1;      // stages per k-slice
-  constexpr int MPS = MT / MH;                      // A row blocks per stage
   constexpr int PPF = FP8 ? 2 : 1;                  // 16-byte pieces per fragment
-  constexpr int NSTG = (FP8 ? 2 : 4) * MH;          // stages per k-step
+  constexpr int NSTG = FP8 ? 2 : 4;                 // stages per k-step: k-slices of the MFMA tiles
   static_assert(LB >= 1 && EBK >= 1, "tile too small for this many waves");
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -319,35 +317,35 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   for (int kk = 0; kk < 4; kk++) fr[kk] = (uint32_t)(n * 128 + (((2 * kk + hh) ^ ((n >> 1) & 7)) * 16));
   const uint32_t fa_base = (uint32_t)(wm * MT * 4096), fb_base = (uint32_t)(wn * NT * 4096);
 
-  uint4 fa[2][MPS][PPF], fb[2][NT][PPF];
-  // fragment read number k of stage st (k-slice st / MH, A half st % MH): first A's, then, where the k-slice is new, B's
-  constexpr int NRA = MPS * PPF, NRB = NT * PPF;
+  uint4 fa[2][MT][PPF], fb[2][NT][PPF];
+  // fragment read number k of stage st: first A's, then B's
+  constexpr int NRA = MT * PPF, NRB = NT * PPF;
   auto read_frag = [&](int st, int k, const uint8_t* sa, const uint8_t* sb) {
     if (k < NRA) {
       const int m = k / PPF, p = k % PPF;
-      fa[st & 1][m][p] = *(const uint4*)(sa + fa_base + ((st % MH) * MPS + m) * 4096 + fr[PPF * (st / MH) + p]);
-    } else if (st % MH == 0) {
+      fa[st & 1][m][p] = *(const uint4*)(sa + fa_base + m * 4096 + fr[PPF * st + p]);
+    } else {
       const int t = (k - NRA) / PPF, p = (k - NRA) % PPF;
-      fb[(st / MH) & 1][t][p] = *(const uint4*)(sb + fb_base + t * 4096 + fr[PPF * (st / MH) + p]);
+      fb[st & 1][t][p] = *(const uint4*)(sb + fb_base + t * 4096 + fr[PPF * st + p]);
     }
   };
   auto mma = [&](int st, int k) {                   // MFMA k of stage st
     const int m = k / NT, t = k % NT;
-    f32x16& c = acc[(st % MH) * MPS + m][t];
+    f32x16& c = acc[m][t];
     if (FP8) {
       i32x8 av, bv;
       __builtin_memcpy(&av, &fa[st & 1][m][0], 32);
-      __builtin_memcpy(&bv, &fb[(st / MH) & 1][t][0], 32);
+      __builtin_memcpy(&bv, &fb[st & 1][t][0], 32);
       // format arguments: A (expanded weight) e4m3; B (grad_Z) e4m3, or e5m2 when BF8; zero scales: the unscaled form
       c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 0, BF8 ? 1 : 0, 0, 0, 0, 0);
     } else {
       bf16x8 av, bv;
       __builtin_memcpy(&av, &fa[st & 1][m][0], 16);
-      __builtin_memcpy(&bv, &fb[(st / MH) & 1][t][0], 16);
+      __builtin_memcpy(&bv, &fb[st & 1][t][0], 16);
       c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
     }
   };
-  constexpr int NM = MPS * NT;                      // MFMAs per stage
+  constexpr int NM = MT * NT;                      // MFMAs per stage
   constexpr int RDW = NM > 4 ? NM / 2 : 1;          // ... of which the first RDW have the next stage's fragment reads between them
   // The MFMAs of stage st; between them the fragment reads of stage st_n (slots na, nb), expansion units u0 .. u0 + nu - 1 (if on;
   // an expansion's result is only converted after further MFMAs) and, behind the last of them, the requests of k-step `lstep`'s

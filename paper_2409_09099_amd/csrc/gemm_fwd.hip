@@ -644,36 +644,34 @@ k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Few tokens (a decode batch): 16 channels x 16 NI tokens by one workgroup whose KW waves take the k-steps in turn.  The packed
+// Few tokens (a decode batch): 16 channels x 16 tokens by one workgroup whose KW waves take the k-steps in turn.  The packed
 // weight is read once and every wave's operands come straight from memory into its registers (a lane's slot of a packed block and
 // two pieces of an X row ARE its fragments): no LDS, no barrier until the waves' sums are added, U k-steps of loads in flight per wave.
 // Bound by the load instructions a CU can take: the 16 rows of X cost more than the weight (bf16 1280 x 5120: 4.2 us with one token,
-// 7.2 with 16), and so do the k-steps past the end that the last turn of KW * U asks for in vain.  Hence U = 2; with U = 4, us
-// (T x O x I): bf16 16x1280x5120 7.50 -> 7.19, 16x768x3072 5.38 -> 5.04, 512x256x1024 5.05 -> 4.33; e4m3 16x1280x5120 5.03 -> 4.69,
+// 7.2 with 16), and so do the k-steps past the end that the last turn of KW * U asks for in vain.  Hence U = 2; us from
+// U = 4 to U = 2 (T x O x I): bf16 16x1280x5120 7.50 -> 7.19, 16x768x3072 5.38 -> 5.04, 512x256x1024 5.05 -> 4.33; e4m3 16x1280x5120 5.03 -> 4.69,
 // 16x5120x1280 4.29 -> 3.58, 48x3072x768 4.41 -> 3.60.  16 waves, or more k-steps in flight, are slower (8.5 and 8.3 us on the first).
-template <bool FP8, int NI, int KW, int U, bool ZF8, bool AMAX>
+template <bool FP8, int KW, int U, bool ZF8, bool AMAX>
 __global__ void __launch_bounds__(64 * KW)
 k_linear_fwd_skinny(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
                     const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
   constexpr int MBLK = FP8 ? 256 : 128;
-  __shared__ __align__(16) uint8_t smem[KW * NI * 1024];
+  __shared__ __align__(16) uint8_t smem[KW * 1024];
   __shared__ uint32_t red[KW];
   const int tm = blockIdx.x % m_tiles, tn = blockIdx.x / m_tiles;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, q = lane >> 4;
-  const int64_t o0 = (int64_t)tm * 16, t0 = (int64_t)tn * (16 * NI);
+  const int64_t o0 = (int64_t)tm * 16, t0 = (int64_t)tn * 16;
   const int nsteps = (int)(k_bytes / 128);
-  const int rows_b = (int)((T - t0) < 16 * NI ? (T - t0) : 16 * NI);
+  const int rows_b = (int)((T - t0) < 16 ? (T - t0) : 16);
   const BufferRsrc ra = make_rsrc(vals + (int64_t)tm * nsteps * 1024, (uint32_t)(nsteps * 1024));
   const BufferRsrc rm = make_rsrc(meta + (int64_t)tm * nsteps * MBLK, (uint32_t)(nsteps * MBLK));
   const BufferRsrc rb = make_rsrc(X + t0 * ldx_bytes, (uint32_t)((rows_b - 1) * ldx_bytes + k_bytes));
   const uint32_t offa = lane * 16, offm = lane * (MBLK / 64), offb = (uint32_t)(j * ldx_bytes + q * 16);
 
-  f32x4 acc[NI];
-#pragma unroll
-  for (int t = 0; t < NI; t++) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (int s = wave; s < nsteps; s += KW * U) {
-    uint4 fa[U], fb[U][NI][2];
+    uint4 fa[U], fb[U][2];
     int fi[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
@@ -685,43 +683,37 @@ k_linear_fwd_skinny(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, i
       fa[u] = buffer_load_b128(ra, offa + dead, (uint32_t)sc * 1024u);
       if (FP8) fi[u] = __builtin_amdgcn_raw_buffer_load_b32(rm, (int)(offm + dead), sc * MBLK, 0);
       else fi[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rm, (int)(offm + dead), sc * MBLK, 0);
-#pragma unroll
-      for (int t = 0; t < NI; t++) {
-        const uint32_t o = (16 * t + j < rows_b ? offb + (uint32_t)(16 * t * ldx_bytes) : 0x80000000u) | dead;
-        fb[u][t][0] = buffer_load_b128(rb, o, (uint32_t)sc * 128u);
-        fb[u][t][1] = buffer_load_b128(rb, o + 64u, (uint32_t)sc * 128u);
-      }
+      const uint32_t o = (j < rows_b ? offb : 0x80000000u) | dead;
+      fb[u][0] = buffer_load_b128(rb, o, (uint32_t)sc * 128u);
+      fb[u][1] = buffer_load_b128(rb, o + 64u, (uint32_t)sc * 128u);
     }
     __builtin_amdgcn_sched_barrier(0);       // the loads of all U k-steps are requested before the first use
 #pragma unroll
-    for (int u = 0; u < U; u++)
-#pragma unroll
-      for (int t = 0; t < NI; t++) {
-        if (FP8) {
-          i32x4 av;
-          i32x8 bv;
-          __builtin_memcpy(&av, &fa[u], 16);
-          __builtin_memcpy(&bv, &fb[u][t][0], 32);
-          acc[t] = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(av, bv, acc[t], fi[u], 0, 0);
-        } else {
-          bf16x8 av;
-          bf16x16 bv;
-          __builtin_memcpy(&av, &fa[u], 16);
-          __builtin_memcpy(&bv, &fb[u][t][0], 32);
-          acc[t] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, bv, acc[t], fi[u], 0, 0);
-        }
+    for (int u = 0; u < U; u++) {
+      if (FP8) {
+        i32x4 av;
+        i32x8 bv;
+        __builtin_memcpy(&av, &fa[u], 16);
+        __builtin_memcpy(&bv, &fb[u][0], 32);
+        acc = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(av, bv, acc, fi[u], 0, 0);
+      } else {
+        bf16x8 av;
+        bf16x16 bv;
+        __builtin_memcpy(&av, &fa[u], 16);
+        __builtin_memcpy(&bv, &fb[u][0], 32);
+        acc = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, bv, acc, fi[u], 0, 0);
       }
+    }
   }
-#pragma unroll
-  for (int t = 0; t < NI; t++) *(f32x4*)(smem + (wave * NI + t) * 1024 + lane * 16) = acc[t];
+  *(f32x4*)(smem + wave * 1024 + lane * 16) = acc;
   __syncthreads();
   uint32_t amax = 0;
-  if (wave < NI) {
-    // wave t adds up token tile t: a lane's four values are channels 4 q .. 4 q + 3 of token j
+  if (wave == 0) {
+    // wave 0 adds up: a lane's four values are channels 4 q .. 4 q + 3 of token j
     f32x4 v = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < KW; w++) v += *(const f32x4*)(smem + (w * NI + wave) * 1024 + lane * 16);
-    const int64_t t = t0 + 16 * wave + j, o = o0 + 4 * q;
+    for (int w = 0; w < KW; w++) v += *(const f32x4*)(smem + w * 1024 + lane * 16);
+    const int64_t t = t0 + j, o = o0 + 4 * q;
     if (AMAX) amax = f2u(__builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])), __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3]))));
     if (t < T && o < O) {
       const float sc = out.scale;
@@ -831,12 +823,12 @@ static void launch_fwd_tile(const void* X, int64_t T, int64_t I, int64_t ldx, co
               (const uint8_t*)X, T, I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
 }
 
-template <bool FP8, int NI, int KW, int U, bool ZF8, bool AMAX>
+template <bool FP8, int KW, int U, bool ZF8, bool AMAX>
 static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, const FwdOut& out, const void* vals,
                               const void* meta, int64_t O, hipStream_t s) {
-  int m_tiles = (int)((O + 15) / 16), n_tiles = (int)((T + 16 * NI - 1) / (16 * NI));
+  int m_tiles = (int)((O + 15) / 16), n_tiles = (int)((T + 15) / 16);
   int64_t eb = FP8 ? 1 : 2;
-  SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_skinny<FP8, NI, KW, U, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(64 * KW), s, (const uint8_t*)X, T,
+  SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_skinny<FP8, KW, U, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(64 * KW), s, (const uint8_t*)X, T,
               I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
 }
 
@@ -953,7 +945,7 @@ static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx,
     case FW_64_KG2: FT(2, 2, 1, 1, 2, 4); break;
     case FW_64x32_KG4: FT(2, 1, 1, 1, 4, 4); break;
     case FW_32_KG4: FT(1, 1, 1, 1, 4, 4); break;
-    default: launch_fwd_skinny<FP8, 1, 8, 2, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
+    default: launch_fwd_skinny<FP8, 8, 2, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
   }
 #undef FT
 }
