@@ -793,7 +793,7 @@ def _wgrad_case(sste, dtype, T, O, I, seed=3, offset=5, **kw):
     ("bf16", 512, 256, 1024),        # the tiny workload
     ("bf16", 64, 8, 8),              # one k-step, one partial tile
     ("bf16", 192, 136, 200),         # ragged O and I tails
-    ("bf16", 4096, 128, 128),        # one tile, token axis split across workgroups
+    ("bf16", 4096, 128, 128),        # one workgroup for the whole token axis of 16 channels
     ("bf16", 2048, 264, 328),        # estimator pre-pass + packed GEMM, ragged channel and feature tails
     ("bf16", 4096, 512, 256),        # pre-pass path, several tiles and splits
     ("e4m3", 512, 256, 1024),
@@ -836,7 +836,8 @@ def test_linear_wgrad_every_tile_shape_with_ragged_tails(sste, dtype, mi, ni, sp
 
 
 def test_linear_wgrad_accumulate_and_reproducible(sste):
-    T, O, I = 4096, 128, 256
+    T, O, I = 4096, 512, 256
+    assert " splits 6 " in sste.describe_plan("wgrad", T, O, I)
     dW1, ref = _wgrad_case(sste, "bf16", T, O, I)
     dW2, _ = _wgrad_case(sste, "bf16", T, O, I)
     assert torch.equal(dW1, dW2)                                   # fixed-order split reduction

@@ -24,20 +24,21 @@ def packed_weight(sste, O, I, wdt, beta=np.float32(1.4830322)):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
-@pytest.mark.parametrize("T,O,I", [
-    (200, 48, 64),             # 64 x 64 tiles, fewer k-steps than the pipeline is deep
-    (65, 1040, 64),            # ... k-steps dealt to two / four groups, the last round of them incomplete; one row in the last tile
-    (500, 4112, 128),          # ... four groups
-    (1100, 1552, 832),
-    (20000, 48, 320),          # 128 x 128 tiles, ragged features
-    (5100, 656, 704),          # 128 x 128, two groups
-    (9000, 272, 448),          # 256 features x 128 tokens
-    (4100, 144, 2112),         # 256 x 256, 64 features in the last tile
-    (16500, 400, 1152),        # whole rounds of 256 x 256 tiles and halves of them, both axes ragged
+@pytest.mark.parametrize("T,O,I,tile16,tile8", [
+    (200, 48, 64, "64x64 kg 1", "64x64 kg 1"),             # fewer k-steps than the pipeline is deep
+    (65, 1040, 64, "64x64 kg 4", "64x64 kg 2"),            # the last round of the groups incomplete; one row in the last tile
+    (500, 4112, 128, "64x64 kg 4", "64x64 kg 4"),
+    (1100, 1552, 832, "64x64 kg 4", "64x64 kg 2"),
+    (20000, 48, 320, "128x128 kg 1", "128x128 kg 1"),      # ragged features
+    (5100, 656, 704, "128x128 kg 2", "128x128 kg 2"),
+    (9000, 272, 448, "256x128 kg 1", "256x128 kg 1"),
+    (4100, 144, 2112, "256x256 kg 1", "256x256 kg 1"),     # 64 features in the last tile
+    (16500, 400, 1152, "256x256+256x128 kg 1", "256x256+256x128 kg 1"),       # both axes ragged
 ])
-def test_linear_dgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
+def test_linear_dgrad_tiles(sste, dtype, T, O, I, tile16, tile8):  # noqa: F811
     if dtype != "bf16" and I % 128:
         I += 64
+    assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith((tile16 if dtype == "bf16" else tile8) + " ")
     wl = WL.WORKLOADS[1]
     dyc, dys, dY = operand(sste, WL.output_gradient(wl, 0, T=T, O=O)[0], dtype)
     wdt = "bf16" if dtype == "bf16" else "e4m3"
@@ -86,29 +87,60 @@ def test_linear_dgrad_ignores_what_lies_between_rows(sste, dtype, T, O, I, tile)
     assert bool(want.isfinite().all()) and torch.equal(got, want)
 
 
+@pytest.mark.parametrize("dtype,T,O,I,tile", DGRAD_PARTIAL_STEPS)
+def test_linear_dgrad_act_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
+    """The activation's backward in the output stage of every tile: the plain product's bf16 gradient (of the same tile) times GELU' of the
+    stored pre-activation, rounded to bf16; pre-activation and result with padding behind their rows."""
+    assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith(tile + " ")
+    dY, dys, packed, ws = gaussian_operands(sste, dtype, T, O, I)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    Hp = torch.empty((T, I + 24), dtype=torch.bfloat16, device="cuda").normal_(0, 1.5, generator=g)
+    out = torch.full((T, I + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    H = Hp[:, :I]
+    sste.linear_dgrad_act(dY, *packed, I, H, dt(sste, dtype), dys, ws, dX=out[:, :I])
+    plain = sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws).double()
+    h = H.double()
+    c, k = 0.7978845608028654, 0.044715
+    th = torch.tanh(c * (h + k * h ** 3))
+    want = plain * (0.5 * (1 + th) + 0.5 * h * (1 - th * th) * c * (1 + 3 * k * h * h))
+    # one bf16 rounding; GELU' itself in float32 (some 1e-6 absolute where its terms cancel)
+    assert bool(((out[:, :I].double() - want).abs() <= want.abs() * 2.0 ** -8 + plain.abs() * 1e-5).all())
+    assert bool((out[:, I:] == 7.0).all())
+
+
+# every tile of the forward product, with the sste_describe_plan text of its shape.  16 x 16: k-steps dealt to eight waves (19 or 20 of them), fewer k-steps than
+# waves, one token and one k-step, turns of 16 k-steps the last half full; the tiles with groups: an incomplete last round of them
 FWD_TILES = [
-    ("bf16", 5, 264, 1280), ("e4m3", 21, 272, 2432),             # 16 x 16, k-steps dealt to eight waves (19 or 20 of them)
-    ("bf16", 82, 1448, 320), ("e4m3", 146, 848, 640),            # 16 x 16, fewer k-steps than waves, three workgroups per CU
-    ("bf16", 76, 2776, 640), ("e4m3", 71, 3472, 896),            # 64 x 32, four groups; 16 x 16
-    ("bf16", 978, 240, 192), ("e4m3", 978, 240, 128),            # 64 x 64
-    ("bf16", 4754, 88, 832), ("e4m3", 602, 352, 384),            # 64 x 64; 16 x 16
-    ("bf16", 8359, 88, 128), ("e4m3", 8389, 80, 256),            # 128 x 64
-    ("bf16", 16872, 88, 384), ("e4m3", 19387, 80, 512),          # 128 x 128, three slots
-    ("bf16", 8885, 152, 128), ("e4m3", 8359, 80, 128),           # 128 x 128, two slots
-    ("bf16", 19747, 536, 128), ("e4m3", 19747, 528, 128),        # 256 x 128, two workgroups per CU
-    ("bf16", 35341, 168, 640), ("e4m3", 25239, 400, 512),        # 256 x 256
-    ("bf16", 22320, 696, 896), ("e4m3", 16503, 1200, 768),       # whole rounds of 256 x 256 tiles and halves of them
-    ("bf16", 1, 1000, 64), ("e4m3", 16, 1296, 5120),             # 16 x 16: one token and one k-step; turns of 16 k-steps, the last half full
-    ("bf16", 33, 1392, 1088), ("e4m3", 33, 2752, 1152),          # 32 x 32, four groups, an incomplete round
-    ("e4m3", 69, 2816, 1152),                                    # 64 x 32, four groups
-    ("bf16", 290, 1656, 1216), ("e4m3", 650, 640, 1152),         # 64 x 64, two groups
+    ("bf16", 5, 264, 1280, "16x16 kg 8 r 4"), ("bf16", 82, 1448, 320, "16x16 kg 8 r 4"), ("bf16", 1, 1000, 64, "16x16 kg 8 r 4"),
+    ("e4m3", 21, 272, 2432, "16x16 kg 8 r 4"), ("e4m3", 146, 848, 640, "16x16 kg 8 r 4"), ("e4m3", 71, 3472, 896, "16x16 kg 8 r 4"), ("e4m3", 602, 352, 384, "16x16 kg 8 r 4"), ("e4m3", 16, 1296, 5120, "16x16 kg 8 r 4"),
+    ("bf16", 33, 1392, 1088, "32x32 kg 4 r 1"),
+    ("e4m3", 33, 2752, 1152, "32x32 kg 4 r 1"),
+    ("bf16", 76, 2776, 640, "64x32 kg 4 r 1"),
+    ("e4m3", 69, 2816, 1152, "64x32 kg 4 r 1"),
+    ("bf16", 978, 240, 192, "64x64 kg 1 r 3"), ("bf16", 4754, 88, 832, "64x64 kg 1 r 3"),
+    ("e4m3", 978, 240, 128, "64x64 kg 1 r 3"),
+    ("bf16", 290, 1656, 1216, "64x64 kg 2 r 1"),
+    ("e4m3", 650, 640, 1152, "64x64 kg 2 r 1"),
+    ("bf16", 8346, 88, 256, "128x64 kg 1 r 2"),
+    ("e4m3", 8389, 80, 256, "128x64 kg 1 r 2"),
+    ("bf16", 16872, 88, 384, "128x128 kg 1 r 2"),
+    ("e4m3", 19387, 80, 512, "128x128 kg 1 r 2"),
+    ("bf16", 8885, 152, 128, "128x128 kg 1 r 3"),
+    ("e4m3", 8359, 80, 128, "128x128 kg 1 r 3"),
+    ("bf16", 19747, 536, 128, "256x128 kg 1 r 2"),
+    ("e4m3", 19747, 528, 128, "256x128 kg 1 r 2"),
+    ("bf16", 35341, 168, 640, "256x256 kg 1 r 1"),
+    ("e4m3", 25239, 400, 512, "256x256 kg 1 r 1"),
+    ("bf16", 22320, 696, 896, "256x256+256x128 kg 1 r 1"),
+    ("e4m3", 16503, 1200, 768, "256x256+256x128 kg 1 r 1"),
 ]
 
 
-@pytest.mark.parametrize("dtype,T,O,I", FWD_TILES)
-def test_linear_fwd_tiles(sste, dtype, T, O, I):  # noqa: F811
+@pytest.mark.parametrize("dtype,T,O,I,tile", FWD_TILES)
+def test_linear_fwd_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     """bf16 output; then, where the format allows it, the e4m3 output with its largest magnitude and the fused activation, held to
     the bf16 output of the same call (which the first comparison has tied to the oracle)."""
+    assert sste.describe_plan("fwd", T, O, I, dt(sste, dtype)).startswith(tile + " ")
     xc, xs, X = operand(sste, WL.activations(WL.WORKLOADS[1], 0, T=T, I=I)[0], dtype)
     rv, rm, ws, vals, meta = packed_weight(sste, O, I, dtype)
     ref = OL.linear_fwd(xc, rv, rm, dtype, xs, ws)
@@ -135,18 +167,27 @@ def test_linear_fwd_tiles(sste, dtype, T, O, I):  # noqa: F811
         assert bool(((dec - want).abs() <= want.abs() * (2.0 ** -4 + 1e-5) + zs * 2.0 ** -9).all())
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
-@pytest.mark.parametrize("T,O,I", [
-    (64, 8, 16), (704, 40, 80), (1152, 296, 136),         # estimator in the operand load: fewer k-steps than waves, incomplete rounds
-    (128, 168, 2448), (3840, 24, 40), (2048, 264, 288),   # 64 x 64; split; two k-groups
-    (128, 1032, 1936), (5632, 72, 1672),                  # 128 x 64; split
-    (1152, 408, 2608), (5376, 72, 2904),                  # 128 x 128; split
-    (3968, 456, 2072),                                    # 128 x 128, two k-groups
-    (192, 1048, 5144),                                    # 192 x 192 over few k-steps
-])
-def test_linear_wgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
-    if dtype != "bf16":
-        T, O, I = -(-T // 128) * 128, -(-O // 16) * 16, -(-I // 16) * 16
+# the shapes of the weight gradient, one split and several: (8-bit?, T, O, I, shape of sste_describe_plan, splits)
+WGRAD_TILES = [
+    (False, 64, 8, 16, "fused", 1), (False, 704, 40, 80, "fused", 1), (False, 1152, 296, 136, "fused", 1),        # fewer k-steps than waves; incomplete rounds
+    (False, 64, 4456, 72, "64x64 kg 1", 1), (False, 3968, 24, 16, "64x64 kg 1", 7),
+    (False, 2176, 264, 264, "64x64 kg 2", 1), (False, 2368, 272, 280, "64x64 kg 2", 1), (False, 7744, 1864, 16, "64x64 kg 2", 8),
+    (False, 64, 1208, 2216, "128x64 kg 1", 1), (False, 3648, 4392, 16, "128x64 kg 1", 7),
+    (False, 704, 3896, 544, "128x128 kg 1", 1), (False, 5760, 152, 2784, "128x128 kg 1", 5), (False, 3840, 936, 2280, "128x128 kg 2", 1),
+    (False, 64, 2504, 2584, "192x192 kg 1", 1), (False, 64, 3832, 2368, "256x192 kg 1", 1), (False, 64, 5192, 2608, "256x256 kg 1", 1),
+    (True, 128, 16, 16, "fused", 1), (True, 768, 48, 80, "fused", 1), (True, 1152, 304, 144, "fused", 1),
+    (True, 128, 4224, 80, "64x64 kg 1", 1), (True, 4224, 16, 16, "64x64 kg 1", 4),
+    (True, 128, 1888, 1616, "128x64 kg 1", 1), (True, 6784, 4304, 16, "128x64 kg 1", 6),
+    (True, 1152, 3888, 528, "128x128 kg 1", 1), (True, 7040, 1248, 784, "128x128 kg 1", 3),
+    (True, 128, 3392, 1808, "192x192 kg 1", 1), (True, 128, 3888, 2400, "256x192 kg 1", 1), (True, 128, 5040, 2480, "256x256 kg 1", 1),
+]
+WGRAD_TILES = [(dtype, *c[1:]) for c in WGRAD_TILES for dtype in (("e4m3", "e5m2") if c[0] else ("bf16",))]
+
+
+@pytest.mark.parametrize("dtype,T,O,I,tile,splits", WGRAD_TILES)
+def test_linear_wgrad_tiles(sste, dtype, T, O, I, tile, splits):  # noqa: F811
+    plan = sste.describe_plan("wgrad", T, O, I, dt(sste, dtype))
+    assert plan.startswith(tile + " ") and f" splits {splits} " in plan, plan
     wl = WL.WORKLOADS[1]
     dyc, dys, dY = operand(sste, WL.output_gradient(wl, 0, T=T, O=O)[0], dtype)
     xc, xs, X = operand(sste, WL.activations(wl, 0, T=T, I=I)[0], "bf16" if dtype == "bf16" else "e4m3")
@@ -157,6 +198,26 @@ def test_linear_wgrad_tiles(sste, dtype, T, O, I):  # noqa: F811
     assert rel_err(got, ref) <= 1e-4                       # the sparse operand is bit-identical: only the order of the sums differs
     twice = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), float(dys), float(xs), dW=dW.clone(), accumulate=True)
     assert torch.allclose(twice, 2.0 * dW, rtol=1e-6, atol=1e-6 * float(dW.abs().max()))
+
+
+@pytest.mark.parametrize("dtype", ["e4m3", "e5m2"])
+def test_linear_wgrad_two_k_groups_8bit(sste, dtype):  # noqa: F811
+    """128 x 128 with two k-groups in 8 bits, which only products too large for the oracle take: equal to the 256 x 256 tile, which is
+    held to the oracle, but for the order of the sums."""
+    T, O, I = 23168, 4112, 896
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    dys, xs = (1e-5 if dtype == "e4m3" else 1e-7), 0.01
+    dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs)[0]
+    assert sste.describe_plan("wgrad", T, O, I, dt(sste, dtype)).startswith("128x128 kg 2 ")
+    got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    try:
+        sste.wgrad_plan_override(8, 4, 2)
+        want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    finally:
+        sste.wgrad_plan_override(0, 0, 0)
+    assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))
 
 
 @pytest.mark.parametrize("dtype,T,O,I", [("bf16", 12288, 3880, 168), ("e4m3", 19072, 5744, 80)])
