@@ -16,7 +16,7 @@
 // would need several: 2112 tokens, 1544 x 832, bf16: 14.1 + 4.4 us (256 x 192 tiles, three splits and their sum) -> 12.9 us (128 x 64).
 // Why not fuse the estimator into the GEMM's operand load everywhere: a GEMM tile that is N columns
 // wide re-derives every group I / N times, and the vector pipe, not the matrix pipe or HBM, sets the time (on the 5120 x 1280 layer
-// a 256-wide tile would issue five times the pre-pass's vector work, about 280 us against the 110 us of the whole GEMM).  The fused
+// a 256-wide tile would issue five times the pre-pass's vector work, about 260 us against the 110 us of the whole GEMM).  The fused
 // kernel (gemm_wgrad_fused.hip) is kept for small problems, where one launch and no workspace matter more.
 #include "common.h"
 #include "mvue_device.h"
