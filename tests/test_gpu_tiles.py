@@ -50,6 +50,15 @@ def test_linear_dgrad_tiles(sste, dtype, T, O, I, tile16, tile8):  # noqa: F811
     assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + np.max(np.abs(ref)) * 1e-4)
 
 
+@pytest.mark.parametrize("dtype,T,O,I", [
+    ("bf16", 198, 208, 4160),          # one k-step per group and a rest, 64 features in the last tile
+    ("bf16", 333, 304, 3968),          # an odd number of k-steps, 13 tokens in the last tile
+    ("e4m3", 277, 144, 3840), ("e5m2", 301, 272, 3456),
+])
+def test_linear_dgrad_tile_of_128_features_64_tokens(sste, dtype, T, O, I):  # noqa: F811
+    test_linear_dgrad_tiles(sste, dtype, T, O, I, "128x64 kg 2", "128x64 kg 2")
+
+
 # every tile of the input gradient, with an incomplete last k-step: (8-bit?, T, O, I, tile of sste_describe_plan)
 DGRAD_PARTIAL_STEPS = [
     (False, 325, 136, 2816, "64x64 kg 1"), (False, 65, 136, 64, "64x64 kg 2"), (False, 65, 416, 64, "64x64 kg 4"),
