@@ -96,9 +96,11 @@ __device__ __forceinline__ float clamp448(float x) { return __builtin_amdgcn_fme
 // whose layer shapes the workloads use (the paper does not name the activation).  Evaluated as x * s with
 // s = 0.5 (1 + tanh(u)) = 1 / (1 + exp(-2u)) on the hardware exp2 / reciprocal: float32, about 1e-6 absolute.
 // The ends behave: exp2 -> inf gives s = 0, exp2 -> 0 gives s = 1.
+// The epilogues that evaluate it are bound by the vector pipe (two quarter-rate instructions and five others per element), so the
+// factors of exp2's argument are multiplied out.
 __device__ __forceinline__ float gelu_sigmoid(float x, float x2) {
-  const float p = __builtin_fmaf(x2, 0.044715f, 1.0f);                    // 1 + 0.044715 x^2
-  const float e = __builtin_amdgcn_exp2f((x * p) * -2.3022081981f);       // exp(-2u): -2 sqrt(2/pi) log2(e) = -2.3022082
+  const float t = __builtin_fmaf(x2, -0.1029432396f, -2.3022081981f);     // -2 sqrt(2/pi) log2(e) (1 + 0.044715 x^2)
+  const float e = __builtin_amdgcn_exp2f(x * t);                          // exp(-2u)
   return __builtin_amdgcn_rcpf(1.0f + e);
 }
 __device__ __forceinline__ float gelu_tanh(float x) { return x * gelu_sigmoid(x, x * x); }
@@ -107,7 +109,7 @@ __device__ __forceinline__ float gelu_tanh_grad(float x) {
   const float x2 = x * x;
   const float s = gelu_sigmoid(x, x2);
   const float q = __builtin_fmaf(x2, 0.2140644488f, 1.5957691216f);       // 2 sqrt(2/pi) (1 + 0.134145 x^2)
-  return __builtin_fmaf(x * q, s - s * s, s);
+  return __builtin_fmaf(x * q, __builtin_fmaf(-s, s, s), s);
 }
 __device__ __forceinline__ float bf16lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }

@@ -75,15 +75,16 @@ struct FwdOut {
 // the requested format and returns max |A| of the piece (float32 bits).
 __device__ __forceinline__ uint32_t fwd_act_piece(const uint4& h, const FwdOut& out, int64_t t, int64_t o) {
   const uint32_t w[4] = {h.x, h.y, h.z, h.w};
-  float a[8];
-  uint32_t m = 0;
+  float a[8], m = 0.0f;
 #pragma unroll
   for (int e = 0; e < 4; e++) {
     a[2 * e] = gelu_tanh(bf16lo_f32(w[e]));
     a[2 * e + 1] = gelu_tanh(bf16hi_f32(w[e]));
-    m = max(m, max(f2u(a[2 * e]) & 0x7FFFFFFFu, f2u(a[2 * e + 1]) & 0x7FFFFFFFu));
   }
   if (out.a8) {
+    // two values per three-operand maximum, their absolute values as source modifiers
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(a[e])), __builtin_fabsf(a[e + 1]));
     const float r = out.a_inv_scale;
     int lo = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[0] * r), clamp448(a[1] * r), 0, false);
     lo = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[2] * r), clamp448(a[3] * r), lo, true);
@@ -95,7 +96,7 @@ __device__ __forceinline__ uint32_t fwd_act_piece(const uint4& h, const FwdOut& 
     uint4 v = make_uint4(bf16_rne_pack(a[0], a[1]), bf16_rne_pack(a[2], a[3]), bf16_rne_pack(a[4], a[5]), bf16_rne_pack(a[6], a[7]));
     store_stream_b128(out.a16 + t * out.lda + o, v);
   }
-  return m;
+  return f2u(m);
 }
 
 // max |acc| of the calling workgroup (NW waves) -> *amax_bits.  `red` is NW dwords of LDS nobody else uses
