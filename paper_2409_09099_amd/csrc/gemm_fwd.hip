@@ -13,12 +13,13 @@
 //
 // Tiling: every wave owns a grid of 16 x 16 MFMA tiles (8 x 4 = 128 channels x 64 tokens in the main
 // shape): per sparse MFMA it reads about 540 B of fragments from LDS, inside the LDS read rate of the CU.
-// Four kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
-//   k_linear_fwd_pipe   software-pipelined 256 x 256 tiles, 8 waves, one workgroup per CU;
+// Five kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
+//   k_linear_fwd_pipe   software-pipelined 256 x 256 and 128 x 256 tiles, 8 waves, one workgroup per CU;
 //   k_linear_fwd_dual   the same tile code for 256 x 256 and 256 x 128 tiles in one grid, for layers
 //                       whose last round of 256 x 256 tiles would fill at most half of the CUs;
-//   k_linear_fwd_tile   256 x 128 (two workgroups per CU) down to 32 x 32 tiles on the 32 x 32 instruction, with
-//                       the contraction split over groups of waves where there are few tiles;
+//   k_linear_fwd_pair   256 x 128 tiles by 4 waves with the same share each, two workgroups per CU;
+//   k_linear_fwd_tile   128 x 128 down to 32 x 32 tiles on the 32 x 32 instruction, with the contraction split over
+//                       groups of waves where there are few tiles;
 //   k_linear_fwd_skinny 16 x 16 tiles straight from memory to registers, for decode batches.
 // Operand tiles travel L2 -> LDS directly (buffer_load ... lds, no staging registers) into rings of
 // LDS slots.  What limits all of them is the L1 of the CU: it keeps 64 line requests in flight, and a
@@ -145,15 +146,100 @@ constexpr int fwd_pipe_smem() {
   return RING > EPI ? RING : EPI;
 }
 
+// Output stage of the pipelined tiles: accumulators -> LDS (row = token, the wave's 16 MI_ channels contiguous) -> 16-byte stores.  Waves
+// 2 x WN; called behind a barrier, with all of the workgroup's LDS free.
+template <int WN, int MI_, int NI_, bool ZF8, bool AMAX>
+__device__ __forceinline__ void fwd_pipe_store(uint8_t* smem, const f32x4 (&acc)[MI_][NI_], int64_t T, int64_t O, const FwdOut& out, int64_t o0,
+                                               int64_t t0) {
+  constexpr int NW = 2 * WN;
+  // row of a token: the wave's channels + pad; bf16 rows of the 256-channel tile are XOR-swizzled instead of padded
+  constexpr int EROW = (MI_ == 8 && !ZF8) ? 256 : 32 * MI_ + 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int j = lane & 15, q = lane >> 4;
+  const float scale = out.scale;
+  uint16_t* __restrict__ Z = out.z16;
+  const int64_t ldz = out.ldz;
+  if (AMAX) {
+    // float maxima of magnitudes: the absolute value is a free source modifier and two values go into one
+    // three-operand maximum (the accumulators are finite)
+    float mf = 0.0f;
+#pragma unroll
+    for (int mi = 0; mi < MI_; mi++)
+#pragma unroll
+      for (int ni = 0; ni < NI_; ni++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) mf = __builtin_fmaxf(mf, __builtin_fabsf(acc[mi][ni][r]));
+    publish_tile_amax<NW>(f2u(mf), out.amax_scale, out.amax_bits, (uint32_t*)smem);
+  }
+  uint8_t* eb = smem + wave * (16 * NI_ * EROW);
+  if (ZF8) {
+    // e4m3 output: a lane's four values of a tile are four consecutive channels = one dword; a token row of
+    // the wave is 16 MI_ bytes
+#pragma unroll
+    for (int mi = 0; mi < MI_; mi++)
+#pragma unroll
+      for (int ni = 0; ni < NI_; ni++) {
+        int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][0] * scale), clamp448(acc[mi][ni][1] * scale), 0, false);
+        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][2] * scale), clamp448(acc[mi][ni][3] * scale), w, true);
+        *(int*)(eb + (16 * ni + j) * EROW + 16 * mi + 4 * q) = w;
+      }
+    constexpr int CHUNKS8 = MI_;                                 // 16-byte chunks (16 channels) per token row
+    constexpr int NCH8 = 16 * NI_ * CHUNKS8;
+#pragma unroll
+    for (int it = 0; it < (NCH8 + 63) / 64; it++) {
+      int c = 64 * it + lane;
+      if (c < NCH8) {
+        int row = c / CHUNKS8, chunk = c % CHUNKS8;
+        uint4 v = *(const uint4*)(eb + row * EROW + chunk * 16);
+        int64_t t = t0 + 16 * NI_ * wn + row, o = o0 + 16 * MI_ * wm + 16 * chunk;
+        if (t < T && o < O) store_stream_b128(out.z8 + t * ldz + o, v);
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int mi = 0; mi < MI_; mi++)
+#pragma unroll
+    for (int ni = 0; ni < NI_; ni++) {
+      uint2 v;
+      v.x = bf16_rne_pack(acc[mi][ni][0] * scale, acc[mi][ni][1] * scale);
+      v.y = bf16_rne_pack(acc[mi][ni][2] * scale, acc[mi][ni][3] * scale);
+      // 16-byte chunk c of token row t sits at position c ^ (t % 16) (MI_ == 8: a row is 256 B = every bank once,
+      // and the padding is not needed): the four-row reads below then run at the full LDS rate, where rows
+      // shifted by the 16-byte pad cost half as much again (measured 567 vs 860 clocks per 128 KiB)
+      if (MI_ == 8) *(uint2*)(eb + (16 * ni + j) * EROW + (((2 * mi + (q >> 1)) ^ j) * 16) + 8 * (q & 1)) = v;
+      else *(uint2*)(eb + (16 * ni + j) * EROW + (16 * mi + 4 * q) * 2) = v;
+    }
+  // same-wave LDS accesses are ordered; no barrier needed for a wave-private region
+  constexpr int CHUNKS = 2 * MI_;                                // 16-byte chunks per token row
+  constexpr int NCH = 16 * NI_ * CHUNKS;
+  uint32_t act_max = 0;
+#pragma unroll
+  for (int it = 0; it < (NCH + 63) / 64; it++) {
+    int c = 64 * it + lane;
+    if (c < NCH) {
+      int row = c / CHUNKS, chunk = c % CHUNKS;
+      uint4 v = *(const uint4*)(eb + row * EROW + (MI_ == 8 ? (chunk ^ (row & 15)) : chunk) * 16);
+      int64_t t = t0 + 16 * NI_ * wn + row, o = o0 + 16 * MI_ * wm + 8 * chunk;
+      if (t < T && o < O) {
+        if (Z) store_stream_b128(Z + t * ldz + o, v);
+        if (out.act) act_max = max(act_max, fwd_act_piece(v, out, t, o));
+      }
+    }
+  }
+  if (out.act && out.amax_bits) {           // uniform over the workgroup
+    __syncthreads();                        // every wave is done with its part of the LDS
+    publish_tile_amax<NW>(act_max, 1.0f, out.amax_bits, (uint32_t*)smem);
+  }
+}
+
 // One output tile: channels [o0, o0 + 32 MI_) x tokens [t0, t0 + 64 NI_).  `smem` is the workgroup's LDS.
 template <bool FP8, int MI_, int NI_, bool ZF8, bool AMAX>
 __device__ __forceinline__ void fwd_pipe_tile(uint8_t* smem, const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes,
                                               int64_t ldx_bytes, const uint8_t* __restrict__ vals,
                                               const uint8_t* __restrict__ meta, int64_t O, const FwdOut& out,
                                               int64_t o0, int64_t t0) {
-  const float scale = out.scale;
-  uint16_t* __restrict__ Z = out.z16;
-  const int64_t ldz = out.ldz;
   constexpr int WN = 4, NW = 8, BM = 32 * MI_, BN = 64 * NI_, NR = 3;
   constexpr int MB = FP8 ? 16 : 8, MBLK = 16 * MB;
   constexpr int LA = (BM / 16 + NW - 1) / NW;                    // weight blocks (1 KiB) per wave and k-step
@@ -161,12 +247,9 @@ __device__ __forceinline__ void fwd_pipe_tile(uint8_t* smem, const uint8_t* __re
   constexpr int LB = NI_;                                        // 8-token slabs (1 KiB) of X
   constexpr int A_BYTES = NW * LA * 1024, M_BYTES = NW * LM * 256;
   constexpr int ASTAGE = A_BYTES + M_BYTES, BSTAGE = BN * 128;
-  // epilogue row: the wave's channels + pad; bf16 rows of the 256-channel tile are XOR-swizzled instead of padded
-  constexpr int EROW = (MI_ == 8 && !ZF8) ? 256 : 32 * MI_ + 16;
   constexpr int NLOAD = LA + LM + LB;                            // issue order inside a k-step: A.., M.., B..
   constexpr int NPIECE = 2 * NI_;                                // 16-byte pieces of the next X fragments
-  static_assert(NR * (ASTAGE + BSTAGE) <= fwd_pipe_smem<FP8, MI_, NI_>() && NW * 16 * NI_ * EROW <= fwd_pipe_smem<FP8, MI_, NI_>(),
-                "LDS size helper out of step with the tile layout");
+  static_assert(NR * (ASTAGE + BSTAGE) <= fwd_pipe_smem<FP8, MI_, NI_>(), "LDS size helper out of step with the tile layout");
   uint8_t* const smemA = smem;
   uint8_t* const smemB = smem + NR * ASTAGE;
 
@@ -306,81 +389,186 @@ __device__ __forceinline__ void fwd_pipe_tile(uint8_t* smem, const uint8_t* __re
 #undef PIPE_STEP
 #undef PIPE_LOAD
 
-  // epilogue: accumulators -> LDS (row = token, the wave's 16 MI_ channels contiguous) -> 16-byte stores
   wait_vmcnt<0>();
   __syncthreads();
-  if (AMAX) {
-    // float maxima of magnitudes: the absolute value is a free source modifier and two values go into one
-    // three-operand maximum (the accumulators are finite)
-    float mf = 0.0f;
+  fwd_pipe_store<WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The same wave tile in workgroups of 2 x WN = 4 waves, 256 channels x 128 tokens, two workgroups per CU: one workgroup's prologue and
+// output stage run beside the other's k-steps.  Two slots per operand.  The one barrier of a k-step stands before its last group of
+// MFMAs, whose fragments are in registers by then: behind it the weight tile of this k-step and the X tile of the next one (read into
+// registers during this one) are free, and what was requested behind the last barrier -- the weight tile of the next k-step, the X tile of the one
+// after -- is complete.  Fetches a third more bytes per result than 256 x 256 tiles and is slower than those on long contractions.
+// On the 16 x 16 instruction, which takes less power per result than the 32 x 32 one of k_linear_fwd_tile's 256 x 128 tile, whose place it took
+// (us, old -> this / 256 x 256 tiles or the two-shape grid; T x O x I): e4m3 32768 x 5120 x 1280 168.7 -> 159.9 / 158.3, 32768 x 3840 x 1280 119.2 ->
+// 117.9 / 118.0; bf16 16384 x 3840 x 1280 103.5 -> 95.4 / 93.5, 16384 x 5120 x 1280 136.1 -> 128.1 / 124.6, 8192 x 3072 x 768 30.3 -> 30.6 / 28.7.
+template <bool FP8, int WN, int MI_, int NI_>
+constexpr int fwd_pair_smem() {
+  constexpr int NW = 2 * WN, MB = FP8 ? 16 : 8;
+  constexpr int RING = 2 * (32 * MI_ * (64 + MB) + 16 * NI_ * WN * 128);
+  constexpr int EPI = NW * 16 * NI_ * (MI_ == 8 ? 256 : 32 * MI_ + 16);
+  return RING > EPI ? RING : EPI;
+}
+
+template <bool FP8, int WN, int MI_, int NI_, bool ZF8, bool AMAX>
+__device__ __forceinline__ void fwd_pair_tile(uint8_t* smem, const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes,
+                                              const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int64_t O, const FwdOut& out,
+                                              int64_t o0, int64_t t0) {
+  constexpr int NW = 2 * WN, BM = 32 * MI_, BN = 16 * NI_ * WN;
+  constexpr int MB = FP8 ? 16 : 8, MBLK = 16 * MB;
+  constexpr int LA = BM / 16 / NW, LM = BM * MB / 256 / NW, LB = BN / 8 / NW;
+  constexpr int A_BYTES = BM * 64, ASTAGE = A_BYTES + BM * MB, BSTAGE = BN * 128;
+  constexpr int NLOAD = LA + LM + LB, NPIECE = 2 * NI_;
+  static_assert(LA * NW * 16 == BM && LM * NW * 256 == BM * MB && LB * NW * 8 == BN, "loads per wave");
+  constexpr int LG = 4;                             // groups behind the barrier that the loads are spread over
+  uint8_t* const smemA = smem;
+  uint8_t* const smemB = smem + 2 * ASTAGE;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int j = lane & 15, q = lane >> 4;
+  const int nsteps = (int)(k_bytes / 128);
+
+  const int64_t rblk0 = o0 / 16, rbn = (O + 15) / 16;
+  const int blks_a = (int)((rbn - rblk0) < BM / 16 ? (rbn - rblk0) : BM / 16);
+  const int rows_b = (int)((T - t0) < BN ? (T - t0) : BN);
+  const i32x4 ba = rsrc_words(vals + rblk0 * nsteps * 1024, (uint32_t)(blks_a * nsteps * 1024));
+  const i32x4 bm = rsrc_words(meta + rblk0 * nsteps * MBLK, (uint32_t)(blks_a * nsteps * MBLK));
+  const i32x4 bb = rsrc_words(X + t0 * ldx_bytes, (uint32_t)((rows_b - 1) * ldx_bytes + k_bytes));
+  uint32_t offa[LA], offb[LB], offm[LM];
 #pragma unroll
-    for (int mi = 0; mi < MI_; mi++)
+  for (int i = 0; i < LA; i++) offa[i] = (uint32_t)((LA * wave + i) * nsteps * 1024 + lane * 16);
 #pragma unroll
-      for (int ni = 0; ni < NI_; ni++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) mf = __builtin_fmaxf(mf, __builtin_fabsf(acc[mi][ni][r]));
-    publish_tile_amax<NW>(f2u(mf), out.amax_scale, out.amax_bits, (uint32_t*)smem);
+  for (int i = 0; i < LB; i++) {
+    const int r = 8 * (LB * wave + i) + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+    offb[i] = (uint32_t)(r * ldx_bytes + c * 16);
   }
-  uint8_t* eb = smem + wave * (16 * NI_ * EROW);
-  if (ZF8) {
-    // e4m3 output: a lane's four values of a tile are four consecutive channels = one dword; a token row of
-    // the wave is 16 MI_ bytes
 #pragma unroll
-    for (int mi = 0; mi < MI_; mi++)
-#pragma unroll
-      for (int ni = 0; ni < NI_; ni++) {
-        int w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][0] * scale), clamp448(acc[mi][ni][1] * scale), 0, false);
-        w = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(acc[mi][ni][2] * scale), clamp448(acc[mi][ni][3] * scale), w, true);
-        *(int*)(eb + (16 * ni + j) * EROW + 16 * mi + 4 * q) = w;
-      }
-    constexpr int CHUNKS8 = MI_;                                 // 16-byte chunks (16 channels) per token row
-    constexpr int NCH8 = 16 * NI_ * CHUNKS8;
-#pragma unroll
-    for (int it = 0; it < (NCH8 + 63) / 64; it++) {
-      int c = 64 * it + lane;
-      if (c < NCH8) {
-        int row = c / CHUNKS8, chunk = c % CHUNKS8;
-        uint4 v = *(const uint4*)(eb + row * EROW + chunk * 16);
-        int64_t t = t0 + 16 * NI_ * wn + row, o = o0 + 16 * MI_ * wm + 16 * chunk;
-        if (t < T && o < O) store_stream_b128(out.z8 + t * ldz + o, v);
-      }
-    }
-    return;
+  for (int i = 0; i < LM; i++) {
+    const int d = 64 * (LM * wave + i) + lane;
+    offm[i] = (uint32_t)((d / (MBLK / 4)) * nsteps * MBLK + 4 * (d % (MBLK / 4)));
   }
+  const uint32_t ldsA = (uint32_t)(uintptr_t)(lds_u8*)smemA;
+  const uint32_t ldsB = (uint32_t)(uintptr_t)(lds_u8*)smemB;
+  constexpr uint32_t DEAD = 0x40000000u;            // scalar offset past every descriptor: the load fetches nothing
+  // load n (0 .. LA + LM - 1: weight of k-step sa into slot pa, then X of k-step sb into slot pb)
+#define PAIR_LOAD(n, sa, pa_, sb, pb_)                                                                       \
+  do {                                                                                                    \
+    if ((n) < LA)                                                                                         \
+      dma_b128(ba, ldsA + (uint32_t)(pa_) * ASTAGE + (LA * wave + (n)) * 1024, offa[(n) < LA ? (n) : 0],    \
+               (sa) < nsteps ? (uint32_t)(sa) * 1024u : DEAD);                                            \
+    else if ((n) < LA + LM)                                                                               \
+      dma_b32(bm, ldsA + (uint32_t)(pa_) * ASTAGE + A_BYTES + (LM * wave + ((n) - LA)) * 256,               \
+              offm[((n) >= LA && (n) < LA + LM) ? (n) - LA : 0],                                          \
+              (sa) < nsteps ? (uint32_t)(sa) * (uint32_t)MBLK : DEAD);                                    \
+    else                                                                                                  \
+      dma_b128(bb, ldsB + (uint32_t)(pb_) * BSTAGE + (LB * wave + ((n) - LA - LM)) * 1024,                  \
+               offb[(n) >= LA + LM ? (n) - LA - LM : 0], (sb) < nsteps ? (uint32_t)(sb) * 128u : DEAD);   \
+  } while (0)
+
+  f32x4 acc[MI_][NI_];
 #pragma unroll
-  for (int mi = 0; mi < MI_; mi++)
+  for (int a = 0; a < MI_; a++)
 #pragma unroll
-    for (int ni = 0; ni < NI_; ni++) {
-      uint2 v;
-      v.x = bf16_rne_pack(acc[mi][ni][0] * scale, acc[mi][ni][1] * scale);
-      v.y = bf16_rne_pack(acc[mi][ni][2] * scale, acc[mi][ni][3] * scale);
-      // 16-byte chunk c of token row t sits at position c ^ (t % 16) (MI_ == 8: a row is 256 B = every bank once,
-      // and the padding is not needed): the four-row reads below then run at the full LDS rate, where rows
-      // shifted by the 16-byte pad cost half as much again (measured 567 vs 860 clocks per 128 KiB)
-      if (MI_ == 8) *(uint2*)(eb + (16 * ni + j) * EROW + (((2 * mi + (q >> 1)) ^ j) * 16) + 8 * (q & 1)) = v;
-      else *(uint2*)(eb + (16 * ni + j) * EROW + (16 * mi + 4 * q) * 2) = v;
-    }
-  // same-wave LDS accesses are ordered; no barrier needed for a wave-private region
-  constexpr int CHUNKS = 2 * MI_;                                // 16-byte chunks per token row
-  constexpr int NCH = 16 * NI_ * CHUNKS;
-  uint32_t act_max = 0;
+    for (int b = 0; b < NI_; b++) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  const uint32_t fa_off = (uint32_t)(MI_ * wm * 1024 + lane * 16);                  // + 1024 mi
+  const uint32_t fm_off = (uint32_t)(A_BYTES + MI_ * wm * MBLK + lane * (MB / 4));  // + MBLK mi
+  const int rb0 = 16 * NI_ * wn + j;                                                // + 16 ni
+  const int cb0 = q ^ ((j >> 1) & 7);
+  const uint32_t fb_off0 = (uint32_t)(rb0 * 128 + cb0 * 16);
+  const uint32_t fb_off1 = (uint32_t)(rb0 * 128 + (cb0 ^ 4) * 16);
+
 #pragma unroll
-  for (int it = 0; it < (NCH + 63) / 64; it++) {
-    int c = 64 * it + lane;
-    if (c < NCH) {
-      int row = c / CHUNKS, chunk = c % CHUNKS;
-      uint4 v = *(const uint4*)(eb + row * EROW + (MI_ == 8 ? (chunk ^ (row & 15)) : chunk) * 16);
-      int64_t t = t0 + 16 * NI_ * wn + row, o = o0 + 16 * MI_ * wm + 8 * chunk;
-      if (t < T && o < O) {
-        if (Z) store_stream_b128(Z + t * ldz + o, v);
-        if (out.act) act_max = max(act_max, fwd_act_piece(v, out, t, o));
-      }
-    }
+  for (int n = 0; n < NLOAD; n++) PAIR_LOAD(n, 0, 0, 0, 0);
+#pragma unroll
+  for (int n = LA + LM; n < NLOAD; n++) PAIR_LOAD(n, 0, 0, 1, 1);
+  uint4 fb0[NI_][2], fb1[NI_][2];     // X fragments: current / next k-step, roles swap every k-step
+  uint4 fa[2];                        // packed-weight fragment of row block mi in fa[mi % 2]
+  int fidx[2];
+  wait_vmcnt<0>();
+  __syncthreads();
+#pragma unroll
+  for (int ni = 0; ni < NI_; ni++) {
+    fb0[ni][0] = *(const uint4*)(smemB + fb_off0 + ni * 2048);
+    fb0[ni][1] = *(const uint4*)(smemB + fb_off1 + ni * 2048);
   }
-  if (out.act && out.amax_bits) {           // uniform over the workgroup
-    __syncthreads();                        // every wave is done with its part of the LDS
-    publish_tile_amax<NW>(act_max, 1.0f, out.amax_bits, (uint32_t*)smem);
+  fa[0] = *(const uint4*)(smemA + fa_off);
+  if (FP8) fidx[0] = *(const int*)(smemA + fm_off);
+  else fidx[0] = *(const uint16_t*)(smemA + fm_off);
+  __syncthreads();                    // X tile 0 has been read
+#pragma unroll
+  for (int n = 0; n < NLOAD; n++)
+    if (spread(n, NLOAD, LG) == 0) PAIR_LOAD(n, 1, 1, 2, 0);
+
+  // one k-step of parity P: MFMAs on BC, next X fragments into BX
+#define PAIR_STEP(BC, BX, P)                                                                              \
+  do {                                                                                                    \
+    const uint8_t* pa = smemA + (P) * ASTAGE;                                                             \
+    const uint8_t* pa1 = smemA + (1 - (P)) * ASTAGE;                                                      \
+    const uint8_t* pb1 = smemB + (1 - (P)) * BSTAGE;                                                      \
+    _Pragma("unroll") for (int mi = 0; mi < MI_; mi++) {                                                  \
+      if (mi == MI_ - 1) {                                                                                \
+        wait_vmcnt<0>();              /* weight tile step + 1 and X tile step + 2 have landed ... */       \
+        __syncthreads();              /* ... for every wave; weight tile step and X tile step + 1 have been read */ \
+      }                                                                                                   \
+      const uint8_t* an = mi < MI_ - 1 ? pa + (mi + 1) * 1024 : pa1;                                      \
+      const uint8_t* mn = mi < MI_ - 1 ? pa + (mi + 1) * MBLK : pa1;                                      \
+      fa[(mi + 1) & 1] = *(const uint4*)(an + fa_off);                                                    \
+      if (FP8) fidx[(mi + 1) & 1] = *(const int*)(mn + fm_off);                                           \
+      else fidx[(mi + 1) & 1] = *(const uint16_t*)(mn + fm_off);                                          \
+      _Pragma("unroll") for (int pc = 0; pc < NPIECE; pc++)                                               \
+        if (spread(pc, NPIECE, MI_ - 1) == mi)                                                            \
+          BX[pc >> 1][pc & 1] = *(const uint4*)(pb1 + ((pc & 1) ? fb_off1 : fb_off0) + (pc >> 1) * 2048); \
+      _Pragma("unroll") for (int n = 0; n < NLOAD; n++) {                                                 \
+        if (mi == MI_ - 1 && spread(n, NLOAD, LG) == 0) PAIR_LOAD(n, step + 2, P, step + 3, 1 - (P));       \
+        if (mi < MI_ - 1 && spread(n, NLOAD, LG) == mi + 1) PAIR_LOAD(n, step + 1, 1 - (P), step + 2, P);   \
+      }                                                                                                   \
+      _Pragma("unroll") for (int ni = 0; ni < NI_; ni++) {                                                \
+        if (FP8) {                                                                                        \
+          i32x4 av;                                                                                       \
+          i32x8 bv;                                                                                       \
+          __builtin_memcpy(&av, &fa[mi & 1], 16);                                                         \
+          __builtin_memcpy(&bv, &BC[ni][0], 32);                                                          \
+          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_16x16x128_fp8_fp8(av, bv, acc[mi][ni], fidx[mi & 1], 0, 0); \
+        } else {                                                                                          \
+          bf16x8 av;                                                                                      \
+          bf16x16 bv;                                                                                     \
+          __builtin_memcpy(&av, &fa[mi & 1], 16);                                                         \
+          __builtin_memcpy(&bv, &BC[ni][0], 32);                                                          \
+          acc[mi][ni] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, bv, acc[mi][ni], fidx[mi & 1], 0, 0); \
+        }                                                                                                 \
+      }                                                                                                   \
+      __builtin_amdgcn_sched_barrier(0);                                                                  \
+    }                                                                                                     \
+  } while (0)
+
+  int step = 0;
+  for (; step + 1 < nsteps; step += 2) {
+    PAIR_STEP(fb0, fb1, 0);
+    step++;
+    PAIR_STEP(fb1, fb0, 1);
+    step--;
   }
+  if (step < nsteps) PAIR_STEP(fb0, fb1, 0);
+#undef PAIR_STEP
+#undef PAIR_LOAD
+  wait_vmcnt<0>();
+  __syncthreads();
+  fwd_pipe_store<WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
+}
+
+template <bool FP8, int WN, int MI_, int NI_, bool ZF8, bool AMAX>
+__global__ void __launch_bounds__(128 * WN, 2)
+k_linear_fwd_pair(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes,
+                  const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
+  __shared__ __align__(1024) uint8_t smem[fwd_pair_smem<FP8, WN, MI_, NI_>()];
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int tm = logical % m_tiles, tn = logical / m_tiles;
+  fwd_pair_tile<FP8, WN, MI_, NI_, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, (int64_t)tm * (32 * MI_),
+                                              (int64_t)tn * (16 * NI_ * WN));
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -836,51 +1024,49 @@ static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, 
 // Choice of the kernel.  Time model in microseconds: base + store * (output bytes at 5 TB/s) + rounds, a workgroup costing F + nk * step
 // with nk its k-steps (each k-group of a workgroup takes a KG-th of them) and step = max(lat, r * thr) for r workgroups sharing a CU;
 // R fit a CU (LDS) and what does not fit runs in further rounds.  The two-shape grid has a row of its own: whole rounds of 256 x 256 tiles
-// and one of 256 x 128 tiles, each with its F and step.  All 8-bit rows and the bf16 rows of the small tiles are fitted to event times of
-// 400 random problems (1 ... 32768 tokens, 64 ... 5120 channels and features).  The bf16 rows from 128 x 128 up are chosen for what the choice
-// costs on 640 random problems (1 ... 32768 tokens, 256 ... 5120 channels and features), timed both on one set of buffers and on sets
-// that rotate through 700 MB (geometric mean of the two): 0.4 % slower than the best tile on the geometric mean, 14 % at worst (20800 x 1136
-// x 384: 25.3 against 22.2 us), 2 % of the problems by more than 5 %; under 512 tokens 0.04 % and 3 %.  Before, with the two-shape grid's
-// time guessed from the 256 x 256 row: 0.7 %, 27 % and 4.8 %, and 8192 x 3072 x 768 ran 256 x 128 tiles (31.7 us inside a training step) instead
-// of the two-shape grid (29.2).  The 8-bit choice on such problems: 2.8 %, 48 % at worst (5696 x 512 x 512: 8.0 against 5.4 us); rows chosen
-// the same way bring 1.2 % there but lose 1 % on the layers of the GPT-2 workloads, which the fitted ones serve within 0.4 %.  The row of
-// the register-only kernel is fitted to 30 problems of 1 ... 512 tokens against the 32 x 32 tile at the same problems; its step falls with
-// the token rows a tile really has (one token: 0.44 of sixteen).
+// and one of 256 x 128 tiles, each with its F and step.  The rows are chosen for what the choice costs on 2400 random problems (1 ... 32768
+// tokens, 64 ... 5120 channels and features, a third of them layers of the GPT-2 workloads), timed in every shape, and for not losing
+// anywhere to the choice before (rows fitted without the 128 x 256 tiles): 0.9 % (bf16) / 0.75 % (8-bit) faster than that one on the
+// geometric mean, by more than 3 % on a tenth of the problems, slower by more than 3 % on 2 / 1 % (12 / 11 % at worst).  They say
+// less about a single shape's time.  128 x 256 tiles are there for what fills a round of them and little more than half a round of others:
+// 1021 x 5120 x 1280 e4m3 11.3 -> 9.1 us.
 struct FwdShape {
   int bm, bn, kg, r, threads;
   double f, lat, thr, base, store;
 };
-enum { FW_256, FW_256x128, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
+enum { FW_256, FW_256x128, FW_128x256, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
 static const FwdShape kFwd16[FW_SHAPES] = {
-  {256, 256, 1, 1, 512, 2.81, 0.636, 0.636, 1.81, 1.16},
-  {256, 128, 1, 2, 256, 3.07, 0.688, 0.406, 1.64, 0.76},
-  {128, 128, 1, 2, 256, 0.60, 0.327, 0.261, 3.04, 1.01},
-  {128, 128, 1, 3, 256, 1.82, 0.472, 0.293, 1.27, 0.88},
-  {128, 64, 1, 2, 256, 0.52, 0.203, 0.187, 3.35, 1.01},
-  {64, 64, 1, 3, 256, 0.70, 0.150, 0.128, 3.19, 1.08},
-  {64, 64, 2, 1, 512, 1.34, 0.256, 0.256, 2.63, 2.13},
-  {64, 32, 4, 1, 512, 1.56, 0.313, 0.313, 2.53, 3.63},
-  {32, 32, 4, 1, 256, 1.55, 0.186, 0.186, 2.55, 3.70},
-  {16, 16, 8, 4, 512, 0.00, 0.525, 0.525, 2.45, 0.02},
+  {256, 256, 1, 1, 512, 7.033, 0.572, 0.590, 0.014, 0.681},
+  {256, 128, 1, 2, 256, 0.159, 1.290, 0.015, 3.052, 0.002},
+  {128, 256, 1, 1, 512, 2.981, 0.384, 0.000, 0.170, 1.968},
+  {128, 128, 1, 2, 256, 2.580, 0.171, 0.319, 0.803, 0.665},
+  {128, 128, 1, 3, 256, 2.798, 0.008, 0.478, 0.500, 0.000},
+  {128, 64, 1, 2, 256, 0.000, 0.201, 0.320, 3.367, 0.092},
+  {64, 64, 1, 3, 256, 0.025, 0.299, 0.315, 2.976, 0.847},
+  {64, 64, 2, 1, 512, 5.159, 0.006, 0.234, 1.318, 0.001},
+  {64, 32, 4, 1, 512, 2.681, 0.355, 0.219, 2.263, 0.000},
+  {32, 32, 4, 1, 256, 2.446, 0.090, 0.379, 1.671, 1.127},
+  {16, 16, 8, 4, 512, 0.028, 0.001, 1.049, 0.113, 0.000},
 };
 static const FwdShape kFwd8[FW_SHAPES] = {
-  {256, 256, 1, 1, 512, 1.86, 0.679, 0.679, 2.96, 0.90},
-  {256, 128, 1, 2, 256, 1.49, 0.591, 0.454, 3.06, 0.77},
-  {128, 128, 1, 2, 256, 0.88, 0.264, 0.279, 3.16, 0.76},
-  {128, 128, 1, 3, 256, 1.11, 0.337, 0.279, 2.69, 0.80},
-  {128, 64, 1, 2, 256, 1.01, 0.133, 0.196, 2.96, 0.77},
-  {64, 64, 1, 3, 256, 1.09, 0.133, 0.128, 2.92, 0.70},
-  {64, 64, 2, 1, 512, 1.89, 0.238, 0.238, 2.17, 0.44},
-  {64, 32, 4, 1, 512, 2.95, 0.305, 0.305, 1.26, 1.71},
-  {32, 32, 4, 1, 256, 1.74, 0.151, 0.151, 2.49, 3.42},
-  {16, 16, 8, 4, 512, 0.00, 0.580, 0.480, 2.40, 0.56},
+  {256, 256, 1, 1, 512, 0.089, 0.930, 0.024, 4.711, 1.093},
+  {256, 128, 1, 2, 256, 2.306, 0.155, 1.014, 2.827, 0.000},
+  {128, 256, 1, 1, 512, 4.175, 0.000, 0.657, 0.513, 0.289},
+  {128, 128, 1, 2, 256, 0.248, 0.001, 0.602, 4.652, 0.239},
+  {128, 128, 1, 3, 256, 0.913, 0.868, 0.435, 2.847, 0.450},
+  {128, 64, 1, 2, 256, 2.360, 0.003, 0.509, 1.932, 0.023},
+  {64, 64, 1, 3, 256, 1.157, 0.001, 0.310, 2.953, 0.185},
+  {64, 64, 2, 1, 512, 0.420, 0.457, 0.010, 3.196, 5.917},
+  {64, 32, 4, 1, 512, 3.849, 0.001, 0.287, 0.013, 17.472},
+  {32, 32, 4, 1, 256, 0.001, 0.273, 0.000, 3.727, 18.888},
+  {16, 16, 8, 4, 512, 0.002, 0.380, 1.162, 0.000, 0.003},
 };
 
 // the two-shape grid: F and step of a round of 256 x 256 tiles, of the last one of 256 x 128 tiles, base, store
 struct FwdDual {
   double f, step, f_half, step_half, base, store;
 };
-static const FwdDual kFwdDual16 = {2.36, 0.709, 2.57, 0.439, 2.32, 1.11}, kFwdDual8 = {1.86, 0.679, 1.86, 0.475, 2.96, 0.90};
+static const FwdDual kFwdDual16 = {3.521, 0.000, 1.893, 0.458, 21.918, 0.003}, kFwdDual8 = {3.736, 0.003, 0.604, 1.146, 5.867, 0.830};
 
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
   const FwdShape* tab = fp8 ? kFwd8 : kFwd16;
@@ -938,7 +1124,14 @@ static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx,
       break;
     }
     case FW_256: launch_fwd_pipe<FP8, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
-    case FW_256x128: FT(2, 2, 4, 2, 1, 2); break;
+    case FW_128x256: launch_fwd_pipe<FP8, 4, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
+    case FW_256x128: {
+      const int m_tiles = (int)((O + 255) / 256), n_tiles = (int)((T + 127) / 128);
+      const int64_t eb = FP8 ? 1 : 2;
+      SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_pair<FP8, 2, 8, 4, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(256), s, (const uint8_t*)X, T,
+                  I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
+      break;
+    }
     case FW_128_R2: FT(2, 2, 2, 2, 1, 3); break;
     case FW_128_R3: FT(2, 2, 2, 2, 1, 2); break;
     case FW_128x64: FT(2, 2, 2, 1, 1, 4); break;

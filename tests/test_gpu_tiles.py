@@ -176,6 +176,14 @@ def test_linear_fwd_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
         assert bool(((dec - want).abs() <= want.abs() * (2.0 ** -4 + 1e-5) + zs * 2.0 ** -9).all())
 
 
+@pytest.mark.parametrize("dtype,T,O,I,tile", [
+    ("bf16", 11639, 280, 896, "128x256 kg 1 r 1"), ("e4m3", 18542, 144, 640, "128x256 kg 1 r 1"),      # 14 and 5 k-steps, ragged both ways
+    ("bf16", 22391, 280, 192, "256x128 kg 1 r 2"), ("e4m3", 14318, 784, 384, "256x128 kg 1 r 2"),      # an odd number of k-steps
+])
+def test_linear_fwd_tiles_of_four_waves_and_of_256_tokens(sste, dtype, T, O, I, tile):  # noqa: F811
+    test_linear_fwd_tiles(sste, dtype, T, O, I, tile)
+
+
 # the shapes of the weight gradient, one split and several: (8-bit?, T, O, I, shape of sste_describe_plan, splits)
 WGRAD_TILES = [
     (False, 64, 8, 16, "fused", 1), (False, 704, 40, 80, "fused", 1), (False, 1152, 296, 136, "fused", 1),        # fewer k-steps than waves; incomplete rounds
