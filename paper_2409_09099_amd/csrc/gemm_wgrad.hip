@@ -86,17 +86,18 @@ k_mvue_pack(const uint8_t* __restrict__ dY, int64_t T, int64_t O, int64_t lddy_b
     }
   }
   // Group ids of this lane: gid_a + e and gid_b + e.  O and och are multiples of CH, so both are too and the
-  // CH consecutive ids share their high word (no carry out of the low word inside the piece).
+  // CH consecutive ids share their high word (no carry out of the low word inside the piece) and adding e is an exclusive or, which the
+  // draw begins with.
   const uint64_t gid_a = (key.first_group + (uint64_t)(s * (KS / 4) + 2 * kp)) * (uint64_t)O + (uint64_t)och, gid_b = gid_a + (uint64_t)O;
   const uint32_t hi_a = (uint32_t)(gid_a >> 32) * 0x9E3779B9u, hi_b = (uint32_t)(gid_b >> 32) * 0x9E3779B9u;
+  const uint32_t lo_a = (uint32_t)gid_a ^ key.k0, lo_b = (uint32_t)gid_b ^ key.k0;
   const int q = kp / PPQ, gp = kp % PPQ;
   // 8-bit: the four token rows' dwords of four channels, transposed 4 x 4 bytes at a time (eight byte permutes
   // for four groups): grp[h][k] holds channel 4 (e / 4) + k with the group's first token in byte 0
   uint32_t grp[2][4] = {};
 #pragma unroll
   for (int e = 0; e < CH; e++) {
-    const uint32_t xa = draw_u32_pre(key.k0, key.k1, (uint32_t)gid_a + (uint32_t)e, hi_a);
-    const uint32_t xb = draw_u32_pre(key.k0, key.k1, (uint32_t)gid_b + (uint32_t)e, hi_b);
+    const uint32_t xa = draw_u32_mixed((lo_a ^ (uint32_t)e) + hi_a, key.k1), xb = draw_u32_mixed((lo_b ^ (uint32_t)e) + hi_b, key.k1);
     const int c = oc * CH + e, row = 16 * q + (c & 15);                // channel inside the tile; row of its block
     uint8_t* const slot = sV + (c >> 4) * VPITCH + row * 16;
     uint32_t m;

@@ -7,12 +7,9 @@
 
 namespace sste {
 
-// 32-bit draw for a group id: three-round multiply-xorshift hash keyed by (k0, k1).  hi_term is the
-// high word of the group id times 0x9E3779B9, which callers that walk consecutive ids hoist out of
-// their loops.
-__device__ __forceinline__ uint32_t draw_u32_pre(uint32_t k0, uint32_t k1, uint32_t gid_lo, uint32_t hi_term) {
-  uint32_t x = gid_lo ^ k0;
-  x += hi_term;
+// 32-bit draw for a group id: three-round multiply-xorshift hash keyed by (k0, k1).  draw_u32_mixed takes it from
+// x = (low word ^ k0) + high word * 0x9E3779B9, which callers that walk consecutive ids form themselves.
+__device__ __forceinline__ uint32_t draw_u32_mixed(uint32_t x, uint32_t k1) {
   x ^= x >> 17;
   x *= 0xED5AD4BBu;
   x += k1;
@@ -24,7 +21,7 @@ __device__ __forceinline__ uint32_t draw_u32_pre(uint32_t k0, uint32_t k1, uint3
   return x;
 }
 __device__ __forceinline__ uint32_t draw_u32(uint32_t k0, uint32_t k1, uint32_t gid_lo, uint32_t gid_hi) {
-  return draw_u32_pre(k0, k1, gid_lo, gid_hi * 0x9E3779B9u);
+  return draw_u32_mixed((gid_lo ^ k0) + gid_hi * 0x9E3779B9u, k1);
 }
 
 // What the rule below costs decides how fast the estimator's kernels run, so the forms are chosen by the measured issue time of the
@@ -45,9 +42,10 @@ __device__ __forceinline__ Sel mvue_select(float m0f, float m1f, float m2f, floa
   uint32_t m0 = f2u(m0f), m1 = f2u(m1f), m2 = f2u(m2f), m3 = f2u(m3f);
   uint32_t a = max(m0, m1), b = min(m0, m1);
   uint32_t cc = max(m2, m3), d = min(m2, m3);
-  uint32_t mx = max(a, cc), mid = min(a, cc);
+  uint32_t mid = min(a, cc);
   float Lo = (u2f(b) + u2f(d)) + u2f(mid);
-  uint32_t clampv = (f2u(Lo) == 0u) ? mx : f2u(Lo);      // Lo is a sum of non-negative terms: +0 or positive
+  // Lo is a sum of non-negative terms: +0 or positive.  Where it is 0 the rule clamps to the largest magnitude, which clamps nothing.
+  uint32_t clampv = (f2u(Lo) == 0u) ? 0xFFFFFFFFu : f2u(Lo);
   float l0 = u2f(min(m0, clampv)), l1 = u2f(min(m1, clampv)), l2 = u2f(min(m2, clampv)), l3 = u2f(min(m3, clampv));
   float P0 = l0;
   float P1 = P0 + l1;
