@@ -386,8 +386,8 @@ int sste_linear_wgrad_noalloc(const void* dY, int64_t T, int64_t O, int64_t lddy
  * written besides dX.
  * Inputs must be finite.  What the kernels do otherwise, and may do differently in another version: an infinite or NaN
  * gradient reaches the results of its own token alone (zero weights make NaN of an infinity); an infinite or NaN
- * PACKED VALUE makes NaN of the 32 features around its own, in every token, because most tiles expand the weight by a
- * matrix product with the identity.
+ * PACKED VALUE makes NaN of the 32 features around its own, in every token, because the weight is expanded by a matrix
+ * product with the identity.
  * Errors: as sste_linear_fwd, with the roles of X / Z taken by dY / dX.
  */
 int sste_linear_dgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, float dy_scale,
