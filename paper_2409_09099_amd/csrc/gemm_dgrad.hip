@@ -91,8 +91,8 @@ __device__ __forceinline__ uint32_t dy_offset(uint32_t off, int piece, int live)
 __device__ __forceinline__ int dy_piece(int lane, int wl) { return 16 * ((lane & 7) ^ ((4 * (wl & 1) + (lane >> 4)) & 7)); }
 
 // Two of the sixteen accumulator registers of an expansion set to zero (the compiler otherwise builds a zero vector and copies it).  Only
-// where no matrix instruction that writes them is in flight, and two wait states ahead of one that reads them: the compiler does not
-// order what it cannot see inside the assembly.
+// where no matrix instruction that writes them is in flight, and two wait states ahead of one that reads them, which settle() holds: the
+// compiler does not know the assembly for a vector instruction and counts none itself.
 __device__ __forceinline__ void zero_pair(f32x16& v, int r) {
   typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
   f32x2 z;
@@ -100,6 +100,9 @@ __device__ __forceinline__ void zero_pair(f32x16& v, int r) {
   v[2 * r] = z[0];
   v[2 * r + 1] = z[1];
 }
+// The wait states between the zeroing of v and the matrix instruction that adds to it.  v is an operand: without one the compiler may
+// issue the matrix instruction ahead of the wait.
+__device__ __forceinline__ void settle(f32x16& v) { asm volatile("s_nop 1" : "+v"(v)); }
 
 // Stores a wave's tile with the backward of the activation that produced this layer's input: grad_H = grad_A * GELU'(H), on the bf16
 // gradient just formed (`piece(row, chunk)`: 16 bytes of it) and the stored pre-activation.  The tile's corner is (t0, i0), `rows` tokens
@@ -322,7 +325,7 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
     else pm = *(const uint16_t*)(slot + P_BYTES + (sl + half * HSL) * SM);
   };
   auto unit_mma = [&](int u) {
-    asm volatile("s_nop 1");                        // behind the zeroing, which the compiler does not know for a vector instruction
+    settle(ex);
     if (FP8) {
       ex = __builtin_amdgcn_smfmac_f32_32x32x64_fp8_fp8(pk, u ? id1 : id0, ex, pm, 0, 0);
     } else {
