@@ -239,6 +239,7 @@ int sste_linear_fwd(const void* X, int64_t T, int64_t I, int64_t ldx, int dtype,
  *                        magnitude of the unrounded output in real units (0 for an empty output), from
  *                        which the caller derives z_scale of a later iteration (delayed scaling: the
  *                        scale used now comes from earlier iterations, see sste_amax_history_push).
+ *                        An infinite acc counts, a NaN does not.
  * acc is the float32 accumulator of the product.  Everything else as sste_linear_fwd.
  */
 int sste_linear_fwd_ex(const void* X, int64_t T, int64_t I, int64_t ldx, int dtype, float x_scale,
@@ -256,7 +257,8 @@ int sste_linear_fwd_ex(const void* X, int64_t T, int64_t I, int64_t ldx, int dty
  *                         A = act(H)                                 evaluated in float32 on the bf16 H,
  *                         stored as RNE_bf16(A) (a_dtype SSTE_BF16, a_scale 1, amax_out NULL) or as
  *                         RNE_e4m3(clamp(A * (1 / a_scale), +-448)) with 1 / a_scale one float32 division
- *                         on the host (a_dtype SSTE_F8E4M3; amax_out required, receives max |A|).
+ *                         on the host (a_dtype SSTE_F8E4M3; amax_out required, receives max |A|, or NaN
+ *                         where an A is NaN, as that of an H of minus infinity is).
  *   sste_linear_dgrad_act dX = RNE_bf16(g * act'(H)),  g = RNE_bf16((dy_scale * w_scale) * acc): the input
  *                         gradient of the layer AFTER the activation, multiplied by the activation's
  *                         derivative at the stored pre-activation H (T x I, bf16, leading dimension ldh).

@@ -73,7 +73,7 @@ struct FwdOut {
 };
 
 // Activation stage of the epilogue on one 16-byte piece (8 consecutive channels of one token): stores A in
-// the requested format and returns max |A| of the piece (float32 bits).
+// the requested format and returns max |A| of the piece (float32 bits; NaN where a value is NaN, whose bits lie above every number's).
 __device__ __forceinline__ uint32_t fwd_act_piece(const uint4& h, const FwdOut& out, int64_t t, int64_t o) {
   const uint32_t w[4] = {h.x, h.y, h.z, h.w};
   float a[8], m = 0.0f;
@@ -83,9 +83,10 @@ __device__ __forceinline__ uint32_t fwd_act_piece(const uint4& h, const FwdOut& 
     a[2 * e + 1] = gelu_tanh(bf16hi_f32(w[e]));
   }
   if (out.a8) {
-    // two values per three-operand maximum, their absolute values as source modifiers
+    // two values per three-operand maximum, their absolute values as source modifiers; of the two float maxima the one that keeps NaN
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(a[e])), __builtin_fabsf(a[e + 1]));
+    for (int e = 0; e < 8; e += 2)
+      m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, __builtin_fabsf(a[e])), __builtin_fabsf(a[e + 1]));
     const float r = out.a_inv_scale;
     int lo = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[0] * r), clamp448(a[1] * r), 0, false);
     lo = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[2] * r), clamp448(a[3] * r), lo, true);

@@ -184,6 +184,22 @@ def test_linear_fwd_tiles_of_four_waves_and_of_256_tokens(sste, dtype, T, O, I, 
     test_linear_fwd_tiles(sste, dtype, T, O, I, tile)
 
 
+@pytest.mark.parametrize("dtype,T,O,I,tile", [c for c in FWD_TILES if c[0] == "e4m3"] + [("e4m3", 18542, 144, 640, "128x256 kg 1 r 1"), ("e4m3", 14318, 784, 384, "256x128 kg 1 r 2")])
+def test_largest_activation_keeps_nan(sste, dtype, T, O, I, tile):  # noqa: F811
+    """A pre-activation of minus infinity makes NaN of its activation, and of the largest magnitude in every tile: a window of
+    magnitudes passes such an iteration over."""
+    assert sste.describe_plan("fwd", T, O, I, dt(sste, dtype)).startswith(tile + " ")
+    vals, meta = gaussian_operands(sste, "e4m3", 64, O, I)[2]
+    X = torch.zeros((T, I), dtype=torch.uint8, device="cuda")
+    X[T - 1] = 0x7E                                        # 448 in e4m3: with the scale below this token's sums leave the range of bf16
+    H, _, amax = sste.linear_fwd_act(X, vals, meta, O, sste.F8E4M3, 1e38, 1.0, a_dtype=sste.F8E4M3, a_scale=1.0)
+    assert bool(H[T - 1].isneginf().any()) and not bool(H.isnan().any()) and bool(H[:T - 1].eq(0).all())
+    assert bool(amax.isnan())
+    H, _, amax = sste.linear_fwd_act(X, vals, meta, O, sste.F8E4M3, 1.0, 3e-4, a_dtype=sste.F8E4M3, a_scale=1.0)
+    want = torch.nn.functional.gelu(H.float(), approximate="tanh").abs().max()
+    assert abs(float(amax) - float(want)) <= 1e-5 * float(want)
+
+
 # the shapes of the weight gradient, one split and several: (8-bit?, T, O, I, shape of sste_describe_plan, splits)
 WGRAD_TILES = [
     (False, 64, 8, 16, "fused", 1), (False, 704, 40, 80, "fused", 1), (False, 1152, 296, 136, "fused", 1),        # fewer k-steps than waves; incomplete rounds
