@@ -137,24 +137,29 @@ __global__ void k_fill_u32_fwd(uint32_t* p, uint32_t v) { *p = v; }
 // constants); where the tile has fewer 1 KiB blocks than 8 waves x loads, the surplus loads address
 // blocks past the end of the tile's buffer descriptor and fetch nothing.
 
+// LDS bytes of the output stage of NW waves: 16 NI_ token rows of the wave's 16 MI_ channels each.  The padded row, that of the e4m3 output
+// and of the narrow tiles, is the longest.
+constexpr int fwd_store_smem(int NW, int MI_, int NI_) { return NW * 16 * NI_ * (32 * MI_ + 16); }
+
 // LDS bytes one tile of the pipelined kernel needs (rings, reused by the epilogue)
 template <bool FP8, int MI_, int NI_>
 constexpr int fwd_pipe_smem() {
   constexpr int NW = 8, NR = 3, MB = FP8 ? 16 : 8;
   constexpr int LA = (32 * MI_ / 16 + NW - 1) / NW, LM = (32 * MI_ * MB / 256 + NW - 1) / NW;
   constexpr int RING = NR * (NW * LA * 1024 + NW * LM * 256 + 64 * NI_ * 128);
-  constexpr int EPI = NW * 16 * NI_ * (32 * MI_ + 16);
+  constexpr int EPI = fwd_store_smem(NW, MI_, NI_);
   return RING > EPI ? RING : EPI;
 }
 
 // Output stage of the pipelined tiles: accumulators -> LDS (row = token, the wave's 16 MI_ channels contiguous) -> 16-byte stores.  Waves
-// 2 x WN; called behind a barrier, with all of the workgroup's LDS free.
-template <int WN, int MI_, int NI_, bool ZF8, bool AMAX>
+// 2 x WN; called behind a barrier, with all LDS bytes of the workgroup free.
+template <int LDS, int WN, int MI_, int NI_, bool ZF8, bool AMAX>
 __device__ __forceinline__ void fwd_pipe_store(uint8_t* smem, const f32x4 (&acc)[MI_][NI_], int64_t T, int64_t O, const FwdOut& out, int64_t o0,
                                                int64_t t0) {
   constexpr int NW = 2 * WN;
   // row of a token: the wave's channels + pad; bf16 rows of the 256-channel tile are XOR-swizzled instead of padded
   constexpr int EROW = (MI_ == 8 && !ZF8) ? 256 : 32 * MI_ + 16;
+  static_assert(NW * 16 * NI_ * EROW <= LDS, "the output stage's rows fit the workgroup's LDS");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int j = lane & 15, q = lane >> 4;
@@ -392,7 +397,7 @@ __device__ __forceinline__ void fwd_pipe_tile(uint8_t* smem, const uint8_t* __re
 
   wait_vmcnt<0>();
   __syncthreads();
-  fwd_pipe_store<WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
+  fwd_pipe_store<fwd_pipe_smem<FP8, MI_, NI_>(), WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -408,7 +413,7 @@ template <bool FP8, int WN, int MI_, int NI_>
 constexpr int fwd_pair_smem() {
   constexpr int NW = 2 * WN, MB = FP8 ? 16 : 8;
   constexpr int RING = 2 * (32 * MI_ * (64 + MB) + 16 * NI_ * WN * 128);
-  constexpr int EPI = NW * 16 * NI_ * (MI_ == 8 ? 256 : 32 * MI_ + 16);
+  constexpr int EPI = fwd_store_smem(NW, MI_, NI_);
   return RING > EPI ? RING : EPI;
 }
 
@@ -423,6 +428,7 @@ __device__ __forceinline__ void fwd_pair_tile(uint8_t* smem, const uint8_t* __re
   constexpr int NLOAD = LA + LM + LB, NPIECE = 2 * NI_;
   static_assert(LA * NW * 16 == BM && LM * NW * 256 == BM * MB && LB * NW * 8 == BN, "loads per wave");
   constexpr int LG = 4;                             // groups behind the barrier that the loads are spread over
+  static_assert(2 * (ASTAGE + BSTAGE) <= fwd_pair_smem<FP8, WN, MI_, NI_>(), "LDS size helper out of step with the tile layout");
   uint8_t* const smemA = smem;
   uint8_t* const smemB = smem + 2 * ASTAGE;
 
@@ -558,7 +564,7 @@ __device__ __forceinline__ void fwd_pair_tile(uint8_t* smem, const uint8_t* __re
 #undef PAIR_LOAD
   wait_vmcnt<0>();
   __syncthreads();
-  fwd_pipe_store<WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
+  fwd_pipe_store<fwd_pair_smem<FP8, WN, MI_, NI_>(), WN, MI_, NI_, ZF8, AMAX>(smem, acc, T, O, out, o0, t0);
 }
 
 template <bool FP8, int WN, int MI_, int NI_, bool ZF8, bool AMAX>
