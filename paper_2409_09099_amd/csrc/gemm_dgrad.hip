@@ -16,7 +16,8 @@
 // consecutive: converted back they ARE the operand fragments of the product (of 32 x 32 instructions; for 16 x 16 ones after a swap of
 // 16-lane rows), and S(W) never passes through the LDS in dense form.  Each wave owns 32 features and ALL tokens of its workgroup's tile,
 // so no block is decoded twice in a workgroup: one expansion per 16 (bf16) or 8 (8-bit) equal shares of matrix time in the 256-token
-// tiles.  The price is that every wave reads the whole grad_Z tile from LDS (256 KiB per k-step of 256 x 256, 35 % of the LDS cycles).
+// tiles.  The price is that every wave reads the whole grad_Z tile from LDS (256 KiB per k-step of 256 x 256, 43 % of
+// its clocks at the measured 128 KiB in 567).
 //
 // What bounds it.  The large tiles are bound by the power the chip allows: a k-step of 256 x 256 takes 2650 (bf16) / 2670 (8-bit) clocks, of
 // which the matrix pipe needs 2176 / 2304, at a clock held down to 1.6 ... 1.8 GHz.  Before (decode by two waves each, or by byte
@@ -36,9 +37,6 @@
 // features it is expanded with.  Asking every packed slot for one, with a second look in a branch, was measured: 2.1 % of a four-layer
 // training step in bf16 (1668 -> 1704 us), 1.8 % of an 8-bit layer of small tiles, so it is not asked.
 // Which tile runs is decided by a time model fitted to a sweep (dgrad_choice).
-// Measured (us before -> after; start: 256-token tiles or their halves only): bf16 512 x 256 x 1024 (T, O, I)
-// 8.2 -> 4.1, 1024^3 20.9 -> 7.8, 2048 x 4096 x 1024 72 -> 33, 4096 x 3072 x 768 54 -> 32, 8192 x 3072 x 768 57 -> 49,
-// 16384 x 1280 x 5120 206 -> 195; e4m3 2048 x 4096 x 1024 36 -> 21.
 // Epilogue as in the forward GEMM: transposed through LDS, 16-byte streaming stores of bf16 rows.
 #include "common.h"
 
@@ -73,13 +71,6 @@ struct DgradArgs {
   const uint16_t* H;       // stored pre-activation, or null
   int64_t ldh;
 };
-
-// One group of a packed e4m3 operand -> its four dense bytes: w holds value0 at byte b0 and value1 at byte b0 + 1, nib =
-// pos0 | pos1 << 2.  A byte permute with a computed selector: selector bytes 0..3 pick from the zero operand, 4..7 from w.
-__device__ __forceinline__ uint32_t expand_group8(uint32_t w, uint32_t b0, uint32_t nib) {
-  const uint32_t sel = ((4u + b0) << (((nib & 3u) << 3) & 31u)) | ((5u + b0) << (((nib & 12u) << 1) & 31u));
-  return __builtin_amdgcn_perm(w, 0u, sel);
-}
 }  // namespace
 
 // grad_Z loads.  A row's bytes past its last channel belong to somebody else (the next token's row, padding of any content): S(W) has
