@@ -64,6 +64,7 @@ DGRAD_PARTIAL_STEPS = [
     (False, 325, 136, 2816, "64x64 kg 1"), (False, 65, 136, 64, "64x64 kg 2"), (False, 65, 416, 64, "64x64 kg 4"),
     (False, 16509, 136, 320, "128x128 kg 1"), (False, 771, 200, 2560, "128x128 kg 2"), (False, 16738, 136, 192, "256x128 kg 1"),
     (False, 11074, 136, 704, "256x256 kg 1"), (False, 10098, 136, 1600, "256x256+256x128 kg 1"),
+    (False, 198, 208, 4160, "128x64 kg 2"), (True, 277, 144, 3840, "128x64 kg 2"), (True, 301, 272, 3456, "128x64 kg 2"),
     (True, 403, 192, 2432, "64x64 kg 1"), (True, 65, 192, 128, "64x64 kg 2"), (True, 65, 272, 128, "64x64 kg 4"),
     (True, 17018, 192, 384, "128x128 kg 1"), (True, 3487, 192, 896, "128x128 kg 2"), (True, 16391, 192, 256, "256x128 kg 1"),
     (True, 4997, 192, 1664, "256x256 kg 1"), (True, 5940, 192, 2816, "256x256+256x128 kg 1"),
@@ -294,6 +295,7 @@ def test_linear_wgrad_without_its_workspace(sste, dtype, T, O, I):  # noqa: F811
 @pytest.mark.parametrize("dtype,T,O,I,tile", [
     ("bf16", 65, 136, 64, "64x64 kg 2"), ("bf16", 65, 416, 64, "64x64 kg 4"), ("bf16", 2340, 144, 1344, "128x128 kg 2"),
     ("e5m2", 65, 272, 128, "64x64 kg 4"), ("e5m2", 18, 560, 128, "64x64 kg 2"), ("e5m2", 834, 272, 3584, "128x128 kg 2"),
+    ("bf16", 333, 304, 3968, "128x64 kg 2"), ("e5m2", 301, 272, 3456, "128x64 kg 2"),       # 5 and 3 k-steps for two groups
 ])
 def test_linear_dgrad_infinity_stays_with_its_weights(sste, dtype, T, O, I, tile):  # noqa: F811
     """The k-groups of a tile end on different k-steps; what an idle group multiplies must not turn an infinite gradient into NaN where
