@@ -530,57 +530,100 @@ bool linear_dgrad_supported(int64_t T, int64_t O, int64_t lddy, int64_t I, int d
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Choice of the tile.  Time model in microseconds: a workgroup costs F + nk * step, nk = its k-steps (each k-group of a workgroup takes
+// Choice of the tile.  Form of a time model in microseconds: a workgroup costs F + nk * step, nk = its k-steps (each k-group of a workgroup takes
 // a KG-th of them) and step = max(lat, r * thr) with r workgroups sharing a CU: lat is the time one k-step's loads, barrier and
 // MFMAs take end to end, thr what a CU needs per workgroup and k-step when its pipes are shared; R workgroups fit a CU (LDS), and what
-// does not fit runs in further rounds; base + store * (output bytes at 5 TB/s) on top.  The two-shape grid has a row of its own.  The rows
-// are chosen for what the choice costs on 1220 random problems (64 ... 32768 tokens, 64 ... 5120 channels and features, a third of them
-// layers of the GPT-2 workloads), timed in every shape: 1.4 % (bf16) / 1.3 % (8-bit) slower than the best shape on the geometric mean, 0.8 /
-// 0.6 % on the GPT-2 layers, 12 / 11 % of the problems by more than 5 %, 28 / 24 % at worst.  They say less about a single shape's time.
+// does not fit runs in further rounds; base + store * (output bytes at 5 TB/s) on top.  The two-shape grid has a row of its own.  Two sets
+// of rows:
+// Weights up to 5120 wide and up to 32768 tokens: the rows rank the tiles and are no times (the two-shape grid's step is 0.05 us in bf16,
+// where a k-step takes 1.6); what they say ends with that range.  They are chosen for what the choice costs on 1220 random problems (64 ...
+// 32768 tokens, 64 ... 5120 channels and features, a third of them layers of the GPT-2 workloads), timed in every shape: 1.4 % (bf16) / 1.3 %
+// (8-bit) slower than the best shape on the geometric mean, 0.8 / 0.6 % on the GPT-2 layers, 12 / 11 % of the problems by more than 5 %,
+// 28 / 24 % at worst.
+// Wider weights or more tokens: rows fitted to the times themselves, no step below the matrix pipe's, so that they hold beyond what was
+// timed.  2600 random problems up to 65536 wide (1 ... 262144 tokens), on one set of buffers and on sets that rotate through 600 MB: 0.2 /
+// 0.1 % slower than the best shape on the geometric mean, 12 % at worst; on 1500 others 0.3 / 0.1 %, 20 / 8 %.  The first set of rows loses
+// 3.6 / 3.4 % there, up to 72 % (70 x 26616 x 23872 bf16: 331 against 193 us).
 struct DgradShape {
   int bm, bn, kg, r, threads;
+};
+struct DgradCost {
   double f, lat, thr, base, store;
 };
 enum { DG_256, DG_256x128, DG_128_KG1, DG_128_KG2, DG_128x64_KG2, DG_64_KG1, DG_64_KG2, DG_64_KG4, DG_SHAPES, DG_DUAL = DG_SHAPES };
-static const DgradShape kDgrad16[DG_SHAPES] = {
-  {256, 256, 1, 1, 512, 7.215, 0.006, 0.570, 0.289, 0.007},
-  {256, 128, 1, 1, 512, 3.800, 0.533, 0.205, 0.856, 0.374},
-  {128, 128, 1, 2, 256, 1.419, 0.409, 0.267, 3.920, 0.006},
-  {128, 128, 2, 1, 512, 4.335, 0.000, 0.741, 0.013, 0.537},
-  {128, 64, 2, 1, 512, 3.600, 0.004, 0.465, 0.428, 0.064},
-  {64, 64, 1, 4, 128, 0.004, 0.823, 0.380, 1.571, 0.684},
-  {64, 64, 2, 2, 256, 1.091, 0.002, 0.287, 2.359, 2.681},
-  {64, 64, 4, 1, 512, 1.829, 0.000, 0.420, 1.904, 3.960},
+static const DgradShape kDgrad[DG_SHAPES] = {
+  {256, 256, 1, 1, 512},
+  {256, 128, 1, 1, 512},
+  {128, 128, 1, 2, 256},
+  {128, 128, 2, 1, 512},
+  {128, 64, 2, 1, 512},
+  {64, 64, 1, 4, 128},
+  {64, 64, 2, 2, 256},
+  {64, 64, 4, 1, 512},
 };
-static const DgradShape kDgrad8[DG_SHAPES] = {
-  {256, 256, 1, 1, 512, 1.805, 0.489, 1.112, 2.327, 0.910},
-  {256, 128, 1, 1, 512, 2.388, 0.008, 0.734, 0.929, 1.177},
-  {128, 128, 1, 2, 256, 1.731, 0.084, 0.391, 3.411, 0.270},
-  {128, 128, 2, 1, 512, 2.832, 0.009, 0.805, 0.758, 1.178},
-  {128, 64, 2, 1, 512, 1.530, 0.631, 0.007, 2.535, 0.015},
-  {64, 64, 1, 4, 128, 0.002, 0.893, 0.319, 2.579, 0.799},
-  {64, 64, 2, 2, 256, 0.948, 0.146, 0.521, 2.326, 1.694},
-  {64, 64, 4, 1, 512, 2.415, 0.010, 0.829, 1.028, 8.210},
+static const DgradCost kDgradCost16[DG_SHAPES] = {
+  {7.215, 0.006, 0.570, 0.289, 0.007},
+  {3.800, 0.533, 0.205, 0.856, 0.374},
+  {1.419, 0.409, 0.267, 3.920, 0.006},
+  {4.335, 0.000, 0.741, 0.013, 0.537},
+  {3.600, 0.004, 0.465, 0.428, 0.064},
+  {0.004, 0.823, 0.380, 1.571, 0.684},
+  {1.091, 0.002, 0.287, 2.359, 2.681},
+  {1.829, 0.000, 0.420, 1.904, 3.960},
+};
+static const DgradCost kDgradCost8[DG_SHAPES] = {
+  {1.805, 0.489, 1.112, 2.327, 0.910},
+  {2.388, 0.008, 0.734, 0.929, 1.177},
+  {1.731, 0.084, 0.391, 3.411, 0.270},
+  {2.832, 0.009, 0.805, 0.758, 1.178},
+  {1.530, 0.631, 0.007, 2.535, 0.015},
+  {0.002, 0.893, 0.319, 2.579, 0.799},
+  {0.948, 0.146, 0.521, 2.326, 1.694},
+  {2.415, 0.010, 0.829, 1.028, 8.210},
+};
+static const DgradCost kDgradWide16[DG_SHAPES] = {
+  {9.678, 0.954, 0.954, 0.179, 0.206},
+  {7.414, 0.571, 0.476, 0.115, 0.219},
+  {2.873, 0.488, 0.399, 2.017, 0.220},
+  {4.000, 0.804, 0.311, 0.109, 0.313},
+  {3.656, 0.592, 0.161, 0.122, 0.201},
+  {0.330, 0.608, 0.131, 0.154, 2.239},
+  {1.614, 0.602, 0.131, 0.125, 5.994},
+  {3.363, 0.701, 0.105, 0.114, 5.935},
+};
+static const DgradCost kDgradWide8[DG_SHAPES] = {
+  {7.059, 1.139, 1.139, 0.167, 0.206},
+  {4.915, 0.761, 0.585, 0.102, 0.733},
+  {1.322, 0.542, 0.447, 2.774, 0.586},
+  {5.048, 0.874, 0.311, 0.147, 0.720},
+  {2.456, 0.893, 0.161, 1.806, 1.666},
+  {0.364, 0.792, 0.173, 1.047, 3.150},
+  {1.625, 0.775, 0.131, 0.126, 3.269},
+  {4.510, 0.864, 0.105, 0.141, 5.854},
 };
 // the two-shape grid: F and step of a round of 256 x 256 tiles, of the last one of 256 x 128 tiles, base, store
 struct DgradDual {
   double f, step, f_half, step_half, base, store;
 };
 static const DgradDual kDgradDual16 = {0.049, 0.050, 0.115, 1.037, 1.285, 1.183}, kDgradDual8 = {0.003, 0.132, 0.004, 1.789, 0.846, 1.294};
+static const DgradDual kDgradWideDual16 = {9.864, 0.871, 8.078, 0.447, 4.760, 0.207}, kDgradWideDual8 = {8.835, 0.884, 0.984, 1.225, 3.051, 0.203};
 
 static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
-  const DgradShape* tab = fp8 ? kDgrad8 : kDgrad16;
+  const bool wide = O > 5120 || I > 5120 || T > 32768;
+  const DgradCost* cost = wide ? (fp8 ? kDgradWide8 : kDgradWide16) : (fp8 ? kDgradCost8 : kDgradCost16);
+  const DgradDual& dual = wide ? (fp8 ? kDgradWideDual8 : kDgradWideDual16) : (fp8 ? kDgradDual8 : kDgradDual16);
   const int64_t steps = (O + (fp8 ? 127 : 63)) / (fp8 ? 128 : 64);
   const double out_us = (double)T * (double)I * 2.0 / 5e6;
   int best = DG_256;
   double best_t = 1e30;
   for (int c = 0; c < DG_SHAPES; c++) {
-    const DgradShape& s = tab[c];
-    const int64_t wgs = ((I + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn);
+    const DgradShape& g = kDgrad[c];
+    const DgradCost& s = cost[c];
+    const int64_t wgs = ((I + g.bm - 1) / g.bm) * ((T + g.bn - 1) / g.bn);
     if (c != DG_256 && wgs > 0x7FFFFFFFll) continue;                                  // grid size
-    const double nk = (double)((steps + s.kg - 1) / s.kg);
-    const int64_t n = (wgs + 255) / 256, full = n / s.r, rem = n % s.r;      // workgroups on the busiest CU: full rounds of r, and a rest
-    double t = s.base + s.store * out_us + (double)full * (s.f + nk * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));
+    const double nk = (double)((steps + g.kg - 1) / g.kg);
+    const int64_t n = (wgs + 255) / 256, full = n / g.r, rem = n % g.r;      // workgroups on the busiest CU: full rounds of r, and a rest
+    double t = s.base + s.store * out_us + (double)full * (s.f + nk * (s.lat > g.r * s.thr ? s.lat : g.r * s.thr));
     if (rem) t += s.f + nk * (s.lat > rem * s.thr ? s.lat : rem * s.thr);
     if (t < best_t) {
       best_t = t;
@@ -588,8 +631,7 @@ static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
     }
     // 256 x 256 tiles whose last round is at most half full: that round as 256 x 128 tiles
     if (c == DG_256 && wgs > 256 && wgs % 256 != 0 && wgs % 256 <= 128) {
-      const DgradDual& d = fp8 ? kDgradDual8 : kDgradDual16;
-      const double td = d.base + d.store * out_us + (double)(wgs / 256) * (d.f + nk * d.step) + d.f_half + nk * d.step_half;
+      const double td = dual.base + dual.store * out_us + (double)(wgs / 256) * (dual.f + nk * dual.step) + dual.f_half + nk * dual.step_half;
       if (td < best_t) {
         best_t = td;
         best = DG_DUAL;
@@ -606,7 +648,7 @@ void describe_dgrad(int64_t T, int64_t O, int64_t I, int dtype, char* text, size
     snprintf(text, n, "256x256+256x128 kg 1 r 1 grid %lld block 512", (long long)(big + big % 256));
     return;
   }
-  const DgradShape& s = kDgrad16[cfg];
+  const DgradShape& s = kDgrad[cfg];
   snprintf(text, n, "%dx%d kg %d r %d grid %lld block %d", s.bm, s.bn, s.kg, s.r, (long long)(((I + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn)), s.threads);
 }
 

@@ -1028,45 +1028,93 @@ static void launch_fwd_skinny(const void* X, int64_t T, int64_t I, int64_t ldx, 
               I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
 }
 
-// Choice of the kernel.  Time model in microseconds: base + store * (output bytes at 5 TB/s) + rounds, a workgroup costing F + nk * step
-// with nk its k-steps (each k-group of a workgroup takes a KG-th of them) and step = max(lat, r * thr) for r workgroups sharing a CU;
+// Choice of the kernel.  Form of a time model in microseconds: base + store * (output bytes at 5 TB/s) + rounds, a workgroup costing F + nk *
+// step with nk its k-steps (each k-group of a workgroup takes a KG-th of them) and step = max(lat, r * thr) for r workgroups sharing a CU;
 // R fit a CU (LDS) and what does not fit runs in further rounds.  The two-shape grid has a row of its own: whole rounds of 256 x 256 tiles
-// and one of 256 x 128 tiles, each with its F and step.  The rows are chosen for what the choice costs on 2400 random problems (1 ... 32768
-// tokens, 64 ... 5120 channels and features, a third of them layers of the GPT-2 workloads), timed in every shape, and for not losing
-// anywhere to the choice before (rows fitted without the 128 x 256 tiles): 0.9 % (bf16) / 0.75 % (8-bit) faster than that one on the
-// geometric mean, by more than 3 % on a tenth of the problems, slower by more than 3 % on 2 / 1 % (12 / 11 % at worst).  They say
-// less about a single shape's time.  128 x 256 tiles are there for what fills a round of them and little more than half a round of others:
-// 1021 x 5120 x 1280 e4m3 11.3 -> 9.1 us.
+// and one of 256 x 128 tiles, each with its F and step.  Two sets of rows:
+// Weights up to 5120 wide and up to 32768 tokens: the rows rank the shapes and are no times (the terms' names say how they enter, not what
+// they measure: the two-shape grid's step is 0 and its base 22 us in bf16); what they say ends with that range.  They are chosen for what the
+// choice costs on 2400 random problems (1 ... 32768 tokens, 64 ... 5120 channels and features, a third of them layers of the GPT-2
+// workloads), timed in every shape, and for not losing anywhere to the choice before (rows fitted without the 128 x 256 tiles): 0.9 %
+// (bf16) / 0.75 % (8-bit) faster than that one on the geometric mean, by more than 3 % on a tenth of the problems, slower by more than
+// 3 % on 2 / 1 % (12 / 11 % at worst).  128 x 256 tiles are there for what fills a round of them and little more than half a round of
+// others: 1021 x 5120 x 1280 e4m3 11.3 -> 9.1 us.
+// Wider weights or more tokens: rows fitted to the times themselves, no step below the matrix pipe's, so that they hold beyond what was
+// timed.  `few`: the share of lat that a lone workgroup saves, with nobody to share L2 and memory.  2600 random problems up to 65536
+// wide (1 ... 262144 tokens), on one set of buffers and on sets that rotate through 600 MB: the choice is 0.5 % slower than the best shape
+// on the geometric mean, 23 / 21 % at worst; on 1500 others 0.5 %, 21 / 47 %.  The first set of rows loses 6.7 / 9.0 % there and up to
+// 2.9 times the time (860 x 4192 x 63616 e4m3: 607 against 205 us), as it sends few tokens to the 64 x 32 and 32 x 32 tiles.
 struct FwdShape {
   int bm, bn, kg, r, threads;
-  double f, lat, thr, base, store;
+};
+struct FwdCost {
+  double f, lat, thr, base, store, few;
 };
 enum { FW_256, FW_256x128, FW_128x256, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
-static const FwdShape kFwd16[FW_SHAPES] = {
-  {256, 256, 1, 1, 512, 7.033, 0.572, 0.590, 0.014, 0.681},
-  {256, 128, 1, 2, 256, 0.159, 1.290, 0.015, 3.052, 0.002},
-  {128, 256, 1, 1, 512, 2.981, 0.384, 0.000, 0.170, 1.968},
-  {128, 128, 1, 2, 256, 2.580, 0.171, 0.319, 0.803, 0.665},
-  {128, 128, 1, 3, 256, 2.798, 0.008, 0.478, 0.500, 0.000},
-  {128, 64, 1, 2, 256, 0.000, 0.201, 0.320, 3.367, 0.092},
-  {64, 64, 1, 3, 256, 0.025, 0.299, 0.315, 2.976, 0.847},
-  {64, 64, 2, 1, 512, 5.159, 0.006, 0.234, 1.318, 0.001},
-  {64, 32, 4, 1, 512, 2.681, 0.355, 0.219, 2.263, 0.000},
-  {32, 32, 4, 1, 256, 2.446, 0.090, 0.379, 1.671, 1.127},
-  {16, 16, 8, 4, 512, 0.028, 0.001, 1.049, 0.113, 0.000},
+static const FwdShape kFwd[FW_SHAPES] = {
+  {256, 256, 1, 1, 512},
+  {256, 128, 1, 2, 256},
+  {128, 256, 1, 1, 512},
+  {128, 128, 1, 2, 256},
+  {128, 128, 1, 3, 256},
+  {128, 64, 1, 2, 256},
+  {64, 64, 1, 3, 256},
+  {64, 64, 2, 1, 512},
+  {64, 32, 4, 1, 512},
+  {32, 32, 4, 1, 256},
+  {16, 16, 8, 4, 512},
 };
-static const FwdShape kFwd8[FW_SHAPES] = {
-  {256, 256, 1, 1, 512, 0.089, 0.930, 0.024, 4.711, 1.093},
-  {256, 128, 1, 2, 256, 2.306, 0.155, 1.014, 2.827, 0.000},
-  {128, 256, 1, 1, 512, 4.175, 0.000, 0.657, 0.513, 0.289},
-  {128, 128, 1, 2, 256, 0.248, 0.001, 0.602, 4.652, 0.239},
-  {128, 128, 1, 3, 256, 0.913, 0.868, 0.435, 2.847, 0.450},
-  {128, 64, 1, 2, 256, 2.360, 0.003, 0.509, 1.932, 0.023},
-  {64, 64, 1, 3, 256, 1.157, 0.001, 0.310, 2.953, 0.185},
-  {64, 64, 2, 1, 512, 0.420, 0.457, 0.010, 3.196, 5.917},
-  {64, 32, 4, 1, 512, 3.849, 0.001, 0.287, 0.013, 17.472},
-  {32, 32, 4, 1, 256, 0.001, 0.273, 0.000, 3.727, 18.888},
-  {16, 16, 8, 4, 512, 0.002, 0.380, 1.162, 0.000, 0.003},
+static const FwdCost kFwdCost16[FW_SHAPES] = {
+  {7.033, 0.572, 0.590, 0.014, 0.681},
+  {0.159, 1.290, 0.015, 3.052, 0.002},
+  {2.981, 0.384, 0.000, 0.170, 1.968},
+  {2.580, 0.171, 0.319, 0.803, 0.665},
+  {2.798, 0.008, 0.478, 0.500, 0.000},
+  {0.000, 0.201, 0.320, 3.367, 0.092},
+  {0.025, 0.299, 0.315, 2.976, 0.847},
+  {5.159, 0.006, 0.234, 1.318, 0.001},
+  {2.681, 0.355, 0.219, 2.263, 0.000},
+  {2.446, 0.090, 0.379, 1.671, 1.127},
+  {0.028, 0.001, 1.049, 0.113, 0.000},
+};
+static const FwdCost kFwdCost8[FW_SHAPES] = {
+  {0.089, 0.930, 0.024, 4.711, 1.093},
+  {2.306, 0.155, 1.014, 2.827, 0.000},
+  {4.175, 0.000, 0.657, 0.513, 0.289},
+  {0.248, 0.001, 0.602, 4.652, 0.239},
+  {0.913, 0.868, 0.435, 2.847, 0.450},
+  {2.360, 0.003, 0.509, 1.932, 0.023},
+  {1.157, 0.001, 0.310, 2.953, 0.185},
+  {0.420, 0.457, 0.010, 3.196, 5.917},
+  {3.849, 0.001, 0.287, 0.013, 17.472},
+  {0.001, 0.273, 0.000, 3.727, 18.888},
+  {0.002, 0.380, 1.162, 0.000, 0.003},
+};
+static const FwdCost kFwdWide16[FW_SHAPES] = {
+  {6.667, 0.604, 0.604, 0.149, 0.736, 0.512},
+  {3.881, 0.990, 0.331, 3.150, 0.203, 0.585},
+  {3.783, 0.489, 0.323, 0.104, 1.395, 0.025},
+  {3.320, 0.279, 0.279, 2.453, 0.206, 0.447},
+  {2.401, 0.721, 0.327, 0.910, 0.912, 0.345},
+  {5.510, 0.174, 0.174, 0.152, 0.896, 0.664},
+  {1.917, 0.343, 0.058, 4.004, 0.878, 0.747},
+  {4.436, 0.294, 0.056, 0.114, 0.217, 0.030},
+  {4.409, 0.340, 0.066, 0.110, 4.462, 0.378},
+  {3.581, 0.202, 0.033, 0.106, 6.000, 0.000},
+  {0.304, 0.405, 0.405, 2.634, 0.205, 0.421},
+};
+static const FwdCost kFwdWide8[FW_SHAPES] = {
+  {5.890, 0.737, 0.737, 0.140, 0.210, 0.385},
+  {2.331, 1.231, 0.551, 2.599, 0.203, 0.699},
+  {4.421, 0.516, 0.369, 0.105, 1.050, 0.719},
+  {1.468, 0.332, 0.332, 2.848, 0.532, 0.478},
+  {1.980, 0.646, 0.323, 2.047, 0.500, 0.020},
+  {4.349, 0.206, 0.206, 0.260, 0.601, 0.705},
+  {0.372, 0.416, 0.058, 3.468, 0.918, 0.799},
+  {4.832, 0.272, 0.056, 0.112, 0.208, 0.011},
+  {4.604, 0.322, 0.066, 0.106, 5.969, 0.393},
+  {3.530, 0.196, 0.033, 0.108, 5.995, 0.001},
+  {0.301, 0.405, 0.405, 2.178, 5.950, 0.472},
 };
 
 // the two-shape grid: F and step of a round of 256 x 256 tiles, of the last one of 256 x 128 tiles, base, store
@@ -1074,30 +1122,34 @@ struct FwdDual {
   double f, step, f_half, step_half, base, store;
 };
 static const FwdDual kFwdDual16 = {3.521, 0.000, 1.893, 0.458, 21.918, 0.003}, kFwdDual8 = {3.736, 0.003, 0.604, 1.146, 5.867, 0.830};
+static const FwdDual kFwdWideDual16 = {9.943, 0.435, 3.580, 0.614, 2.986, 0.208}, kFwdWideDual8 = {7.671, 0.512, 0.673, 0.858, 1.193, 0.203};
 
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
-  const FwdShape* tab = fp8 ? kFwd8 : kFwd16;
+  const bool wide = O > 5120 || I > 5120 || T > 32768;
+  const FwdCost* cost = wide ? (fp8 ? kFwdWide8 : kFwdWide16) : (fp8 ? kFwdCost8 : kFwdCost16);
+  const FwdDual& dual = wide ? (fp8 ? kFwdWideDual8 : kFwdWideDual16) : (fp8 ? kFwdDual8 : kFwdDual16);
   const int64_t steps = I / (fp8 ? 128 : 64);
   const double out_us = (double)T * (double)O * 2.0 / 5e6;
   int best = FW_256;
   double best_t = 1e30;
   for (int c = 0; c < FW_SHAPES; c++) {
-    const FwdShape& s = tab[c];
-    const int64_t wgs = ((O + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn);
+    const FwdShape& g = kFwd[c];
+    const FwdCost& s = cost[c];
+    const int64_t wgs = ((O + g.bm - 1) / g.bm) * ((T + g.bn - 1) / g.bn);
     if (c != FW_256 && wgs > 0x7FFFFFFFll) continue;                                  // grid size
-    const double nk = (double)((steps + s.kg - 1) / s.kg), fixed = s.base + s.store * out_us;
-    const int64_t n = (wgs + NUM_CU - 1) / NUM_CU, full = n / s.r, rem = n % s.r;      // workgroups on the busiest CU: full rounds of r, and a rest
+    const double nk = (double)((steps + g.kg - 1) / g.kg), fixed = s.base + s.store * out_us;
+    const int64_t n = (wgs + NUM_CU - 1) / NUM_CU, full = n / g.r, rem = n % g.r;      // workgroups on the busiest CU: full rounds of r, and a rest
     const double part = c == FW_16_KG8 && T < 16 ? 0.4 + 0.6 / 16.0 * (double)T : 1.0;
-    double t = fixed + (double)full * (s.f + nk * part * (s.lat > s.r * s.thr ? s.lat : s.r * s.thr));
-    if (rem) t += s.f + nk * part * (s.lat > rem * s.thr ? s.lat : rem * s.thr);
+    const double lat = wgs < NUM_CU ? s.lat * (1.0 - s.few * (1.0 - (double)wgs / NUM_CU)) : s.lat;
+    double t = fixed + (double)full * (s.f + nk * part * (lat > g.r * s.thr ? lat : g.r * s.thr));
+    if (rem) t += s.f + nk * part * (lat > rem * s.thr ? lat : rem * s.thr);
     if (t < best_t) {
       best_t = t;
       best = c;
     }
     // 256 x 256 tiles whose last round is at most half full: that round as 256 x 128 tiles
     if (c == FW_256 && wgs > NUM_CU && wgs % NUM_CU != 0 && wgs % NUM_CU <= NUM_CU / 2) {
-      const FwdDual& d = fp8 ? kFwdDual8 : kFwdDual16;
-      t = d.base + d.store * out_us + (double)(wgs / NUM_CU) * (d.f + nk * d.step) + d.f_half + nk * d.step_half;
+      t = dual.base + dual.store * out_us + (double)(wgs / NUM_CU) * (dual.f + nk * dual.step) + dual.f_half + nk * dual.step_half;
       if (t < best_t) {
         best_t = t;
         best = FW_DUAL;
@@ -1114,7 +1166,7 @@ void describe_fwd(int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t
     snprintf(text, n, "256x256+256x128 kg 1 r 1 grid %lld block 512", (long long)(big + big % NUM_CU));
     return;
   }
-  const FwdShape& s = kFwd16[cfg];
+  const FwdShape& s = kFwd[cfg];
   snprintf(text, n, "%dx%d kg %d r %d grid %lld block %d", s.bm, s.bn, s.kg, s.r, (long long)(((O + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn)), s.threads);
 }
 

@@ -331,6 +331,31 @@ def test_describe_plan(op, sizes, dtype, want):
     assert sste.describe_plan(op, *sizes, dtype) == want
 
 
+# Weights wider than 5120 and more than 32768 tokens, timed in every tile: the tiles within 10 % of the fastest one, and, as comments, the
+# time in us in the tile that rows of the choice which hold only up to 5120 wide would take.
+@pytest.mark.parametrize("op,dtype,T,O,I,tiles", [
+    ("fwd", 0, 28, 4128, 58048, ["32x32 kg 4 r 1"]),                       # 88.3; 64x32 kg 4 127.3
+    ("fwd", 0, 10, 792, 34496, ["16x16 kg 8 r 4"]),                        # 28.0; 64x32 kg 4 51.7
+    ("fwd", 0, 148, 6824, 59584, ["128x64 kg 1 r 2"]),                     # 249; 64x64 kg 2 395
+    ("fwd", 0, 94, 10688, 2624, ["128x64 kg 1 r 2"]),                      # 14.1; 64x32 kg 4 20.2
+    ("fwd", 0, 2620, 6080, 11776, ["256x128 kg 1 r 2"]),                   # 187; the two-shape grid 266
+    ("fwd", 1, 1, 51376, 1280, ["16x16 kg 8 r 4"]),                        # 9.2; 32x32 kg 4 21.9
+    ("fwd", 1, 1006, 2032, 20096, ["128x64 kg 1 r 2"]),                    # 45.7; 64x32 kg 4 116
+    ("fwd", 1, 104, 8080, 37888, ["64x64 kg 2 r 1"]),                      # 62.2; 64x32 kg 4 111
+    ("fwd", 1, 860, 4192, 63616, ["128x128 kg 1 r 2"]),                    # 205; 64x32 kg 4 607
+    ("fwd", 1, 9, 48528, 1280, ["64x64 kg 1 r 3", "16x16 kg 8 r 4", "128x64 kg 1 r 2"]),                 # 10.3; 32x32 kg 4 20.6
+    ("dgrad", 0, 70, 26616, 23872, ["128x128 kg 2 r 1"]),                  # 193; 64x64 kg 4 331
+    ("dgrad", 0, 894, 65160, 2176, ["128x64 kg 2 r 1"]),                   # 364; 64x64 kg 4 536
+    ("dgrad", 0, 47, 736, 37248, ["64x64 kg 1 r 4"]),                      # 11.3; 256x128 14.4
+    ("dgrad", 1, 83, 19328, 17536, ["128x128 kg 2 r 1"]),                  # 74.0; 128x128 kg 1 98.1
+    ("dgrad", 1, 12, 6256, 34304, ["64x64 kg 2 r 2", "64x64 kg 1 r 4", "256x128 kg 1 r 1"]),             # 41.2; 128x64 kg 2 56.7
+    ("dgrad", 1, 75349, 80, 128, ["128x128 kg 1 r 2"]),                    # 9.1; the two-shape grid 12.9
+])
+def test_choice_of_the_tile_holds_for_wide_weights(op, dtype, T, O, I, tiles):
+    import paper_2409_09099_amd as sste
+    assert sste.describe_plan(op, T, O, I, dtype).split(" grid ")[0] in tiles
+
+
 def test_describe_plan_refuses(lib):
     f = lib.sste_describe_plan
     f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]
