@@ -19,8 +19,8 @@
 // tiles.  The price is that every wave reads the whole grad_Z tile from LDS (256 KiB per k-step of 256 x 256, 43 % of
 // its clocks at the measured 128 KiB in 567).
 //
-// What bounds it.  The large tiles are bound by the power the chip allows: a k-step of 256 x 256 takes 2650 (bf16) / 2670 (8-bit) clocks, of
-// which the matrix pipe needs 2176 / 2304, at a clock held down to 1.6 ... 1.8 GHz.  Before (decode by two waves each, or by byte
+// What bounds it.  The large tiles run at the clock that the power limit leaves, 1.6 ... 1.8 GHz: a k-step of 256 x 256 takes 2650 (bf16) /
+// 2670 (8-bit) clocks, of which the matrix pipe needs 2176 / 2304.  Before (decode by two waves each, or by byte
 // permutes through the LDS) it took 2990 / 3740 clocks at 1.75 / 1.99 GHz; so of 11 / 29 % fewer clocks 10 / 14 % of time are left, and what
 // counts is work per result: the 16 x 16 instructions of bf16 sustain 1.87 ... 2.04 PFLOP/s on random operands in registers against 1.76 of the
 // 32 x 32 ones (hence the former in the large bf16 tiles, with the two operands exchanged in turn: 4 % faster; 8-bit tiles lose 4 % to
@@ -32,7 +32,8 @@
 // k-steps in flight divide that.
 // Measured (us before -> after, T x O x I): bf16 2112 x 1544 x 832 16.7 -> 12.9, 4096 x 3072 x 768 31.0 -> 23.5, 8192 x 3072 x 768 56 -> 50,
 // 16384 x 4096 x 1024 123 -> 111, 16384 x 5120 x 1280 205 -> 183, 16384 x 1280 x 5120 201 -> 179; e5m2 3200 x 1552 x 896 15.8 -> 12.2,
-// 32768 x 1280 x 5120 249 -> 223, 32768 x 5120 x 1280 214 -> 191; e4m3 2048 x 4096 x 1024 20.3 -> 17.9.
+// 32768 x 1280 x 5120 249 -> 223, 32768 x 5120 x 1280 214 -> 191; e4m3 2048 x 4096 x 1024 20.3 -> 17.9.  One or two k-steps are slower, a
+// wave's serial chain being twice as long: 8-bit 3.3 / 3.6 -> 3.8 / 4.2 (median of small problems), bf16 3.3 / 3.6 -> 3.7 / 3.9.
 // The identity product is exact for finite values; an infinite or NaN packed value (the interface rules them out) makes NaN of the 32
 // features it is expanded with.  Asking every packed slot for one, with a second look in a branch, was measured: 2.1 % of a four-layer
 // training step in bf16 (1668 -> 1704 us), 1.8 % of an 8-bit layer of small tiles, so it is not asked.

@@ -4,7 +4,7 @@
 //   1. k_mvue_pack: the estimator is applied once per group of four tokens and the result is written
 //      to the workspace as a packed 2:4 operand in sparse-MFMA fragment order (the format of
 //      include/sste.h with rows = output channels, columns = tokens).  It streams dY once: at about
-//      85 vector instructions per group (bf16; 70 for 8-bit types) the bf16 kernel runs at the rate of a
+//      90 vector instructions per group (bf16; 72 for 8-bit types) the bf16 kernel runs at the rate of a
 //      plain copy, the 8-bit kernel (twice the groups per byte) is bound by the vector pipe.
 //   2. k_wgrad_gemm (large tiles) or k_wgrad_tile (small ones): sparse MFMA GEMM, rows = channels o, columns =
 //      input features i, contraction = tokens.  The packed operand is loaded like the packed weight of the
