@@ -32,8 +32,8 @@
 // k-steps in flight divide that.
 // Measured (us before -> after, T x O x I): bf16 2112 x 1544 x 832 16.7 -> 12.9, 4096 x 3072 x 768 31.0 -> 23.5, 8192 x 3072 x 768 56 -> 50,
 // 16384 x 4096 x 1024 123 -> 111, 16384 x 5120 x 1280 205 -> 183, 16384 x 1280 x 5120 201 -> 179; e5m2 3200 x 1552 x 896 15.8 -> 12.2,
-// 32768 x 1280 x 5120 249 -> 223, 32768 x 5120 x 1280 214 -> 191; e4m3 2048 x 4096 x 1024 20.3 -> 17.9.  One or two k-steps are slower, a
-// wave's serial chain being twice as long: 8-bit 3.3 / 3.6 -> 3.8 / 4.2 (median of small problems), bf16 3.3 / 3.6 -> 3.7 / 3.9.
+// 32768 x 1280 x 5120 249 -> 223, 32768 x 5120 x 1280 214 -> 191; e4m3 2048 x 4096 x 1024 20.3 -> 17.9.  One and two k-steps, which
+// a wave decodes and multiplies in a longer serial chain: within 3 % of before.
 // The identity product is exact for finite values; an infinite or NaN packed value (the interface rules them out) makes NaN of the 32
 // features it is expanded with.  Asking every packed slot for one, with a second look in a branch, was measured: 2.1 % of a four-layer
 // training step in bf16 (1668 -> 1704 us), 1.8 % of an 8-bit layer of small tiles, so it is not asked.
@@ -218,6 +218,11 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   constexpr int FP = FP8 ? 2 : 1;                   // 16-byte pieces per fragment
   constexpr int D = FP8 ? 2 : 4;                    // fragments read ahead
   constexpr int NH = NF / 2;
+  // The last k-step by itself, without the waiting, loading and decoding for a next one, and no loads of k-steps past the last ahead of the
+  // first: in the small tiles, whose problems may have one or two k-steps (geometric mean over random problems of one / two k-steps: 8-bit 9 /
+  // 6 % faster, bf16 6 / 2 %; the 64 x 64 tiles over all lengths 3 ... 10 %).  Long contractions gain little: the bf16 tiles of 128
+  // features measured 0 ... 1 % slower and keep the plain loop, as the large tiles do.
+  constexpr bool PEEL = WF == 2 || (FP8 && WF == 4);
   // The loads of a k-step are issued behind its barrier, every second fragment one where there are enough: in one burst they fill the queue
   // and stop the wave (5120 x 1280 weights, 32768 tokens, e4m3: 204 -> 196 us).  load_at(l): the fragment, counted from the barrier, with
   // which load l goes; the first L1 loads go in the k-step of the barrier, the others in the next one.
@@ -394,11 +399,14 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
   // prologue
   if (nloc > 0) {
 #pragma unroll
-    for (int k = 0; k < NS; k++)
+    for (int k = 0; k < NS; k++) {
+      if (PEEL && k >= nloc) break;             // k-steps past the last one are never multiplied
 #pragma unroll
       for (int l = 0; l < LPW; l++)
         if (k < NS - 1 || l < L1) load(l, k, k);
-    wait_vmcnt<LB + (NS - 3) * LPW + L1>();   // packed slots of k-steps 0 and 1, grad_Z tile 0
+    }
+    if (PEEL && nloc < NS) wait_vmcnt<0>();     // everything; the waits of the k-steps count on loads that were not issued
+    else wait_vmcnt<LB + (NS - 3) * LPW + L1>();   // packed slots of k-steps 0 and 1, grad_Z tile 0
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 8; r++) zero_pair(ex, r);
@@ -416,47 +424,52 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
     slot_read(1, ring);
   }
 
-  int slot = 0, slot1 = 1, slotp = NS - 1;
-  for (int s = 0; s < nloc; s++) {
+  int s = 0, slot = 0, slot1 = 1, slotp = NS - 1;
+  // k-step s; behind the last one (small tiles) there is nothing to wait for, to load and to decode
+  auto step = [&](auto last_) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last_)::value;
     const uint8_t* const p0 = ring + slot * SLOT;
     const uint8_t* const p1 = ring + slot1 * SLOT;
     static_for<2 * NHM>([&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value, half = k / NHM, f = k / MB, mi = k % MB, m = f & 1 ? MB - 1 - mi : mi, u = k % NHM / UW, w = k % UW;
-      if (f == NF - D && mi == 0) {
+      constexpr bool DECODE = !LAST || half == 0;
+      if (!LAST && f == NF - D && mi == 0) {
         // grad_Z tile s + 1 and the packed slots of s + 2 have landed (grad_Z s + 2 and what is newer may be in flight) ...
         wait_vmcnt<LB + (NS - 3) * LPW>();
         __syncthreads();                 // ... for every wave; the slot of s has been read
       }
       // decoding for the next half k-step: (s, 1) during half 0, (s + 1, 0) during half 1
-      if (w == 0) unit_mma(u);
+      if (DECODE && w == 0) unit_mma(u);
       __builtin_amdgcn_sched_barrier(0);
       mma(f, m);
       __builtin_amdgcn_sched_barrier(0);
       if (mi == MB - 1) {
         if (f + D < NF) read_b(f + D, p0);
-        else read_b(f + D - NF, p1);
+        else if (!LAST) read_b(f + D - NF, p1);
       }
       // k-step s + NS, into the slot that the barrier freed; not in one burst, which fills the queue and stops the wave
-      if (mi == 0) {
+      if (!LAST && mi == 0) {
 #pragma unroll
         for (int l = 0; l < LPW; l++) {
           if (NF - D + load_at(l) == f) load(l, s + NS, slot);
           if (load_at(l) - D == f) load(l, s + NS - 1, slotp);
         }
       }
-      if (w == 0 && u == NU - 1) slot_read(half, p1);      // the packed slot of the half after the next one
+      if (!LAST && w == 0 && u == NU - 1) slot_read(half, p1);      // the packed slot of the half after the next one
 #pragma unroll
       for (int e = 0; e < 8; e++)
-        if (cvt_at(e) == w) unit_cvt(u, 1 - half, e);
+        if (DECODE && cvt_at(e) == w) unit_cvt(u, 1 - half, e);
 #pragma unroll
       for (int r = 0; r < 8; r++)
-        if (zero_at(r) == w) zero_pair(ex, r);
+        if (DECODE && zero_at(r) == w && !(LAST && u == NU - 1)) zero_pair(ex, r);
       __builtin_amdgcn_sched_barrier(0);
     });
     slotp = slot;
     slot = slot1;
     slot1 = slot1 == NS - 1 ? 0 : slot1 + 1;
-  }
+  };
+  for (; s < (PEEL ? nloc - 1 : nloc); s++) step(std::false_type());
+  if (PEEL && nloc > 0) step(std::true_type());
   wait_vmcnt<0>();
   __syncthreads();
   if (KG > 1) {

@@ -59,6 +59,22 @@ def test_linear_dgrad_tile_of_128_features_64_tokens(sste, dtype, T, O, I):  # n
     test_linear_dgrad_tiles(sste, dtype, T, O, I, "128x64 kg 2", "128x64 kg 2")
 
 
+# the tiles that take the last k-step by itself: 1 ... 5 k-steps per group of waves, fewer and more than the pipeline is deep
+@pytest.mark.parametrize("dtype,T,O,I,tile", [
+    ("bf16", 29, 16, 64, "64x64 kg 1"), ("bf16", 17, 96, 64, "64x64 kg 1"), ("bf16", 22, 144, 1152, "64x64 kg 1"), ("bf16", 16485, 224, 64, "64x64 kg 1"),
+    ("bf16", 28, 144, 64, "64x64 kg 2"), ("bf16", 22, 272, 64, "64x64 kg 2"), ("bf16", 59, 400, 832, "64x64 kg 2"), ("bf16", 19, 560, 64, "64x64 kg 2"),
+    ("bf16", 20, 496, 64, "64x64 kg 4"), ("bf16", 24, 704, 64, "64x64 kg 4"), ("bf16", 21, 784, 64, "64x64 kg 4"),
+    ("e4m3", 41, 16, 128, "64x64 kg 1"), ("e5m2", 270, 160, 3328, "64x64 kg 1"), ("e4m3", 554, 272, 3712, "64x64 kg 1"),
+    ("e4m3", 17, 176, 128, "64x64 kg 2"), ("e5m2", 141, 272, 128, "64x64 kg 2"), ("e4m3", 20, 544, 128, "64x64 kg 2"), ("e4m3", 49, 784, 2048, "64x64 kg 2"),
+    ("e4m3", 17, 336, 128, "64x64 kg 4"), ("e4m3", 17, 992, 128, "64x64 kg 4"), ("e5m2", 20, 1408, 128, "64x64 kg 4"), ("e4m3", 19, 1648, 128, "64x64 kg 4"),
+    ("e4m3", 344, 144, 3072, "128x64 kg 2"), ("e4m3", 258, 272, 3584, "128x64 kg 2"), ("e5m2", 262, 592, 3328, "128x64 kg 2"), ("e4m3", 267, 784, 3456, "128x64 kg 2"),
+    ("e4m3", 1579, 16, 3584, "128x128 kg 1"), ("e5m2", 3762, 144, 1408, "128x128 kg 1"), ("e4m3", 867, 272, 3584, "128x128 kg 1"), ("e4m3", 2173, 400, 2560, "128x128 kg 1"),
+    ("e4m3", 3589, 144, 896, "128x128 kg 2"), ("e4m3", 845, 400, 2432, "128x128 kg 2"), ("e4m3", 785, 544, 2560, "128x128 kg 2"), ("e5m2", 648, 784, 3072, "128x128 kg 2"),
+])
+def test_linear_dgrad_last_step_by_itself(sste, dtype, T, O, I, tile):  # noqa: F811
+    test_linear_dgrad_tiles(sste, dtype, T, O, I, tile, tile)
+
+
 # every tile of the input gradient, with an incomplete last k-step: (8-bit?, T, O, I, tile of sste_describe_plan)
 DGRAD_PARTIAL_STEPS = [
     (False, 325, 136, 2816, "64x64 kg 1"), (False, 65, 136, 64, "64x64 kg 2"), (False, 65, 416, 64, "64x64 kg 4"),
