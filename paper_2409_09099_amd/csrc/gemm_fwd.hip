@@ -13,13 +13,14 @@
 //
 // Tiling: every wave owns a grid of 16 x 16 MFMA tiles (8 x 4 = 128 channels x 64 tokens in the main
 // shape): per sparse MFMA it reads about 540 B of fragments from LDS, inside the LDS read rate of the CU.
-// Five kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
+// Six kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
 //   k_linear_fwd_pipe   software-pipelined 256 x 256 and 128 x 256 tiles, 8 waves, one workgroup per CU;
 //   k_linear_fwd_dual   the same tile code for 256 x 256 and 256 x 128 tiles in one grid, for layers
 //                       whose last round of 256 x 256 tiles would fill at most half of the CUs;
 //   k_linear_fwd_pair   256 x 128 tiles by 4 waves with the same share each, two workgroups per CU;
 //   k_linear_fwd_tile   128 x 128 down to 32 x 32 tiles on the 32 x 32 instruction, with the contraction split over
 //                       groups of waves where there are few tiles;
+//   k_linear_fwd_dual128 128 x 128 tiles and 128 x 64 halves in one grid, for little more than one tile per CU;
 //   k_linear_fwd_skinny 16 x 16 tiles straight from memory to registers, for decode batches.
 // Operand tiles travel L2 -> LDS directly (buffer_load ... lds, no staging registers) into rings of
 // LDS slots.  What limits all of them is the L1 of the CU: it keeps 64 line requests in flight, and a
@@ -598,10 +599,11 @@ constexpr int fwd_tile_smem() {
   return M1 > RED ? M1 : RED;
 }
 
+// One output tile: channels [32 WM MT tm, ...) x tokens [t0, t0 + 32 WN NT).
 template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS, bool ZF8, bool AMAX>
-__global__ void __launch_bounds__(64 * WM * WN * KG, 1)
-k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
-                  const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
+__device__ __forceinline__ void fwd_tile(uint8_t* smem, const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes,
+                                         const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int64_t O, const FwdOut& out, int tm,
+                                         int64_t t0) {
   constexpr int NWG = WM * WN, NW = NWG * KG;
   constexpr int BM = 32 * WM * MT, BN = 32 * WN * NT;
   constexpr int MB = FP8 ? 16 : 8, MBLK = 16 * MB;
@@ -609,16 +611,13 @@ k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int
   constexpr int LPW = LA + LB + LM;
   constexpr int A_BYTES = BM * 64, M_BYTES = NWG * LM * 256, SLOT = A_BYTES + M_BYTES + BN * 128;
   static_assert(LA >= 1 && LB >= 1, "tile too small for this many waves");
-  __shared__ __align__(1024) uint8_t smem[fwd_tile_smem<FP8, WM, WN, MT, NT, KG, NS>()];
-  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int tm = logical % m_tiles, tn = logical / m_tiles;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = KG > 1 ? wave_all / NWG : 0, wave = KG > 1 ? wave_all % NWG : wave_all;
   const int wm = wave / WN, wn = wave % WN;
   const int n = lane & 31, hh = lane >> 5;
-  const int64_t o0 = (int64_t)tm * BM, t0 = (int64_t)tn * BN;
+  const int64_t o0 = (int64_t)tm * BM;
   const int nsteps = (int)(k_bytes / 128);
   const int nloc = (nsteps + KG - 1) / KG;
   uint8_t* const ring = smem + kg * NS * SLOT;
@@ -839,6 +838,41 @@ k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int
   }
 }
 
+template <bool FP8, int WM, int WN, int MT, int NT, int KG, int NS, bool ZF8, bool AMAX>
+__global__ void __launch_bounds__(64 * WM * WN * KG, 1)
+k_linear_fwd_tile(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
+                  const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles) {
+  __shared__ __align__(1024) uint8_t smem[fwd_tile_smem<FP8, WM, WN, MT, NT, KG, NS>()];
+  const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+  fwd_tile<FP8, WM, WN, MT, NT, KG, NS, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, logical % m_tiles,
+                                                   (int64_t)(logical / m_tiles) * (32 * WN * NT));
+}
+
+// Two shapes in one grid, two workgroups per CU: 128 x 128 tiles 0 .. n_big - 1, and the others as 128 x 64 halves (fwd_halves says when and why).
+template <bool FP8>
+constexpr int fwd_dual128_smem() {
+  constexpr int BIG = fwd_tile_smem<FP8, 2, 2, 2, 2, 1, 3>(), HALF = fwd_tile_smem<FP8, 2, 2, 2, 1, 1, 4>();
+  return BIG > HALF ? BIG : HALF;
+}
+template <bool FP8, bool ZF8, bool AMAX>
+__global__ void __launch_bounds__(256, 2)
+k_linear_fwd_dual128(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes, const uint8_t* __restrict__ vals,
+                     const uint8_t* __restrict__ meta, int64_t O, FwdOut out, int m_tiles, int n_big) {
+  __shared__ __align__(1024) uint8_t smem[fwd_dual128_smem<FP8>()];
+  static_assert(2 * fwd_dual128_smem<FP8>() <= 160 * 1024, "two workgroups per CU");
+  const int bid = blockIdx.x;
+  if (bid < n_big) {
+    const int logical = xcd_contiguous(bid, n_big);
+    fwd_tile<FP8, 2, 2, 2, 2, 1, 3, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, logical % m_tiles, (int64_t)(logical / m_tiles) * 128);
+  } else {
+    const int h = xcd_contiguous(bid - n_big, (int)gridDim.x - n_big);
+    const int tile = n_big + (h >> 1);
+    const int64_t t0 = (int64_t)(tile / m_tiles) * 128 + 64 * (h & 1);
+    if (t0 >= T) return;                       // second half of a ragged last token tile: nothing to do
+    fwd_tile<FP8, 2, 2, 2, 1, 1, 4, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, tile % m_tiles, t0);
+  }
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Few tokens (a decode batch): 16 channels x 16 tokens by one workgroup whose KW waves take the k-steps in turn.  The packed
 // weight is read once and every wave's operands come straight from memory into its registers (a lane's slot of a packed block and
@@ -1050,7 +1084,7 @@ struct FwdShape {
 struct FwdCost {
   double f, lat, thr, base, store, few;
 };
-enum { FW_256, FW_256x128, FW_128x256, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES };
+enum { FW_256, FW_256x128, FW_128x256, FW_128_R2, FW_128_R3, FW_128x64, FW_64, FW_64_KG2, FW_64x32_KG4, FW_32_KG4, FW_16_KG8, FW_SHAPES, FW_DUAL = FW_SHAPES, FW_DUAL128 };
 static const FwdShape kFwd[FW_SHAPES] = {
   {256, 256, 1, 1, 512},
   {256, 128, 1, 2, 256},
@@ -1124,11 +1158,24 @@ struct FwdDual {
 static const FwdDual kFwdDual16 = {3.521, 0.000, 1.893, 0.458, 21.918, 0.003}, kFwdDual8 = {3.736, 0.003, 0.604, 1.146, 5.867, 0.830};
 static const FwdDual kFwdWideDual16 = {9.943, 0.435, 3.580, 0.614, 2.986, 0.208}, kFwdWideDual8 = {7.671, 0.512, 0.673, 0.858, 1.193, 0.203};
 
+// 128 x 128 tiles that are more than one per CU and at most one and a half: the excess runs as twice as many 128 x 64 halves, so that every CU gets
+// one tile and at most one half, and not some of them two tiles (or a 128 x 256 one) and the others one or none.  On 240 + 360 random problems of
+// that kind (weights up to 5120 wide; wider ones and more tokens), against the shape that the rows below choose: 7 / 6 % (bf16) and 5 / 3 % (8-bit)
+// faster on the geometric mean, at worst 3 / 4 % slower.  Not taken where it lost: up to three k-steps beyond 320 tiles (up to 7 %), more than 32
+// k-steps in 8 bits (up to 8 %; the 128 x 256 tiles fetch fewer bytes), and where the last tile may be mostly padding (below 512 tokens; channels
+// that fill less than three quarters of their tiles: 2 ... 5 % faster, up to 7 % slower).
+// (1021 x 5120 x 1280 e4m3 with the activation 16.5 -> 14.7 us.)
+static bool fwd_halves(bool fp8, int64_t T, int64_t O, int64_t steps) {
+  const int64_t tiles = ((O + 127) / 128) * ((T + 127) / 128);
+  return T >= 512 && 4 * O >= 3 * 128 * ((O + 127) / 128) && tiles > NUM_CU && tiles <= NUM_CU * 3 / 2 && (steps >= 4 || tiles <= NUM_CU * 5 / 4) && (!fp8 || steps <= 32);
+}
+
 static int fwd_choice(bool fp8, int64_t T, int64_t O, int64_t I) {
   const bool wide = O > 5120 || I > 5120 || T > 32768;
   const FwdCost* cost = wide ? (fp8 ? kFwdWide8 : kFwdWide16) : (fp8 ? kFwdCost8 : kFwdCost16);
   const FwdDual& dual = wide ? (fp8 ? kFwdWideDual8 : kFwdWideDual16) : (fp8 ? kFwdDual8 : kFwdDual16);
   const int64_t steps = I / (fp8 ? 128 : 64);
+  if (fwd_halves(fp8, T, O, steps)) return FW_DUAL128;
   const double out_us = (double)T * (double)O * 2.0 / 5e6;
   int best = FW_256;
   double best_t = 1e30;
@@ -1166,6 +1213,11 @@ void describe_fwd(int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t
     snprintf(text, n, "256x256+256x128 kg 1 r 1 grid %lld block 512", (long long)(big + big % NUM_CU));
     return;
   }
+  if (cfg == FW_DUAL128) {
+    const int64_t tiles = ((O + 127) / 128) * ((T + 127) / 128);
+    snprintf(text, n, "128x128+128x64 kg 1 r 2 grid %lld block 256", (long long)(2 * tiles - NUM_CU));
+    return;
+  }
   const FwdShape& s = kFwd[cfg];
   snprintf(text, n, "%dx%d kg %d r %d grid %lld block %d", s.bm, s.bn, s.kg, s.r, (long long)(((O + s.bm - 1) / s.bm) * ((T + s.bn - 1) / s.bn)), s.threads);
 }
@@ -1189,6 +1241,13 @@ static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx,
       const int64_t eb = FP8 ? 1 : 2;
       SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_pair<FP8, 2, 8, 4, ZF8, AMAX>), dim3((unsigned)(m_tiles * n_tiles)), dim3(256), s, (const uint8_t*)X, T,
                   I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles);
+      break;
+    }
+    case FW_DUAL128: {
+      const int m_tiles = (int)((O + 127) / 128), tiles = m_tiles * (int)((T + 127) / 128);
+      const int64_t eb = FP8 ? 1 : 2;
+      SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_dual128<FP8, ZF8, AMAX>), dim3((unsigned)(2 * tiles - NUM_CU)), dim3(256), s, (const uint8_t*)X, T,
+                  I * eb, ldx * eb, (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles, NUM_CU);
       break;
     }
     case FW_128_R2: FT(2, 2, 2, 2, 1, 3); break;

@@ -344,3 +344,23 @@ def test_linear_wgrad_infinity_stays_with_its_records(sste, T, O, I, tile):  # n
     assert bool(got[:, 7].isinf().eq(recorded).all()) and bool(got[:, 7].isfinite().eq(~recorded).all())
     got[:, 7] = 0.0
     assert bool(got.isfinite().all())
+
+
+# the grid of 128 x 128 tiles and 128 x 64 halves: 286 ... 384 tiles, the last token tile's second half empty or not, incomplete last channel tiles and k-steps
+HALVES = "128x128+128x64 kg 1"
+
+
+@pytest.mark.parametrize("dtype,T,O,I", [("bf16", 2690, 1544, 256), ("bf16", 5000, 1016, 64), ("bf16", 6100, 1000, 320),
+                                         ("e4m3", 2690, 1552, 512), ("e4m3", 6100, 1008, 640)])
+def test_linear_fwd_tiles_and_halves(sste, dtype, T, O, I):  # noqa: F811
+    test_linear_fwd_tiles(sste, dtype, T, O, I, HALVES)
+    if dtype == "e4m3":
+        test_largest_activation_keeps_nan(sste, dtype, T, O, I, HALVES)
+
+
+@pytest.mark.parametrize("dtype,T,O,I", [("bf16", 5420, 400, 832), ("bf16", 8150, 448, 768), ("e4m3", 5480, 528, 896), ("e5m2", 5420, 656, 896),
+                                         ("e5m2", 2000, 528, 3072)])
+def test_linear_dgrad_tiles_and_halves(sste, dtype, T, O, I):  # noqa: F811
+    test_linear_dgrad_tiles(sste, dtype, T, O, I, HALVES, HALVES)
+    test_linear_dgrad_ignores_what_lies_between_rows(sste, dtype, T, O, I, HALVES)
+    test_linear_dgrad_act_tiles(sste, dtype, T, O, I, HALVES)
