@@ -153,28 +153,33 @@ __device__ __forceinline__ void flush_slot(const uint8_t* lds, int64_t blk, uint
 // 512 B).  Measured against lanes that read their own slot's weights (16 bytes out of each of 64 lines per load): the matrices of a
 // 12-layer, 768-wide model with float32 dense weights and e4m3 values 339 -> 210 us (1.07 GB, the rate of a plain copy), 36 layers
 // of width 1280 in bf16 1262 -> 1214 us (6.46 GB).
+// Nothing this pass reads or writes but the packed operand is looked at again before the next iteration, so weight and gradient carry the
+// streaming hint both ways (211 -> 186 us and 1219 -> 1129 us; on the gradient alone 202 and 1185, on the weight's stores alone nothing), and a
+// wave of the multi-tensor kernel takes one block, not two (175 and 1049 us = 6.1 TB/s, above the rate of a plain copy: two reads to a write).
+// With both, streams that are contiguous per XCD are slower (181 and 1089), and so is the packed operand with the hint where it is not
+// larger than the cache (187).
 template <bool FP8, bool F32, bool STREAM = false>
 __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ G, int64_t O, int32_t steps, int64_t blk,
                                           int64_t ldw_bytes, int64_t ldg, float alpha, float beta, float val_scale,
                                           uint4* __restrict__ vals, void* __restrict__ meta, int lane, uint8_t* lds) {
   constexpr int NG = FP8 ? 8 : 4, GPR = 4 * NG;          // groups per operand lane; per row of the block
   constexpr int RPL = 64 / GPR, NL = 16 / RPL;           // rows per load, loads
-  const int64_t rb = blk / steps;
+  const int64_t rb = (uint32_t)blk / (uint32_t)steps;    // 2^32 blocks would be 4 T weights
   const int32_t s = (int32_t)(blk - rb * steps);
   const int grp = lane % GPR, r0 = lane / GPR, q = grp / NG, g = grp % NG;
   const int64_t col = ((int64_t)s * GPR + grp) * 4;
   f32x4 gr[NL], wf[NL];
-  uint2 wb[NL];
+  i32x2 wb[NL];
 #pragma unroll
   for (int c = 0; c < NL; c++) {
     const int64_t row = rb * 16 + RPL * c + r0;
     if (row < O) {
-      gr[c] = *(const f32x4*)(G + row * ldg + col);
-      if (F32) wf[c] = *(const f32x4*)(W + row * ldw_bytes + col * 4);
-      else wb[c] = *(const uint2*)(W + row * ldw_bytes + col * 2);
+      gr[c] = __builtin_nontemporal_load((const f32x4*)(G + row * ldg + col));
+      if (F32) wf[c] = __builtin_nontemporal_load((const f32x4*)(W + row * ldw_bytes + col * 4));
+      else wb[c] = __builtin_nontemporal_load((const i32x2*)(W + row * ldw_bytes + col * 2));
     } else {
       gr[c] = wf[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      wb[c] = make_uint2(0, 0);
+      wb[c] = (i32x2){0, 0};
     }
   }
 #pragma unroll
@@ -182,13 +187,14 @@ __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ 
     const int sl = 16 * q + RPL * c + r0;
     const int64_t row = rb * 16 + RPL * c + r0;
     f32x4 w = wf[c];
-    if (!F32) w = (f32x4){u2f(wb[c].x << 16), u2f(wb[c].x & 0xFFFF0000u), u2f(wb[c].y << 16), u2f(wb[c].y & 0xFFFF0000u)};
+    const uint32_t wx = (uint32_t)wb[c][0], wy = (uint32_t)wb[c][1];
+    if (!F32) w = (f32x4){u2f(wx << 16), u2f(wx & 0xFFFF0000u), u2f(wy << 16), u2f(wy & 0xFFFF0000u)};
 #pragma unroll
     for (int e = 0; e < 4; e++) w[e] = w[e] - alpha * gr[c][e];
     uint32_t lo = bf16_rne_pack(w[0], w[1]), hi = bf16_rne_pack(w[2], w[3]);
     if (row < O) {
-      if (F32) *(f32x4*)(W + row * ldw_bytes + col * 4) = w;
-      else *(uint2*)(W + row * ldw_bytes + col * 2) = make_uint2(lo, hi);
+      if (F32) __builtin_nontemporal_store(w, (f32x4*)(W + row * ldw_bytes + col * 4));
+      else __builtin_nontemporal_store((i32x2){(int)lo, (int)hi}, (i32x2*)(W + row * ldw_bytes + col * 2));
     } else {
       lo = hi = 0;                                       // rows past the last one are recorded as zeros, whatever alpha is
     }
@@ -233,37 +239,22 @@ struct UpdateTableItem {
 };
 static_assert(sizeof(UpdateTableItem) == 80, "table item size is part of the C ABI (SSTE_UPDATE_TABLE_ITEM_BYTES)");
 
-// A wave of the multi-tensor kernels takes kBatchRun consecutive global blocks: one table search, then
-// it walks on through the table (items are sorted by first_block; empty items own no block and are
-// stepped over).
-constexpr int kBatchRun = 2;
-
 template <bool FP8, bool F32, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_sgd_project_pack_batch(const UpdateTableItem* __restrict__ table, int n_items, int64_t total_blocks, float alpha) {
   const int lane = threadIdx.x & 63;
-  const int64_t blk0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * kBatchRun;
-  if (blk0 >= total_blocks) return;
-  int lo = 0, hi = n_items - 1;                          // last item whose first_block <= blk0
+  const int64_t blk = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (blk >= total_blocks) return;
+  int lo = 0, hi = n_items - 1;                          // last item whose first_block <= blk: empty items own no block and are stepped over
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
-    if (table[mid].first_block <= blk0) lo = mid;
+    if (table[mid].first_block <= blk) lo = mid;
     else hi = mid - 1;
   }
   __shared__ __align__(16) uint8_t lds[4][kPackSlot];
-  UpdateTableItem it = table[lo];
-  int64_t next_first = lo + 1 < n_items ? table[lo + 1].first_block : total_blocks;
-  for (int b = 0; b < kBatchRun; b++) {
-    const int64_t blk = blk0 + b;
-    if (blk >= total_blocks) break;
-    while (blk >= next_first) {
-      lo++;
-      it = table[lo];
-      next_first = lo + 1 < n_items ? table[lo + 1].first_block : total_blocks;
-    }
-    sgd_block<FP8, F32, STREAM>(it.W, it.G, it.O, it.steps, blk - it.first_block, it.ldw_bytes, it.ldg, alpha, it.beta, it.val_scale,
-                              it.vals, it.meta, lane, lds[threadIdx.x >> 6]);
-  }
+  const UpdateTableItem it = table[lo];
+  sgd_block<FP8, F32, STREAM>(it.W, it.G, it.O, it.steps, blk - it.first_block, it.ldw_bytes, it.ldg, alpha, it.beta, it.val_scale, it.vals, it.meta,
+                              lane, lds[threadIdx.x >> 6]);
 }
 
 template <bool FP8, bool AMAX, bool GAMMA>
@@ -306,6 +297,11 @@ struct PackTableItem {
   int32_t pad;
 };
 static_assert(sizeof(PackTableItem) == 64, "table item size is part of the C ABI (SSTE_PACK_TABLE_ITEM_BYTES)");
+
+// A wave of the multi-tensor kernels takes kBatchRun consecutive global blocks: one table search, then
+// it walks on through the table (items are sorted by first_block; empty items own no block and are
+// stepped over).
+constexpr int kBatchRun = 2;
 
 template <bool FP8, bool STREAM>
 __global__ void __launch_bounds__(256)
@@ -385,7 +381,7 @@ hipError_t launch_sgd_project_pack(void* W, bool w_f32, int64_t O, int64_t I, in
 hipError_t launch_sgd_project_pack_batch(const void* table, int n_items, int64_t total_blocks, bool w_f32, int val_dtype,
                                          float alpha, hipStream_t s) {
   if (n_items == 0 || total_blocks == 0) return hipSuccess;
-  dim3 grid((unsigned)((total_blocks + 4 * kBatchRun - 1) / (4 * kBatchRun))), block(256);
+  dim3 grid((unsigned)((total_blocks + 3) / 4)), block(256);
   const UpdateTableItem* t = (const UpdateTableItem*)table;
   bool fp8 = val_dtype == SSTE_F8E4M3;
   // packed output larger than the 256 MB cache: nobody reads it back from the cache, write it with the streaming hint
