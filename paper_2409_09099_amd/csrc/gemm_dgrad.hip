@@ -40,6 +40,7 @@
 // Which tile runs is decided by a time model fitted to a sweep (dgrad_choice).
 // Epilogue as in the forward GEMM: transposed through LDS, 16-byte streaming stores of bf16 rows.
 #include "common.h"
+#include "gelu_table.h"
 
 #include <stdio.h>
 
@@ -47,6 +48,8 @@
 #include <utility>
 
 namespace sste {
+
+__device__ constexpr GeluTable kGeluGrad = gelu_grad_table();
 
 namespace {
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -96,37 +99,28 @@ __device__ __forceinline__ void zero_pair(f32x16& v, int r) {
 // issue the matrix instruction ahead of the wait.
 __device__ __forceinline__ void settle(f32x16& v) { asm volatile("s_nop 1" : "+v"(v)); }
 
-// Stores a wave's tile with the backward of the activation that produced this layer's input: grad_H = grad_A * GELU'(H), on the bf16
-// gradient just formed (`piece(row, chunk)`: 16 bytes of it) and the stored pre-activation.  The tile's corner is (t0, i0), `rows` tokens
-// of `ch` 16-byte chunks, NIT chunks per lane.  H is requested AHEAD chunks in advance: asked for one by one, each between its bounds
-// check and its use, the loads cost a memory latency each (32768 x 1280 x 5120 e5m2: 380 -> 338 us, 277 without the activation;
-// 16384 x 1024 x 4096 bf16: 181 -> 164; 8192 x 768 x 3072 e4m3: 49 -> 44).
-template <int NIT, class Piece>
-__device__ __forceinline__ void dgrad_store_act(const DgradArgs& a, int64_t t0, int64_t i0, int rows, int ch, int lane, Piece piece) {
-  if (t0 >= a.T || i0 >= a.I) return;
-  constexpr int AHEAD = NIT < 8 ? NIT : 8;
-  const int live_rows = (int)(a.T - t0 < rows ? a.T - t0 : rows), live_cols = (int)(a.I - i0 < 8 * ch ? a.I - i0 : 8 * ch);
-  uint4 h[AHEAD];
-  auto fetch = [&](int it) {                        // a lane outside the matrix reads the tile's first chunk
-    const int c = 64 * it + lane, row = c / ch, chunk = c % ch;
-    const bool live = row < live_rows && 8 * chunk < live_cols;
-    const i32x4 v = __builtin_nontemporal_load((const i32x4*)(a.H + (t0 + (live ? row : 0)) * a.ldh + i0 + (live ? 8 * chunk : 0)));
-    return make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
-  };
+// Which tiles take the activation's derivative from the table (gelu_table.h): those whose lookups are worth the table's 24 KiB.
+template <int WF, int NT>
+constexpr bool dgrad_table() { return WF * NT >= 16; }
+
+// Backward of the activation that produced this layer's input: grad_H = grad_A * GELU'(H), on 16 bytes of the bf16 gradient just formed and
+// of the stored pre-activation.
+template <bool TABLE>
+__device__ __forceinline__ uint4 dgrad_act_piece(const uint8_t* tab, const uint4& v, const uint4& hv) {
+  const uint32_t g[4] = {v.x, v.y, v.z, v.w}, hw[4] = {hv.x, hv.y, hv.z, hv.w};
+  float d[8];
+  if (TABLE) gelu_lookup8(tab, hw, d);
+  if (!TABLE || gelu_not_in_table(hw)) {
 #pragma unroll
-  for (int it = 0; it < AHEAD; it++) h[it] = fetch(it);
-#pragma unroll
-  for (int it = 0; it < NIT; it++) {
-    const int c = 64 * it + lane, row = c / ch, chunk = c % ch;
-    const uint4 v = piece(row, chunk), hv = h[it % AHEAD];
-    if (it + AHEAD < NIT) h[it % AHEAD] = fetch(it + AHEAD);
-    const uint32_t g[4] = {v.x, v.y, v.z, v.w}, hw[4] = {hv.x, hv.y, hv.z, hv.w};
-    uint32_t r[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++)
-      r[e] = bf16_rne_pack(bf16lo_f32(g[e]) * gelu_tanh_grad(bf16lo_f32(hw[e])), bf16hi_f32(g[e]) * gelu_tanh_grad(bf16hi_f32(hw[e])));
-    if (row < live_rows && 8 * chunk < live_cols) store_stream_b128(a.dX + (t0 + row) * a.lddx + i0 + 8 * chunk, make_uint4(r[0], r[1], r[2], r[3]));
+    for (int e = 0; e < 4; e++) {
+      d[2 * e] = gelu_tanh_grad(bf16lo_f32(hw[e]));
+      d[2 * e + 1] = gelu_tanh_grad(bf16hi_f32(hw[e]));
+    }
   }
+  uint32_t r[4];
+#pragma unroll
+  for (int e = 0; e < 4; e++) r[e] = bf16_rne_pack(bf16lo_f32(g[e]) * d[2 * e], bf16hi_f32(g[e]) * d[2 * e + 1]);
+  return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
 // Accumulators of a wave's 32 features x 32 NT tokens: 16 x 16 or 32 x 32 blocks of the matrix instruction.  Register 4 g + r of lane l
@@ -151,6 +145,27 @@ __device__ __forceinline__ void dgrad_store(uint8_t* smem, const DgradArgs& a, c
   const float scale = a.scale;
   auto key = [](int row) { return CH >= 16 ? (row & 15) : (row / (16 / (CH < 16 ? CH : 16))) % CH; };
   auto flip = [](int row) { return M16 ? 0 : (row >> 4) & 1; };
+  // Activation: the table's loads and the first of H's go ahead of the staging writes.  H is requested AHEAD chunks in advance: asked for one by
+  // one, each between its bounds check and its use, the loads cost a memory latency each (32768 x 1280 x 5120 e5m2: 380 -> 338 us,
+  // 277 without the activation; 16384 x 1024 x 4096 bf16: 181 -> 164; 8192 x 768 x 3072 e4m3: 49 -> 44).
+  constexpr bool TABLE = dgrad_table<WF, NT>();
+  constexpr int AHEAD = NIT < 8 ? NIT : 8;
+  uint8_t* const tab = smem + 32 * NT * 64 * WF;
+  const int r0 = ROWS * (KG > 1 ? kg * WF + wave : wave);
+  const int live_rows = (int)(a.T - t0 < 32 * NT ? a.T - t0 : 32 * NT) - r0, live_cols = (int)(a.I - i0 < 8 * CH ? a.I - i0 : 8 * CH);
+  uint4 h[AHEAD];
+  auto fetch = [&](int it) {                        // a lane outside the matrix reads the tile's first chunk
+    const int c = 64 * it + lane, row = c / CH, chunk = c % CH;
+    const bool live = row < live_rows && 8 * chunk < live_cols;
+    const i32x4 v = __builtin_nontemporal_load((const i32x4*)(a.H + (t0 + (live ? r0 + row : 0)) * a.ldh + i0 + (live ? 8 * chunk : 0)));
+    return make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
+  };
+  if (a.H) {
+    if (TABLE) gelu_table_load<WF * KG>(tab, kGeluGrad, KG > 1 ? kg * WF + wave : wave, lane);
+#pragma unroll
+    for (int it = 0; it < AHEAD; it++) h[it] = fetch(it);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   if (KG == 1 || kg == 0) {                       // group 0 holds the sums
 #pragma unroll
     for (int t = 0; t < A::NB; t++)
@@ -166,14 +181,21 @@ __device__ __forceinline__ void dgrad_store(uint8_t* smem, const DgradArgs& a, c
           *(uint2*)(smem + row * (16 * CH) + ((chunk ^ key(row)) * 16) + 8 * ((half & 1) ^ flip(row))) = v;
         }
   }
+  if (TABLE && a.H) wait_vmcnt<0>();
   __syncthreads();
-  const int r0 = ROWS * (KG > 1 ? kg * WF + wave : wave);
   auto piece = [&](int row, int chunk) {
     const uint4 v = *(const uint4*)(smem + (r0 + row) * (16 * CH) + ((chunk ^ key(r0 + row)) * 16));
     return flip(r0 + row) ? make_uint4(v.z, v.w, v.x, v.y) : v;
   };
   if (a.H) {
-    dgrad_store_act<NIT>(a, t0 + r0, i0, ROWS, CH, lane, piece);
+#pragma unroll
+    for (int it = 0; it < NIT; it++) {
+      const int c = 64 * it + lane, row = c / CH, chunk = c % CH;
+      const uint4 v = piece(row, chunk), hv = h[it % AHEAD];
+      if (it + AHEAD < NIT) h[it % AHEAD] = fetch(it + AHEAD);
+      const uint4 r = dgrad_act_piece<TABLE>(tab, v, hv);
+      if (row < live_rows && 8 * chunk < live_cols) store_stream_b128(a.dX + (t0 + r0 + row) * a.lddx + i0 + 8 * chunk, r);
+    }
     return;
   }
 #pragma unroll
@@ -189,7 +211,7 @@ __device__ __forceinline__ void dgrad_store(uint8_t* smem, const DgradArgs& a, c
 template <bool FP8, int WF, int NT, int KG, int NS>
 constexpr int dgrad_smem() {
   constexpr int RING = KG * NS * (32 * WF * (64 + (FP8 ? 16 : 8)) + 32 * NT * 128);
-  constexpr int EPI = 32 * NT * 64 * WF;
+  constexpr int EPI = 32 * NT * 64 * WF + (dgrad_table<WF, NT>() ? GELU_TABLE_BYTES : 0);
   constexpr int RED = (KG - 1) * WF * NT * 4096;
   constexpr int M1 = RING > EPI ? RING : EPI;
   return M1 > RED ? M1 : RED;

@@ -134,6 +134,26 @@ def test_linear_dgrad_act_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     assert bool((out[:, I:] == 7.0).all())
 
 
+# tiles that take the derivative from the table and one that does not
+@pytest.mark.parametrize("dtype,T,O,I,tile", [("bf16", 1100, 1552, 832, "64x64 kg 4"), ("bf16", 771, 200, 2560, "128x128 kg 2"), ("e4m3", 16391, 192, 256, "256x128 kg 1"),
+                                              ("bf16", 10098, 136, 1600, "256x256+256x128 kg 1"), ("e5m2", 5420, 656, 896, "128x128+128x64 kg 1")])
+def test_linear_dgrad_act_every_preactivation(sste, dtype, T, O, I, tile):  # noqa: F811
+    """All bf16 patterns as pre-activation: a correctly rounded product with GELU' (some 1e-6 of its float32 evaluation aside), NaN for
+    infinities and NaN, which leave the other seven values of their 16 bytes alone."""
+    assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith(tile + " ")
+    dY, dys, packed, ws = gaussian_operands(sste, dtype, T, O, I)
+    H = ((torch.arange(T * I, device="cuda") * 40503) % 65536 - 32768).to(torch.int16).view(torch.bfloat16).view(T, I)
+    got = sste.linear_dgrad_act(dY, *packed, I, H, dt(sste, dtype), dys, ws).double()
+    plain = sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws).double()
+    assert bool(got[~H.isfinite()].isnan().all())
+    live = H.abs() <= 1e12                               # the formula cubes it in float32, whose largest value is the cube of 7e12
+    h = torch.where(live, H, 0.0).double()
+    c, k = 0.7978845608028654, 0.044715
+    th = torch.tanh(c * (h + k * h ** 3))
+    want = plain * (0.5 * (1 + th) + torch.where(h.abs() < 100, 0.5 * h * (1 - th * th) * c * (1 + 3 * k * h * h), 0.0))
+    assert bool((((got - want).abs() <= want.abs() * 2.0 ** -8 + plain.abs() * 1e-5) | ~live).all())
+
+
 # every tile of the forward product, with the sste_describe_plan text of its shape.  16 x 16: k-steps dealt to eight waves (19 or 20 of them), fewer k-steps than
 # waves, one token and one k-step, turns of 16 k-steps the last half full; the tiles with groups: an incomplete last round of them
 FWD_TILES = [
