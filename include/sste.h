@@ -414,7 +414,8 @@ int sste_wgrad_plan_override(int mi, int ni, int splits);
  * launched).  op is SSTE_K_FWD, SSTE_K_DGRAD or SSTE_K_WGRAD (below); for the weight gradient the answer is that of a call
  * with its full workspace.  The line starts with the tile, output rows of the kernel x columns ("256x128"; "256x256+256x128"
  * for the two-shape grids; "fused" for the weight gradient without a pre-pass), and goes on with "kg K" (groups of
- * waves that share the contraction out), "r R" (workgroups that fit a CU), for the weight gradient "splits S chunks C",
+ * waves that share the contraction out), "r R" (workgroups that fit a CU), for the weight gradient "splits S chunks C"
+ * ("splits 5/2": five workgroups for every two tiles),
  * and "grid N block M" (of one chunk).  Unknown op or dtype, or a size that the product itself refuses -> ERR_VALUE; NULL text -> ERR_NULL.
  */
 int sste_describe_plan(int op, int64_t T, int64_t O, int64_t I, int dtype, char* text, size_t text_bytes);

@@ -290,6 +290,35 @@ def test_linear_wgrad_two_k_groups_8bit(sste, dtype):  # noqa: F811
     assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))
 
 
+# groups of two to four tiles dealt to a number of workgroups that they do not divide: incomplete last group or not, ragged on both axes
+@pytest.mark.parametrize("dtype,T,O,I,tile,parts", [
+    ("bf16", 11520, 5760, 992, "256x256 kg 1", "8/3"), ("bf16", 13184, 4592, 1936, "256x256 kg 1", "7/4"), ("bf16", 22656, 5952, 528, "256x192 kg 1", "7/2"),
+    ("bf16", 15680, 528, 5440, "192x192 kg 1", "11/4"), ("e4m3", 30464, 5616, 544, "256x192 kg 1", "15/4"), ("e5m2", 32512, 5456, 672, "256x256 kg 1", "15/4"),
+    ("e4m3", 22656, 528, 5952, "192x192 kg 1", "8/3"),
+])
+def test_linear_wgrad_tiles_in_groups(sste, dtype, T, O, I, tile, parts):  # noqa: F811
+    """Equal to the same product in splits, which the oracle holds at smaller sizes, but for the order of the float32 sums."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    dys = xs = 1.0
+    if dtype != "bf16":
+        dys, xs = (1e-5 if dtype == "e4m3" else 1e-7), 0.01
+        dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs)[0]
+    plan = sste.describe_plan("wgrad", T, O, I, dt(sste, dtype))
+    assert plan.startswith(tile + " ") and f" splits {parts} " in plan, plan
+    got = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, dW=torch.full((O, I), 3.0, device="cuda"))
+    assert torch.equal(sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs), got)
+    twice = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, dW=got.clone(), accumulate=True)
+    try:
+        sste.wgrad_plan_override(8, 4, 2)
+        want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    finally:
+        sste.wgrad_plan_override(0, 0, 0)
+    assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))
+    assert torch.allclose(twice, 2.0 * got, rtol=1e-6, atol=1e-6 * float(got.abs().max()))
+
+
 @pytest.mark.parametrize("dtype,T,O,I", [("bf16", 12288, 3880, 168), ("e4m3", 19072, 5744, 80)])
 def test_linear_wgrad_token_chunks(sste, dtype, T, O, I):  # noqa: F811
     """Narrow problems whose sparse operand does not fit the scratch at once: equal to their own parts added up."""
