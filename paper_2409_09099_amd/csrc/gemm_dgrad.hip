@@ -529,8 +529,8 @@ __device__ __forceinline__ void dgrad_tile(uint8_t* smem, const DgradArgs& a, in
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// kernels: one tile shape for the whole grid, or whole rounds of 256 x 256 tiles (workgroups 0 .. n_big - 1) followed by the tiles of
-// the last, partial round as twice as many 256 x 128 tiles, so that the round takes half a tile time on twice the CUs
+// kernels: one tile shape for the whole grid; or 256 x 256 tiles (workgroups 0 .. n_big - 1: all of them, or whole rounds followed by the tiles of
+// the last, partial round as twice as many 256 x 128 tiles, so that the round takes half a tile time on twice the CUs)
 template <bool FP8, bool BF8, bool M16, int WF, int NT, int KG, int NS>
 __global__ void __launch_bounds__(64 * WF * KG, 2)
 k_linear_dgrad(DgradArgs a, int m_tiles) {
@@ -541,19 +541,23 @@ k_linear_dgrad(DgradArgs a, int m_tiles) {
 
 template <bool FP8, bool BF8>
 __global__ void __launch_bounds__(512, 2)
-k_linear_dgrad_dual(DgradArgs a, int m_tiles, int n_big) {
+k_linear_dgrad_dual(DgradArgs a, TileOrder order, int n_big) {
   __shared__ __align__(1024) uint8_t smem[dgrad_smem<FP8, 8, 8, 1, 3>()];
   static_assert(dgrad_smem<FP8, 8, 4, 1, 4>() <= dgrad_smem<FP8, 8, 8, 1, 3>(), "the half tile fits in the full tile's LDS");
   const int bid = blockIdx.x;
   if (bid < n_big) {
     const int logical = xcd_contiguous(bid, n_big);
-    dgrad_tile<FP8, BF8, !FP8, 8, 8, 1, 3>(smem, a, logical % m_tiles, (int64_t)(logical / m_tiles) * 256);
+    int tm, tn;
+    tile_at(order, logical, tm, tn);
+    dgrad_tile<FP8, BF8, !FP8, 8, 8, 1, 3>(smem, a, tm, (int64_t)tn * 256);
   } else {
     const int h = xcd_contiguous(bid - n_big, (int)gridDim.x - n_big);      // half-tile number
     const int tile = n_big + (h >> 1);
-    const int64_t t0 = (int64_t)(tile / m_tiles) * 256 + 128 * (h & 1);
+    int tm, tn;
+    tile_at(order, tile, tm, tn);
+    const int64_t t0 = (int64_t)tn * 256 + 128 * (h & 1);
     if (t0 >= a.T) return;                     // second half of a ragged last token tile: nothing to do
-    dgrad_tile<FP8, BF8, !FP8, 8, 4, 1, 4>(smem, a, tile % m_tiles, t0);
+    dgrad_tile<FP8, BF8, !FP8, 8, 4, 1, 4>(smem, a, tm, t0);
   }
 }
 
@@ -738,9 +742,10 @@ static void launch_dgrad_type(const DgradArgs& a, hipStream_t s) {
     SSTE_LAUNCH(SSTE_K_DGRAD, kernel, dim3((unsigned)(mt * ((a.T + bn - 1) / bn))), dim3(threads), s, a, mt);
   };
   switch (cfg) {
+    case DG_256:
     case DG_DUAL: {
-      const int64_t big = (int64_t)m256 * ((a.T + 255) / 256), rem = big % 256;
-      SSTE_LAUNCH(SSTE_K_DGRAD, (k_linear_dgrad_dual<FP8, BF8>), dim3((unsigned)(big + rem)), dim3(512), s, a, m256, (int)(big - rem));
+      const int64_t big = (int64_t)m256 * ((a.T + 255) / 256), rem = cfg == DG_DUAL ? big % 256 : 0;
+      SSTE_LAUNCH(SSTE_K_DGRAD, (k_linear_dgrad_dual<FP8, BF8>), dim3((unsigned)(big + rem)), dim3(512), s, a, tile_order(m256, (a.T + 255) / 256), (int)(big - rem));
       break;
     }
     case DG_DUAL128: {
@@ -748,7 +753,6 @@ static void launch_dgrad_type(const DgradArgs& a, hipStream_t s) {
       SSTE_LAUNCH(SSTE_K_DGRAD, (k_linear_dgrad_dual128<FP8, BF8>), dim3((unsigned)(2 * tiles - 256)), dim3(256), s, a, m128, 256);
       break;
     }
-    case DG_256: tile(k_linear_dgrad<FP8, BF8, !FP8, 8, 8, 1, 3>, 256, 256, 512); break;
     case DG_256x128: tile(k_linear_dgrad<FP8, BF8, !FP8, 8, 4, 1, 4>, 256, 128, 512); break;
     case DG_128_KG1: tile(k_linear_dgrad<FP8, BF8, false, 4, 4, 1, 3>, 128, 128, 256); break;
     case DG_128_KG2: tile(k_linear_dgrad<FP8, BF8, false, 4, 4, 2, 3>, 128, 128, 512); break;

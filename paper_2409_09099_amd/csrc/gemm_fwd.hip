@@ -14,8 +14,8 @@
 // Tiling: every wave owns a grid of 16 x 16 MFMA tiles (8 x 4 = 128 channels x 64 tokens in the main
 // shape): per sparse MFMA it reads about 540 B of fragments from LDS, inside the LDS read rate of the CU.
 // Six kernels share the operand layouts; a time model fitted to a sweep picks one (fwd_choice):
-//   k_linear_fwd_pipe   software-pipelined 256 x 256 and 128 x 256 tiles, 8 waves, one workgroup per CU;
-//   k_linear_fwd_dual   the same tile code for 256 x 256 and 256 x 128 tiles in one grid, for layers
+//   k_linear_fwd_pipe   software-pipelined 128 x 256 tiles, 8 waves, one workgroup per CU;
+//   k_linear_fwd_dual   the same tile code for 256 x 256 tiles and, in the same grid, 256 x 128 tiles for layers
 //                       whose last round of 256 x 256 tiles would fill at most half of the CUs;
 //   k_linear_fwd_pair   256 x 128 tiles by 4 waves with the same share each, two workgroups per CU;
 //   k_linear_fwd_tile   128 x 128 down to 32 x 32 tiles on the 32 x 32 instruction, with the contraction split over
@@ -987,7 +987,7 @@ k_linear_fwd_pipe(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int
                                           (int64_t)tn * (64 * NI_));
 }
 
-// Two tile shapes in one grid, for layers whose 256 x 256 tiles fill the CUs a whole number of times plus
+// 256 x 256 tiles (n_big all of them), or two tile shapes in one grid, for layers whose 256 x 256 tiles fill the CUs a whole number of times plus
 // a remainder of at most half a round: the first n_big workgroups take 256 x 256 tiles, the rest take
 // the remaining tiles as 256 x 128 halves.  The last round then has twice as many, half as long
 // workgroups instead of leaving more than half of the CUs idle for a full tile time.
@@ -995,18 +995,20 @@ template <bool FP8, bool ZF8, bool AMAX>
 __global__ void __launch_bounds__(512, 1)
 k_linear_fwd_dual(const uint8_t* __restrict__ X, int64_t T, int64_t k_bytes, int64_t ldx_bytes,
                   const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta,
-                  int64_t O, FwdOut out, int m_tiles, int n_big) {
+                  int64_t O, FwdOut out, TileOrder order, int n_big) {
   __shared__ __align__(1024) uint8_t smem[fwd_pipe_smem<FP8, 8, 4>()];
   static_assert(fwd_pipe_smem<FP8, 8, 2>() <= fwd_pipe_smem<FP8, 8, 4>(), "the half tile fits in the full tile's LDS");
   const int bid = blockIdx.x;
   if (bid < n_big) {
     const int logical = xcd_contiguous(bid, n_big);
-    const int tm = logical % m_tiles, tn = logical / m_tiles;
+    int tm, tn;
+    tile_at(order, logical, tm, tn);
     fwd_pipe_tile<FP8, 8, 4, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, (int64_t)tm * 256, (int64_t)tn * 256);
   } else {
     const int h = xcd_contiguous(bid - n_big, (int)gridDim.x - n_big);      // half-tile number
     const int tile = n_big + (h >> 1);
-    const int tm = tile % m_tiles, tn = tile / m_tiles;
+    int tm, tn;
+    tile_at(order, tile, tm, tn);
     const int64_t t0 = (int64_t)tn * 256 + 128 * (h & 1);
     if (t0 >= T) return;                       // second half of a ragged last token tile: nothing to do
     fwd_pipe_tile<FP8, 8, 2, ZF8, AMAX>(smem, X, T, k_bytes, ldx_bytes, vals, meta, O, out, (int64_t)tm * 256, t0);
@@ -1032,7 +1034,7 @@ static void launch_fwd_dual(const void* X, int64_t T, int64_t I, int64_t ldx, co
   dim3 grid((unsigned)(n_big + n_small)), block(512);
   int64_t eb = FP8 ? 1 : 2;
   SSTE_LAUNCH(SSTE_K_FWD, (k_linear_fwd_dual<FP8, ZF8, AMAX>), grid, block, s, (const uint8_t*)X, T, I * eb, ldx * eb,
-              (const uint8_t*)vals, (const uint8_t*)meta, O, out, m_tiles, n_big);
+              (const uint8_t*)vals, (const uint8_t*)meta, O, out, tile_order(m_tiles, n_tiles), n_big);
 }
 
 bool linear_fwd_supported(int64_t T, int64_t I, int64_t ldx, int64_t O, int dtype) {
@@ -1229,12 +1231,12 @@ static void launch_fwd_variant(const void* X, int64_t T, int64_t I, int64_t ldx,
   const int cfg = fwd_choice(FP8, T, O, I);
 #define FT(WM, WN, MT, NT, KG, NS) launch_fwd_tile<FP8, WM, WN, MT, NT, KG, NS, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s)
   switch (cfg) {
+    case FW_256:
     case FW_DUAL: {
-      const int64_t big_tiles = ((O + 255) / 256) * ((T + 255) / 256);
-      launch_fwd_dual<FP8, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, (int)(big_tiles - big_tiles % NUM_CU), s);
+      const int64_t tiles = ((O + 255) / 256) * ((T + 255) / 256);
+      launch_fwd_dual<FP8, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, (int)(cfg == FW_DUAL ? tiles - tiles % NUM_CU : tiles), s);
       break;
     }
-    case FW_256: launch_fwd_pipe<FP8, 8, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
     case FW_128x256: launch_fwd_pipe<FP8, 4, 4, ZF8, AMAX>(X, T, I, ldx, out, vals, meta, O, s); break;
     case FW_256x128: {
       const int m_tiles = (int)((O + 255) / 256), n_tiles = (int)((T + 127) / 128);
