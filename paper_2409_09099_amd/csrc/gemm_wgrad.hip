@@ -4,7 +4,7 @@
 //   1. k_mvue_pack: the estimator is applied once per group of four tokens and the result is written
 //      to the workspace as a packed 2:4 operand in sparse-MFMA fragment order (the format of
 //      include/sste.h with rows = output channels, columns = tokens).  It streams dY once: at about
-//      90 vector instructions per group (bf16; 72 for 8-bit types) the bf16 kernel runs at the rate of a
+//      84 vector instructions per group (bf16; 61 for 8-bit types) the bf16 kernel runs at the rate of a
 //      plain copy, the 8-bit kernel (twice the groups per byte) is bound by the vector pipe.
 //   2. k_wgrad_gemm (large tiles) or k_wgrad_tile (small ones): sparse MFMA GEMM, rows = channels o, columns =
 //      input features i, contraction = tokens.  The packed operand is loaded like the packed weight of the
@@ -44,11 +44,14 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 // 1. estimator -> packed operand.  One workgroup: one k-step (64 / 128 tokens) x BC channels.  A lane works on the two groups of eight
 // consecutive tokens for VB bytes of channels, so that each of its results is a whole metadata byte and a 4-byte (bf16: 8-byte) piece
 // of the packed values.  Measured against one group per lane in four rows of 16 bytes: e5m2 32768 x 5120 83 -> 76 us, e4m3 3200 x 1552
-// 8.4 -> 6.6, bf16 16384 x 4096 41.2 -> 40.2.
+// 8.4 -> 6.6, bf16 16384 x 4096 41.2 -> 40.2.  The 8-bit kernel is bound by its vector instructions: 73 a group -> 61 (counts of the recorded
+// positions from sign bits by byte permutes, one comparison and for e4m3 a minimum less, the shared first step of the hash, fixed distances
+// in the staging LDS): 32768 x 5120 78 -> 65 us (e4m3), 78 -> 71 (e5m2), 32768 x 3840 59 -> 51, 32768 x 1280 23.4 -> 20.8.
 template <bool FP8, int BC, int VB>
 constexpr int mvue_threads() { return (FP8 ? 128 : 64) / 8 * BC * (FP8 ? 1 : 2) / VB; }
 
-template <bool FP8, bool BF8, int BC, int VB>
+// LOW: every group id is below 2^32.  Ids that differ in their last bits then share the first step of the hash but for those bits.
+template <bool FP8, bool BF8, int BC, int VB, bool LOW>
 __global__ void __launch_bounds__((mvue_threads<FP8, BC, VB>()))
 k_mvue_pack(const uint8_t* __restrict__ dY, int64_t T, int64_t O, int64_t lddy_bytes, RngKey key,
             uint8_t* __restrict__ vals, uint8_t* __restrict__ meta) {
@@ -92,15 +95,20 @@ k_mvue_pack(const uint8_t* __restrict__ dY, int64_t T, int64_t O, int64_t lddy_b
   const uint64_t gid_a = (key.first_group + (uint64_t)(s * (KS / 4) + 2 * kp)) * (uint64_t)O + (uint64_t)och, gid_b = gid_a + (uint64_t)O;
   const uint32_t hi_a = (uint32_t)(gid_a >> 32) * 0x9E3779B9u, hi_b = (uint32_t)(gid_b >> 32) * 0x9E3779B9u;
   const uint32_t lo_a = (uint32_t)gid_a ^ key.k0, lo_b = (uint32_t)gid_b ^ key.k0;
+  const uint32_t fold_a = lo_a ^ (lo_a >> 17), fold_b = lo_b ^ (lo_b >> 17);
   const int q = kp / PPQ, gp = kp % PPQ;
+  // the lane's channels are consecutive rows of one block: its first value and metadata byte, and the rows follow at fixed distances
+  static_assert(16 % CH == 0, "channels of a lane inside a block");
+  const int blk = oc * CH / 16, row0 = 16 * q + oc * CH % 16;
+  uint8_t* const slot0 = sV + blk * VPITCH + row0 * 16 + (FP8 ? 4 : 8) * gp;
+  uint8_t* const meta0 = sM + blk * MPITCH + row0 * PPQ + gp;
   // 8-bit: the four token rows' dwords of four channels, transposed 4 x 4 bytes at a time (eight byte permutes
   // for four groups): grp[h][k] holds channel 4 (e / 4) + k with the group's first token in byte 0
   uint32_t grp[2][4] = {};
 #pragma unroll
   for (int e = 0; e < CH; e++) {
-    const uint32_t xa = draw_u32_mixed((lo_a ^ (uint32_t)e) + hi_a, key.k1), xb = draw_u32_mixed((lo_b ^ (uint32_t)e) + hi_b, key.k1);
-    const int c = oc * CH + e, row = 16 * q + (c & 15);                // channel inside the tile; row of its block
-    uint8_t* const slot = sV + (c >> 4) * VPITCH + row * 16;
+    const uint32_t xa = LOW ? draw_u32_folded(fold_a ^ (uint32_t)e, key.k1) : draw_u32_mixed((lo_a ^ (uint32_t)e) + hi_a, key.k1);
+    const uint32_t xb = LOW ? draw_u32_folded(fold_b ^ (uint32_t)e, key.k1) : draw_u32_mixed((lo_b ^ (uint32_t)e) + hi_b, key.k1);
     uint32_t m;
     if (FP8) {
       if ((e & 3) == 0) {
@@ -115,17 +123,17 @@ k_mvue_pack(const uint8_t* __restrict__ dY, int64_t T, int64_t O, int64_t lddy_b
           grp[h][3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
         }
       }
-      *(uint32_t*)(slot + 4 * gp) = mvue_pair_f8<BF8>(grp[0][e & 3], grp[1][e & 3], xa, xb, m);
+      *(uint32_t*)(slot0 + 16 * e) = mvue_pair_f8<BF8>(grp[0][e & 3], grp[1][e & 3], xa, xb, m);
     } else {
       const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
       uint2 v;
       uint32_t ma, mb;
       v.x = mvue_group_bf16(__builtin_amdgcn_perm(rdy[1][e >> 1], rdy[0][e >> 1], sel), __builtin_amdgcn_perm(rdy[3][e >> 1], rdy[2][e >> 1], sel), xa, ma);
       v.y = mvue_group_bf16(__builtin_amdgcn_perm(rdy[5][e >> 1], rdy[4][e >> 1], sel), __builtin_amdgcn_perm(rdy[7][e >> 1], rdy[6][e >> 1], sel), xb, mb);
-      *(uint2*)(slot + 8 * gp) = v;
+      *(uint2*)(slot0 + 16 * e) = v;
       m = 0xEEu - (ma + (mb << 4));
     }
-    sM[(c >> 4) * MPITCH + row * PPQ + gp] = (uint8_t)m;
+    meta0[PPQ * e] = (uint8_t)m;
   }
   __syncthreads();
 
@@ -150,15 +158,21 @@ static void launch_mvue_pack(const void* dY, int64_t T, int64_t O, int64_t lddy,
   // wider rows per lane.  Crossover near 2^25 elements (bf16 16384 x 1280: 16.9 against 17.4 us, 16384 x 4096: 42.9 against 40.2;
   // e4m3 3200 x 1552: 6.6 against 7.6, 32768 x 3840: equal, 32768 x 5120: 84 against 76).
   const bool small = !product_reaches(T, O, 1ll << 25);
-#define MP_CASE(F8, B8, BC, VB)                                                                                          \
+  const bool low = (unsigned __int128)(key.first_group + (uint64_t)(T / 4)) * (uint64_t)O <= 0x100000000ull;
+#define MP_LAUNCH(F8, B8, BC, VB, LOW)                                                                                   \
   do {                                                                                                                   \
     const dim3 grid((unsigned)((O + BC - 1) / BC), (unsigned)(T / ks)), block(mvue_threads<F8, BC, VB>());               \
     if (timed_kind >= 0)                                                                                                 \
-      SSTE_LAUNCH(timed_kind, (k_mvue_pack<F8, B8, BC, VB>), grid, block, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
+      SSTE_LAUNCH(timed_kind, (k_mvue_pack<F8, B8, BC, VB, LOW>), grid, block, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
                   (uint8_t*)vals, (uint8_t*)meta);                                                                       \
     else                                                                                                                 \
-      hipLaunchKernelGGL((k_mvue_pack<F8, B8, BC, VB>), grid, block, 0, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
+      hipLaunchKernelGGL((k_mvue_pack<F8, B8, BC, VB, LOW>), grid, block, 0, s, (const uint8_t*)dY, T, O, lddy*(F8 ? 1 : 2), key, \
                          (uint8_t*)vals, (uint8_t*)meta);                                                                \
+  } while (0)
+#define MP_CASE(F8, B8, BC, VB)                   \
+  do {                                            \
+    if (low) MP_LAUNCH(F8, B8, BC, VB, true);     \
+    else MP_LAUNCH(F8, B8, BC, VB, false);        \
   } while (0)
 #define MP_TYPE(BC, VB)                                          \
   do {                                                           \
@@ -170,6 +184,7 @@ static void launch_mvue_pack(const void* dY, int64_t T, int64_t O, int64_t lddy,
   else MP_TYPE(128, 8);
 #undef MP_TYPE
 #undef MP_CASE
+#undef MP_LAUNCH
 }
 
 hipError_t launch_mvue_materialize(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, RngKey key,
