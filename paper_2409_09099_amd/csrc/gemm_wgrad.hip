@@ -20,6 +20,7 @@
 // kernel (gemm_wgrad_fused.hip) is kept for small problems, where one launch and no workspace matter more.
 #include "common.h"
 #include "mvue_device.h"
+#include "wgrad_deal.h"
 
 #include <atomic>
 #include <mutex>
@@ -206,23 +207,6 @@ hipError_t launch_mvue_materialize(const void* dY, int64_t T, int64_t O, int64_t
 // reads below -- 4 (8) consecutive token rows x 16 features per 16 lanes, the four lane quarters 8 (16)
 // rows apart -- off each other's banks.
 
-// How the k-steps of the tiles are dealt to workgroups.  `members` tiles, one from each of as many equal runs of `groups` tiles, make a group,
-// whose k-steps laid end to end are cut at bound[0 .. parts] and worked off by `parts` workgroups.  One member: splits of the token axis.
-// Several: the number of workgroups per tile is a fraction, so that 100 tiles keep 250 of 256 CUs busy (five workgroups for every two)
-// where two each would keep 200.  A workgroup whose part crosses from one member into the next does two segments; the segments of a
-// member are summed in k order.  Workgroups of the same part number run next to each other and read the same k-steps, as with splits.
-// On 120 random problems that the plan deals so, the whole weight gradient against splits: 5.8 % faster on the geometric mean, 5 % slower at
-// worst, six by more than 1 %.  32768 x 5120 x 1280 e4m3: product 127 -> 114.5 us, the sum of three partials per tile for two 13 -> 17;
-// 16384 x 1280 x 5120 bf16: 134 -> 121 and 13 -> 18.  Inside a training step, where the chip holds a lower clock, half of that is left.  Groups
-// of five to eight tiles lose the shared reads again (seventeen workgroups for seven tiles: up to 10 % slower).  Adding a tile's segments
-// up in the workgroup that ends last instead would leave the reading to one CU per tile, at an eighth of what all of them draw.
-constexpr int DEAL_MEMBERS = 4, DEAL_PARTS = 32;
-struct WgradDeal {
-  int members, parts, groups;
-  uint32_t segments;                      // of member m: bits 4 m .. 4 m + 3 (one member: not used, it has `parts`)
-  int bound[DEAL_PARTS + 1];
-  int first[DEAL_MEMBERS];                // the part that holds a member's first k-step
-};
 // The tile order: channel tiles or feature tiles run fastest.
 struct WgradTiles {
   int m_tiles, n_tiles, features_fastest;
@@ -782,50 +766,6 @@ static double wgrad_model_us(const WgradShape& w, int64_t O, int64_t I, int64_t 
   return t;
 }
 
-// A group of `members` tiles dealt to `parts` workgroups so that each takes the same time, a segment costing F and its k-steps; false
-// where a segment would be too short to be worth its F.
-static bool deal_group(WgradDeal& d, double f, double step, int64_t steps, int members, int parts, int groups) {
-  constexpr double SHORTEST = 4.0;                            // k-steps
-  d = WgradDeal{};
-  d.members = members;
-  d.parts = parts;
-  d.groups = groups;
-  const double share = ((double)(members * steps) * step + (double)(parts + members - 1) * f) / (double)parts;
-  double at = 0.0;
-  for (int c = 0; c < parts; c++) {
-    double left = share;
-    while (left > f + SHORTEST * step && at < (double)(members * steps)) {
-      const double member_end = (double)steps * (double)((int64_t)(at / (double)steps) + 1), take = (left - f) / step;
-      if (at + take > member_end - SHORTEST) {                // up to the member's end
-        left -= f + (member_end - at) * step;
-        at = member_end;
-      } else {
-        at = (double)(int64_t)(at + take + 0.5);
-        left = 0.0;
-      }
-    }
-    d.bound[c + 1] = (int)at;
-  }
-  d.bound[parts] = (int)(members * steps);
-  for (int m = 0; m < members; m++) {
-    int segments = 0;
-    for (int c = 0; c < parts; c++) {
-      const int64_t a = m * steps > d.bound[c] ? m * steps : d.bound[c], b = (m + 1) * steps < d.bound[c + 1] ? (m + 1) * steps : d.bound[c + 1];
-      if (a >= b) continue;
-      if (!segments) d.first[m] = c;
-      else if (c != d.first[m] + segments) return false;
-      segments++;
-    }
-    if (segments > 15) return false;
-    d.segments |= (uint32_t)segments << (4 * m);
-  }
-  return true;
-}
-static int most_segments(const WgradDeal& d) {
-  int most = 0;
-  for (int m = 0; m < d.members; m++) most = (int)((d.segments >> (4 * m)) & 15u) > most ? (int)((d.segments >> (4 * m)) & 15u) : most;
-  return most;
-}
 static double dealt_model_us(const WgradShape& w, const WgradDeal& d, int64_t O, int64_t I, int64_t steps) {
   const double step = w.lat > w.thr ? w.lat : w.thr, out_us = (double)O * (double)I * 4.0 / 5e6;
   double longest = 0.0, planes = 0.0;
