@@ -325,8 +325,10 @@ float sste_amax_history_push(sste_amax_history* h, float amax, float format_max)
  *                 aligned.  Large problems keep the sparsified operand there (packed, about 0.56 x the
  *                 bytes of dY) next to the partial sums of the token-axis splits, which are reduced in
  *                 a fixed order, so the result is bitwise reproducible from run to run.  May be NULL
- *                 when that size is 0.  Problems with T < 2048, O < 256 or I < 256 also run with less
- *                 (or NULL, or misaligned), at the speed of the fused kernel.
+ *                 when that size is 0.  The size changes from version to version: ask this one.  Problems with
+ *                 T < 2048, O < 256 or I < 256 also run with less (or NULL, or misaligned), at the speed of the
+ *                 fused kernel; others whose plan deals tiles in groups ("splits 5/2" in sste_describe_plan) also
+ *                 with the size of plain splits, the sums of a result's parts then in another order.
  */
 int sste_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, float dy_scale,
                       const void* X, int64_t I, int64_t ldx, float x_scale,

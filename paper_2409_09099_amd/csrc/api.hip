@@ -515,7 +515,7 @@ int sste_linear_wgrad_noalloc(const void* dY, int64_t T, int64_t O, int64_t lddy
   float scale = dy_scale * x_scale;
   if (is_8bit(dtype)) scale *= 2.0f;            // the sparsified 8-bit operand is stored halved
   return hip_status(launch_linear_wgrad(dY, T, O, lddy, dtype, X, I, ldx, scale, derive_key(seed, offset), dW, lddw, accumulate, ws,
-                                        (hipStream_t)hip_stream),
+                                        (size_t)SSTE_NOALLOC_SCRATCH_BYTES, (hipStream_t)hip_stream),
                     "linear_wgrad_noalloc launch");
 }
 
@@ -543,6 +543,7 @@ int sste_linear_wgrad_at(const void* dY, int64_t T, int64_t O, int64_t lddy, int
   st = check_first_token("linear_wgrad", first_token, T, O);
   if (st != SSTE_OK) return st;
   size_t need = sste_wgrad_workspace_bytes(T, O, I, dtype);
+  if (workspace && workspace_bytes < need) need = wgrad_least_workspace_bytes(T, O, I, dtype);
   // a short or narrow problem given no workspace, too small or a misaligned one runs the fused kernel, which needs none (the same function
   // of its arguments, slower where the packed path was the choice)
   if ((workspace_bytes < need || !workspace || !aligned16(workspace)) && (T < 2048 || O < 256 || I < 256)) need = 0, workspace = nullptr;
@@ -556,7 +557,7 @@ int sste_linear_wgrad_at(const void* dY, int64_t T, int64_t O, int64_t lddy, int
   RngKey key = derive_key(seed, offset);
   key.first_group = (uint64_t)(first_token / 4);
   return hip_status(launch_linear_wgrad(dY, T, O, lddy, dtype, X, I, ldx, scale, key, dW, lddw, accumulate,
-                                        workspace, (hipStream_t)hip_stream),
+                                        workspace, workspace_bytes, (hipStream_t)hip_stream),
                     "linear_wgrad launch");
 }
 

@@ -265,6 +265,7 @@ hipError_t launch_linear_fwd_act(const void* X, int64_t T, int64_t I, int64_t ld
                                  int a_dtype, float a_inv_scale, float* amax_out, hipStream_t s);
 bool linear_fwd_supported(int64_t T, int64_t I, int64_t ldx, int64_t O, int dtype);
 size_t wgrad_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype);
+size_t wgrad_least_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype);
 bool linear_wgrad_supported(int64_t T, int64_t O, int64_t I, int64_t ldx, int dtype);
 bool wgrad_plan_override(int mi, int ni, int splits);
 // sste_describe_plan's line for a problem that the product accepts
@@ -274,6 +275,6 @@ void describe_wgrad(int64_t T, int64_t O, int64_t I, int dtype, char* text, size
 void* noalloc_scratch(hipError_t* err);   // this GPU's copy of the library's static scratch array
 hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X,
                                int64_t I, int64_t ldx, float scale, RngKey key, float* dW, int64_t lddw,
-                               int accumulate, void* ws, hipStream_t s);
+                               int accumulate, void* ws, size_t ws_bytes, hipStream_t s);
 
 }  // namespace sste

@@ -807,7 +807,8 @@ bool wgrad_plan_override(int mi, int ni, int splits) {
   return true;
 }
 
-static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
+// deals: tiles may be dealt in groups.
+static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype, bool deals) {
   WgradPlan p{};
   const bool fp8 = dtype != SSTE_BF16;
   const int ks = fp8 ? 128 : 64;
@@ -864,7 +865,7 @@ static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
   const size_t operand_bytes = vals_bytes + meta_bytes;
   const bool fits = operand_bytes + c.partial_bytes <= SSTE_NOALLOC_SCRATCH_BYTES;
   for (int k = WG_256x256; k <= WG_256x192; k++) {
-    if (!long_wide || fs || (fshape >= 0 && k != fshape)) continue;
+    if (!deals || !long_wide || fs || (fshape >= 0 && k != fshape)) continue;
     const int64_t tiles = ((O + tab[k].bm - 1) / tab[k].bm) * ((I + tab[k].bn - 1) / tab[k].bn);
     if (tiles >= NUM_CU) continue;
     for (int members = 2; members <= DEAL_MEMBERS; members++) {
@@ -897,10 +898,11 @@ static WgradPlan make_wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
 }
 
 // The plan of a problem, kept per thread for the last few problems asked for (a call asks several times, and a layer calls again).
-static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
+static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype, bool deals = true) {
   struct Entry {
     int64_t T, O, I;
     int dtype, shape, splits;
+    bool deals;
     WgradPlan plan;
     bool used;
   };
@@ -908,10 +910,10 @@ static WgradPlan wgrad_plan(int64_t T, int64_t O, int64_t I, int dtype) {
   static thread_local unsigned oldest = 0;
   const int shape = g_force_shape, splits = g_force_splits;
   for (const Entry& e : cache)
-    if (e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits) return e.plan;
+    if (e.used && e.T == T && e.O == O && e.I == I && e.dtype == dtype && e.shape == shape && e.splits == splits && e.deals == deals) return e.plan;
   Entry& e = cache[oldest];
   oldest = (oldest + 1) % 16;
-  e = Entry{T, O, I, dtype, shape, splits, make_wgrad_plan(T, O, I, dtype), true};
+  e = Entry{T, O, I, dtype, shape, splits, deals, make_wgrad_plan(T, O, I, dtype, deals), true};
   return e.plan;
 }
 
@@ -1011,6 +1013,15 @@ size_t wgrad_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype) {
   return wgrad_plan(T, O, I, dtype).bytes();
 }
 
+// What a call needs at least: where the plan deals tiles in groups and a workspace for that is missing, the splits it would take otherwise, whose
+// partial sums may be fewer.
+size_t wgrad_least_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype) {
+  const WgradPlan p = wgrad_plan(T, O, I, dtype);
+  if (p.deal.members <= 1) return p.bytes();
+  const size_t splits = wgrad_plan(T, O, I, dtype, false).bytes();
+  return splits < p.bytes() ? splits : p.bytes();
+}
+
 bool linear_wgrad_supported(int64_t T, int64_t O, int64_t I, int64_t ldx, int dtype) {
   int64_t eb = dtype != SSTE_BF16 ? 1 : 2;
   if (product_reaches(O / 128 + 1, I / 128 + 1, 0x80000000ll / 32)) return false;
@@ -1021,7 +1032,7 @@ bool linear_wgrad_supported(int64_t T, int64_t O, int64_t I, int64_t ldx, int dt
 
 hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t lddy, int dtype, const void* X,
                                int64_t I, int64_t ldx, float scale, RngKey key, float* dW, int64_t lddw,
-                               int accumulate, void* ws, hipStream_t s) {
+                               int accumulate, void* ws, size_t ws_bytes, hipStream_t s) {
   if (O == 0 || I == 0) return hipSuccess;
   bool fp8 = dtype != SSTE_BF16;
   int ks = fp8 ? 128 : 64, eb = fp8 ? 1 : 2;
@@ -1034,7 +1045,8 @@ hipError_t launch_linear_wgrad(const void* dY, int64_t T, int64_t O, int64_t ldd
     }
     return hipGetLastError();
   }
-  const WgradPlan p = wgrad_plan(T, O, I, dtype);
+  WgradPlan p = wgrad_plan(T, O, I, dtype);
+  if (p.deal.members > 1 && ws_bytes < p.bytes()) p = wgrad_plan(T, O, I, dtype, false);
   if (!p.packed || !ws || product_reaches(T, ldx, (1ll << 31) / eb)) return launch_wgrad_fused(dY, T, O, lddy, dtype, X, I, ldx, key, scale, accumulate, dW, lddw, s);
   uint8_t* const vals = (uint8_t*)ws;
   uint8_t* const meta = vals + p.vals_bytes;

@@ -31,6 +31,7 @@ bool linear_fwd_supported(int64_t T, int64_t I, int64_t ldx, int64_t O, int dtyp
   return true;
 }
 size_t wgrad_workspace_bytes(int64_t T, int64_t O, int64_t I, int) { return (size_t)T * (size_t)O + (size_t)O * (size_t)I * 16; }   // unsigned: wraps, no overflow
+size_t wgrad_least_workspace_bytes(int64_t T, int64_t O, int64_t I, int dtype) { return wgrad_workspace_bytes(T, O, I, dtype) / 2; }
 bool linear_wgrad_supported(int64_t, int64_t, int64_t, int64_t, int) { return true; }
 bool wgrad_plan_override(int mi, int ni, int splits) {
   return ((mi == 0 && ni == 0) || (mi == 8 && ni == 4) || (mi == 6 && ni == 3) || (mi == 8 && ni == 3)) && splits >= 0 && splits <= 32;
@@ -39,5 +40,5 @@ void describe_fwd(int64_t, int64_t, int64_t, int, char*, size_t) { reached("desc
 void describe_dgrad(int64_t, int64_t, int64_t, int, char*, size_t) { reached("describe_dgrad"); }
 void describe_wgrad(int64_t, int64_t, int64_t, int, char*, size_t) { reached("describe_wgrad"); }
 void* noalloc_scratch(hipError_t*) { reached("noalloc_scratch"); }
-hipError_t launch_linear_wgrad(const void*, int64_t, int64_t, int64_t, int, const void*, int64_t, int64_t, float, RngKey, float*, int64_t, int, void*, hipStream_t) { reached("linear_wgrad"); }
+hipError_t launch_linear_wgrad(const void*, int64_t, int64_t, int64_t, int, const void*, int64_t, int64_t, float, RngKey, float*, int64_t, int, void*, size_t, hipStream_t) { reached("linear_wgrad"); }
 }  // namespace sste

@@ -319,6 +319,31 @@ def test_linear_wgrad_tiles_in_groups(sste, dtype, T, O, I, tile, parts):  # noq
     assert torch.allclose(twice, 2.0 * got, rtol=1e-6, atol=1e-6 * float(got.abs().max()))
 
 
+# the same with a workspace that holds plain splits only: (tile and splits of the plan without groups)
+@pytest.mark.parametrize("dtype,T,O,I,mi,ni,splits", [("bf16", 13184, 4592, 1936, 8, 3, 1), ("bf16", 11520, 5760, 992, 8, 4, 2), ("e5m2", 32512, 5456, 672, 8, 4, 3)])
+def test_linear_wgrad_groups_without_their_workspace(sste, dtype, T, O, I, mi, ni, splits):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(4)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    dys = xs = 1.0
+    if dtype != "bf16":
+        dys, xs = 1e-7, 0.01
+        dY, X = sste.cast_fp8(dY, dys, dt(sste, dtype))[0], sste.cast_fp8(X, xs)[0]
+    assert "/" in sste.describe_plan("wgrad", T, O, I, dt(sste, dtype))
+    full = sste.wgrad_workspace_bytes(T, O, I, dt(sste, dtype))
+    try:
+        sste.wgrad_plan_override(mi, ni, splits)
+        plain = sste.wgrad_workspace_bytes(T, O, I, dt(sste, dtype))
+        want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs)
+    finally:
+        sste.wgrad_plan_override(0, 0, 0)
+    assert plain < full
+    for size in (plain, full - 1):
+        assert torch.equal(sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")), want)
+    with pytest.raises(sste.SsteError, match="workspace"):
+        sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(plain - 1, dtype=torch.uint8, device="cuda"))
+
+
 @pytest.mark.parametrize("dtype,T,O,I", [("bf16", 12288, 3880, 168), ("e4m3", 19072, 5744, 80)])
 def test_linear_wgrad_token_chunks(sste, dtype, T, O, I):  # noqa: F811
     """Narrow problems whose sparse operand does not fit the scratch at once: equal to their own parts added up."""
