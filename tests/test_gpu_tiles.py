@@ -344,6 +344,24 @@ def test_linear_wgrad_groups_without_their_workspace(sste, dtype, T, O, I, mi, n
         sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, workspace=torch.empty(plain - 1, dtype=torch.uint8, device="cuda"))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
+@pytest.mark.parametrize("T,O,I,packed", [(256, 64, 64, False), (4096, 512, 512, True)])
+def test_linear_wgrad_keeps_nan(sste, dtype, T, O, I, packed):  # noqa: F811
+    """A NaN in a group of four tokens that holds another non-zero element makes NaN of its channel's gradient, wherever it stands."""
+    assert sste.describe_plan("wgrad", T, O, I, dt(sste, dtype)).startswith("fused") != packed
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1)
+    if dtype != "bf16":
+        X = sste.cast_fp8(X, 0.0125)[0]
+    one = {"bf16": 0x3A80, "e4m3": 0x30, "e5m2": 0x30}[dtype]
+    groups = [[one * bool(others >> k & 1) for k in range(4)] for others in range(1, 16)]
+    cases = [g[:p] + [-1] + g[p + 1:] for g in groups for p in range(4) if any(g[:p] + g[p + 1:])] + [[-1] * 4]
+    dY = torch.zeros((T, O), dtype=torch.int16 if dtype == "bf16" else torch.uint8, device="cuda")
+    for c, g in enumerate(cases):                     # channel c, the c-th group of tokens
+        dY[4 * c:4 * c + 4, c] = torch.tensor([(0x7FC0 if dtype == "bf16" else 0x7F) if v < 0 else v for v in g], device="cuda")
+    got = sste.linear_wgrad(dY.view(torch.bfloat16) if dtype == "bf16" else dY, X, 3, 4, dt(sste, dtype))
+    assert len(cases) <= O and bool(got[:len(cases)].isnan().all()) and bool((got[len(cases):] == 0).all())
+
+
 @pytest.mark.parametrize("dtype,T,O,I", [("bf16", 12288, 3880, 168), ("e4m3", 19072, 5744, 80)])
 def test_linear_wgrad_token_chunks(sste, dtype, T, O, I):  # noqa: F811
     """Narrow problems whose sparse operand does not fit the scratch at once: equal to their own parts added up."""
