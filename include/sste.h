@@ -266,7 +266,9 @@ int sste_linear_fwd_ex(const void* X, int64_t T, int64_t I, int64_t ldx, int dty
  *
  * act: SSTE_ACT_GELU_TANH, 0.5 h (1 + tanh(sqrt(2 / pi) (h + 0.044715 h^3))) -- the paper does not name the
  * activation; this is the one of the GPT-2 models whose layer shapes its experiments use.  Its derivative
- * is the analytic one.  float32 arithmetic with the hardware's exp2 / reciprocal (about 1e-6 absolute).
+ * is the analytic one.  float32 arithmetic with the hardware's exp2 / reciprocal; large tiles take the derivative from a table instead, rounded
+ * from float64 for 2^-21 <= |h| < 8, with 1/2 below and the last entries (1 to within 1e-19, 0 likewise) above.  Either way about 1e-6 absolute, 1 or 0 for
+ * every large finite h, and NaN for an infinite or NaN h, which leaves its neighbours alone.
  * Everything not listed is as in sste_linear_fwd / sste_linear_dgrad (A takes the role of Z: T x O, lda).
  */
 enum { SSTE_ACT_NONE = 0, SSTE_ACT_GELU_TANH = 1 };

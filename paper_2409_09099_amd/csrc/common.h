@@ -104,12 +104,13 @@ __device__ __forceinline__ float gelu_sigmoid(float x, float x2) {
   return __builtin_amdgcn_rcpf(1.0f + e);
 }
 __device__ __forceinline__ float gelu_tanh(float x) { return x * gelu_sigmoid(x, x * x); }
-// d/dx: s + x s (1 - s) * 2 du/dx, du/dx = sqrt(2/pi) (1 + 3 * 0.044715 x^2)
+// d/dx: s + x s (1 - s) * 2 du/dx, du/dx = sqrt(2/pi) (1 + 3 * 0.044715 x^2).  1 or 0 for every large finite x: s (1 - s) is 0 there, x^2 stops short of
+// an infinity and x goes to the zero first.  NaN for infinities and NaN.
 __device__ __forceinline__ float gelu_tanh_grad(float x) {
-  const float x2 = x * x;
+  const float x2 = __builtin_fminf(x * x, 1e30f);
   const float s = gelu_sigmoid(x, x2);
   const float q = __builtin_fmaf(x2, 0.2140644488f, 1.5957691216f);       // 2 sqrt(2/pi) (1 + 0.134145 x^2)
-  return __builtin_fmaf(x * q, __builtin_fmaf(-s, s, s), s);
+  return __builtin_fmaf(x * __builtin_fmaf(-s, s, s), q, s);
 }
 __device__ __forceinline__ float bf16lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16hi_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }

@@ -109,8 +109,10 @@ template <bool TABLE>
 __device__ __forceinline__ uint4 dgrad_act_piece(const uint8_t* tab, const uint4& v, const uint4& hv) {
   const uint32_t g[4] = {v.x, v.y, v.z, v.w}, hw[4] = {hv.x, hv.y, hv.z, hv.w};
   float d[8];
-  if (TABLE) gelu_lookup8(tab, hw, d);
-  if (!TABLE || gelu_not_in_table(hw)) {
+  if (TABLE) {
+    gelu_lookup8(tab, hw, d);
+    if (gelu_not_in_table(hw)) gelu_mark_nan8(hw, d);
+  } else {
 #pragma unroll
     for (int e = 0; e < 4; e++) {
       d[2 * e] = gelu_tanh_grad(bf16lo_f32(hw[e]));

@@ -138,15 +138,16 @@ def test_linear_dgrad_act_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
 @pytest.mark.parametrize("dtype,T,O,I,tile", [("bf16", 1100, 1552, 832, "64x64 kg 4"), ("bf16", 771, 200, 2560, "128x128 kg 2"), ("e4m3", 16391, 192, 256, "256x128 kg 1"),
                                               ("bf16", 10098, 136, 1600, "256x256+256x128 kg 1"), ("e5m2", 5420, 656, 896, "128x128+128x64 kg 1")])
 def test_linear_dgrad_act_every_preactivation(sste, dtype, T, O, I, tile):  # noqa: F811
-    """All bf16 patterns as pre-activation: a correctly rounded product with GELU' (some 1e-6 of its float32 evaluation aside), NaN for
-    infinities and NaN, which leave the other seven values of their 16 bytes alone."""
+    """All bf16 patterns as pre-activation: a correctly rounded product with GELU' (some 1e-6 of its float32 evaluation aside), also for the largest
+    finite ones; NaN for infinities and NaN, which leave the other values of their 16 bytes alone."""
     assert sste.describe_plan("dgrad", T, O, I, dt(sste, dtype)).startswith(tile + " ")
     dY, dys, packed, ws = gaussian_operands(sste, dtype, T, O, I)
     H = ((torch.arange(T * I, device="cuda") * 40503) % 65536 - 32768).to(torch.int16).view(torch.bfloat16).view(T, I)
-    got = sste.linear_dgrad_act(dY, *packed, I, H, dt(sste, dtype), dys, ws).double()
-    plain = sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws).double()
-    assert bool(got[~H.isfinite()].isnan().all())
-    live = H.abs() <= 1e12                               # the formula cubes it in float32, whose largest value is the cube of 7e12
+    live = H.isfinite()
+    got16 = sste.linear_dgrad_act(dY, *packed, I, H, dt(sste, dtype), dys, ws)
+    alone = sste.linear_dgrad_act(dY, *packed, I, torch.where(live, H, 0.0), dt(sste, dtype), dys, ws)
+    got, plain = got16.double(), sste.linear_dgrad(dY, *packed, I, dt(sste, dtype), dys, ws).double()
+    assert bool(got[~live].isnan().all()) and torch.equal(got16[live], alone[live])
     h = torch.where(live, H, 0.0).double()
     c, k = 0.7978845608028654, 0.044715
     th = torch.tanh(c * (h + k * h ** 3))
