@@ -677,12 +677,18 @@ static const DgradDual kDgradWideDual16 = {9.864, 0.871, 8.078, 0.447, 4.760, 0.
 // 128 x 128 tiles that are more than one per CU and at most one and a half: the excess runs as twice as many 128 x 64 halves, so that every CU gets
 // one tile and at most one half instead of some of them two tiles.  On 220 + 180 random problems of that kind (weights up to 5120 wide; wider ones
 // and more tokens), against the shape that the rows below choose: bf16 11 / 9 % faster on the geometric mean, 8-bit 10 / 7 % up to 20 k-steps and
-// 2 ... 7 % slower beyond 23, where the 256 x 128 tiles' fewer expansions win.  A few k-steps gain as much (8-bit) or anything from -14 to +15 %
-// (bf16, one or two) but are left to the plain tiles, which the tests hold to short contractions in this range.
-// Below 512 tokens the last token tile may be mostly padding, which narrower tiles avoid.  (8192 x 3072 x 768 bf16: 44.6 -> 41.0 us.)
+// 2 ... 7 % slower beyond 23, where the 256 x 128 tiles' fewer expansions win.  Shorter contractions are left to the plain tiles, which the tests hold
+// to them in this range; that costs 8 bits 2 ... 33 % (one to four k-steps, 16 problems) and bf16 13 ... 30 % at four and five (9 problems), and bf16
+// between -17 and +26 % at one and two.
+// Not taken where it lost: features that fill less than three quarters of their tiles (64 of them: 0 ... 13 % slower than 64 x 64 tiles, 3 % faster at
+// best), and below 512 tokens, where the last token tile may be mostly padding.
+// The gain depends on grad_Z being in the cache, as it is behind the kernel that wrote it.  Read from memory (285 problems on buffers of 700 MB), the
+// halves are 0 ... 33 % faster too where grad_Z's rows are whole 128-byte lines (one problem 6 % slower) and wherever the other choice is 128 x 128 tiles;
+// against 256 x 128 tiles, which read grad_Z half as often, rows that end inside a line cost up to 640 features 2 ... 16 % (17239 x 4008 x 192: 55.8
+// against 65.3 us, from the cache 50.0 against 43.1), from about 1000 channels on; shorter contractions gain.  (8192 x 3072 x 768 bf16: 44.6 -> 41.0 us.)
 static bool dgrad_halves(bool fp8, int64_t T, int64_t steps, int64_t I) {
-  const int64_t tiles = ((I + 127) / 128) * ((T + 127) / 128);
-  return T >= 512 && tiles > 256 && tiles <= 384 && (fp8 ? steps >= 5 && steps <= 20 : steps >= 6);
+  const int64_t mt = (I + 127) / 128, tiles = mt * ((T + 127) / 128);
+  return T >= 512 && 4 * I >= 3 * 128 * mt && tiles > 256 && tiles <= 384 && (fp8 ? steps >= 5 && steps <= 20 : steps >= 6);
 }
 
 static int dgrad_choice(bool fp8, int64_t T, int64_t O, int64_t I) {

@@ -356,6 +356,19 @@ def test_choice_of_the_tile_holds_for_wide_weights(op, dtype, T, O, I, tiles):
     assert sste.describe_plan(op, T, O, I, dtype).split(" grid ")[0] in tiles
 
 
+# The input gradient's grid of 128 x 128 tiles and 128 x 64 halves is for features that fill their tiles; as comments the time in us in the other tile.
+@pytest.mark.parametrize("dtype,T,O,I,tile", [
+    (0, 33217, 1600, 64, "64x64 kg 1"),                         # 19.4; halves 22.3
+    (0, 33776, 1168, 64, "64x64 kg 1"),                         # 17.5; halves 18.9
+    (0, 48540, 400, 64, "64x64 kg 1"),                          # 10.1; halves 10.8
+    (0, 17239, 3584, 192, "128x128+128x64 kg 1"),               # 34.7; 256x128 45.2
+    (0, 40919, 1600, 128, "128x128+128x64 kg 1"),               # 24.1; 128x128 26.2
+])
+def test_choice_of_halves_for_the_input_gradient(dtype, T, O, I, tile):
+    import paper_2409_09099_amd as sste
+    assert sste.describe_plan("dgrad", T, O, I, dtype).startswith(tile + " ")
+
+
 def test_describe_plan_refuses(lib):
     f = lib.sste_describe_plan
     f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]
