@@ -191,28 +191,6 @@ __device__ __forceinline__ int xcd_contiguous(int bid, int nblk) {
   const int xcd = bid % XCDS, slot = bid / XCDS;
   return (rem == 0 || xcd < rem) ? xcd * per_xcd + slot : rem * per_xcd + (xcd - rem) * (per_xcd - 1) + slot;
 }
-// Order of the 256 x 256 tiles of a product with a packed weight: `runs` runs of weight tiles (of 256 channels or features), each with all of its
-// token tiles before the next run's; inside a run the weight's tiles run fastest.  A run of about ten where the weight has 18 tiles or more: an
-// XCD goes through the tiles of a run again in every round, and half of a weight 5120 wide stays in its 4 MB of L2 (or more of it
-// does) where the whole does not.  Random products of 256 x 256 tiles, against one run, geometric mean (worst): 18 ... 20 tiles and more than a
-// round of them, forward 8-bit 4.1 % faster (1.5 % faster), bf16 equal (1.1 % slower), input gradient 0.8 / 1.2 % faster (0.5 % slower); 35
-// with 21 ... 73 tiles, four runs: 4 % faster (0.3 % slower).  Below 18 tiles two runs gain nothing, below 10 they lose up to 14 %, a round's
-// tiles then being far from square.  32768 x 5120 x 1280 e4m3 forward 153.4 -> 146.3 us, 16384 x 1280 x 5120 bf16 input gradient
-// 181.3 -> 177.9.
-struct TileOrder {
-  int m_tiles, n_tiles, runs;
-};
-inline TileOrder tile_order(int64_t m_tiles, int64_t n_tiles) {
-  const int64_t runs = m_tiles >= 18 && m_tiles * n_tiles > 256 ? (m_tiles + 2) / 10 : 1;
-  return {(int)m_tiles, (int)n_tiles, (int)(runs < 4 ? runs : 4)};
-}
-__device__ __forceinline__ void tile_at(const TileOrder& o, int logical, int& tm, int& tn) {
-  const int b = ((logical / o.n_tiles + 1) * o.runs - 1) / o.m_tiles;     // run b: weight tiles first .. first + width - 1
-  const int first = b * o.m_tiles / o.runs, width = (b + 1) * o.m_tiles / o.runs - first;
-  const int r = logical - first * o.n_tiles;
-  tm = first + r % width;
-  tn = r / width;
-}
 // MFMA group (0 .. groups-1) in which item idx of n evenly spread items is issued
 constexpr int spread(int idx, int n, int groups) { return idx * groups / n; }
 

@@ -41,6 +41,7 @@
 // Epilogue as in the forward GEMM: transposed through LDS, 16-byte streaming stores of bf16 rows.
 #include "common.h"
 #include "gelu_table.h"
+#include "tile_order.h"
 
 #include <stdio.h>
 

@@ -41,6 +41,7 @@
 // in turn) works on a contiguous range of tiles, o-tiles fastest: the packed weight stays in that
 // XCD's L2 and an X tile is fetched from HBM once per XCD.
 #include "common.h"
+#include "tile_order.h"
 
 #include <stdio.h>
 

@@ -462,7 +462,7 @@ def test_linear_dgrad_tiles_and_halves(sste, dtype, T, O, I):  # noqa: F811
 # 256 x 256 tiles in several runs of the weight's tiles (18 of them and more), of unequal width: (dtype, T, O, I, tile)
 @pytest.mark.parametrize("dtype,T,O,I,tile", [
     ("bf16", 3376, 4752, 832, "256x256+256x128 kg 1"), ("e4m3", 5257, 4624, 512, "256x256 kg 1"), ("bf16", 2433, 9888, 640, "256x256 kg 1"),
-    ("e4m3", 2054, 9664, 384, "256x256+256x128 kg 1"),
+    ("e4m3", 2054, 9664, 384, "256x256+256x128 kg 1"), ("e4m3", 814, 23568, 384, "256x256+256x128 kg 1"),   # the last: 93 tiles in nine runs
 ])
 def test_linear_fwd_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     test_linear_fwd_tiles(sste, dtype, T, O, I, tile)
@@ -470,7 +470,7 @@ def test_linear_fwd_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
 
 @pytest.mark.parametrize("dtype,T,O,I,tile", [
     ("bf16", 3389, 144, 4864, "256x256+256x128 kg 1"), ("e5m2", 5141, 400, 4864, "256x256 kg 1"), ("bf16", 2461, 272, 11520, "256x256 kg 1"),
-    ("e4m3", 3020, 112, 10752, "256x256 kg 1"),
+    ("e4m3", 3020, 112, 10752, "256x256 kg 1"), ("bf16", 700, 272, 19072, "256x256 kg 1"),
 ])
 def test_linear_dgrad_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     test_linear_dgrad_tiles(sste, dtype, T, O, I, tile, tile)
