@@ -559,7 +559,7 @@ def test_mvue_materialize_bit_exact(sste, dtype, case):
         assert np.array_equal(gv, rv), (case, seed, np.argwhere(gv != rv)[:5])
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "e4m3"])
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
 def test_mvue_group_ids_beyond_32_bits_and_token_shards(sste, dtype):
     """The draw takes the 64-bit group id ((first_token + t) / 4) * O + o.  Shards of the token axis placed
     where the ids cross 2^32 inside the tensor, and far beyond it, against the oracle bit for bit; and a
@@ -580,6 +580,27 @@ def test_mvue_group_ids_beyond_32_bits_and_token_shards(sste, dtype):
     with pytest.raises(sste.SsteError) as ei:
         sste.mvue_materialize(dYd, 9, 3, dt(sste, dtype), first_token=6)
     assert ei.value.status == 2
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3", "e5m2"])
+def test_mvue_group_ids_beyond_32_bits_in_a_large_tensor(sste, dtype):
+    """2^25 elements take wider rows per lane than the shards of 512 tokens, which the oracle holds: the same operand bit for bit, for ids that cross
+    2^32 at the third row of groups and for ids below it."""
+    T, O = 8192, 4096
+    g = torch.Generator(device="cuda").manual_seed(9)
+    dY = torch.empty((T, O), dtype=torch.bfloat16, device="cuda").normal_(0, 1e-3, generator=g)
+    if dtype != "bf16":
+        dY = sste.cast_fp8(dY, 1e-5 if dtype == "e4m3" else 1e-7, dt(sste, dtype))[0]
+    ks = 64 if dtype == "bf16" else 128
+
+    def blocks(first_token, rows):
+        vals, meta = sste.mvue_materialize(dY[rows], 9, 3, dt(sste, dtype), first_token=first_token)
+        return vals.view(torch.uint8).reshape(O // 16, -1, 1024), meta.view(torch.uint8).reshape(O // 16, -1, 2 * ks)
+    for first_token in (4 * ((1 << 20) - 3), 0):                              # (2^20 - 3) * 4096 = 2^32 - 12288
+        v, m = blocks(first_token, slice(None))
+        for t in (0, 4096, T - 512):
+            sv, sm = blocks(first_token + t, slice(t, t + 512))
+            assert torch.equal(v[:, t // ks:(t + 512) // ks], sv) and torch.equal(m[:, t // ks:(t + 512) // ks], sm), (first_token, t)
 
 
 @pytest.mark.parametrize("T,O,I", [(512, 256, 128), (4096, 512, 256)])       # in-GEMM estimator; pre-pass + packed GEMM

@@ -222,6 +222,27 @@ def test_linear_fwd_tiles_of_four_waves_and_of_256_tokens(sste, dtype, T, O, I, 
     test_linear_fwd_tiles(sste, dtype, T, O, I, tile)
 
 
+@pytest.mark.parametrize("dtype,T,O,I", [("bf16", 16417, 4096, 64), ("e4m3", 32801, 4096, 128), ("e4m3", 16417, 4096, 128)])
+def test_activation_larger_than_half_of_the_cache(sste, dtype, T, O, I):  # noqa: F811
+    """An activation of more than 128 MiB, which is written with the streaming hint (in 8 bits: of 64 MiB, as bf16 of 128)."""
+    _, _, packed, ws = gaussian_operands(sste, dtype, 64, O, I)
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(6))
+    xs = 1.0
+    if dtype != "bf16":
+        xs = 0.0125
+        X = sste.cast_fp8(X, xs)[0]
+    H, A, _ = sste.linear_fwd_act(X, *packed, O, dt(sste, dtype), xs, ws)
+    want = torch.nn.functional.gelu(H.double(), approximate="tanh")
+    assert T * O * 2 > 128 << 20 and torch.equal(H, sste.linear_fwd(X, *packed, O, dt(sste, dtype), xs, ws))
+    assert bool(((A.double() - want).abs() <= want.abs() * 2.0 ** -8 + 1e-6).all())
+    if dtype != "bf16":
+        a_scale = float(want.abs().max()) / 448.0
+        A8, amax = sste.linear_fwd_act(X, *packed, O, dt(sste, dtype), xs, ws, a_dtype=sste.F8E4M3, a_scale=a_scale)[1:]
+        assert abs(float(amax) - float(want.abs().max())) <= 1e-5 * float(want.abs().max())
+        dec = A8.view(torch.float8_e4m3fn).double() * a_scale
+        assert bool(((dec - want).abs() <= want.abs() * (2.0 ** -4 + 1e-5) + a_scale * 2.0 ** -9 + 1e-6).all())
+
+
 @pytest.mark.parametrize("dtype,T,O,I,tile", [c for c in FWD_TILES if c[0] == "e4m3"] + [("e4m3", 18542, 144, 640, "128x256 kg 1 r 1"), ("e4m3", 14318, 784, 384, "256x128 kg 1 r 2")])
 def test_largest_activation_keeps_nan(sste, dtype, T, O, I, tile):  # noqa: F811
     """A pre-activation of minus infinity makes NaN of its activation, and of the largest magnitude in every tile: a window of
@@ -318,6 +339,22 @@ def test_linear_wgrad_tiles_in_groups(sste, dtype, T, O, I, tile, parts):  # noq
         sste.wgrad_plan_override(0, 0, 0)
     assert torch.allclose(got, want, rtol=0, atol=1e-5 * float(want.abs().max()))
     assert torch.allclose(twice, 2.0 * got, rtol=1e-6, atol=1e-6 * float(got.abs().max()))
+
+    # padded rows of dY, X and dW, and a shard's place in the batch
+    def padded(m):
+        wide = torch.full((T, m.shape[1] + 80), -1, dtype=torch.int16 if dtype == "bf16" else torch.int8, device="cuda").view(m.dtype)
+        wide[:, :m.shape[1]] = m
+        return wide[:, :m.shape[1]]
+    wide = torch.full((O, I + 12), 3.0, device="cuda")
+    sste.linear_wgrad(padded(dY), padded(X), 5, 8, dt(sste, dtype), dys, xs, dW=wide[:, :I])
+    assert torch.equal(wide[:, :I], got) and bool((wide[:, I:] == 3.0).all())
+    shard = sste.linear_wgrad(padded(dY), padded(X), 5, 8, dt(sste, dtype), dys, xs, dW=wide[:, :I], first_token=4 * T)
+    try:
+        sste.wgrad_plan_override(8, 4, 2)
+        want = sste.linear_wgrad(dY, X, 5, 8, dt(sste, dtype), dys, xs, first_token=4 * T)
+    finally:
+        sste.wgrad_plan_override(0, 0, 0)
+    assert not torch.equal(shard, got) and torch.allclose(shard, want, rtol=0, atol=1e-5 * float(want.abs().max()))
 
 
 # the same with a workspace that holds plain splits only: (tile and splits of the plan without groups)
@@ -439,6 +476,25 @@ def test_linear_wgrad_infinity_stays_with_its_records(sste, T, O, I, tile):  # n
     assert bool(got.isfinite().all())
 
 
+def check_linear_fwd_padded_rows(sste, dtype, T, O, I):  # noqa: F811
+    """Padded rows of X, Z and A: no bit of the result differs from that of contiguous ones, and the padding of Z and A stays as it was."""
+    X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(6))
+    xs, (_, _, packed, ws) = 1.0, gaussian_operands(sste, dtype, 64, O, I)
+    if dtype != "bf16":
+        xs = 0.0125
+        X = sste.cast_fp8(X, xs)[0]
+    wide = torch.full((T, I + 48), -1, dtype=torch.int16 if dtype == "bf16" else torch.int8, device="cuda").view(X.dtype)      # NaN in either format
+    wide[:, :I] = X
+    Z, A = (torch.full((T, O + 24), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    sste.linear_fwd(wide[:, :I], *packed, O, dt(sste, dtype), xs, ws, Z=Z[:, :O])
+    want = sste.linear_fwd(X, *packed, O, dt(sste, dtype), xs, ws)
+    assert bool(want.isfinite().all()) and torch.equal(Z[:, :O], want) and bool((Z[:, O:] == 7.0).all())
+    Z.fill_(7.0)
+    sste.linear_fwd_act(wide[:, :I], *packed, O, dt(sste, dtype), xs, ws, H=Z[:, :O], A=A[:, :O])
+    assert torch.equal(Z[:, :O], want) and bool((Z[:, O:] == 7.0).all()) and bool((A[:, O:] == 7.0).all())
+    assert torch.equal(A[:, :O], sste.linear_fwd_act(X, *packed, O, dt(sste, dtype), xs, ws)[1])
+
+
 # the grid of 128 x 128 tiles and 128 x 64 halves: 286 ... 384 tiles, the last token tile's second half empty or not, incomplete last channel tiles and k-steps
 HALVES = "128x128+128x64 kg 1"
 
@@ -447,6 +503,7 @@ HALVES = "128x128+128x64 kg 1"
                                          ("e4m3", 2690, 1552, 512), ("e4m3", 6100, 1008, 640)])
 def test_linear_fwd_tiles_and_halves(sste, dtype, T, O, I):  # noqa: F811
     test_linear_fwd_tiles(sste, dtype, T, O, I, HALVES)
+    check_linear_fwd_padded_rows(sste, dtype, T, O, I)
     if dtype == "e4m3":
         test_largest_activation_keeps_nan(sste, dtype, T, O, I, HALVES)
 
@@ -466,6 +523,7 @@ def test_linear_dgrad_tiles_and_halves(sste, dtype, T, O, I):  # noqa: F811
 ])
 def test_linear_fwd_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     test_linear_fwd_tiles(sste, dtype, T, O, I, tile)
+    check_linear_fwd_padded_rows(sste, dtype, T, O, I)
 
 
 @pytest.mark.parametrize("dtype,T,O,I,tile", [
