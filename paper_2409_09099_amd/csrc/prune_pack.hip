@@ -158,7 +158,12 @@ __device__ __forceinline__ void flush_slot(const uint8_t* lds, int64_t blk, uint
 // wave of the multi-tensor kernel takes one block, not two (175 and 1049 us = 6.1 TB/s, above the rate of a plain copy: two reads to a write).
 // With both, streams that are contiguous per XCD are slower (181 and 1089), and so is the packed operand with the hint where it is not
 // larger than the cache (187).
-template <bool FP8, bool F32, bool STREAM = false>
+// Models whose weights and gradients fit the 256 MB cache: behind the gradients' writing, or with the cache full of other data, the hint is 0 ... 8 %
+// faster as well (4 layers of width 768 ... 2 of width 1280, 85 ... 315 MB); only an update repeated with nothing in between, which finds all of it in the
+// cache, is 2 ... 9 % slower with it.  The single-tensor kernel, called right behind the weight gradient it reads, takes the hint above 256 MiB only
+// (DENSE): at 5120 x 1280 it gains nothing there (14.5 against 14.2 us, float32 weight equal) and loses 19 % on a repeated call (15.6 -> 18.5 us); from
+// 12288 x 5120 on it gains 10 ... 25 %, around 256 MiB both are equal.
+template <bool FP8, bool F32, bool STREAM = false, bool DENSE = true>
 __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ G, int64_t O, int32_t steps, int64_t blk,
                                           int64_t ldw_bytes, int64_t ldg, float alpha, float beta, float val_scale,
                                           uint4* __restrict__ vals, void* __restrict__ meta, int lane, uint8_t* lds) {
@@ -168,15 +173,20 @@ __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ 
   const int32_t s = (int32_t)(blk - rb * steps);
   const int grp = lane % GPR, r0 = lane / GPR, q = grp / NG, g = grp % NG;
   const int64_t col = ((int64_t)s * GPR + grp) * 4;
+  auto load = [](auto* p) { return DENSE ? __builtin_nontemporal_load(p) : *p; };
+  auto store = [](auto v, auto* p) {
+    if (DENSE) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
   f32x4 gr[NL], wf[NL];
   i32x2 wb[NL];
 #pragma unroll
   for (int c = 0; c < NL; c++) {
     const int64_t row = rb * 16 + RPL * c + r0;
     if (row < O) {
-      gr[c] = __builtin_nontemporal_load((const f32x4*)(G + row * ldg + col));
-      if (F32) wf[c] = __builtin_nontemporal_load((const f32x4*)(W + row * ldw_bytes + col * 4));
-      else wb[c] = __builtin_nontemporal_load((const i32x2*)(W + row * ldw_bytes + col * 2));
+      gr[c] = load((const f32x4*)(G + row * ldg + col));
+      if (F32) wf[c] = load((const f32x4*)(W + row * ldw_bytes + col * 4));
+      else wb[c] = load((const i32x2*)(W + row * ldw_bytes + col * 2));
     } else {
       gr[c] = wf[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
       wb[c] = (i32x2){0, 0};
@@ -193,8 +203,8 @@ __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ 
     for (int e = 0; e < 4; e++) w[e] = w[e] - alpha * gr[c][e];
     uint32_t lo = bf16_rne_pack(w[0], w[1]), hi = bf16_rne_pack(w[2], w[3]);
     if (row < O) {
-      if (F32) __builtin_nontemporal_store(w, (f32x4*)(W + row * ldw_bytes + col * 4));
-      else __builtin_nontemporal_store((i32x2){(int)lo, (int)hi}, (i32x2*)(W + row * ldw_bytes + col * 2));
+      if (F32) store(w, (f32x4*)(W + row * ldw_bytes + col * 4));
+      else store((i32x2){(int)lo, (int)hi}, (i32x2*)(W + row * ldw_bytes + col * 2));
     } else {
       lo = hi = 0;                                       // rows past the last one are recorded as zeros, whatever alpha is
     }
@@ -209,16 +219,16 @@ __device__ __forceinline__ void sgd_block(uint8_t* W, const float* __restrict__ 
   flush_slot<FP8, STREAM>(lds, blk, vals, meta, lane);
 }
 
-template <bool FP8, bool F32>
+template <bool FP8, bool F32, bool DENSE>
 __global__ void __launch_bounds__(256)
 k_sgd_project_pack(uint8_t* W, const float* __restrict__ G, int64_t O, int32_t steps, int64_t n_blocks,
                    int64_t ldw_bytes, int64_t ldg, float alpha, float beta, float val_scale,
                    uint4* __restrict__ vals, void* __restrict__ meta) {
   const int lane = threadIdx.x & 63;
-  const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t blk = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (blk >= n_blocks) return;
   __shared__ __align__(16) uint8_t lds[4][kPackSlot];
-  sgd_block<FP8, F32>(W, G, O, steps, blk, ldw_bytes, ldg, alpha, beta, val_scale, vals, meta, lane, lds[threadIdx.x >> 6]);
+  sgd_block<FP8, F32, false, DENSE>(W, G, O, steps, blk, ldw_bytes, ldg, alpha, beta, val_scale, vals, meta, lane, lds[threadIdx.x >> 6]);
 }
 
 // Many tensors in one grid, like k_project_pack_batch.  80 bytes per item, layout shared with api.hip.
@@ -367,14 +377,21 @@ hipError_t launch_sgd_project_pack(void* W, bool w_f32, int64_t O, int64_t I, in
   dim3 grid((unsigned)((n + 3) / 4)), block(256);
   uint8_t* w = (uint8_t*)W;
   int64_t ldw_bytes = ldw * (w_f32 ? 4 : 2);
-#define SGD_CASE(F8, F32)                                                                                      \
-  SSTE_LAUNCH(SSTE_K_SGD_PROJECT_PACK, (k_sgd_project_pack<F8, F32>), grid, block, s, w, G, O, (int32_t)steps, n, \
+  const bool dense = product_reaches(n * 16, (fp8 ? 128 : 64) * (w_f32 ? 8 : 6), (256ll << 20) + 1);      // bytes of weight and gradient
+#define SGD_LAUNCH(F8, F32, DENSE)                                                                                         \
+  SSTE_LAUNCH(SSTE_K_SGD_PROJECT_PACK, (k_sgd_project_pack<F8, F32, DENSE>), grid, block, s, w, G, O, (int32_t)steps, n, \
               ldw_bytes, ldg, alpha, beta, val_scale, (uint4*)vals, meta)
+#define SGD_CASE(F8, F32)                     \
+  do {                                        \
+    if (dense) SGD_LAUNCH(F8, F32, true);     \
+    else SGD_LAUNCH(F8, F32, false);          \
+  } while (0)
   if (fp8 && w_f32) SGD_CASE(true, true);
   else if (fp8) SGD_CASE(true, false);
   else if (w_f32) SGD_CASE(false, true);
   else SGD_CASE(false, false);
 #undef SGD_CASE
+#undef SGD_LAUNCH
   return hipGetLastError();
 }
 

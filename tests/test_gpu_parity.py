@@ -290,6 +290,21 @@ def test_sgd_project_pack_batch_whole_model_sized_launch(sste, master, dtype):
     assert np.array_equal(host(vals[k]).numpy().view(fv.dtype).reshape(-1), fv)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "e4m3"])
+@pytest.mark.parametrize("master", ["bf16", "f32"])
+@pytest.mark.parametrize("O,I", [(10953, 4096), (83, 512)])                   # weight and gradient of more than 256 MiB: the single-tensor call streams them
+def test_sgd_project_pack_of_one_tensor_equals_the_batch(sste, master, dtype, O, I):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    W0 = torch.empty((O, I), dtype=torch.bfloat16 if master == "bf16" else torch.float32, device="cuda").normal_(0, 0.02, generator=g)
+    G = torch.empty((O, I + 4), device="cuda").normal_(0, 2e-2, generator=g)[:, :I]
+    assert (O * I * (4 + W0.element_size()) > 256 << 20) == (O > 1000)
+    vscale = 1.0 if dtype == "bf16" else 0.0007
+    W1, W2 = W0.clone(), W0.clone()
+    v1, m1 = sste.sgd_project_pack(W1, G, 0.3, 1.31, dt(sste, dtype), vscale)
+    vs, ms = sste.UpdateBatch([W2], [G], [1.31], dt(sste, dtype), [vscale]).launch(0.3)
+    assert torch.equal(W1, W2) and not torch.equal(W1, W0) and torch.equal(v1, vs[0]) and torch.equal(m1, ms[0])
+
+
 @pytest.mark.parametrize("master", ["bf16", "f32"])
 @pytest.mark.parametrize("dtype", ["bf16", "e4m3"])
 @pytest.mark.parametrize("case", ["cfg1", "ragged_strided", "alpha0"])
