@@ -22,7 +22,14 @@ constexpr TileOrder tile_order(int64_t m_tiles, int64_t n_tiles) {
   const int64_t runs = m_tiles >= 18 && m_tiles * n_tiles > 256 ? (m_tiles + 2) / 10 : 1, most = m_tiles <= 73 ? 4 : 64;
   return {(int)m_tiles, (int)n_tiles, (int)(runs < most ? runs : most)};
 }
+// One run needs one division, several need five, which a workgroup does before its first load: 5888 x 688 x 2944 e4m3 input gradient (296 workgroups)
+// 25.6 us with the one, 26.2 with the five.
 constexpr void tile_at(const TileOrder& o, int logical, int& tm, int& tn) {
+  if (o.runs == 1) {
+    tm = logical % o.m_tiles;
+    tn = logical / o.m_tiles;
+    return;
+  }
   const int b = ((logical / o.n_tiles + 1) * o.runs - 1) / o.m_tiles;     // run b: weight tiles first .. first + width - 1
   const int first = b * o.m_tiles / o.runs, width = (b + 1) * o.m_tiles / o.runs - first;
   const int r = logical - first * o.n_tiles;
