@@ -73,9 +73,11 @@ struct FwdOut {
   int64_t lda;
   float a_inv_scale;
   // A is the next product's operand: written with the streaming hint only where it is larger than half of the 256 MB cache, from which that
-  // product otherwise reads it.  Against the hint everywhere (us): two layers 1280 -> 5120 -> 1280 forward, bf16 2048 tokens 64.7 -> 53.7, 333
-  // tokens of width 768 17.1 -> 15.5, e4m3 1021 tokens 30.3 -> 26.9; with the backward pass, bf16 width 1024, 4096 tokens 239.5 -> 228, 8192
-  // tokens 403 -> 391.5, 16384 tokens (128 MiB of A) 700 -> 698; 8 bits equal, with 160 MiB 1376 -> 1380.
+  // product otherwise reads it, and in bf16 only.  Against the hint everywhere (us): two layers 1280 -> 5120 -> 1280 forward, bf16 2048 tokens 64.7 -> 53.7,
+  // 333 tokens of width 768 17.1 -> 15.5, e4m3 1021 tokens 30.3 -> 26.9; with the backward pass, which reads A once more, bf16 width 1024, 4096 tokens
+  // 239.5 -> 228, 8192 tokens 403 -> 391.5, 16384 tokens (128 MiB of A) 675 -> 666; e4m3 width 1280, 32768 tokens (160 MiB, the largest) 1368 -> 1360.
+  // The product that writes A takes up to 20 % longer by itself without the hint, and the one that reads it less.  Both together, 78 random pairs:
+  // up to 100 MB of A between 0.7 % slower and 32 % faster (7 % on the mean), 100 ... 134 MB between 4 % slower and 13 % faster (1 %).
   int a_stream;
 };
 
@@ -100,8 +102,7 @@ __device__ __forceinline__ uint32_t fwd_act_piece(const uint4& h, const FwdOut& 
     int hi = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[4] * r), clamp448(a[5] * r), 0, false);
     hi = __builtin_amdgcn_cvt_pk_fp8_f32(clamp448(a[6] * r), clamp448(a[7] * r), hi, true);
     i32x2 v = {lo, hi};
-    if (out.a_stream) __builtin_nontemporal_store(v, (i32x2*)(out.a8 + t * out.lda + o));
-    else *(i32x2*)(out.a8 + t * out.lda + o) = v;
+    *(i32x2*)(out.a8 + t * out.lda + o) = v;
   } else {
     uint4 v = make_uint4(bf16_rne_pack(a[0], a[1]), bf16_rne_pack(a[2], a[3]), bf16_rne_pack(a[4], a[5]), bf16_rne_pack(a[6], a[7]));
     if (out.a_stream) store_stream_b128(out.a16 + t * out.lda + o, v);
@@ -1323,7 +1324,7 @@ hipError_t launch_linear_fwd_act(const void* X, int64_t T, int64_t I, int64_t ld
   out.a8 = a_dtype == SSTE_F8E4M3 ? (uint8_t*)A : nullptr;
   out.lda = lda;
   out.a_inv_scale = a_inv_scale;
-  out.a_stream = product_reaches(T, O * (a_dtype == SSTE_F8E4M3 ? 1 : 2), (128ll << 20) + 1);
+  out.a_stream = a_dtype != SSTE_F8E4M3 && product_reaches(T, O * 2, (128ll << 20) + 1);
   if (dtype == SSTE_F8E4M3) launch_fwd_variant<true, false, false>(X, T, I, ldx, out, vals, meta, O, s);
   else launch_fwd_variant<false, false, false>(X, T, I, ldx, out, vals, meta, O, s);
   return hipGetLastError();

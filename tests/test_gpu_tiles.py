@@ -223,8 +223,8 @@ def test_linear_fwd_tiles_of_four_waves_and_of_256_tokens(sste, dtype, T, O, I, 
 
 
 @pytest.mark.parametrize("dtype,T,O,I", [("bf16", 16417, 4096, 64), ("e4m3", 32801, 4096, 128), ("e4m3", 16417, 4096, 128)])
-def test_activation_larger_than_half_of_the_cache(sste, dtype, T, O, I):  # noqa: F811
-    """An activation of more than 128 MiB, which is written with the streaming hint (in 8 bits: of 64 MiB, as bf16 of 128)."""
+def test_large_activation(sste, dtype, T, O, I):  # noqa: F811
+    """An activation of more than 128 MiB, which is written with the streaming hint in bf16, and in 8 bits of about 64 and 128 MiB."""
     _, _, packed, ws = gaussian_operands(sste, dtype, 64, O, I)
     X = torch.empty((T, I), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(6))
     xs = 1.0
