@@ -157,8 +157,9 @@ static void launch_mvue_pack(const void* dY, int64_t T, int64_t O, int64_t lddy,
   const bool fp8 = dtype != SSTE_BF16;
   const int ks = fp8 ? 128 : 64;
   // Many short-lived lanes fill the chip on small problems and keep each lane's chain of estimators short; large ones stream better with
-  // wider rows per lane.  Crossover near 2^25 elements (bf16 16384 x 1280: 16.9 against 17.4 us, 16384 x 4096: 42.9 against 40.2;
-  // e4m3 3200 x 1552: 6.6 against 7.6, 32768 x 3840: equal, 32768 x 5120: 84 against 76).
+  // wider rows per lane.  Crossover at 2^25 elements (narrow against wide, bf16 16384 x 1280: 15.0 / 15.3 us, 16384 x 2048: 21.6 / 20.8, 16384 x 4096:
+  // 39.8 / 37.5; e4m3 3200 x 1552: 7.2 / 7.0, 16384 x 1280: 11.9 / 11.4, 16384 x 2048: 17.9 / 16.5, 32768 x 5120: 84.9 / 59.7).  With the 8-bit
+  // estimator as short as it is now, 8-bit problems between 2^24 and 2^25 elements are 4 ... 8 % slower for it.
   const bool small = !product_reaches(T, O, 1ll << 25);
   const bool low = (unsigned __int128)(key.first_group + (uint64_t)(T / 4)) * (uint64_t)O <= 0x100000000ull;
 #define MP_LAUNCH(F8, B8, BC, VB, LOW)                                                                                   \
@@ -795,7 +796,9 @@ static double dealt_model_us(const WgradShape& w, const WgradDeal& d, int64_t O,
 }
 
 // The two ways to run a problem, same units: estimator pre-pass (streaming) and a second launch before the packed GEMM; or the fused
-// kernel, whose workgroups fill a CU each and whose time per k-step is the vector pipe's.
+// kernel, whose workgroups fill a CU each and whose time per k-step is the vector pipe's.  The pre-pass's 8-bit row is that of an estimator half as
+// fast as today's (0.36e-6 us per element).  Refitted, it would take the packed path in 9 of 1000 random problems that run the fused kernel now, narrow ones of a few us,
+// and would let 7 of 10000 grow out of the built-in scratch, whose calls without a workspace of their own run today.
 static double mvue_model_us(int64_t T, int64_t O, bool fp8) {
   const double t = 3.7 + (fp8 ? 0.56e-6 : 0.68e-6) * (double)T * (double)O;
   return (t > 4.5 ? t : 4.5) + 1.0;

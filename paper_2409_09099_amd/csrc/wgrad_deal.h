@@ -9,9 +9,11 @@ namespace sste {
 // Several: the number of workgroups per tile is a fraction, so that 100 tiles keep 250 of 256 CUs busy (five workgroups for every two)
 // where two each would keep 200.  A workgroup whose part crosses from one member into the next does two segments; the segments of a
 // member are summed in k order.  Workgroups of the same part number run next to each other and read the same k-steps, as with splits.
-// On 120 random problems that the plan deals so, the whole weight gradient against splits: 5.8 % faster on the geometric mean, 5 % slower at
-// worst, six by more than 1 %.  32768 x 5120 x 1280 e4m3: product 127 -> 114.5 us, the sum of three partials per tile for two 13 -> 17;
-// 16384 x 1280 x 5120 bf16: 134 -> 121 and 13 -> 18.  Inside a training step, where the chip holds a lower clock, half of that is left.  Groups
+// On 180 random problems that the plan deals so, the whole weight gradient against splits: 6.4 % faster on the geometric mean, 5 % slower at
+// worst, eight by more than 1 %.  The plan deals one random layer of 2048 tokens and more in 140 so, and every layer of 5120 x 1280.  32768 x 5120 x 1280 e4m3: product
+// 127 -> 114.5 us, the sum of three partials per tile for two 13 -> 17; 16384 x 1280 x 5120 bf16: 134 -> 121 and 13 -> 18.  Inside a training step,
+// where the chip holds a lower clock, half of that is left.  The kernel pays for it with scalar registers: the loop over segments keeps 17 ... 23 of them in lanes of
+// a vector register, read back inside the main loop, and needs 250 ... 253 vector registers for the 227 of the plain form.  Groups
 // of five to eight tiles lose the shared reads again (seventeen workgroups for seven tiles: up to 10 % slower).  Adding a tile's segments
 // up in the workgroup that ends last instead would leave the reading to one CU per tile, at an eighth of what all of them draw.
 constexpr int DEAL_MEMBERS = 4, DEAL_PARTS = 32, DEAL_SHORTEST = 4;      // shortest segment, k-steps
