@@ -11,7 +11,8 @@ namespace sste {
 // round of them, forward 8-bit 4.1 % faster (1.5 % faster), bf16 equal (1.1 % slower), input gradient 0.8 / 1.2 % faster (0.5 % slower); 42 ...
 // 73 tiles 4.6 % faster (0.4 % slower), 74 ... 256 tiles 5.6 % faster (0.3 % slower).  Below 18 tiles two runs gain nothing, below 10 they lose up to
 // 14 %, a round's tiles then being far from square.  32768 x 5120 x 1280 e4m3 forward 153.4 -> 146.3 us, 16384 x 1280 x 5120 bf16 input gradient
-// 181.3 -> 177.9.
+// 181.3 -> 177.9.  Fetched from memory by a forward product of a block of width 1280 (mean of its four): e4m3, 32768 tokens 200 -> 145 MB, bf16, 16384
+// tokens 277 -> 230 MB.
 // Up to 73 tiles there are at most four runs, of up to 18 tiles: runs of ten are as fast on the mean and up to 2.5 % slower on 8-bit products of few
 // k-steps.  Four for every weight, of up to 64 tiles, lost beyond (3.7 % slower than one run at worst, 3000 x 65536 x 5120 bf16 forward 1119 us against
 // 988).  More than 256 tiles are not measured; from 64 runs on they get wider, which keeps the products below in 32 bits.
