@@ -532,3 +532,5 @@ def test_linear_fwd_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
 ])
 def test_linear_dgrad_runs_of_tiles(sste, dtype, T, O, I, tile):  # noqa: F811
     test_linear_dgrad_tiles(sste, dtype, T, O, I, tile, tile)
+    test_linear_dgrad_ignores_what_lies_between_rows(sste, dtype, T, O, I, tile)
+    test_linear_dgrad_act_tiles(sste, dtype, T, O, I, tile)
