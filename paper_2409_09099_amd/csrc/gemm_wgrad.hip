@@ -796,8 +796,8 @@ static double dealt_model_us(const WgradShape& w, const WgradDeal& d, int64_t O,
 }
 
 // The two ways to run a problem, same units: estimator pre-pass (streaming) and a second launch before the packed GEMM; or the fused
-// kernel, whose workgroups fill a CU each and whose time per k-step is the vector pipe's.  The pre-pass's 8-bit row is that of an estimator half as
-// fast as today's (0.36e-6 us per element).  Refitted, it would take the packed path in 9 of 1000 random problems that run the fused kernel now, narrow ones of a few us,
+// kernel, whose workgroups fill a CU each and whose time per k-step is the vector pipe's.  The pre-pass's 8-bit row is that of an estimator that took
+// one and a half times as long as today's (0.36e-6 us per element).  Refitted, it would take the packed path in 9 of 1000 random problems that run the fused kernel now, narrow ones of a few us,
 // and would let 7 of 10000 grow out of the built-in scratch, whose calls without a workspace of their own run today.
 static double mvue_model_us(int64_t T, int64_t O, bool fp8) {
   const double t = 3.7 + (fp8 ? 0.56e-6 : 0.68e-6) * (double)T * (double)O;
